@@ -232,12 +232,15 @@ typedef struct cf_surface {
  * resident kernels with one wave of channels.  The server runs these
  * problems as one whole solve per request.  Execution: by
  * default one launch per wave of resident channels (any mix of orders),
- * each block carrying one channel through all its steps; tile_variant 1
- * keeps the fields in registers with an LDS exchange (real runs: grids of up
- * to 10240 cells in FP32, 6144 in FP64; complex runs, both parts in
- * registers: 6144 and 3072; and only when the device's LDS holds the
- * exchange array of 3 values per cell and part; otherwise variant 2 runs),
- * 2 keeps them in global memory, 0 picks 1 when it fits.  CF_FLAG_SPLIT (and CF_PATH_PLAIN) use one launch per half
+ * each block carrying one channel through all its steps.  tile_variant 1
+ * keeps the fields in registers (real runs: grids of up to 10240 cells in
+ * FP32, 6144 in FP64; complex runs, both parts in registers: 6144 and 3072;
+ * and only when the device's LDS holds 3 values per cell and part; otherwise
+ * variant 2 runs), in patches of cells per thread where a patch shape covers
+ * the grid (a periodic axis must be a multiple of the patch) and with an LDS
+ * exchange of every cell elsewhere,
+ * 2 keeps them in global memory, 0 picks 1 when it fits (a larger grid that
+ * a patch shape still covers also stays in registers and reports 2).  CF_FLAG_SPLIT (and CF_PATH_PLAIN) use one launch per half
  * step.  All give bitwise-identical results; cf_result.fused/tile_variant
  * report the variant that ran.
  */

@@ -24,6 +24,7 @@
 #include "device.hpp"
 #include "plan.hpp"
 #include "solver.hpp"
+#include "red_patch.hpp"
 #include "red_span.hpp"
 
 struct cf_problem {
@@ -883,6 +884,76 @@ void pml_order(const cf::Problem& p, const Layout& L, char* ws, cf::Grid2D& g, i
     g.pml_tab[1] = base + per_axis[0];
 }
 
+// Coefficient classes of the cells of a reduced problem (see PatchClasses):
+// materials whose coefficients agree (same mu in the H group, same eps in the
+// E group; held components all alike) share a class.  False when there are
+// more classes than a launch carries.
+bool patch_classes(const cf::Problem& p, std::vector<uint16_t>& cls, cf::PatchClasses& out) {
+    cls.assign(p.ncell, 0);
+    for (int grp = 0; grp < 2; ++grp) {
+        // rank[id]: 0 when the id holds the field at 0, else 1 + the first
+        // material with the same value
+        const std::vector<double>& v = grp == 0 ? p.mu : p.eps;
+        uint8_t rank[256] = {};
+        for (int id = 0; id < p.nmat; ++id) {
+            if (!std::isfinite(v[id])) continue;
+            int k = 0;
+            while (v[k] != v[id]) ++k;
+            rank[id] = (uint8_t)(k + 1);
+        }
+        out.n[grp] = 1;
+        std::fill(out.id[grp][0], out.id[grp][0] + 3, (uint8_t)cf::kNullId);
+        const uint8_t* id0 = p.ids[grp == 0 ? CF_HX : CF_EX].data();
+        const uint8_t* id1 = p.ids[grp == 0 ? CF_HY : CF_EY].data();
+        const uint8_t* id2 = p.ids[grp == 0 ? CF_HZ : CF_EZ].data();
+        std::map<uint32_t, int> of{{0u, 0}};
+        uint32_t last = 0;
+        int last_c = 0;
+        for (int64_t k = 0; k < p.ncell; ++k) {
+            const uint8_t r[3] = {rank[id0[k]], rank[id1[k]], rank[id2[k]]};
+            const uint32_t key = r[0] | (uint32_t(r[1]) << 8) | (uint32_t(r[2]) << 16);
+            if (key != last) {
+                auto it = of.find(key);
+                if (it == of.end()) {
+                    if (out.n[grp] >= cf::kPatchClasses) return false;
+                    it = of.emplace(key, out.n[grp]++).first;
+                    for (int c = 0; c < 3; ++c)
+                        out.id[grp][it->second][c] = r[c] ? (uint8_t)(r[c] - 1) : (uint8_t)cf::kNullId;
+                }
+                last = key;
+                last_c = it->second;
+            }
+            cls[k] |= (uint16_t)(last_c << (8 * grp));
+        }
+    }
+    return true;
+}
+
+// LDS table sizes of the patch kernel over a solve's channels.
+cf::PatchSizes patch_sizes(const cf::Problem& p, const Staged& st) {
+    cf::PatchSizes z{1, 1, 1};
+    auto box = [&](const int32_t* idx, int n) {
+        int x0 = p.nx, x1 = -1, y0 = p.ny, y1 = -1;
+        for (int k = 0; k < n; ++k) {
+            const int x = idx[k] % p.nx, y = idx[k] / p.nx;
+            x0 = std::min(x0, x);
+            x1 = std::max(x1, x);
+            y0 = std::min(y0, y);
+            y1 = std::max(y1, y);
+        }
+        if (n > 0) z.box = std::max(z.box, (x1 - x0 + 1) * (y1 - y0 + 1));
+    };
+    std::map<std::pair<int, int>, bool> seen;   // channels of a face share their tables
+    for (const cf::ChanDev& d : st.dev) {
+        z.samples = std::max(z.samples, d.nsamp);
+        z.points = std::max(z.points, d.P);
+        if (!seen.emplace(std::make_pair(d.g_off, d.u_off), true).second) continue;
+        box(st.gidx.data() + d.g_off, d.nsamp * d.P);
+        box(st.uidx.data() + d.u_off, d.n_uniq);
+    }
+    return z;
+}
+
 template <typename T>
 cf_status run_reduced(const cf::Problem& p, const cf_opts& o, const Staged& st, const Layout& L, char* ws,
                   hipStream_t s, std::vector<double>& acc_out, std::vector<double>& gamma_out, double* device_ms,
@@ -962,6 +1033,8 @@ cf_status run_reduced(const cf::Problem& p, const cf_opts& o, const Staged& st, 
         const double cm = cf::order_courant(p, o.courant, m);
         ord.steps[m] = cf::order_steps(p, o, m);
         ord.dt[m] = cm / p.grid.res;
+        const double loss = 0.5 * o.sigma * ord.dt[m];
+        ord.la[m] = (1.0 - loss) / (1.0 + loss);
         ord.coup[m] = p.coupling(m);
         const double phi = p.bloch ? p.kxs[m] * p.nx / p.grid.res : 0.0;   // k_x L
         ord.ph_c[m] = std::cos(phi);
@@ -992,26 +1065,31 @@ cf_status run_reduced(const cf::Problem& p, const cf_opts& o, const Staged& st, 
     CF_HIP(up(L.rinv, rows.data(), rows.size() * sizeof(T)));
     ord.rows = ws + L.rinv;
     const T* drows = reinterpret_cast<const T*>(ws + L.rinv);
-    // material ids packed in 4 bits per component for the register kernel
-    // (15 = wall id), when every id fits
+    // cells' coefficient classes for the patch kernel; the material ids packed
+    // in 4 bits per component (15 = wall id), when every id fits, for the
+    // register kernel, which takes the grids no patch shape covers.  Both use
+    // the same region: the ids go up only when the patch kernel declined.
+    cf::PatchClasses classes{};
+    std::vector<uint16_t> cls;
+    cf::PatchSizes psizes{};
+    if (st.red_res && o.tile_variant != 2 && patch_classes(p, cls, classes)) {
+        CF_HIP(up(L.idp, cls.data(), cls.size() * 2));
+        classes.cls = reinterpret_cast<const uint16_t*>(ws + L.idp);
+        psizes = patch_sizes(p, st);
+    }
     std::vector<uint32_t> idw;
-    if (st.red_res) {
+    auto pack_ids = [&]() -> hipError_t {
+        if (!idw.empty()) return hipSuccess;
         idw.assign(p.ncell, 0u);
-        bool fits = true;
-        for (int c = 0; c < cf::kNumComp && fits; ++c)
+        for (int c = 0; c < cf::kNumComp; ++c)
             for (int64_t k = 0; k < p.ncell; ++k) {
                 const int id = p.ids[c][k];
-                if (id >= 15 && id != cf::kWallId) {
-                    fits = false;
-                    break;
-                }
+                if (id >= 15 && id != cf::kWallId) return hipSuccess;
                 idw[k] |= uint32_t(id == cf::kWallId ? 15 : id) << (4 * c);
             }
-        if (fits) {
-            CF_HIP(up(L.idp, idw.data(), idw.size() * 4));
-            ord.idw = reinterpret_cast<const uint32_t*>(ws + L.idp);
-        }
-    }
+        ord.idw = reinterpret_cast<const uint32_t*>(ws + L.idp);
+        return up(L.idp, idw.data(), idw.size() * 4);
+    };
 
     hipEvent_t e0, e1;
     CF_HIP(hipEventCreate(&e0));
@@ -1056,8 +1134,16 @@ cf_status run_reduced(const cf::Problem& p, const cf_opts& o, const Staged& st, 
                 }
                 const bool take = smp.begin(s);
                 int used = 0;
-                STEP_OK(cf::launch_red_resident_span<T>(o.tile_variant, fields, dch, sl, w.n_all, g, ord, span, tabs,
-                                                        dA, dacc, dgam, (int)C, s, &used));
+                bool patched = false;
+                STEP_OK(cf::launch_red_patch<T>(fields, dch, sl, w.n_all, g, ord, span, tabs, classes, psizes, dA,
+                                                dacc, dgam, (int)C, s, &patched));
+                if (patched) {
+                    used = cf::red_regs_covers<T>(g, ord.cplx) ? 1 : 2;
+                } else {
+                    if (o.tile_variant != 2) STEP_OK(pack_ids());
+                    STEP_OK(cf::launch_red_resident_span<T>(o.tile_variant, fields, dch, sl, w.n_all, g, ord, span,
+                                                            tabs, dA, dacc, dgam, (int)C, s, &used));
+                }
                 smp.end(take, s, cu, cu * state_bytes);
                 timing->variant = std::max(timing->variant, used - 1);
                 d0 = d1;

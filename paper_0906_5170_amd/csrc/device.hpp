@@ -190,6 +190,7 @@ struct RedOrders {
     // 4 c; 15 stands for the wall id), or null when an id does not fit
     const uint32_t* idw;
     const void* rows;                 // 6 row factors per row (field precision)
+    double la[kMaxOrders];            // a of the field group that carries the conductivity (the other's is 1)
     double coup[kMaxOrders];       // coupling of each order: m, or k dx
     double ph_c[kMaxOrders];       // Bloch phase across the periodic x edge (complex runs)
     double ph_s[kMaxOrders];

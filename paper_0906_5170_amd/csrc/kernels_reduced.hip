@@ -47,6 +47,8 @@
 
 #include "../../include/casimir_fdtd.h"
 #include "device.hpp"
+#include "red_common.hpp"
+#include "red_patch.hpp"
 #include "red_span.hpp"
 #include "yee_common.hpp"
 
@@ -64,17 +66,6 @@ inline dim3 grid_red(const Grid2D& g, int nslots) {
     const int tiles = ((g.nx + BX - 1) / BX) * ((g.ny + BY - 1) / BY);
     return dim3(tiles, nslots, 1);
 }
-
-// Reduced update, with M the coupling of the run (m, or k dx) and the curls
-// in undivided form:
-//   h_x/h_z: ((A e_z(j+1) - B e_z) - M e_y) C       h_y/h_r: M e_x D - d_x e_z
-//   e_x/e_z: ((P h_z - Q h_z(j-1)) + M h_y) D       e_y/e_r: -M h_x C - d_x h_z
-//   h_z/h_phi and e_z/e_phi: the Cartesian two-dimensional forms;
-// cylindrical (CYL): (A, B, C, D, P, Q) = (j + 1/2, j - 1/2, 1/j, 1/(j - 1/2),
-// j, j - 1), row 0 the axis with its own rules; k_z: all 1.  The row table
-// holds 6 values per row (field precision); the kernels read C and D from it
-// and form the others from j.
-enum { RA = 0, RB, RC, RD, RP, RQ, kRowFactors };
 
 // Updated h components (hx, hy, hz) of a cell at row j from its own fields,
 // the neighbours e(j+1) (ezu, exu) and e(i+1) (ezr, eyr) and the (a, b)
@@ -239,20 +230,6 @@ struct RedRun {
     const T* rows;
     T pc, ps;
 };
-
-// Complex runs keep the real part of the six components in the first
-// 6 x ncell values of a channel block and the imaginary part in the next.
-// The x neighbour across the periodic edge of part `part` (0 real, 1
-// imaginary): forward (F[nx] = p F[0]) or backward (F[-1] = conj(p) F[nx-1]),
-// from the wrapped cell's own-part value a and other-part value b.
-template <typename T>
-__device__ __forceinline__ T bloch_fwd(T a, T b, int part, T pc, T ps) {
-    return part == 0 ? a * pc - b * ps : a * pc + b * ps;
-}
-template <typename T>
-__device__ __forceinline__ T bloch_bwd(T a, T b, int part, T pc, T ps) {
-    return part == 0 ? a * pc + b * ps : a * pc - b * ps;
-}
 
 // H update of cell (i, j), part `part`, of the channel block F in global memory.
 // psi: the channel's CPML block (k_z runs with in-plane layers), or nullptr.
@@ -979,14 +956,6 @@ template <>
 constexpr RegVariant kRegVariants<double>[kNumRegVariants] = {{1, 1024}, {2, 1024}, {3, 1024}, {4, 1024}, {6, 1024},
                                                                {6, 1024}};
 
-// LDS bytes a block may take on the current device
-inline size_t device_lds_limit() {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 65536;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return 65536;
-    return (size_t)v;
-}
-
 // Dynamic LDS above 64 KB needs the kernel's attribute raised first.  The
 // attribute is a cap and is only ever raised (under a lock), so solves on
 // concurrent host threads never lower it below what another one launches
@@ -1114,6 +1083,15 @@ hipError_t resident_launch(int variant, T* fields, const ChanDev* ch, const int*
                        t, dA, acc, gamma, gamma_stride);
     return hipGetLastError();
 }
+
+template <typename T>
+bool red_regs_covers(const Grid2D& g, int cplx) {
+    constexpr int last = kNumRegVariants - 1;
+    const RegVariant v = kRegVariants<T>[cplx ? kCplxRegVariants<T> - 1 : last];
+    return g.ncell <= (int64_t)v.K * v.NTH && regs_lds_bytes<T>(g, cplx ? 2 : 1) + 64 <= device_lds_limit();
+}
+template bool red_regs_covers<float>(const Grid2D&, int);
+template bool red_regs_covers<double>(const Grid2D&, int);
 
 template <typename T>
 hipError_t launch_red_resident_span(int variant, T* fields, const ChanDev* ch, const int* slots, int nslots,

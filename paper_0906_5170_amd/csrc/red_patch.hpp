@@ -1,0 +1,45 @@
+// Patch kernel of the reduced problems (cylindrical orders, k_z and Bloch
+// points): launch interface.
+#pragma once
+
+#include "device.hpp"
+#include "red_span.hpp"
+
+namespace cf {
+
+// Coefficient classes of the cells.  A cell's H class names the triple of
+// materials its H_x, H_y, H_z coefficients come from, its E class the triple
+// of E_x, E_y, E_z; cls[cell] = H class | E class << 8.  Class 0 holds no
+// field (every b is 0).  id[g][c] lists one material id per component for
+// class c of group g (0 H, 1 E); ids whose coefficients agree share a class.
+constexpr int kPatchClasses = 64;
+struct PatchClasses {
+    const uint16_t* cls;                // device, one word per cell
+    int n[2];                           // classes in use per group (with class 0)
+    uint8_t id[2][kPatchClasses][3];
+};
+
+// Largest bounding box (cells) of the interpolation points of one channel's
+// source or measured component, and largest samples x points of a channel's
+// face: they size the block's LDS tables.
+struct PatchSizes {
+    int box, samples, points;
+};
+
+// LDS bytes a block may take on the current device.
+inline size_t device_lds_limit() {
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 65536;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return 65536;
+    return (size_t)v;
+}
+
+// As launch_red_resident_span, for grids a patch shape covers: *launched
+// tells whether one did (nothing is launched otherwise).
+template <typename T>
+hipError_t launch_red_patch(T* fields, const ChanDev* ch, const int* slots, int nslots, const Grid2D& g,
+                            const RedOrders& ord, const RedSpan& span, const SurfTables& t, const PatchClasses& pc,
+                            const PatchSizes& ps, double dA, double* acc, double* gamma, int gamma_stride,
+                            hipStream_t s, bool* launched);
+
+}  // namespace cf

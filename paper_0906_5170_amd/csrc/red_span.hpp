@@ -39,4 +39,8 @@ hipError_t launch_red_resident_span(int variant, T* fields, const ChanDev* ch, c
                                     double dA, double* acc, double* gamma, int gamma_stride, hipStream_t s,
                                     int* used);
 
+// Whether the register kernel (variant 1) covers the grid.
+template <typename T>
+bool red_regs_covers(const Grid2D& g, int cplx);
+
 }  // namespace cf
