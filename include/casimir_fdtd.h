@@ -65,7 +65,9 @@ typedef enum {
  * y; cylindrical problems along the tube axis (x) only, the tube wall
  * staying PEC (CF_E_ARG at creation otherwise).  In 2D, k_z and
  * cylindrical problems the split half-step kernels carry the layers (the
- * fused and resident kernels do not); each cylindrical order uses the
+ * fused kernels do not; k_z problems with real fields whose grid fits a
+ * CU's registers and LDS stay on chip, all steps in one launch, with
+ * bitwise the split kernels' results); each cylindrical order uses the
  * profile of its own time step.  The kick and the consistent start stretch
  * their differences inside a layer as every later step does. */
 enum { CF_BC_PEC = 0, CF_BC_PERIODIC = 1, CF_BC_PML = 2 };
@@ -179,9 +181,10 @@ typedef struct cf_materials {
      * X = 4 / dt^2, K^2 = (8 + (k_max dx)^2) / dx^2 in 2D (k_max: the largest
      * |k_z| of a k_z problem), for each dispersive material (eps, mu); a
      * strong term lowers the stable Courant number well below the Yee limit
-     * at eps.  Dispersive problems run on the split half-step kernels (the
-     * fused and resident kernels do not take them) and are not served
-     * (CF_E_UNSUPPORTED). */
+     * at eps.  Dispersive problems run on the split half-step kernels, or on
+     * chip as problems with CPML layers do, and are not served
+     * (CF_E_UNSUPPORTED).  cf_result.fused and tile_variant are 0 for
+     * dispersive problems and problems with in-plane layers on either path. */
     int n_lorentz;
     const double* lorentz_deps;
     const double* lorentz_w0;

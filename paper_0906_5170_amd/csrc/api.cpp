@@ -892,13 +892,13 @@ bool patch_classes(const cf::Problem& p, std::vector<uint16_t>& cls, cf::PatchCl
     cls.assign(p.ncell, 0);
     for (int grp = 0; grp < 2; ++grp) {
         // rank[id]: 0 when the id holds the field at 0, else 1 + the first
-        // material with the same value
+        // material with the same value (a dispersive material its own)
         const std::vector<double>& v = grp == 0 ? p.mu : p.eps;
         uint8_t rank[256] = {};
         for (int id = 0; id < p.nmat; ++id) {
             if (!std::isfinite(v[id])) continue;
             int k = 0;
-            while (v[k] != v[id]) ++k;
+            while (k < id && (v[k] != v[id] || (grp == 1 && (p.has_terms(k) || p.has_terms(id))))) ++k;
             rank[id] = (uint8_t)(k + 1);
         }
         out.n[grp] = 1;
@@ -926,6 +926,35 @@ bool patch_classes(const cf::Problem& p, std::vector<uint16_t>& cls, cf::PatchCl
             cls[k] |= (uint16_t)(last_c << (8 * grp));
         }
     }
+    return true;
+}
+
+// Lorentz rows of an open or dispersive run of the patch kernel: row 0 without
+// a term, then one row [1 / eps, (c1, c2, c3) per term] per dispersive
+// material, and the row of each E class and component.  False when there are
+// more rows than a launch carries.
+bool patch_lorentz(const cf::Problem& p, const std::vector<double>& lor, const cf::PatchClasses& pc,
+                   cf::PatchOpen& op) {
+    op.n_lor = p.dispersive ? p.n_lor : 0;
+    op.lor_rows = 1;
+    std::memset(op.lor, 0, sizeof(op.lor));
+    std::memset(op.lrow, 0, sizeof(op.lrow));
+    if (!p.dispersive) return true;
+    const int stride = cf::kLorStride(p.n_lor);
+    std::map<int, int> row_of;
+    for (int c = 1; c < pc.n[1]; ++c)
+        for (int q = 0; q < 3; ++q) {
+            const int id = pc.id[1][c][q];
+            if (id >= p.nmat || lor[(size_t)id * stride] == 0.0) continue;
+            auto it = row_of.find(id);
+            if (it == row_of.end()) {
+                if (op.lor_rows >= 4 || p.n_lor > 4) return false;
+                it = row_of.emplace(id, op.lor_rows).first;
+                for (int k = 0; k < 1 + 3 * p.n_lor; ++k) op.lor[op.lor_rows][k] = lor[(size_t)id * stride + 1 + k];
+                ++op.lor_rows;
+            }
+            op.lrow[c][q] = (uint8_t)it->second;
+        }
     return true;
 }
 
@@ -1077,6 +1106,22 @@ cf_status run_reduced(const cf::Problem& p, const cf_opts& o, const Staged& st, 
         classes.cls = reinterpret_cast<const uint16_t*>(ws + L.idp);
         psizes = patch_sizes(p, st);
     }
+    // an open or dispersive k_z run on the patch kernel needs no field blocks:
+    // their region holds the classes and the blocks' CPML values
+    cf::PatchOpen open{};
+    bool try_open = p.kz && !p.bloch && (st.pml2d || p.dispersive) && o.path != CF_PATH_PLAIN &&
+                    !(o.flags & CF_FLAG_SPLIT);
+    if (try_open && patch_classes(p, cls, classes) && patch_lorentz(p, lor, classes, open)) {
+        const size_t head = align_up(cls.size() * 2, 256);
+        CF_HIP(up(L.fields, cls.data(), cls.size() * 2));
+        classes.cls = reinterpret_cast<const uint16_t*>(ws + L.fields);
+        psizes = patch_sizes(p, st);
+        open.cls = cls.data();
+        open.scratch = ws + L.fields + head;
+        open.scratch_bytes = (int64_t)field_bytes - (int64_t)head;
+    } else {
+        try_open = false;
+    }
     std::vector<uint32_t> idw;
     auto pack_ids = [&]() -> hipError_t {
         if (!idw.empty()) return hipSuccess;
@@ -1119,8 +1164,19 @@ cf_status run_reduced(const cf::Problem& p, const cf_opts& o, const Staged& st, 
         err = (expr);                     \
         if (err != hipSuccess) goto done; \
     } while (0)
+    bool opened = false;
     STEP_OK(hipEventRecord(e0, s));
+    if (try_open) {
+        // one order (k_z point) has every order's steps
+        const cf::RedSpan span = cf::red_span(ord, n_ord, 0, o.n_steps, o.n_steps);
+        const double cu = (double)C * p.ncell * o.n_steps;
+        const bool take = smp.begin(s);
+        STEP_OK(cf::launch_red_patch<T>(fields, dch, nullptr, (int)C, g, ord, span, tabs, classes, psizes, &open, dA,
+                                        dacc, dgam, (int)C, s, &opened));
+        if (opened) smp.end(take, s, cu, cu * state_bytes);
+    }
     for (const Wave& w : st.waves) {
+        if (opened) break;
         const int* sl = dslots + w.all_off;
         if (st.red_res) {
             // one launch per part: every channel of the wave, any mix of orders
@@ -1135,8 +1191,8 @@ cf_status run_reduced(const cf::Problem& p, const cf_opts& o, const Staged& st, 
                 const bool take = smp.begin(s);
                 int used = 0;
                 bool patched = false;
-                STEP_OK(cf::launch_red_patch<T>(fields, dch, sl, w.n_all, g, ord, span, tabs, classes, psizes, dA,
-                                                dacc, dgam, (int)C, s, &patched));
+                STEP_OK(cf::launch_red_patch<T>(fields, dch, sl, w.n_all, g, ord, span, tabs, classes, psizes,
+                                                nullptr, dA, dacc, dgam, (int)C, s, &patched));
                 if (patched) {
                     used = cf::red_regs_covers<T>(g, ord.cplx) ? 1 : 2;
                 } else {

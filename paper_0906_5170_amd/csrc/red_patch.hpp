@@ -26,6 +26,18 @@ struct PatchSizes {
     int box, samples, points;
 };
 
+// Open (CPML) and dispersive k_z runs: host-side classes, Lorentz rows (row 0
+// has no term; [1 / eps, (c1, c2, c3) per term]) with the row of each E class
+// and component, and device memory for the blocks' CPML values.
+struct PatchOpen {
+    const uint16_t* cls;
+    int n_lor, lor_rows;
+    double lor[4][13];
+    uint8_t lrow[kPatchClasses][3];
+    void* scratch;
+    int64_t scratch_bytes;
+};
+
 // LDS bytes a block may take on the current device.
 inline size_t device_lds_limit() {
     int dev = 0, v = 0;
@@ -35,11 +47,14 @@ inline size_t device_lds_limit() {
 }
 
 // As launch_red_resident_span, for grids a patch shape covers: *launched
-// tells whether one did (nothing is launched otherwise).
+// tells whether one did (nothing is launched otherwise).  slots == nullptr:
+// the channels 0 .. nslots - 1.  op: an open or dispersive run (whole span
+// only, the grid's CPML set as for the split kernels); it uses no field
+// blocks.
 template <typename T>
 hipError_t launch_red_patch(T* fields, const ChanDev* ch, const int* slots, int nslots, const Grid2D& g,
                             const RedOrders& ord, const RedSpan& span, const SurfTables& t, const PatchClasses& pc,
-                            const PatchSizes& ps, double dA, double* acc, double* gamma, int gamma_stride,
-                            hipStream_t s, bool* launched);
+                            const PatchSizes& ps, const PatchOpen* op, double dA, double* acc, double* gamma,
+                            int gamma_stride, hipStream_t s, bool* launched);
 
 }  // namespace cf

@@ -22,8 +22,9 @@ def cf():
     return cf
 
 
-def block_problem(nx, ny, bc, kx=(), n_steps=9):
-    """Two dielectric blocks and a PEC strip around a stress surface."""
+def block_problem(nx, ny, bc, kx=(), n_steps=150):
+    """Two dielectric blocks and a PEC strip around a stress surface; enough
+    steps for every wall to answer."""
     prims = [Box((-BIG, -BIG, -BIG), (BIG, 1, BIG), 1), Box((nx - 3, 3, -BIG), (nx - 2, ny - 3, BIG), 3),
              Box((5, 5, -BIG), (7, 7, BIG), 2)]
     kz = (0.7, 2.9)
@@ -38,7 +39,7 @@ def both(cf, wl, precision):
     o = dict(sigma=wl.sigma, courant=wl.courant, n_steps=wl.n_steps, pol="3D", kernel="general",
              precision=precision, keep_gamma=True)
     a, b = p.solve(**o), p.solve(split=True, **o)
-    assert a["fused"] and not b["fused"]
+    assert a["fused"] == (not wl.lorentz and "pml" not in wl.bc) and not b["fused"]
     for key in ("per_channel", "gamma"):
         assert np.all(np.isfinite(a[key])) and np.any(a[key] != 0.0), key
         assert np.array_equal(a[key], b[key]), (wl.shape, wl.bc, precision, key)
@@ -74,5 +75,43 @@ def test_bloch(cf, shape, bc_y, precision):
 @pytest.mark.parametrize("res,length", [(10, 5.0), (16, 7.0), (23, 6.1), (31, 8.3)])
 def test_cylindrical(cf, res, length, precision):
     from casimir_inputs import cyl_piston
-    wl = cyl_piston(res, h_u=0.9, length_u=length, n_harm=2, m_max=3, n_steps=9)
+    wl = cyl_piston(res, h_u=0.9, length_u=length, n_harm=2, m_max=3, n_steps=150)
     both(cf, wl, precision)
+
+
+POLES = ((3.0, 3.0), (1.5, 5.0))
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("res,pml,poles", [(10, 0.4, POLES[:1]), (16, 0.5, ()), (21, 0.3, POLES), (28, 0.5, POLES[:1])])
+def test_open_guides(cf, res, pml, poles, precision):
+    """CPML on four sides (layers that end inside a patch) and up to two
+    Lorentz terms; the largest grid takes E_z into LDS in FP32."""
+    from casimir_inputs import kz_workload, waveguides_open_2d
+    wl = waveguides_open_2d(res, 0.5, 0.25, 0.5, 0.5, pml, 1.5, poles, n_harm=3, n_steps=150)
+    both(cf, kz_workload(wl, [0.7, 2.9], [0.4, 0.3]), precision)
+
+
+def test_open_guides_at_the_largest_grid(cf):
+    """130 x 90 cells, FP32: the CPML values and polarizations nearly fill the
+    block's LDS; 64 channels need several launches at two resident channels."""
+    from casimir_inputs import kz_workload, waveguides_open_2d
+    wl = waveguides_open_2d(40, 0.5, 0.25, 0.25, 0.5, 0.5, 1.5, POLES[:1], n_harm=4, n_steps=150)
+    wl = kz_workload(wl, [0.7, 2.9], [0.4, 0.3])
+    both(cf, wl, "fp32")
+    p = cf.Problem.from_workload(wl)
+    o = dict(sigma=wl.sigma, courant=wl.courant, n_steps=wl.n_steps, pol="3D", kernel="general", precision="fp32")
+    assert np.array_equal(p.solve(**o)["per_channel"], p.solve(max_resident=2, **o)["per_channel"])
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_open_along_one_axis(cf, precision):
+    from casimir_inputs import kz_workload, slabs_open_1d
+    wl = slabs_open_1d(20, 0.5, 0.25, 0.35, 0.5, 1.5, POLES, n_steps=150)
+    both(cf, kz_workload(wl, [0.7, 2.9], [0.4, 0.3]), precision)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_dispersive_without_layers(cf, precision):
+    wl = block_problem(37, 29, WALLS)
+    both(cf, wl.replace(lorentz={2: POLES}), precision)
