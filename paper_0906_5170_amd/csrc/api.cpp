@@ -926,6 +926,7 @@ bool patch_classes(const cf::Problem& p, std::vector<uint16_t>& cls, cf::PatchCl
             cls[k] |= (uint16_t)(last_c << (8 * grp));
         }
     }
+    out.h_uniform = std::all_of(cls.begin(), cls.end(), [](uint16_t c) { return (c & 255) == 1; });
     return true;
 }
 

@@ -1,0 +1,10 @@
+// Patch kernel of the reduced problems, FP64 fields (red_patch_kernel.hpp).
+#include "red_patch_kernel.hpp"
+
+namespace cf {
+
+template hipError_t launch_red_patch<double>(double*, const ChanDev*, const int*, int, const Grid2D&, const RedOrders&,
+                                         const RedSpan&, const SurfTables&, const PatchClasses&, const PatchSizes&,
+                                         const PatchOpen*, double, double*, double*, int, hipStream_t, bool*);
+
+}  // namespace cf

@@ -16,6 +16,7 @@ constexpr int kPatchClasses = 64;
 struct PatchClasses {
     const uint16_t* cls;                // device, one word per cell
     int n[2];                           // classes in use per group (with class 0)
+    int h_uniform;                      // every cell has H class 1
     uint8_t id[2][kPatchClasses][3];
 };
 
