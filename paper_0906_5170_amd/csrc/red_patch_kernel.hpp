@@ -26,9 +26,10 @@
 // reads four neighbours and writes three values in LDS per cell and half step
 // and recomputes every cell's coordinates; a patch of 5 x 5 cells reads and
 // writes 1.6 and computes none.  k_z piston (80 x 40, 1856 channels, 2000
-// steps, FP32): 56.5 -> 15.4 ms on the device (17.3 with the H coefficients
-// looked up, see HU); Bloch grating (48 x 60, 4096 complex channels, 2000
-// steps, FP32): 177.7 -> 59.7 ms (63.3).
+// steps, FP32): 56.5 -> 14.7 ms on the device (17.3 with the H coefficients
+// looked up, see HU; 15.4 with copies of updated fields, see upd_h); Bloch
+// grating (48 x 60, 4096 complex channels, 2000 steps, FP32): 177.7 -> 54.4 ms
+// (59.7 with the copies).
 #pragma once
 
 #include <algorithm>
@@ -157,17 +158,25 @@ __device__ __forceinline__ B3<T> class_b(const char* tab, uint32_t cls) {
     return B3<T>{q[0], q[1], q[2]};
 }
 
+// x <- a x -/+ b d in x's own register (MODE 0), or the consistent start's
+// (b / 2) d.  The three-source form matters: with v_fmac the compiler forms
+// the sum in the product's register and copies all 6 values of a cell back
+// every step.
 template <typename T, int MODE>
-__device__ __forceinline__ T upd_h(T a, T x, T b, T d) {
-    return MODE == 0 ? yee::sub(a, x, b, d) : yee::half(b, d);
+__device__ __forceinline__ void upd_h(T& x, T a, T b, T d) {
+    if constexpr (MODE == 0) yee::sub_into(x, a, b, d);
+    else x = yee::half(b, d);
 }
 template <typename T, int MODE>
-__device__ __forceinline__ T upd_e(T a, T x, T b, T d) {
-    return MODE == 0 ? yee::add(a, x, b, d) : yee::half(b, d);
+__device__ __forceinline__ void upd_e(T& x, T a, T b, T d) {
+    if constexpr (MODE == 0) yee::add_into(x, a, b, d);
+    else x = yee::half(b, d);
 }
 
-// HU: every cell of the grid has the same H class, so the H half step takes
-// its three b values as scalars (cells of a patch beyond the grid then keep
+constexpr bool patch_packs(bool lz, bool open) { return lz && !open; }
+
+// HU: every cell of the grid has the same H class, so the H half step takes its
+// three b values as scalars (cells of a patch beyond the grid then keep
 // H = 0 because E is 0 there and above and to the right of them).
 // MW: waves per SIMD the register budget is sized for (the launch keeps the
 // block within 4 MW waves).
@@ -176,14 +185,14 @@ __device__ __forceinline__ T upd_e(T a, T x, T b, T d) {
 // buffer, with two more barriers per step.  For the largest grids: 8400 cells
 // in FP64 need 18 per thread, 216 registers of field values, 180 without E_z
 // (cylindrical piston, 400 x 21, 126 channels, FP64, 6000 base steps: 291 ms
-// on the global-memory kernel, 61.4 ms here).
+// on the global-memory kernel, 57.3 ms here).
 // OPEN (k_z runs): in-plane CPML and Lorentz polarizations.  Each psi and
 // polarization belongs to one cell and so to one thread: psi of the x
 // differences and the polarizations in LDS, psi of the y differences in
 // memory (L2), loaded one row ahead, in a scratch region per block.  Two
 // waveguides (130 x 90, CPML of 20 cells on four sides, one Lorentz term, 1024
 // channels, 1000 steps, FP32): 476 ms on the split kernels, which move every
-// field through memory twice a step, 53.7 ms here (107.6 with row-major threads
+// field through memory twice a step, 51.8 ms here (107.6 with row-major threads
 // and each polarization advanced by its patch's thread: the few waves with
 // dispersive cells then held up every step for 15 us).
 template <typename T, int CX, int B, bool CYL, bool CPLX, int MW, bool LZ, bool OPEN, bool HU>
@@ -307,19 +316,26 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
     for (int k = tid; k < d.nsamp; k += nthr) sb[k] = as_global(t.basis)[d.basis_off + k];
 
     // ---- the patch's classes, neighbours and masks ---------------------
-    uint32_t cw[(NC + 1) / 2];
+    // the cells' classes, H and E in 16 bits; where the registers are short (LZ)
+    // and one H class needs no lookup, 4 bits of E class each (cylindrical
+    // piston, 400 x 21, FP64: 62.5 -> 57.3 ms; elsewhere the words cost less than
+    // their extraction: k_z piston 14.7 against 15.3 ms)
+    constexpr bool C4 = HU && patch_packs(LZ, OPEN);
+    constexpr int CPW = C4 ? 8 : 2, CB = 32 / CPW, NW = (NC + CPW - 1) / CPW;
+    uint32_t cw[NW];
     uint32_t in_m = 0;                             // cells inside the measured component's box
     const int sx0 = s_box[0], sy0 = s_box[1], sbw = s_box[2] - sx0 + 1, sbh = s_box[3] - sy0 + 1;
     uint32_t in_s = 0;                             // cells inside the source's box
 #pragma unroll
-    for (int k = 0; k < (NC + 1) / 2; ++k) cw[k] = 0;
+    for (int k = 0; k < NW; ++k) cw[k] = 0;
 #pragma unroll
     for (int r = 0; r < B; ++r)
 #pragma unroll
         for (int j = 0; j < CX; ++j) {
             const int k = r * CX + j, x = x0 + j, y = y0 + r;
             if (act && x < nx && y < ny) {
-                cw[k >> 1] |= (uint32_t)as_global(pc.cls)[y * nx + x] << (16 * (k & 1));
+                const uint32_t c = as_global(pc.cls)[y * nx + x];
+                cw[k / CPW] |= (C4 ? c >> 8 : c) << (CB * (k % CPW));
                 if (x >= mx0 && x <= s_box[6] && y >= my0 && y <= s_box[7]) in_m |= 1u << k;
                 if (x >= sx0 && x <= s_box[2] && y >= sy0 && y <= s_box[3]) in_s |= 1u << k;
             }
@@ -354,7 +370,7 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
 
     T e0[NP][B][CX], e1[NP][B][CX], e2[LZ ? 1 : NP][LZ ? 1 : B][CX], h0[NP][B][CX], h1[NP][B][CX], h2[NP][B][CX];
     // E_z of row r (this patch) as a row of values
-    auto ez_row = [&](int p, int r, T (&v)[CX]) {
+    auto ez_row = [&](int p, int r, T (&v)[CX]) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < CX; ++j) {
             if constexpr (LZ) v[j] = zme[r * CX + j];
@@ -414,7 +430,7 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
         any_l = __builtin_amdgcn_readfirstlane(__any(li >= 0)) != 0;
     }
     // y psi of row r, group grp (0: H, 1: E), into ya / yb
-    auto load_y = [&](int grp, int r) {
+    auto load_y = [&](int grp, int r) __attribute__((always_inline)) {
         if constexpr (OPEN) {
             if (any_y) {
                 const int yst = opaque(ny_t);      // no addresses kept across rows
@@ -433,7 +449,7 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
     // the x differences in the group's first and second psi slot; da, db: the
     // y differences.  The next row's y psi are loaded before this row's
     // arithmetic.
-    auto stretch = [&](int grp, int r, T (&xa)[CX], T (&xb)[CX], T (&da)[CX], T (&db)[CX]) {
+    auto stretch = [&](int grp, int r, T (&xa)[CX], T (&xb)[CX], T (&da)[CX], T (&db)[CX]) __attribute__((always_inline)) {
         if constexpr (OPEN) {
             asm volatile("" : "+v"(xq), "+v"(yq));
             if (any_y) {
@@ -481,7 +497,7 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
     // (cell, component) items, advance their P from E^m and leave there what
     // the E update of D = eps_inf E + sum P subtracts (the operations of
     // yee::lorentz_step).
-    auto share_e = [&]() {
+    auto share_e = [&]() __attribute__((always_inline)) {
         if constexpr (OPEN) {
             if (any_l) {
 #pragma unroll
@@ -496,7 +512,7 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
             }
         }
     };
-    auto polarize = [&]() {
+    auto polarize = [&]() __attribute__((always_inline)) {
         if constexpr (OPEN) {
             const int items = pa.items;
             constexpr int G = 4;                   // items of a thread in flight
@@ -538,15 +554,17 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
         }
     };
 
-    auto cls = [&](int k, int grp) { return (cw[k >> 1] >> (16 * (k & 1) + 8 * grp)) & 255u; };
+    auto cls = [&](int k, int grp) {
+        return C4 ? (cw[k / CPW] >> (CB * (k % CPW))) & 15u : (cw[k / CPW] >> (CB * (k % CPW) + 8 * grp)) & 255u;
+    };
     // the class words pass through an empty asm statement in every half step,
     // and rows through a scheduling barrier: otherwise the compiler keeps the
     // coefficients' addresses of every cell in registers across the steps, or
     // loads many rows' coefficients ahead, and spills
-    auto half_h = [&](auto mode) {
+    auto half_h = [&](auto mode) __attribute__((always_inline)) {
         constexpr int MODE = decltype(mode)::value;
 #pragma unroll
-        for (int k = 0; k < (NC + 1) / 2; ++k) asm volatile("" : "+v"(cw[k]));
+        for (int k = 0; k < NW; ++k) asm volatile("" : "+v"(cw[k]));
 #pragma unroll
         for (int r = 0; r < B; ++r) {
             __builtin_amdgcn_sched_barrier(0);
@@ -617,9 +635,10 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
                         cr = M * ex - xz;
                     }
                     const T cp = xy - yx;
-                    T vx = upd_h<T, MODE>(a_h, h0[p][r][j], b.x, cz);
-                    T vy = upd_h<T, MODE>(a_h, h1[p][r][j], b.y, cr);
-                    T vz = upd_h<T, MODE>(a_h, h2[p][r][j], b.z, cp);
+                    T &vx = h0[p][r][j], &vy = h1[p][r][j], &vz = h2[p][r][j];
+                    upd_h<T, MODE>(vx, a_h, b.x, cz);
+                    upd_h<T, MODE>(vy, a_h, b.y, cr);
+                    upd_h<T, MODE>(vz, a_h, b.z, cp);
                     if (CYL && r == 0) {
                         // order 0 alone has h_z on the axis; h_r lies outside, h_phi is 0
                         vx = axis && M != T(0) ? T(0) : vx;
@@ -629,17 +648,14 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
                     // computed here: between the branches of an open row the
                     // compiler would put the updates off to the last one
                     if constexpr (OPEN) asm volatile("" : "+v"(vx), "+v"(vy), "+v"(vz));
-                    h0[p][r][j] = vx;
-                    h1[p][r][j] = vy;
-                    h2[p][r][j] = vz;
                 }
             }
         }
     };
-    auto half_e = [&](auto mode) {
+    auto half_e = [&](auto mode) __attribute__((always_inline)) {
         constexpr int MODE = decltype(mode)::value;
 #pragma unroll
-        for (int k = 0; k < (NC + 1) / 2; ++k) asm volatile("" : "+v"(cw[k]));
+        for (int k = 0; k < NW; ++k) asm volatile("" : "+v"(cw[k]));
 #pragma unroll
         for (int r = 0; r < B; ++r) {
             __builtin_amdgcn_sched_barrier(0);
@@ -691,7 +707,8 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
             }
             T ezN[NP][CX];                         // E_z of the row, updated below
 #pragma unroll
-            for (int p = 0; p < NP; ++p) ez_row(p, r, ezN[p]);
+            for (int p = 0; p < NP; ++p)
+                if constexpr (LZ) ez_row(p, r, ezN[p]);
 #pragma unroll
             for (int j = 0; j < CX; ++j) {
                 const B3<T> b = class_b<T>(tab_e, cls(r * CX + j, 1));
@@ -719,9 +736,10 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
                                 lz = at[2];
                             }
                         }
-                    T vx = upd_e<T, MODE>(a_e, e0[p][r][j], b.x, cz);
-                    T vy = upd_e<T, MODE>(a_e, e1[p][r][j], b.y, cr);
-                    T vz = upd_e<T, MODE>(a_e, ezN[p][j], b.z, cp);
+                    T &vx = e0[p][r][j], &vy = e1[p][r][j], &vz = LZ ? ezN[p][j] : e2[LZ ? 0 : p][LZ ? 0 : r][j];
+                    upd_e<T, MODE>(vx, a_e, b.x, cz);
+                    upd_e<T, MODE>(vy, a_e, b.y, cr);
+                    upd_e<T, MODE>(vz, a_e, b.z, cp);
                     if constexpr (OPEN && MODE == 0) {
                         vx -= lx;
                         vy -= ly;
@@ -733,15 +751,12 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
                         vz = axis ? T(0) : vz;
                     }
                     if constexpr (OPEN) asm volatile("" : "+v"(vx), "+v"(vy), "+v"(vz));
-                    e0[p][r][j] = vx;
-                    e1[p][r][j] = vy;
                     if constexpr (LZ) zme[r * CX + j] = vz;
-                    else e2[p][r][j] = vz;
                 }
             }
         }
     };
-    auto publish_e = [&]() {
+    auto publish_e = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
 #pragma unroll
@@ -756,7 +771,7 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
             }
         }
     };
-    auto publish_h = [&]() {
+    auto publish_h = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
 #pragma unroll
@@ -850,7 +865,11 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
     const bool meas_h = d.meas_slot >= 3;
     const int ms = d.meas_slot % 3;
     int mbase = (y0 - my0) * mbw + (x0 - mx0);
-    const bool has_m = __any(in_m != 0);
+    uint32_t wave_m = 0;                           // cells some lane of the wave measures
+#pragma unroll
+    for (int k = 0; k < NC; ++k) wave_m |= __any((in_m >> k) & 1u) ? 1u << k : 0u;
+    wave_m = __builtin_amdgcn_readfirstlane(wave_m);
+    const bool has_m = wave_m != 0;
     const bool summing = tid >= nthr - 64;
     const int lane = tid & 63;
     const int nsamp = d.nsamp, P = d.P;
@@ -858,15 +877,28 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
         s_acc[0] = acc[2 * slot];
         s_acc[1] = acc[2 * slot + 1];
     }
-    auto put = [&](const T (&f)[B][CX]) {
+    auto put = [&](auto grp) __attribute__((always_inline)) {                     // 0: an H component, 1: an E component
         asm volatile("" : "+v"(in_m), "+v"(mbase));   // no masks or addresses kept across steps
 #pragma unroll
         for (int r = 0; r < B; ++r)
 #pragma unroll
             for (int j = 0; j < CX; ++j)
-                if ((in_m >> (r * CX + j)) & 1u) stage[mbase + r * mbw + j] = f[r][j];
+                if ((wave_m >> (r * CX + j)) & 1u) {
+                    T a, b, c;
+                    if constexpr (decltype(grp)::value == 0) {
+                        a = h0[0][r][j];
+                        b = h1[0][r][j];
+                        c = h2[0][r][j];
+                    } else {
+                        a = e0[0][r][j];
+                        b = e1[0][r][j];
+                        if constexpr (LZ) c = zme[r * CX + j];
+                        else c = e2[0][r][j];
+                    }
+                    if ((in_m >> (r * CX + j)) & 1u) stage[mbase + r * mbw + j] = ms == 0 ? a : ms == 1 ? b : c;
+                }
     };
-    auto measure = [&](int step) {
+    auto measure = [&](int step) __attribute__((always_inline)) {
         const double kt = ktab[step];
         // partial v: the samples of the threads 64 v .. 64 v + 63 of the
         // block sum the other kernels take, added in the same order
@@ -900,11 +932,7 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
         load_y(1, 0);
         if (OVERLAY) __syncthreads();
         publish_h();
-        if (meas_h && has_m) {
-            if (ms == 0) put(h0[0]);
-            else if (ms == 1) put(h1[0]);
-            else put(h2[0]);
-        }
+        if (meas_h && has_m) put(std::integral_constant<int, 0>{});
         __syncthreads();
         if (meas_h && summing) measure(step);
         half_e(std::integral_constant<int, 0>{});
@@ -912,17 +940,7 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
         if (OVERLAY) __syncthreads();
         publish_e();
         share_e();
-        if (!meas_h && has_m) {
-            if (ms == 0) put(e0[0]);
-            else if (ms == 1) put(e1[0]);
-            else if constexpr (LZ) {
-#pragma unroll
-                for (int r = 0; r < B; ++r)
-#pragma unroll
-                    for (int j = 0; j < CX; ++j)
-                        if ((in_m >> (r * CX + j)) & 1u) stage[mbase + r * mbw + j] = zme[r * CX + j];
-            } else put(e2[0]);
-        }
+        if (!meas_h && has_m) put(std::integral_constant<int, 1>{});
         __syncthreads();
         if (!meas_h && summing) measure(step);
     }
@@ -1002,6 +1020,11 @@ struct PatchShapes<double, false, true> {
 
 constexpr int kCUs = 256;
 
+// one H class, and few enough E classes for a shape that packs them
+inline bool patch_hu(const PatchClasses& pc, const PatchShape& q, bool open) {
+    return pc.h_uniform && (pc.n[1] <= 16 || !patch_packs(q.lz, open));
+}
+
 struct PatchPlan {
     int shape = -1;
     PatchArgs args{};
@@ -1060,7 +1083,7 @@ PatchPlan plan_patch(bool cyl, const Grid2D& g, int nslots, const PatchClasses& 
     PatchPlan best;
     for (int k = 0; k < SH::n; ++k) {
         const PatchShape& q = SH::s[k];
-        if (!q.any && !pc.h_uniform) continue;
+        if (!q.any && !patch_hu(pc, q, OPEN)) continue;
         // a periodic axis wraps at a patch edge
         if ((g.perx && g.nx % q.cx) || (!cyl && g.pery && g.ny % q.b)) continue;
         PatchArgs a{};
@@ -1139,7 +1162,7 @@ hipError_t patch_dispatch(T* fields, const ChanDev* ch, const int* slots, int ns
                     e = hipGetLastError();
                 }
             };
-            if (pc.h_uniform) run(&k_red_patch<T, q.cx, q.b, CYL, CPLX, q.mw, q.lz, OPEN, true>);
+            if (patch_hu(pc, q, OPEN)) run(&k_red_patch<T, q.cx, q.b, CYL, CPLX, q.mw, q.lz, OPEN, true>);
             else if constexpr (q.any) run(&k_red_patch<T, q.cx, q.b, CYL, CPLX, q.mw, q.lz, OPEN, false>);
         }
     };
