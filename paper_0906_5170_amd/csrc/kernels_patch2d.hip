@@ -1,0 +1,485 @@
+// Patch kernel of the Cartesian 2D problems: one block advances one channel,
+// every field value in a register.
+#include <algorithm>
+
+#include "../../include/casimir_fdtd.h"
+#include "lds.hpp"
+#include "patch2d.hpp"
+#include "yee_common.hpp"
+
+namespace cf {
+
+namespace {
+
+using yee::as_global;
+
+// Exchange entry of a patch: its edge row (cx values), then its edge column
+// (b values), each from a 16-byte boundary.  The stride is an odd number of
+// 16-byte words, so that consecutive threads' vector accesses spread over all
+// banks.
+template <typename T>
+constexpr int p2_up(int n) { return (n + 16 / (int)sizeof(T) - 1) / (16 / (int)sizeof(T)) * (16 / (int)sizeof(T)); }
+template <typename T>
+constexpr int p2_stride(int cx, int b) {
+    constexpr int v = 16 / (int)sizeof(T);
+    const int s = p2_up<T>(p2_up<T>(cx) + b);
+    return (s / v) % 2 ? s : s + v;
+}
+
+struct P2Lds {
+    int xe, xh, stage, sw, sb, so, total;
+};
+template <typename T>
+P2Lds p2_lds(int cx, int b, int n, const Patch2DSizes& z) {
+    P2Lds l{};
+    int off = 0;
+    auto take = [&](size_t bytes) {
+        const int at = off;
+        off = (int)((off + bytes + 15) / 16 * 16);
+        return at;
+    };
+    const size_t entries = (size_t)(n + 2) * p2_stride<T>(cx, b) * sizeof(T);   // + zeros, + a spare to write to
+    l.xe = take(entries);
+    l.xh = take(entries);
+    l.stage = take((size_t)z.box * sizeof(T));
+    l.sw = take((size_t)z.samples * z.points * 8);
+    l.sb = take((size_t)z.samples * 8);
+    l.so = take((size_t)z.samples * z.points * 2);
+    l.total = off;
+    return l;
+}
+
+// v where bit k of `bits` is set, else 0 (one bit-field extract and one and).
+__device__ __forceinline__ float masked(float v, uint32_t bits, int k) {
+    return __int_as_float(__float_as_int(v) & __builtin_amdgcn_sbfe((int)bits, k, 1));
+}
+__device__ __forceinline__ double masked(double v, uint32_t bits, int k) {
+    const int m = __builtin_amdgcn_sbfe((int)bits, k, 1);
+    return __hiloint2double(__double2hiint(v) & m, __double2loint(v) & m);
+}
+
+// One block advances one channel; thread k holds patch k of the channel's list,
+// CX x B cells with every field value in registers, over all steps of the
+// launch.  Only patches with a cell that can change are listed, so conductors
+// cost nothing; a neighbour that is not listed holds 0 and is read from an
+// entry of zeros.  Per half step a patch writes one edge row and one edge
+// column to LDS and reads its neighbours' (E: bottom row and left column; H:
+// top row and right column), with one barrier.
+//
+// Coefficients: b != 0 holds one a per field group (1, or the conductivity's
+// factor), and where b = 0 the field is 0 whatever a is, so a is a scalar.
+// Patch2DCoef says where b comes from.
+//
+// What bounds it: VALU issue (11 instructions per cell-update, 2 more per
+// masked E component) and the register file, which caps a channel's cells: 3
+// to 6 values per cell of 512 KB.  The tiles (k_rb2d) compute 64 x 64 cells
+// for 52 x 52, whole waves of conductor but not less, and reload everything
+// every 6 steps.  400 x 200 piston (14000 live cells, 448 channels, 10000
+// steps, FP32): 108.4 -> 37.4 ms on the device.  Small grids are bound by the
+// latency of a step (two LDS exchanges, two barriers): 80 x 40 piston (1040
+// live cells, FP64) 2.9 -> 0.6 us per step.  The surface sum has a wave of its
+// own, a step behind the others, with the lane's offsets and weights in
+// registers: read from LDS by an ordinary wave they took 0.9 us per step.
+template <typename T, int POL, int CX, int B, int MW, int COEF>
+__global__ __launch_bounds__(256 * MW) __attribute__((amdgpu_waves_per_eu(MW)))
+void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, const InstDev* __restrict__ insts,
+               const Patch2DInst* __restrict__ heads, const Patch2DCell* __restrict__ lists, int kmax, int mclock,
+               int src, int dst, P2Lds l) {
+    constexpr bool TM = POL == CF_POL_TM;
+    constexpr int C0 = TM ? CF_EZ : CF_EX, C1 = TM ? CF_HX : CF_EY, C2 = TM ? CF_HY : CF_HZ;
+    constexpr int NE = TM ? 1 : 2, NH = 3 - NE, NC = CX * B;
+    constexpr int S = p2_stride<T>(CX, B), RO = p2_up<T>(CX);
+    static_assert(NC <= 32, "one mask bit per cell of the patch");
+    extern __shared__ __align__(16) char lds[];
+    __shared__ int s_box[4];                       // box of the measured points
+    const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int slot = slots[blockIdx.x];
+    const ChanDev d = ch[slot];
+    const InstDev g = insts[d.inst];
+    const Patch2DInst hd = heads[d.inst];
+    const SurfTables& t = g.t;
+    const int m0 = mclock - g.start;               // instance's own step
+    const int ksteps = min(kmax, g.nsteps - m0);
+    if (m0 < 0 || ksteps <= 0) return;             // not started / finished
+    const int n = hd.n[TM ? 0 : 1];
+    const int nx = g.nx, ny = g.ny;
+    const auto lk = as_global(static_cast<const T*>(g.lut)) + d.kind * 6 * 256 * 2;   // (a, b) of (comp, id)
+
+    T* const XE = reinterpret_cast<T*>(lds + l.xe);
+    T* const XH = reinterpret_cast<T*>(lds + l.xh);
+    T* const stage = reinterpret_cast<T*>(lds + l.stage);
+    double* const sw = reinterpret_cast<double*>(lds + l.sw);
+    double* const sb = reinterpret_cast<double*>(lds + l.sb);
+    uint16_t* const so = reinterpret_cast<uint16_t*>(lds + l.so);
+
+    // ---- surface tables and the zero entries ---------------------------
+    const int npt = d.nsamp * d.P;
+    if (tid < 4) s_box[tid] = tid < 2 ? 0x7fffffff : -1;
+    for (int k = tid; k < S; k += nthr) XE[n * S + k] = XH[n * S + k] = T(0);
+    __syncthreads();
+    for (int k = tid; k < npt; k += nthr) {
+        const int c = as_global(t.gidx)[d.g_off + k], i = c % nx, j = c / nx;
+        atomicMin(&s_box[0], i);
+        atomicMin(&s_box[1], j);
+        atomicMax(&s_box[2], i);
+        atomicMax(&s_box[3], j);
+    }
+    __syncthreads();
+    const int mx0 = s_box[0], my0 = s_box[1], mx1 = s_box[2], my1 = s_box[3], mbw = mx1 - mx0 + 1;
+    for (int k = tid; k < npt; k += nthr) {
+        const int c = as_global(t.gidx)[d.g_off + k];
+        so[k] = (uint16_t)((c / nx - my0) * mbw + (c % nx - mx0));
+        sw[k] = as_global(t.gw)[d.g_off + k];
+    }
+    for (int k = tid; k < d.nsamp; k += nthr) sb[k] = as_global(t.basis)[d.basis_off + k];
+
+    if (wave == (nthr >> 6) - 1) {
+        // ---- the block's last wave: surface sum and accumulation of every
+        // step, while the others take the next one (the samples before their
+        // H half, the total before their E half)
+        const auto acc = as_global(g.acc + 2 * d.local);
+        const auto ktab = as_global(g.ktab) + m0;
+        const int nsamp = d.nsamp, P = d.P;
+        double acc_s = acc[0], acc_c = acc[1];
+        // partial v: the samples of the threads 64 v .. 64 v + 63 of the block
+        // sum the other kernels take
+        auto advance = [&](auto gather, auto& part) __attribute__((always_inline)) {
+            auto total = [&](int step, double kt) __attribute__((always_inline)) {
+                double sum = yee::wave_total(part[0]);
+#pragma unroll
+                for (int v = 1; v < (int)(sizeof(part) / sizeof(part[0])); ++v)
+                    if (v * 64 < nsamp) sum += yee::wave_total(part[v]);
+                const double G = g.dA * sum;
+                yee::neumaier(acc_s, acc_c, (g.dt * kt) * G);
+                if (lane == 0 && g.gamma) as_global(g.gamma)[(int64_t)(m0 + step) * g.gamma_stride + d.local] = G;
+            };
+            for (int step = 0; step < ksteps; ++step) {
+                const double kt = ktab[max(step - 1, 0)];
+                if (step > 0) gather();
+                __syncthreads();
+                if (step > 0) total(step - 1, kt);
+                __syncthreads();
+            }
+            const double kt = ktab[ksteps - 1];
+            gather();
+            total(ksteps - 1, kt);
+        };
+        __syncthreads();
+        constexpr int NV = 2, NPT = 4;
+        if (nsamp <= 64 * NV && P <= NPT) {
+            // the lane's samples: offsets, weights and basis values in registers
+            double w[NV][NPT], b[NV], part[NV];
+            uint32_t at[NV][NPT];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const int i = v * 64 + lane;
+                b[v] = i < nsamp ? sb[i] : 0.0;
+#pragma unroll
+                for (int q = 0; q < NPT; ++q) {
+                    const bool in = i < nsamp && q < P;
+                    at[v][q] = in ? so[i * P + q] : 0u;
+                    w[v][q] = in ? sw[i * P + q] : 0.0;
+                }
+            }
+            advance(
+                [&]() __attribute__((always_inline)) {
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) {
+                        if (v * 64 >= nsamp) break;
+                        T f[NPT];
+#pragma unroll
+                        for (int q = 0; q < NPT; ++q) f[q] = stage[at[v][q]];
+                        double x = 0.0;
+#pragma unroll
+                        for (int q = 0; q < NPT; ++q)
+                            if (q < P) x += w[v][q] * (double)f[q];
+                        part[v] = v * 64 + lane < nsamp ? 0.0 + b[v] * x : 0.0;
+                    }
+                },
+                part);
+        } else {
+            double part[4];
+            advance(
+                [&]() __attribute__((always_inline)) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        part[v] = 0.0;
+                        for (int i = v * 64 + lane; i < nsamp; i += yee::kSurfThreads) {
+                            double x = 0.0;
+                            for (int q = 0; q < P; ++q) x += sw[i * P + q] * (double)stage[so[i * P + q]];
+                            part[v] += sb[i] * x;
+                        }
+                    }
+                },
+                part);
+        }
+        if (lane == 0) {
+            acc[0] = acc_s;
+            acc[1] = acc_c;
+        }
+        return;
+    }
+
+    // ---- the patch: neighbours, coefficients, fields ----------------------
+    const bool act = tid < n;
+    Patch2DCell pc{};
+    if (act) pc = lists[hd.off[TM ? 0 : 1] + tid];
+    const int x0 = pc.x0, y0 = pc.y0;
+    const T* const er = XE + (act ? pc.right : n) * S + RO;   // E column of the patch to the right
+    const T* const eu = XE + (act ? pc.up : n) * S;           // E row of the patch above
+    const T* const hl = XH + (act ? pc.left : n) * S + RO;    // H column of the patch to the left
+    const T* const hb = XH + (act ? pc.down : n) * S;         // H row of the patch below
+    T* const xe = XE + (act ? tid : n + 1) * S;
+    T* const xh = XH + (act ? tid : n + 1) * S;
+    // a, b of the materials the cells share
+    const T a_e = lk[(C0 * 256 + hd.id_e) * 2], a_h = lk[(C2 * 256 + hd.id_h) * 2];
+    const T be = yee::lane_value(lk[(C0 * 256 + hd.id_e) * 2 + 1], 0);
+    const T bh = yee::lane_value(lk[(C2 * 256 + hd.id_h) * 2 + 1], 0);
+
+    T f0[B][CX], f1[B][CX], f2[B][CX];
+    uint32_t live[NE];                             // kMaskB: the E components that are not held at 0
+    constexpr int KE = COEF == kMaskB ? 1 : NC, KH = COEF == kRegAll ? NC : 1;
+    T ke[NE][KE], kh[NH][KH];                      // kRegE, kRegAll: b of the cells
+    uint32_t in_m = 0;                             // cells inside the measured box
+#pragma unroll
+    for (int e = 0; e < NE; ++e) live[e] = 0;
+    {
+        const auto F0 = as_global(static_cast<const T*>(src ? g.fb : g.fa)) + d.field_off;
+        const auto F1 = F0 + g.ncell;
+        const auto F2 = F1 + g.ncell;
+        const auto I0 = as_global(g.ids[C0]), I1 = as_global(g.ids[C1]), I2 = as_global(g.ids[C2]);
+#pragma unroll
+        for (int r = 0; r < B; ++r) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < CX; ++j) {
+                const int x = x0 + j, y = y0 + r, k = r * CX + j;
+                const bool in = act && x < nx && y < ny;
+                const uint32_t c = in ? (uint32_t)(y * nx + x) : 0u;
+                const T v0 = F0[c], v1 = F1[c], v2 = F2[c];
+                f0[r][j] = in ? v0 : T(0);
+                f1[r][j] = in ? v1 : T(0);
+                f2[r][j] = in ? v2 : T(0);
+                const uint32_t i0 = in ? I0[c] : kNullId, i1 = in ? I1[c] : kNullId, i2 = in ? I2[c] : kNullId;
+                const T b0 = lk[(C0 * 256 + i0) * 2 + 1];
+                if constexpr (COEF == kMaskB) {
+                    live[0] |= b0 != T(0) ? 1u << k : 0u;
+                    if constexpr (!TM) live[NE - 1] |= lk[(C1 * 256 + i1) * 2 + 1] != T(0) ? 1u << k : 0u;
+                } else {
+                    ke[0][k % KE] = b0;
+                    if constexpr (!TM) ke[NE - 1][k % KE] = lk[(C1 * 256 + i1) * 2 + 1];
+                }
+                if constexpr (COEF == kRegAll) {
+                    if constexpr (TM) kh[0][k % KH] = lk[(C1 * 256 + i1) * 2 + 1];
+                    kh[NH - 1][k % KH] = lk[(C2 * 256 + i2) * 2 + 1];
+                }
+                if (in && x >= mx0 && x <= mx1 && y >= my0 && y <= my1) in_m |= 1u << k;
+            }
+        }
+    }
+    const int mbase = (y0 - my0) * mbw + x0 - mx0;
+    // the wave's cells inside the box, as a scalar
+    uint32_t wave_m = in_m;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) wave_m |= __shfl_xor(wave_m, off, 64);
+    wave_m = __builtin_amdgcn_readfirstlane(wave_m);
+    const int ms = d.meas_slot;
+
+    auto b_e = [&](int e, int k) __attribute__((always_inline)) -> T {
+        if constexpr (COEF == kMaskB) return masked(be, live[e], k);
+        else return ke[e][k % KE];
+    };
+    auto b_h = [&](int h, int k) __attribute__((always_inline)) -> T {
+        if constexpr (COEF == kRegAll) return kh[h][k % KH];
+        else return bh;
+    };
+    auto half_h = [&]() __attribute__((always_inline)) {
+        T eR[B], eU[CX];
+#pragma unroll
+        for (int r = 0; r < B; ++r) eR[r] = er[r];
+#pragma unroll
+        for (int r = 0; r < B; ++r) {
+            __builtin_amdgcn_sched_barrier(0);     // rows in turn: the registers hold one row's temporaries
+            if (r + 2 == B || B == 1)
+#pragma unroll
+                for (int j = 0; j < CX; ++j) eU[j] = eu[j];
+#pragma unroll
+            for (int j = 0; j < CX; ++j) {
+                const int k = r * CX + j;
+                if constexpr (TM) {
+                    const T ez = f0[r][j];
+                    const T ezr = j + 1 < CX ? f0[r][(j + 1) % CX] : eR[r];
+                    const T ezu = r + 1 < B ? f0[(r + 1) % B][j] : eU[j];
+                    yee::sub_into(f1[r][j], a_h, b_h(0, k), ezu - ez);
+                    yee::sub_into(f2[r][j], a_h, b_h(NH - 1, k), ez - ezr);
+                } else {
+                    const T ex = f0[r][j], ey = f1[r][j];
+                    const T eyr = j + 1 < CX ? f1[r][(j + 1) % CX] : eR[r];
+                    const T exu = r + 1 < B ? f0[(r + 1) % B][j] : eU[j];
+                    yee::sub_into(f2[r][j], a_h, b_h(0, k), (eyr - ey) - (exu - ex));
+                }
+            }
+        }
+    };
+    auto half_e = [&]() __attribute__((always_inline)) {
+        if constexpr (COEF == kMaskB)   // no b values kept across steps
+#pragma unroll
+            for (int e = 0; e < NE; ++e) asm volatile("" : "+v"(live[e]));
+        T hL[B], hD[CX];
+#pragma unroll
+        for (int j = 0; j < CX; ++j) hD[j] = hb[j];
+#pragma unroll
+        for (int r = 0; r < B; ++r) hL[r] = hl[r];
+        // the row and column that wait for the neighbours' values last
+#pragma unroll
+        for (int r = B - 1; r >= 0; --r) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = CX - 1; j >= 0; --j) {
+                const int k = r * CX + j;
+                if constexpr (TM) {
+                    const T hx = f1[r][j], hy = f2[r][j];
+                    const T hyl = j > 0 ? f2[r][(j + CX - 1) % CX] : hL[r];
+                    const T hxd = r > 0 ? f1[(r + B - 1) % B][j] : hD[j];
+                    yee::add_into(f0[r][j], a_e, b_e(0, k), (hy - hyl) - (hx - hxd));
+                } else {
+                    const T hz = f2[r][j];
+                    const T hzl = j > 0 ? f2[r][(j + CX - 1) % CX] : hL[r];
+                    const T hzd = r > 0 ? f2[(r + B - 1) % B][j] : hD[j];
+                    yee::add_into(f0[r][j], a_e, b_e(0, k), hz - hzd);
+                    yee::sub_into(f1[r][j], a_e, b_e(NE - 1, k), hz - hzl);
+                }
+            }
+        }
+    };
+    // bottom E row and left E column; top H row and right H column
+    auto publish_e = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < CX; ++j) xe[j] = f0[0][j];
+#pragma unroll
+        for (int r = 0; r < B; ++r) xe[RO + r] = TM ? f0[r][0] : f1[r][0];
+    };
+    auto publish_h = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < CX; ++j) xh[j] = TM ? f1[B - 1][j] : f2[B - 1][j];
+#pragma unroll
+        for (int r = 0; r < B; ++r) xh[RO + r] = f2[r][CX - 1];
+    };
+    auto put = [&]() __attribute__((always_inline)) {
+        asm volatile("" : "+v"(in_m));             // no masks kept across steps
+#pragma unroll
+        for (int r = 0; r < B; ++r)
+#pragma unroll
+            for (int j = 0; j < CX; ++j)
+                if ((wave_m >> (r * CX + j)) & 1u) {
+                    const T a = f0[r][j], b = f1[r][j], c = f2[r][j];
+                    if ((in_m >> (r * CX + j)) & 1u) stage[mbase + r * mbw + j] = ms == 0 ? a : ms == 1 ? b : c;
+                }
+    };
+    publish_e();
+    __syncthreads();
+    for (int step = 0; step < ksteps; ++step) {
+        half_h();
+        publish_h();
+        __syncthreads();
+        half_e();
+        publish_e();
+        if (wave_m) put();
+        __syncthreads();
+    }
+    const auto F0 = as_global(static_cast<T*>(dst ? g.fb : g.fa)) + d.field_off;
+    const auto F1 = F0 + g.ncell;
+    const auto F2 = F1 + g.ncell;
+#pragma unroll
+    for (int r = 0; r < B; ++r)
+#pragma unroll
+        for (int j = 0; j < CX; ++j)
+            if (act && x0 + j < nx && y0 + r < ny) {
+                const uint32_t c = (uint32_t)((y0 + r) * nx + x0 + j);
+                F0[c] = f0[r][j];
+                F1[c] = f1[r][j];
+                F2[c] = f2[r][j];
+            }
+}
+
+// Shapes (columns, rows, waves per SIMD of the register budget, coefficients).
+// None spills in the step loop; 128 registers hold up to 32 cells with masks,
+// 20 with E values, 12 with all values (12, 8, 6 in FP64).
+template <typename T>
+struct P2Shapes;
+template <>
+struct P2Shapes<float> {
+    static constexpr int n = 10;
+    static constexpr Patch2DShape s[n] = {{8, 4, 4, kMaskB},  {6, 5, 4, kMaskB}, {5, 5, 4, kMaskB}, {5, 4, 4, kRegE},
+                                          {4, 4, 4, kRegE},   {4, 2, 4, kRegE},  {2, 2, 4, kRegE},  {4, 3, 4, kRegAll},
+                                          {3, 2, 4, kRegAll}, {2, 2, 4, kRegAll}};
+};
+template <>
+struct P2Shapes<double> {
+    static constexpr int n = 6;
+    static constexpr Patch2DShape s[n] = {{4, 3, 4, kMaskB}, {4, 2, 4, kRegE},   {3, 2, 4, kRegE},
+                                          {2, 2, 4, kRegE},  {3, 2, 4, kRegAll}, {2, 2, 4, kRegAll}};
+};
+
+template <typename T, int V>
+hipError_t p2_launch(int shape, int pol, int threads, const P2Lds& l, const ChanDev* ch, const int* slots, int nslots,
+                     const InstDev* inst, const Patch2DInst* heads, const Patch2DCell* lists, int kmax, int m, int src,
+                     int dst, hipStream_t s) {
+    if constexpr (V >= P2Shapes<T>::n) {
+        return hipErrorInvalidValue;
+    } else {
+        if (shape != V)
+            return p2_launch<T, V + 1>(shape, pol, threads, l, ch, slots, nslots, inst, heads, lists, kmax, m, src,
+                                       dst, s);
+        constexpr Patch2DShape q = P2Shapes<T>::s[V];
+        if (threads > 256 * q.mw) return hipErrorInvalidValue;
+        auto run = [&](auto kernel) -> hipError_t {
+            if (!lds_allow(reinterpret_cast<const void*>(kernel), (size_t)l.total)) return hipErrorInvalidValue;
+            hipLaunchKernelGGL(kernel, dim3(nslots), dim3(threads), l.total, s, ch, slots, inst, heads, lists, kmax, m,
+                               src, dst, l);
+            return hipGetLastError();
+        };
+        return pol == CF_POL_TM ? run(&k_patch2d<T, CF_POL_TM, q.cx, q.b, q.mw, q.coef>)
+                                : run(&k_patch2d<T, CF_POL_TE, q.cx, q.b, q.mw, q.coef>);
+    }
+}
+
+}  // namespace
+
+template <typename T>
+int patch2d_shapes(Patch2DShape* out, int max) {
+    const int n = std::min(P2Shapes<T>::n, max);
+    for (int k = 0; k < n; ++k) out[k] = P2Shapes<T>::s[k];
+    return n;
+}
+
+template <typename T>
+size_t patch2d_lds(const Patch2DShape& q, int n, const Patch2DSizes& z) {
+    return (size_t)p2_lds<T>(q.cx, q.b, n, z).total;
+}
+
+template <typename T>
+hipError_t launch_patch2d(int shape, int pol, const ChanDev* ch, const int* slots, int nslots, const InstDev* inst,
+                          const Patch2DInst* heads, const Patch2DCell* lists, int n, const Patch2DSizes& z, int kmax,
+                          int m, int src, int dst, hipStream_t s) {
+    if (nslots <= 0) return hipSuccess;
+    if (shape < 0 || shape >= P2Shapes<T>::n || n < 0 || kmax < 1) return hipErrorInvalidValue;
+    const Patch2DShape& q = P2Shapes<T>::s[shape];
+    // a wave of its own takes the surface sums
+    const int threads = (n + 63) / 64 * 64 + 64;
+    return p2_launch<T, 0>(shape, pol, threads, p2_lds<T>(q.cx, q.b, n, z), ch, slots, nslots, inst, heads, lists, kmax,
+                           m, src, dst, s);
+}
+
+#define CF_INSTANTIATE(T)                                                                                          \
+    template int patch2d_shapes<T>(Patch2DShape*, int);                                                            \
+    template size_t patch2d_lds<T>(const Patch2DShape&, int, const Patch2DSizes&);                                 \
+    template hipError_t launch_patch2d<T>(int, int, const ChanDev*, const int*, int, const InstDev*,               \
+                                          const Patch2DInst*, const Patch2DCell*, int, const Patch2DSizes&, int,   \
+                                          int, int, int, hipStream_t);
+CF_INSTANTIATE(float)
+CF_INSTANTIATE(double)
+#undef CF_INSTANTIATE
+
+}  // namespace cf

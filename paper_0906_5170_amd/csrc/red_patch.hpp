@@ -3,6 +3,7 @@
 #pragma once
 
 #include "device.hpp"
+#include "lds.hpp"
 #include "red_span.hpp"
 
 namespace cf {
@@ -38,14 +39,6 @@ struct PatchOpen {
     void* scratch;
     int64_t scratch_bytes;
 };
-
-// LDS bytes a block may take on the current device.
-inline size_t device_lds_limit() {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 65536;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return 65536;
-    return (size_t)v;
-}
 
 // As launch_red_resident_span, for grids a patch shape covers: *launched
 // tells whether one did (nothing is launched otherwise).  slots == nullptr:

@@ -33,8 +33,6 @@
 #pragma once
 
 #include <algorithm>
-#include <map>
-#include <mutex>
 #include <type_traits>
 
 #include "../../include/casimir_fdtd.h"
@@ -121,24 +119,6 @@ struct PatchArgs {
     double lor[4][13];           // [row][1 / eps, (c1, c2, c3) per term]
     uint8_t lrow[kPatchClasses][3];
 };
-
-// s of lane l plus s of lane l + off for off = 32 .. 1, as
-// yee::wave_partial_store orders it: the wave's sum in lane 0.
-template <int N>
-__device__ __forceinline__ double row_shl(double v) {
-    const int lo = __double2loint(v), hi = __double2hiint(v);
-    return __hiloint2double(__builtin_amdgcn_mov_dpp(hi, 0x100 | N, 0xf, 0xf, true),
-                            __builtin_amdgcn_mov_dpp(lo, 0x100 | N, 0xf, 0xf, true));
-}
-__device__ __forceinline__ double wave_total(double s) {
-    s += __shfl_down(s, 32, 64);
-    s += __shfl_down(s, 16, 64);
-    s += row_shl<8>(s);
-    s += row_shl<4>(s);
-    s += row_shl<2>(s);
-    s += row_shl<1>(s);
-    return s;
-}
 
 // A uniform value the compiler cannot see through.
 __device__ __forceinline__ int opaque(int v) {
@@ -913,7 +893,7 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
                 for (int q = 0; q < P; ++q) x += sw[i * P + q] * (double)stage[so[i * P + q]];
                 s += sb[i] * x;
             }
-            s = wave_total(s);
+            s = yee::wave_total(s);
             total = v == 0 ? s : total + s;
         }
         if (lane == 0) {
@@ -1117,25 +1097,6 @@ PatchPlan plan_patch(bool cyl, const Grid2D& g, int nslots, const PatchClasses& 
     return best;
 }
 
-// Dynamic LDS above 64 KB needs the kernel's attribute raised first (a cap,
-// only ever raised, under a lock); false when the runtime refuses.
-bool patch_lds_ok(const void* kernel, size_t lds) {
-    if (lds <= 65536) return true;
-    static std::mutex mu;
-    static std::map<std::pair<int, const void*>, size_t> cap;
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return false;
-    std::lock_guard<std::mutex> lk(mu);
-    size_t& c = cap[{dev, kernel}];
-    if (lds <= c) return true;
-    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    c = lds;
-    return true;
-}
-
 template <typename T, bool CYL, bool CPLX, bool OPEN>
 hipError_t patch_dispatch(T* fields, const ChanDev* ch, const int* slots, int nslots, const Grid2D& g,
                           const RedOrders& ord, const RedSpan& sp, const SurfTables& t, const PatchClasses& pc,
@@ -1152,7 +1113,7 @@ hipError_t patch_dispatch(T* fields, const ChanDev* ch, const int* slots, int ns
             constexpr PatchShape q = SH::s[V];
             if (V != pl.shape) return;
             const auto run = [&](auto kernel) {
-                if (!patch_lds_ok(reinterpret_cast<const void*>(kernel), pl.args.lds.total)) return;
+                if (!lds_allow(reinterpret_cast<const void*>(kernel), pl.args.lds.total)) return;
                 *launched = true;
                 // an open run's launches take as many channels as there are scratch regions
                 for (int first = 0; first < nslots && e == hipSuccess; first += pl.blocks) {

@@ -101,6 +101,8 @@ struct StencilTiming {
     int launches = 0;
     int variant = -1;
     int steps_run = -1;     // time steps run (-1: all of opts.n_steps)
+    int launch_steps = 0;   // 2D patch kernel: steps of a launch (0: not used),
+    double live_cells[2] = {0, 0};   // and cells it advances per channel and polarization slot
 };
 
 // Time-convergence stop: every `every` steps the partial force F(T') is

@@ -157,6 +157,36 @@ __device__ __forceinline__ void wave_partial_store(double s, double* red) {
     if ((threadIdx.x & 63) == 0 && threadIdx.x < kSurfThreads) red[threadIdx.x >> 6] = s;
 }
 
+// The same sum in lane 0 with fewer LDS permutes, for waves that hold a whole
+// partial: s of lane l plus s of lane l + off, off = 32 .. 1.
+template <int N>
+__device__ __forceinline__ double row_shl(double v) {
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(hi, 0x100 | N, 0xf, 0xf, true),
+                            __builtin_amdgcn_mov_dpp(lo, 0x100 | N, 0xf, 0xf, true));
+}
+// s of the other half (row of 16) in the lanes of the lower one: the swap of
+// two copies leaves them every lower and every upper part.
+__device__ __forceinline__ double upper_half(double v) {
+    const uint32_t lo = (uint32_t)__double2loint(v), hi = (uint32_t)__double2hiint(v);
+    return __hiloint2double((int)__builtin_amdgcn_permlane32_swap(hi, hi, false, false)[1],
+                            (int)__builtin_amdgcn_permlane32_swap(lo, lo, false, false)[1]);
+}
+__device__ __forceinline__ double upper_row(double v) {
+    const uint32_t lo = (uint32_t)__double2loint(v), hi = (uint32_t)__double2hiint(v);
+    return __hiloint2double((int)__builtin_amdgcn_permlane16_swap(hi, hi, false, false)[1],
+                            (int)__builtin_amdgcn_permlane16_swap(lo, lo, false, false)[1]);
+}
+__device__ __forceinline__ double wave_total(double s) {
+    s += upper_half(s);
+    s += upper_row(s);
+    s += row_shl<8>(s);
+    s += row_shl<4>(s);
+    s += row_shl<2>(s);
+    s += row_shl<1>(s);
+    return s;
+}
+
 // Gamma sum of one channel by the first kSurfThreads threads of a block:
 // thread t takes samples t, t + kSurfThreads, ...; sum_p w X in FP64 per
 // sample, weighted by the basis row; then a fixed-order reduction over the
