@@ -239,13 +239,28 @@ void patch2d_sizes(const std::vector<cf::ChanDev>& dev, const std::vector<int32_
     }
 }
 
+// The shapes of a problem's polarizations (used: its channels per polarization
+// slot; launched with it: the channels `together`), or false when one has none.
+bool patch2d_pick(const cf::Patch2DSet& set, int precision, const int used[2], const int together[2],
+                  const cf::Patch2DSizes& z, std::array<int, 2>& shape) {
+    const size_t lim = cf::device_lds_limit();
+    for (int q = 0; q < 2; ++q) {
+        shape[q] = used[q] > 0 ? cf::patch2d_choose(set, precision, q, together[q], z, lim) : -1;
+        if (used[q] > 0 && shape[q] < 0) return false;
+    }
+    return true;
+}
+
 // Heads and lists of a launch's instances as the kernel reads them: instance
-// i's lists are those of sets[i] for shape[q] (polarization slot q; -1: none).
-std::vector<char> patch2d_blob(const std::vector<const cf::Patch2DSet*>& sets, const int shape[2]) {
+// i's lists are those of sets[i] for shape[i][q] (polarization slot q; -1: none).
+std::vector<char> patch2d_blob(const std::vector<const cf::Patch2DSet*>& sets,
+                               const std::vector<std::array<int, 2>>& shapes) {
     std::vector<cf::Patch2DInst> heads(sets.size());
     std::vector<cf::Patch2DCell> cells;
     for (size_t i = 0; i < sets.size(); ++i) {
+        const std::array<int, 2>& shape = shapes[i];
         heads[i] = cf::Patch2DInst{};
+        if (!sets[i]) continue;
         heads[i].id_e = sets[i]->id_e;
         heads[i].id_h = sets[i]->id_h;
         for (int q = 0; q < 2; ++q) {
@@ -1565,17 +1580,14 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
     if (variant >= 0 && o.tile_variant == 0) {
         patches = cached_patches(p, o.precision);
         patch2d_sizes(st.dev, st.gidx, p.nx, psizes);
-        const size_t lim = cf::device_lds_limit();
         for (const Wave& w : st.waves) {
-            std::array<int, 2> sh{-1, -1};
-            for (int q = 0; q < 2; ++q) {
-                const int n = q == 0 ? w.n_tm : w.n_te;
-                if (n > 0) sh[q] = cf::patch2d_choose(*patches, o.precision, q, n, psizes, lim);
-                if (n > 0 && sh[q] < 0) patches = nullptr;
-                if (!patches) break;
+            std::array<int, 2> sh;
+            const int num[2] = {w.n_tm, w.n_te};
+            if (!patch2d_pick(*patches, o.precision, num, num, psizes, sh)) {
+                patches = nullptr;
+                break;
             }
-            if (!patches) break;
-            host_patches.push_back(patch2d_blob({patches.get()}, sh.data()));
+            host_patches.push_back(patch2d_blob({patches.get()}, {sh}));
             pshape.push_back(sh);
             if (host_patches.back().size() > field_bytes) {
                 patches = nullptr;
@@ -2180,8 +2192,9 @@ BatchLayout batch_layout(const BatchPlan& B, const cf_opts& o) {
 
 template <typename T>
 cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, char* ws, hipStream_t s,
-                    std::vector<double>& acc_out, double* device_ms, StencilTiming* timing) {
+                    std::vector<double>& acc_out, double* device_ms, std::vector<StencilTiming>& timing) {
     const int n = (int)B.probs.size();
+    timing.assign(n, StencilTiming());
     std::deque<std::vector<uint8_t>> keep8;
     std::deque<std::vector<T>> keepT;
     std::deque<std::vector<double>> keepD;
@@ -2284,7 +2297,66 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
         }
         return make_work(slots, tl, st);
     };
-    const int n_tm = (int)B.tm.size(), n_te = (int)B.te.size();
+    // Problems whose live cells fit a compute unit's registers go to the 2D
+    // patch kernel (see run), every shape's channels in one launch per
+    // polarization, the longest first; the rest to the tiles.  The patch lists
+    // lie in the second field array of such a problem, the channel lists behind
+    // the tiles' work items.
+    std::vector<std::shared_ptr<const cf::Patch2DSet>> keep_sets(n);
+    std::vector<const cf::Patch2DSet*> psets(n, nullptr);
+    std::vector<std::array<int, 2>> pshapes(n, {-1, -1});
+    std::vector<char> blob;
+    size_t blob_at = 0;                                // field offset of the lists in Bf
+    struct PatchGroup {
+        int shape, n;                                  // n: longest patch list
+        std::vector<std::pair<double, int>> slots;     // (cells, slot)
+        size_t at;                                     // byte offset of its channel list
+    };
+    std::map<int, PatchGroup> groups[2];               // per polarization slot: by shape
+    std::vector<int> tiles[2], patch_slots[2];         // slots per path
+    cf::Patch2DSizes psizes{1, 1, 1};
+    if (o.tile_variant == 0) {
+        const int together[2] = {(int)B.tm.size(), (int)B.te.size()};
+        for (int i = 0; i < n; ++i) patch2d_sizes(B.st[i].dev, B.st[i].gidx, B.probs[i]->nx, psizes);
+        size_t room = 0;
+        for (int i = 0; i < n; ++i) {
+            keep_sets[i] = cached_patches(*B.probs[i], o.precision);
+            const int used[2] = {B.inst_tm_n[i], B.inst_te_n[i]};
+            if (!patch2d_pick(*keep_sets[i], o.precision, used, together, psizes, pshapes[i])) {
+                pshapes[i] = {-1, -1};
+                continue;
+            }
+            psets[i] = keep_sets[i].get();
+            const size_t elems = (i + 1 < n ? B.field_off[i + 1] : B.field_elems) - B.field_off[i];
+            if (elems * sizeof(T) > room) {
+                room = elems * sizeof(T);
+                blob_at = B.field_off[i];
+            }
+        }
+        blob = patch2d_blob(psets, pshapes);
+        if (blob.size() > room) std::fill(psets.begin(), psets.end(), nullptr);
+    }
+    for (int q = 0; q < 2; ++q) {
+        for (int sl : q == 0 ? B.tm : B.te) {
+            const int i = B.dev[sl].inst;
+            if (!psets[i]) {
+                tiles[q].push_back(sl);
+                continue;
+            }
+            const int v = pshapes[i][q];
+            PatchGroup& gr = groups[q].try_emplace(v, PatchGroup{v, 0, {}, 0}).first->second;
+            gr.n = std::max(gr.n, (int)psets[i]->lists[q][v].size());
+            gr.slots.emplace_back(-psets[i]->cells[q][v], sl);
+        }
+        for (auto& kv : groups[q]) {
+            std::stable_sort(kv.second.slots.begin(), kv.second.slots.end(),
+                             [](const auto& a, const auto& b) { return a.first < b.first; });
+            kv.second.at = patch_slots[q].size() * sizeof(int);
+            for (const auto& c : kv.second.slots) patch_slots[q].push_back(c.second);
+        }
+    }
+    const bool any_patch = !groups[0].empty() || !groups[1].empty();
+    const int n_tm = (int)tiles[0].size(), n_te = (int)tiles[1].size();
     hipError_t err = hipSuccess;
     hipEvent_t e0, e1;
     CF_HIP(hipEventCreate(&e0));
@@ -2303,9 +2375,10 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
         for (int v : B.variants_ok)
             if (v == o.tile_variant - 1) variant = v;
         if (variant < 0) variant = B.variants_ok[0];
-    } else if (B.variants_ok.size() > 1) {
+    } else if (B.variants_ok.size() > 1 && n_tm + n_te > 0) {
         std::ostringstream k;
         k << "batch fp" << (sizeof(T) == 8 ? 64 : 32) << " n" << n << " ch" << B.C << " cells" << B.field_elems;
+        if (any_patch) k << " tiled" << n_tm + n_te;
         int cached;
         if (tune_lookup(k.str(), &cached) &&
             std::find(B.variants_ok.begin(), B.variants_ok.end(), cached) != B.variants_ok.end()) {
@@ -2315,7 +2388,7 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
             for (int v : B.variants_ok) {
                 keepI.push_back(insts_for(v));
                 BSTEP(up(L.inst, keepI.back().data(), n * sizeof(cf::InstDev)));
-                const std::vector<int>& sl = n_tm >= n_te ? B.tm : B.te;
+                const std::vector<int>& sl = n_tm >= n_te ? tiles[0] : tiles[1];
                 keepW.push_back(work_for(v, sl));
                 BSTEP(up(L.work, keepW.back().data(), keepW.back().size() * sizeof(cf::WorkItem)));
                 const int kh = B.st[0].shapes[v].kh, nw = (int)keepW.back().size();
@@ -2336,20 +2409,38 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
             tune_store(k.str(), variant);
         }
     }
-    timing->variant = variant;
     {
         const int kh = B.st[0].shapes[variant].kh;
+        const int patch_steps = std::min({std::max(256, (o.n_steps + 15) / 16), o.n_steps, 1 << 14});
+        for (int i = 0; i < n; ++i) {
+            timing[i].variant = variant;
+            if (!psets[i]) continue;
+            timing[i].launch_steps = patch_steps;
+            for (int q = 0; q < 2; ++q)
+                if (pshapes[i][q] >= 0) timing[i].live_cells[q] = psets[i]->cells[q][pshapes[i][q]];
+        }
         keepI.push_back(insts_for(variant));
         BSTEP(up(L.inst, keepI.back().data(), n * sizeof(cf::InstDev)));
-        keepW.push_back(work_for(variant, B.tm));
+        keepW.push_back(work_for(variant, tiles[0]));
         const int nw_tm = (int)keepW.back().size();
         BSTEP(up(L.work, keepW.back().data(), nw_tm * sizeof(cf::WorkItem)));
-        keepW.push_back(work_for(variant, B.te));
+        keepW.push_back(work_for(variant, tiles[1]));
         const int nw_te = (int)keepW.back().size();
         BSTEP(up(L.work + B.work_items * sizeof(cf::WorkItem), keepW.back().data(), nw_te * sizeof(cf::WorkItem)));
+        const size_t region = B.work_items * sizeof(cf::WorkItem);
+        const size_t pat[2] = {L.work + nw_tm * sizeof(cf::WorkItem), L.work + region + nw_te * sizeof(cf::WorkItem)};
+        for (int q = 0; q < 2; ++q) {
+            const size_t bytes = patch_slots[q].size() * sizeof(int);
+            if (pat[q] + bytes > L.work + (q + 1) * region) BSTEP(hipErrorInvalidValue);
+            BSTEP(up(pat[q], patch_slots[q].data(), bytes));
+        }
         BSTEP(hipMemsetAsync(dacc, 0, (size_t)B.C * 2 * 8, s));
         BSTEP(hipMemsetAsync(A, 0, fbytes, s));
-        BSTEP(hipMemsetAsync(Bf, 0, fbytes, s));   // cells the fused kernel skips stay zero in both arrays
+        if (n_tm + n_te > 0)
+            BSTEP(hipMemsetAsync(Bf, 0, fbytes, s));   // cells the fused kernel skips stay zero in both arrays
+        const cf::Patch2DInst* heads = reinterpret_cast<const cf::Patch2DInst*>(Bf + blob_at);
+        const cf::Patch2DCell* cells = reinterpret_cast<const cf::Patch2DCell*>(heads + n);
+        if (any_patch) BSTEP(up(L.fB + blob_at * sizeof(T), blob.data(), blob.size()));
         BSTEP(hipEventRecord(e0, s));
         BSTEP(cf::launch_kick<T>(A, dch, dl, B.C, B.max_uniq, tabs, s));
         for (int i = 0; i < n; ++i) {
@@ -2363,27 +2454,46 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
             BSTEP(cf::launch_e2d<T>(CF_POL_TE, 1, A, dch, te, B.inst_te_n[i], g, lut, s));
         }
         int launches = 0;
-        // the TE launches on a second stream (a parallel branch of the graph
-        // when captured), so that each polarization's launch tail overlaps
-        // the other's
+        // each polarization of each path on a stream of its own (parallel
+        // branches of the graph when captured), so that one's launch tails
+        // overlap the others'
         SideStreams side;
-        const bool split_pol = n_tm > 0 && n_te > 0 && !(o.flags & CF_FLAG_TIME_STENCIL);
-        if (split_pol) BSTEP(side.create(1));
+        int n_stream = 0, lane[2][2];                  // [path: tiles, patches][polarization]
+        for (int k = 0; k < 2; ++k)
+            for (int q = 0; q < 2; ++q) {
+                const bool used = k == 0 ? !tiles[q].empty() : !groups[q].empty();
+                lane[k][q] = used && !(o.flags & CF_FLAG_TIME_STENCIL) ? n_stream++ : 0;
+            }
+        const bool split_pol = n_stream > 1;
+        if (split_pol) BSTEP(side.create(n_stream - 1));
         BSTEP(graph.begin());
         {
             const hipStream_t ls = graph.launch_stream(s);
             hipError_t body = split_pol ? side.open(ls) : hipSuccess;
+            auto on = [&](int k, int q) { return lane[k][q] == 0 ? ls : side.s[lane[k][q] - 1]; };
             if (body == hipSuccess)
                 body = [&]() -> hipError_t {
-                    const hipStream_t ts = split_pol ? side.s[0] : ls;
+                    for (int m = 0; m < o.n_steps; m += patch_steps)
+                        for (int q = 0; q < 2; ++q)
+                            for (const auto& kv : groups[q]) {
+                                const PatchGroup& gr = kv.second;
+                                const hipError_t e = cf::launch_patch2d<T>(
+                                    gr.shape, q == 0 ? CF_POL_TM : CF_POL_TE, dch,
+                                    reinterpret_cast<const int*>(ws + pat[q] + gr.at), (int)gr.slots.size(), dinst,
+                                    heads, cells, gr.n, psizes, std::min(patch_steps, o.n_steps - m), m, 0, 0,
+                                    on(1, q));
+                                if (e != hipSuccess) return e;
+                                ++launches;
+                            }
                     int parity = 0;
-                    for (int m = 0; m < o.n_steps; m += kh) {
+                    for (int m = 0; m < o.n_steps && n_tm + n_te > 0; m += kh) {
                         hipError_t e = hipSuccess;
                         if (n_tm)
-                            e = cf::launch_tb2d<T>(variant, CF_POL_TM, dch, dwork, nw_tm, dinst, kh, m, parity, ls);
+                            e = cf::launch_tb2d<T>(variant, CF_POL_TM, dch, dwork, nw_tm, dinst, kh, m, parity,
+                                                   on(0, 0));
                         if (e == hipSuccess && n_te)
                             e = cf::launch_tb2d<T>(variant, CF_POL_TE, dch, dwork + B.work_items, nw_te, dinst, kh, m,
-                                                   parity, ts);
+                                                   parity, on(0, 1));
                         if (e != hipSuccess) return e;
                         launches += (n_tm > 0) + (n_te > 0);
                         parity ^= 1;
@@ -2391,12 +2501,12 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
                     return hipSuccess;
                 }();
             if (split_pol && !side.s.empty()) {
-                const hipError_t ec = side.close(ls);   // joins the branch before the capture ends
+                const hipError_t ec = side.close(ls);   // joins the branches before the capture ends
                 if (body == hipSuccess) body = ec;
             }
             BSTEP(graph.end(s, body));
         }
-        timing->launches = launches;
+        for (StencilTiming& t : timing) t.launches = launches;
         BSTEP(hipEventRecord(e1, s));
         BSTEP(hipEventSynchronize(e1));
         float ms = 0;
@@ -2705,16 +2815,16 @@ static cf_status cf_batch_solve_impl(cf_problem* const* probs, int n, const cf_o
         hipStream_t s = static_cast<hipStream_t>(o->stream);
         std::vector<double> acc;
         double ms = 0;
-        StencilTiming tim;
-        cf_status rs = o->precision == CF_FP64 ? run_batch<double>(B, L, oo, ws, s, acc, &ms, &tim)
-                                               : run_batch<float>(B, L, oo, ws, s, acc, &ms, &tim);
+        std::vector<StencilTiming> tim;
+        cf_status rs = o->precision == CF_FP64 ? run_batch<double>(B, L, oo, ws, s, acc, &ms, tim)
+                                               : run_batch<float>(B, L, oo, ws, s, acc, &ms, tim);
         if (owned) (void)hipFree(owned);
         if (rs != CF_OK) return rs;
         for (size_t k = 0; k < fused_idx.size(); ++k) {
             const int i = fused_idx[k];
             const size_t Ci = B.chans[k].size();
             std::vector<double> ai(acc.begin() + 2 * (size_t)B.base[k], acc.begin() + 2 * ((size_t)B.base[k] + Ci));
-            const bool finite = fill_result(*B.probs[k], B.chans[k], ai, {}, oo, ms, tim, B.st[k], &outs[i]);
+            const bool finite = fill_result(*B.probs[k], B.chans[k], ai, {}, oo, ms, tim[k], B.st[k], &outs[i]);
             if (!finite) return fail(CF_E_NONFINITE, "a force accumulator is not finite");
             done[i] = true;
         }

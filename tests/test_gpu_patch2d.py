@@ -104,3 +104,19 @@ def test_waves_graph_and_stop(cf):
     assert 50 < s["n_steps_run"] < wl.n_steps
     t = solve(p, wl.replace(n_steps=s["n_steps_run"]), "fp32")
     assert np.array_equal(t["per_channel"], s["per_channel"])
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("graph", [False, True])
+def test_batch(cf, graph, precision):
+    """A batch of problems of both kinds (patches of several shapes, tiles)
+    gives every problem what its own split solve gives, twice."""
+    wls = [problem(13, 14, W), problem(97, 83, W, "filled"), problem(260, 200, W), problem(61, 37, W, "mixed"),
+           problem(24, 31, ("periodic", "pec", "periodic")), problem(61, 37, W)]
+    wls = [w.replace(n_steps=70) for w in wls]
+    probs = [cf.Problem.from_workload(w) for w in wls]
+    o = dict(sigma=0.9, courant=0.5, n_steps=70, pol="TM+TE", kernel="general", precision=precision)
+    for some in (probs, probs[:2], probs[2:3], probs):
+        for r, p in zip(cf.batch_solve(some, graph=graph, **o), some):
+            b = p.solve(split=True, **o)
+            assert r["fused"] and np.array_equal(r["per_channel"], b["per_channel"])
