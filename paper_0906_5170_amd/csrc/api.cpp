@@ -219,8 +219,6 @@ std::shared_ptr<const cf::Patch2DSet> cached_patches(const cf::Problem& p, int p
     return set;
 }
 
-// Largest box of measured points and largest samples x points of the channels
-// of `dev` (a problem of row length nx).
 void patch2d_sizes(const std::vector<cf::ChanDev>& dev, const std::vector<int32_t>& gidx, int nx, cf::Patch2DSizes& z) {
     std::map<int, bool> seen;   // channels of a face share their tables
     for (const cf::ChanDev& d : dev) {
@@ -239,8 +237,6 @@ void patch2d_sizes(const std::vector<cf::ChanDev>& dev, const std::vector<int32_
     }
 }
 
-// The shapes of a problem's polarizations (used: its channels per polarization
-// slot; launched with it: the channels `together`), or false when one has none.
 bool patch2d_pick(const cf::Patch2DSet& set, int precision, const int used[2], const int together[2],
                   const cf::Patch2DSizes& z, std::array<int, 2>& shape) {
     const size_t lim = cf::device_lds_limit();
@@ -251,31 +247,24 @@ bool patch2d_pick(const cf::Patch2DSet& set, int precision, const int used[2], c
     return true;
 }
 
-// Heads and lists of a launch's instances as the kernel reads them: instance
-// i's lists are those of sets[i] for shape[i][q] (polarization slot q; -1: none).
-std::vector<char> patch2d_blob(const std::vector<const cf::Patch2DSet*>& sets,
-                               const std::vector<std::array<int, 2>>& shapes) {
-    std::vector<cf::Patch2DInst> heads(sets.size());
-    std::vector<cf::Patch2DCell> cells;
-    for (size_t i = 0; i < sets.size(); ++i) {
-        const std::array<int, 2>& shape = shapes[i];
-        heads[i] = cf::Patch2DInst{};
-        if (!sets[i]) continue;
-        heads[i].id_e = sets[i]->id_e;
-        heads[i].id_h = sets[i]->id_h;
-        for (int q = 0; q < 2; ++q) {
-            if (shape[q] < 0) continue;
-            const auto& l = sets[i]->lists[q][shape[q]];
-            heads[i].off[q] = (int32_t)cells.size();
-            heads[i].n[q] = (int32_t)l.size();
-            cells.insert(cells.end(), l.begin(), l.end());
-        }
-    }
-    std::vector<char> out(heads.size() * sizeof(heads[0]) + cells.size() * sizeof(cf::Patch2DCell));
-    std::memcpy(out.data(), heads.data(), heads.size() * sizeof(heads[0]));
-    if (!cells.empty())
-        std::memcpy(out.data() + heads.size() * sizeof(heads[0]), cells.data(), cells.size() * sizeof(cf::Patch2DCell));
+std::vector<cf::Patch2DCell> patch2d_cells(const cf::Patch2DSet& set, const std::array<int, 2>& shape) {
+    std::vector<cf::Patch2DCell> out;
+    for (int q = 0; q < 2; ++q)
+        if (shape[q] >= 0) out.insert(out.end(), set.lists[q][shape[q]].begin(), set.lists[q][shape[q]].end());
     return out;
+}
+
+cf::Patch2DInst patch2d_head(const cf::Patch2DSet& set, const std::array<int, 2>& shape, const cf::Patch2DCell* at) {
+    cf::Patch2DInst h{};
+    h.id_e = set.id_e;
+    h.id_h = set.id_h;
+    for (int q = 0; q < 2; ++q) {
+        if (shape[q] < 0) continue;
+        h.cells[q] = at;
+        h.n[q] = (int32_t)set.lists[q][shape[q]].size();
+        at += h.n[q];
+    }
+    return h;
 }
 
 // 3D: for every (plane z, row y), whether some E component of the row can be
@@ -1575,7 +1564,8 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
     // lists lie in the second field array, which only the tiles need.
     std::shared_ptr<const cf::Patch2DSet> patches;
     cf::Patch2DSizes psizes{1, 1, 1};
-    std::deque<std::vector<char>> host_patches;
+    std::deque<std::vector<cf::Patch2DCell>> host_cells;
+    std::deque<cf::Patch2DInst> host_heads;
     std::vector<std::array<int, 2>> pshape;
     if (variant >= 0 && o.tile_variant == 0) {
         patches = cached_patches(p, o.precision);
@@ -1587,12 +1577,14 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
                 patches = nullptr;
                 break;
             }
-            host_patches.push_back(patch2d_blob({patches.get()}, {sh}));
+            host_cells.push_back(patch2d_cells(*patches, sh));
             pshape.push_back(sh);
-            if (host_patches.back().size() > field_bytes) {
+            if (sizeof(cf::Patch2DInst) + host_cells.back().size() * sizeof(cf::Patch2DCell) > field_bytes) {
                 patches = nullptr;
                 break;
             }
+            host_heads.push_back(patch2d_head(*patches, sh, reinterpret_cast<const cf::Patch2DCell*>(
+                                                                ws + L.fields2 + sizeof(cf::Patch2DInst))));
         }
     }
     // Steps of a patch launch: where the channels outnumber the compute units,
@@ -1747,11 +1739,11 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
         if (variant >= 0 && patches) {
             const size_t wi = (size_t)(&w - st.waves.data());
             const std::array<int, 2>& sh = pshape[wi];
-            const std::vector<char>& blob = host_patches[wi];
             STEP_OK(upload_inst(make_inst(st.plans[variant], true)));
-            STEP_OK(hipMemcpyAsync(ws + L.fields2, blob.data(), blob.size(), hipMemcpyHostToDevice, s));
+            STEP_OK(hipMemcpyAsync(ws + L.fields2, &host_heads[wi], sizeof(cf::Patch2DInst), hipMemcpyHostToDevice, s));
+            STEP_OK(hipMemcpyAsync(ws + L.fields2 + sizeof(cf::Patch2DInst), host_cells[wi].data(),
+                                   host_cells[wi].size() * sizeof(cf::Patch2DCell), hipMemcpyHostToDevice, s));
             const cf::Patch2DInst* heads = reinterpret_cast<const cf::Patch2DInst*>(ws + L.fields2);
-            const cf::Patch2DCell* cells = reinterpret_cast<const cf::Patch2DCell*>(heads + 1);
             const int kh = st.shapes[variant].kh, num[2] = {w.n_tm, w.n_te};
             // the polarizations on two streams, as for the tiles
             const bool split_pol = !smp.on && !conv.on && w.n_tm > 0 && w.n_te > 0;
@@ -1771,7 +1763,7 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
                             const bool take = smp.begin(ls);
                             const hipError_t e = cf::launch_patch2d<T>(
                                 sh[q], q == 0 ? CF_POL_TM : CF_POL_TE, dch, q == 0 ? s_tm : s_te, num[q], dinst, heads,
-                                cells, (int)patches->lists[q][sh[q]].size(), psizes, ks, m, 0, 0,
+                                (int)patches->lists[q][sh[q]].size(), psizes, ks, m,
                                 split_pol && q == 1 ? side.s[0] : ls);
                             if (e != hipSuccess) return e;
                             const double cu = (double)num[q] * p.ncell * ks;
@@ -2305,7 +2297,8 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
     std::vector<std::shared_ptr<const cf::Patch2DSet>> keep_sets(n);
     std::vector<const cf::Patch2DSet*> psets(n, nullptr);
     std::vector<std::array<int, 2>> pshapes(n, {-1, -1});
-    std::vector<char> blob;
+    std::vector<cf::Patch2DCell> cells;
+    std::vector<cf::Patch2DInst> heads(n);
     size_t blob_at = 0;                                // field offset of the lists in Bf
     struct PatchGroup {
         int shape, n;                                  // n: longest patch list
@@ -2333,8 +2326,16 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
                 blob_at = B.field_off[i];
             }
         }
-        blob = patch2d_blob(psets, pshapes);
-        if (blob.size() > room) std::fill(psets.begin(), psets.end(), nullptr);
+        const cf::Patch2DCell* at = reinterpret_cast<const cf::Patch2DCell*>(
+            reinterpret_cast<const cf::Patch2DInst*>(Bf + blob_at) + n);
+        for (int i = 0; i < n; ++i) {
+            if (!psets[i]) continue;
+            heads[i] = patch2d_head(*psets[i], pshapes[i], at + cells.size());
+            const auto c = patch2d_cells(*psets[i], pshapes[i]);
+            cells.insert(cells.end(), c.begin(), c.end());
+        }
+        if (n * sizeof(heads[0]) + cells.size() * sizeof(cells[0]) > room)
+            std::fill(psets.begin(), psets.end(), nullptr);
     }
     for (int q = 0; q < 2; ++q) {
         for (int sl : q == 0 ? B.tm : B.te) {
@@ -2438,9 +2439,12 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
         BSTEP(hipMemsetAsync(A, 0, fbytes, s));
         if (n_tm + n_te > 0)
             BSTEP(hipMemsetAsync(Bf, 0, fbytes, s));   // cells the fused kernel skips stay zero in both arrays
-        const cf::Patch2DInst* heads = reinterpret_cast<const cf::Patch2DInst*>(Bf + blob_at);
-        const cf::Patch2DCell* cells = reinterpret_cast<const cf::Patch2DCell*>(heads + n);
-        if (any_patch) BSTEP(up(L.fB + blob_at * sizeof(T), blob.data(), blob.size()));
+        const cf::Patch2DInst* dheads = reinterpret_cast<const cf::Patch2DInst*>(Bf + blob_at);
+        if (any_patch) {
+            const size_t at = L.fB + blob_at * sizeof(T);
+            BSTEP(up(at, heads.data(), n * sizeof(heads[0])));
+            BSTEP(up(at + n * sizeof(heads[0]), cells.data(), cells.size() * sizeof(cells[0])));
+        }
         BSTEP(hipEventRecord(e0, s));
         BSTEP(cf::launch_kick<T>(A, dch, dl, B.C, B.max_uniq, tabs, s));
         for (int i = 0; i < n; ++i) {
@@ -2480,8 +2484,7 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
                                 const hipError_t e = cf::launch_patch2d<T>(
                                     gr.shape, q == 0 ? CF_POL_TM : CF_POL_TE, dch,
                                     reinterpret_cast<const int*>(ws + pat[q] + gr.at), (int)gr.slots.size(), dinst,
-                                    heads, cells, gr.n, psizes, std::min(patch_steps, o.n_steps - m), m, 0, 0,
-                                    on(1, q));
+                                    dheads, gr.n, psizes, std::min(patch_steps, o.n_steps - m), m, on(1, q));
                                 if (e != hipSuccess) return e;
                                 ++launches;
                             }

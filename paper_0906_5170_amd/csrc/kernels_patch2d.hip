@@ -83,8 +83,7 @@ __device__ __forceinline__ double masked(double v, uint32_t bits, int k) {
 template <typename T, int POL, int CX, int B, int MW, int COEF>
 __global__ __launch_bounds__(256 * MW) __attribute__((amdgpu_waves_per_eu(MW)))
 void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, const InstDev* __restrict__ insts,
-               const Patch2DInst* __restrict__ heads, const Patch2DCell* __restrict__ lists, int kmax, int mclock,
-               int src, int dst, P2Lds l) {
+               const Patch2DInst* __restrict__ heads, int kmax, int mclock, P2Lds l) {
     constexpr bool TM = POL == CF_POL_TM;
     constexpr int C0 = TM ? CF_EZ : CF_EX, C1 = TM ? CF_HX : CF_EY, C2 = TM ? CF_HY : CF_HZ;
     constexpr int NE = TM ? 1 : 2, NH = 3 - NE, NC = CX * B;
@@ -224,7 +223,10 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, co
     // ---- the patch: neighbours, coefficients, fields ----------------------
     const bool act = tid < n;
     Patch2DCell pc{};
-    if (act) pc = lists[hd.off[TM ? 0 : 1] + tid];
+    if (act) {
+        const auto q = as_global(hd.cells[TM ? 0 : 1]) + tid;
+        pc = {q->x0, q->y0, q->right, q->left, q->up, q->down, 0, 0};
+    }
     const int x0 = pc.x0, y0 = pc.y0;
     const T* const er = XE + (act ? pc.right : n) * S + RO;   // E column of the patch to the right
     const T* const eu = XE + (act ? pc.up : n) * S;           // E row of the patch above
@@ -245,7 +247,7 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, co
 #pragma unroll
     for (int e = 0; e < NE; ++e) live[e] = 0;
     {
-        const auto F0 = as_global(static_cast<const T*>(src ? g.fb : g.fa)) + d.field_off;
+        const auto F0 = as_global(static_cast<const T*>(g.fa)) + d.field_off;
         const auto F1 = F0 + g.ncell;
         const auto F2 = F1 + g.ncell;
         const auto I0 = as_global(g.ids[C0]), I1 = as_global(g.ids[C1]), I2 = as_global(g.ids[C2]);
@@ -388,7 +390,7 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, co
         if (wave_m) put();
         __syncthreads();
     }
-    const auto F0 = as_global(static_cast<T*>(dst ? g.fb : g.fa)) + d.field_off;
+    const auto F0 = as_global(static_cast<T*>(g.fa)) + d.field_off;
     const auto F1 = F0 + g.ncell;
     const auto F2 = F1 + g.ncell;
 #pragma unroll
@@ -424,20 +426,18 @@ struct P2Shapes<double> {
 
 template <typename T, int V>
 hipError_t p2_launch(int shape, int pol, int threads, const P2Lds& l, const ChanDev* ch, const int* slots, int nslots,
-                     const InstDev* inst, const Patch2DInst* heads, const Patch2DCell* lists, int kmax, int m, int src,
-                     int dst, hipStream_t s) {
+                     const InstDev* inst, const Patch2DInst* heads, int kmax, int m, hipStream_t s) {
     if constexpr (V >= P2Shapes<T>::n) {
         return hipErrorInvalidValue;
     } else {
         if (shape != V)
-            return p2_launch<T, V + 1>(shape, pol, threads, l, ch, slots, nslots, inst, heads, lists, kmax, m, src,
-                                       dst, s);
+            return p2_launch<T, V + 1>(shape, pol, threads, l, ch, slots, nslots, inst, heads, kmax, m, s);
         constexpr Patch2DShape q = P2Shapes<T>::s[V];
         if (threads > 256 * q.mw) return hipErrorInvalidValue;
         auto run = [&](auto kernel) -> hipError_t {
             if (!lds_allow(reinterpret_cast<const void*>(kernel), (size_t)l.total)) return hipErrorInvalidValue;
-            hipLaunchKernelGGL(kernel, dim3(nslots), dim3(threads), l.total, s, ch, slots, inst, heads, lists, kmax, m,
-                               src, dst, l);
+            hipLaunchKernelGGL(kernel, dim3(nslots), dim3(threads), l.total, s, ch, slots, inst, heads, kmax, m,
+                               l);
             return hipGetLastError();
         };
         return pol == CF_POL_TM ? run(&k_patch2d<T, CF_POL_TM, q.cx, q.b, q.mw, q.coef>)
@@ -461,23 +461,21 @@ size_t patch2d_lds(const Patch2DShape& q, int n, const Patch2DSizes& z) {
 
 template <typename T>
 hipError_t launch_patch2d(int shape, int pol, const ChanDev* ch, const int* slots, int nslots, const InstDev* inst,
-                          const Patch2DInst* heads, const Patch2DCell* lists, int n, const Patch2DSizes& z, int kmax,
-                          int m, int src, int dst, hipStream_t s) {
+                          const Patch2DInst* heads, int n, const Patch2DSizes& z, int kmax, int m, hipStream_t s) {
     if (nslots <= 0) return hipSuccess;
     if (shape < 0 || shape >= P2Shapes<T>::n || n < 0 || kmax < 1) return hipErrorInvalidValue;
     const Patch2DShape& q = P2Shapes<T>::s[shape];
     // a wave of its own takes the surface sums
     const int threads = (n + 63) / 64 * 64 + 64;
-    return p2_launch<T, 0>(shape, pol, threads, p2_lds<T>(q.cx, q.b, n, z), ch, slots, nslots, inst, heads, lists, kmax,
-                           m, src, dst, s);
+    return p2_launch<T, 0>(shape, pol, threads, p2_lds<T>(q.cx, q.b, n, z), ch, slots, nslots, inst, heads, kmax,
+                           m, s);
 }
 
 #define CF_INSTANTIATE(T)                                                                                          \
     template int patch2d_shapes<T>(Patch2DShape*, int);                                                            \
     template size_t patch2d_lds<T>(const Patch2DShape&, int, const Patch2DSizes&);                                 \
     template hipError_t launch_patch2d<T>(int, int, const ChanDev*, const int*, int, const InstDev*,               \
-                                          const Patch2DInst*, const Patch2DCell*, int, const Patch2DSizes&, int,   \
-                                          int, int, int, hipStream_t);
+                                          const Patch2DInst*, int, const Patch2DSizes&, int, int, hipStream_t);
 CF_INSTANTIATE(float)
 CF_INSTANTIATE(double)
 #undef CF_INSTANTIATE

@@ -32,13 +32,12 @@ struct Patch2DCell {
 };
 static_assert(sizeof(Patch2DCell) == 16, "one 16-byte load per thread");
 
-// Device head of an instance: its lists' first entries and lengths per
-// polarization (0 TM, 1 TE), and an E and an H material whose a, b its cells
-// carry.
+// Head of an instance: its lists and their lengths per polarization (0 TM,
+// 1 TE), and an E and an H material whose a, b its cells carry.
 struct Patch2DInst {
-    int32_t off[2], n[2];
+    const Patch2DCell* cells[2];
+    int32_t n[2];
     int32_t id_e, id_h;
-    int32_t pad[2];
 };
 
 // Box of the measured points and samples x points of a channel, the largest
@@ -52,12 +51,11 @@ template <typename T>
 size_t patch2d_lds(const Patch2DShape& q, int n, const Patch2DSizes& z);
 
 // Advances the channels slots[0 .. nslots - 1] (all of polarization pol) by
-// min(kmax, remaining steps of the instance) steps from launch-clock step m:
-// fields from buffer `src` of the instance (0: fa, 1: fb) to buffer `dst`
-// (which may be the same).  n: longest list of the launch's instances.
+// min(kmax, remaining steps of the instance) steps from launch-clock step m, in
+// the instance's buffer fa.  heads: one per instance.  n: longest list of the
+// launch's instances.
 template <typename T>
 hipError_t launch_patch2d(int shape, int pol, const ChanDev* ch, const int* slots, int nslots, const InstDev* inst,
-                          const Patch2DInst* heads, const Patch2DCell* lists, int n, const Patch2DSizes& z, int kmax,
-                          int m, int src, int dst, hipStream_t s);
+                          const Patch2DInst* heads, int n, const Patch2DSizes& z, int kmax, int m, hipStream_t s);
 
 }  // namespace cf

@@ -41,6 +41,7 @@
 #include "../../include/casimir_fdtd.h"
 #include "arena.hpp"
 #include "device.hpp"
+#include "lds.hpp"
 #include "plan.hpp"
 #include "solver.hpp"
 
@@ -67,6 +68,11 @@ struct Req {
     cfi::Staged st;
     bool fused = false;
     int variant = -1;                 // fused variant of this request
+    std::shared_ptr<const cf::Patch2DSet> patches;   // fused: on the 2D patch kernel (null: tiles)
+    std::array<int, 2> pshape{-1, -1};
+    cf::Patch2DSizes psizes{1, 1, 1};
+    std::vector<cf::Patch2DCell> cells;   // its patch lists
+    double live_cells[2] = {0, 0};
     int v3 = -1;                      // fused 3D step variant (-1: split 3D kernels)
     int v3s = -1;                     // its single-step band shape (a step without a partner in the tick)
     cfi::ConvergenceStop conv;        // time-convergence stop (single-wave requests)
@@ -113,6 +119,7 @@ void drop_tables(Req& r) {
     std::vector<uint32_t>().swap(r.idp);
     std::vector<uint8_t>().swap(r.ids);
     std::vector<uint8_t>().swap(r.lut);
+    std::vector<cf::Patch2DCell>().swap(r.cells);
     std::vector<double>().swap(r.ktab);
     std::vector<double>().swap(r.pml);
     std::vector<int32_t>().swap(r.st.gidx);
@@ -146,6 +153,7 @@ struct cf_server {
     long long clock = 0;
     int parity = 0;
     int kh = 8;                       // steps per tick
+    bool tiles_only = false;          // a tile variant was asked for
     std::vector<int> prefer;          // fused variants in order of preference (same steps per launch)
     // fused group tables (server-owned device memory)
     char* group = nullptr;
@@ -156,8 +164,14 @@ struct cf_server {
         int variant, pol;
         size_t off;                   // first work item in the concatenated lists
         int n;
+        // 2D patch kernel (shape >= 0): byte offset of the channel list behind
+        // the work items, channels, longest patch list, LDS sizes
+        int shape = -1;
+        int longest = 0;
+        cf::Patch2DSizes sizes{1, 1, 1};
     };
     std::vector<Launch> launches;     // fused launches of one tick
+    size_t heads_off = 0;             // the patch launches' instance heads, behind the work items
     // tick timing: events around the fused launches and each non-fused
     // request's steps, and the fused launches' device time last tick
     std::vector<hipEvent_t> ev;
@@ -170,6 +184,7 @@ struct cf_server {
     std::deque<std::vector<cf::ChanDev>> keep_ch;
     std::deque<std::vector<cf::InstDev>> keep_inst;
     std::deque<std::vector<cf::WorkItem>> keep_work;
+    std::deque<std::vector<char>> keep_patch;
     // statistics
     uint64_t n_submitted = 0, n_completed = 0, n_failed = 0, n_cancelled = 0;
     double busy_s = 0;
@@ -236,6 +251,24 @@ std::string prepare(cf_server* S, Req& r) {
                 break;
             }
     r.fused = r.variant >= 0;
+    // with the tiling left to the server, a request whose live cells fit a
+    // compute unit's registers takes the 2D patch kernel; its lists lie in the
+    // second field array.  Shapes are chosen for a full device.
+    r.patches = nullptr;
+    if (r.fused && !S->tiles_only) {
+        auto set = cfi::cached_patches(p, S->precision);
+        cfi::patch2d_sizes(r.st.dev, r.st.gidx, p.nx, r.psizes);
+        int used[2] = {0, 0};
+        for (const cf::Channel& c : r.chans) ++used[c.pol == CF_POL_TE ? 1 : 0];
+        const int together[2] = {std::max(used[0], 1024), std::max(used[1], 1024)};
+        if (cfi::patch2d_pick(*set, S->precision, used, together, r.psizes, r.pshape)) {
+            r.cells = cfi::patch2d_cells(*set, r.pshape);
+            const size_t room = (size_t)r.C * r.st.ncomp * p.ncell * (S->precision == CF_FP64 ? 8 : 4);
+            if (r.cells.size() * sizeof(cf::Patch2DCell) <= room) r.patches = set;
+            for (int q = 0; q < 2; ++q)
+                if (r.pshape[q] >= 0) r.live_cells[q] = set->cells[q][r.pshape[q]];
+        }
+    }
     // 3D requests take the fused z-streaming step when it applies: in FP32
     // the two-step kernel (12 waves of 1 row; steps go in pairs within a clock
     // tick), else the single-step band shape of 8 waves of 1 row, else the
@@ -368,7 +401,11 @@ hipError_t start_wave(cf_server* S, Req& r, T* f) {
     const size_t fbytes = (size_t)r.st.resident * r.st.ncomp * p.ncell * sizeof(T);
     hipError_t e;
     if ((e = hipMemsetAsync(f, 0, fbytes, s)) != hipSuccess) return e;
-    if (r.fused || r.v3 >= 0) {
+    if (r.patches) {
+        if ((e = hipMemcpyAsync(b + r.o_fb, r.cells.data(), r.cells.size() * sizeof(cf::Patch2DCell),
+                                hipMemcpyHostToDevice, s)) != hipSuccess)
+            return e;
+    } else if (r.fused || r.v3 >= 0) {
         // the fused kernels never write the cells they skip: zero in both arrays
         char* other = b + (reinterpret_cast<char*>(f) == b + r.o_fa ? r.o_fb : r.o_fa);
         if ((e = hipMemsetAsync(other, 0, fbytes, s)) != hipSuccess) return e;
@@ -429,8 +466,8 @@ hipError_t admit(cf_server* S, Req& r) {
     r.done = 0;
     r.credit = 0;
     r.sps = 0;
-    // a fused request is kicked into the buffer the next fused launch reads
-    T* f = reinterpret_cast<T*>(b + (r.fused && S->parity ? r.o_fb : r.o_fa));
+    // a tiled request is kicked into the buffer the next fused launch reads
+    T* f = reinterpret_cast<T*>(b + (r.fused && !r.patches && S->parity ? r.o_fb : r.o_fa));
     return start_wave<T>(S, r, f);
 }
 
@@ -446,6 +483,15 @@ hipError_t rebuild_group(cf_server* S) {
         std::vector<int> third;                          // surface tile per slot
     };
     std::map<std::pair<int, int>, SlotTiles> lists;   // (v, pol) -> slots, tiles, surface tiles
+    // patch launches by shape and polarization; the cells of a slot's patches
+    // order a launch's channels, longest first
+    struct SlotPatches {
+        cf_server::Launch l;
+        std::vector<std::pair<double, int>> slots;
+    };
+    std::vector<SlotPatches> patches;
+    std::vector<cf::Patch2DInst> heads;
+    const size_t lim = cf::device_lds_limit();
     for (auto& rp : S->active) {
         Req& r = *rp;
         if (!r.fused) continue;
@@ -479,11 +525,47 @@ hipError_t rebuild_group(cf_server* S) {
         I.gamma_stride = r.C;
         I.t = Dev<T>::tabs(b, r);
         inst.push_back(I);
+        heads.push_back({});
+        SlotPatches* to[2] = {nullptr, nullptr};
+        if (r.patches) {
+            heads.back() = cfi::patch2d_head(*r.patches, r.pshape,
+                                             reinterpret_cast<const cf::Patch2DCell*>(b + r.o_fb));
+            size_t idx[2] = {0, 0};
+            for (int q = 0; q < 2; ++q) {
+                if (r.pshape[q] < 0) continue;
+                const int v = r.pshape[q], pol = q == 0 ? CF_POL_TM : CF_POL_TE, n = heads.back().n[q];
+                // a launch of the shape whose LDS still fits with this request
+                size_t k = 0;
+                cf_server::Launch l;
+                for (; k < patches.size(); ++k) {
+                    l = patches[k].l;
+                    if (l.shape != v || l.pol != pol) continue;
+                    l.longest = std::max(l.longest, n);
+                    l.sizes.box = std::max(l.sizes.box, r.psizes.box);
+                    l.sizes.samples = std::max(l.sizes.samples, r.psizes.samples);
+                    l.sizes.points = std::max(l.sizes.points, r.psizes.points);
+                    if (cf::patch2d_lds<T>(r.patches->shapes[v], l.longest, l.sizes) <= lim) break;
+                }
+                if (k == patches.size()) {
+                    l = {-1, pol, 0, 0, v, n, r.psizes};
+                    patches.push_back({});
+                }
+                patches[k].l = l;
+                idx[q] = k;
+            }
+            for (int q = 0; q < 2; ++q)
+                if (r.pshape[q] >= 0) to[q] = &patches[idx[q]];
+        }
         for (int c = 0; c < r.C; ++c) {
             cf::ChanDev d = r.st.dev[c];
             d.inst = ii;
             const int slot = (int)ch.size();
             ch.push_back(d);
+            if (r.patches) {
+                const int q = r.chans[c].pol == CF_POL_TE ? 1 : 0;
+                to[q]->slots.emplace_back(-r.live_cells[q], slot);
+                continue;
+            }
             auto& l = lists[{r.variant, r.chans[c].pol}];
             l.first.push_back(slot);
             l.second.push_back(&cfi::live_tiles(pl, r.chans[c].pol));
@@ -497,8 +579,29 @@ hipError_t rebuild_group(cf_server* S) {
         launches.push_back({kv.first.first, kv.first.second, work.size(), (int)w.size()});
         work.insert(work.end(), w.begin(), w.end());
     }
-    if (ch.size() > S->cap_ch || inst.size() > S->cap_inst || work.size() > S->cap_work) return hipErrorOutOfMemory;
+    // heads and channel lists of the patch launches behind the work items
+    S->heads_off = cfi::align_up(work.size() * sizeof(cf::WorkItem), 256);
+    std::vector<char> raw;
+    if (!patches.empty()) {
+        raw.resize(heads.size() * sizeof(cf::Patch2DInst));
+        std::memcpy(raw.data(), heads.data(), raw.size());
+        for (SlotPatches& g : patches) {
+            std::stable_sort(g.slots.begin(), g.slots.end(),
+                             [](const auto& a, const auto& c) { return a.first < c.first; });
+            g.l.off = S->heads_off + raw.size();
+            g.l.n = (int)g.slots.size();
+            for (const auto& c : g.slots) {
+                const char* q = reinterpret_cast<const char*>(&c.second);
+                raw.insert(raw.end(), q, q + sizeof(int));
+            }
+            launches.push_back(g.l);
+        }
+    }
+    if (ch.size() > S->cap_ch || inst.size() > S->cap_inst || work.size() > S->cap_work ||
+        S->heads_off + raw.size() > S->cap_work * sizeof(cf::WorkItem))
+        return hipErrorOutOfMemory;
     hipStream_t s = S->stream;
+    S->keep_patch.push_back(std::move(raw));
     S->keep_ch.push_back(std::move(ch));
     S->keep_inst.push_back(std::move(inst));
     S->keep_work.push_back(std::move(work));
@@ -515,14 +618,37 @@ hipError_t rebuild_group(cf_server* S) {
     if (!kw.empty() && (e = hipMemcpyAsync(S->group + S->g_work, kw.data(), kw.size() * sizeof(cf::WorkItem),
                                            hipMemcpyHostToDevice, s)) != hipSuccess)
         return e;
+    if (!S->keep_patch.back().empty() &&
+        (e = hipMemcpyAsync(S->group + S->g_work + S->heads_off, S->keep_patch.back().data(),
+                            S->keep_patch.back().size(), hipMemcpyHostToDevice, s)) != hipSuccess)
+        return e;
     S->launches = std::move(launches);
     S->membership_changed = false;
     return hipSuccess;
 }
 
-// One tick: K steps of every resident request.
+// Ticks that may run as one: where every resident request is on the 2D patch
+// kernel, whose launches take any number of steps, as many as stay within a
+// millisecond of device time and end by the next tick in which a request
+// finishes or is checked for convergence.
+int merged_ticks(const cf_server* S) {
+    if (!(S->group_s > 0)) return 1;
+    long long n = std::min<long long>((long long)(1e-3 / S->group_s), 64);
+    for (const auto& rp : S->active) {
+        const Req& r = *rp;
+        if (!r.fused || !r.patches) return 1;
+        const long long done = S->clock - r.start;
+        long long left = r.opts.n_steps - done;
+        if (r.conv.on) left = std::min<long long>(left, r.conv.next - done);
+        n = std::min(n, (left + S->kh - 1) / S->kh);
+    }
+    return (int)std::max<long long>(n, 1);
+}
+
+// One tick: K steps of every resident request (`ticks` times K where every one
+// is on the patch kernel).
 template <typename T>
-hipError_t tick(cf_server* S) {
+hipError_t tick(cf_server* S, int ticks) {
     hipStream_t s = S->stream;
     hipError_t e;
     S->n_marks = 0;
@@ -552,10 +678,18 @@ hipError_t tick(cf_server* S) {
             if ((e = hipEventRecord(S->fork, s)) != hipSuccess) return e;
             if ((e = hipStreamWaitEvent(S->side, S->fork, 0)) != hipSuccess) return e;
         }
-        for (const auto& l : S->launches)
-            if ((e = cf::launch_tb2d<T>(l.variant, l.pol, gch, gw + l.off, l.n, gin, S->kh, (int)S->clock,
-                                        S->parity, split && l.pol == CF_POL_TE ? S->side : s)) != hipSuccess)
-                return e;
+        for (const auto& l : S->launches) {
+            const hipStream_t ls = split && l.pol == CF_POL_TE ? S->side : s;
+            if (l.shape >= 0)
+                e = cf::launch_patch2d<T>(
+                    l.shape, l.pol, gch, reinterpret_cast<const int*>(S->group + S->g_work + l.off), l.n, gin,
+                    reinterpret_cast<const cf::Patch2DInst*>(S->group + S->g_work + S->heads_off), l.longest, l.sizes,
+                    S->kh * ticks, (int)S->clock, ls);
+            else
+                e = cf::launch_tb2d<T>(l.variant, l.pol, gch, gw + l.off, l.n, gin, S->kh, (int)S->clock, S->parity,
+                                       ls);
+            if (e != hipSuccess) return e;
+        }
         if (split) {
             if ((e = hipEventRecord(S->join, S->side)) != hipSuccess) return e;
             if ((e = hipStreamWaitEvent(s, S->join, 0)) != hipSuccess) return e;
@@ -693,7 +827,7 @@ void plan_steps(cf_server* S) {
 
 // Device times of the tick just drained: the fused launches and each
 // non-fused request's steps (events recorded by tick in this order).
-void read_times(cf_server* S) {
+void read_times(cf_server* S, int ticks) {
     if (S->n_marks < 2) return;
     auto span = [&](size_t a) {
         float ms = 0;
@@ -701,7 +835,7 @@ void read_times(cf_server* S) {
     };
     bool any_fused = false;
     for (auto& rp : S->active) any_fused = any_fused || rp->fused;
-    const double g = span(0);
+    const double g = span(0) / ticks;
     if (any_fused && g > 0) S->group_s = S->group_s > 0 ? 0.5 * (S->group_s + g) : g;
     size_t k = 1;
     for (auto& rp : S->active) {
@@ -787,9 +921,10 @@ void loop(cf_server* S) {
         }
         // ---- one tick ----
         plan_steps(S);
+        const int ticks = merged_ticks(S);
         const double t0 = now_s();
         lk.unlock();
-        hipError_t e = tick<T>(S);
+        hipError_t e = tick<T>(S, ticks);
         if (e == hipSuccess) e = hipStreamSynchronize(S->stream);
         lk.lock();
         S->busy_s += now_s() - t0;
@@ -808,8 +943,8 @@ void loop(cf_server* S) {
             S->cv.notify_all();
             continue;
         }
-        read_times(S);
-        S->clock += S->kh;
+        read_times(S, ticks);
+        S->clock += S->kh * ticks;
         S->parity ^= 1;
         for (auto& rp : S->active)
             if (!rp->fused && !rp->whole) rp->done += rp->tick_steps;
@@ -817,6 +952,7 @@ void loop(cf_server* S) {
         S->keep_ch.clear();
         S->keep_inst.clear();
         S->keep_work.clear();
+        S->keep_patch.clear();
         // ---- retire finished requests / start next channel waves ----
         for (auto it = S->active.begin(); it != S->active.end();) {
             Req& r = **it;
@@ -915,6 +1051,7 @@ static cf_status cf_server_create_impl(size_t hbm_budget_bytes, int precision, i
     // of 7 rows, 8 steps per launch), the first FP64 shape
     const int first = tile_variant > 0 ? tile_variant - 1 : (precision == CF_FP64 ? 0 : std::min(12, nv - 1));
     S->kh = sh[first].kh;
+    S->tiles_only = tile_variant > 0;
     // the preferred variant, then every other one with the same steps per
     // launch (wider tiles take surfaces the preferred one cannot hold)
     S->prefer.push_back(first);
@@ -1040,6 +1177,10 @@ static cf_status report(cf_server* S, const std::shared_ptr<Req>& r, int* state,
         cfi::StencilTiming tim;
         tim.steps_run = r->steps_run;
         tim.variant = r->variant >= 0 ? r->variant : r->v3;   // fused 2D tile or fused 3D band shape
+        if (r->patches) {
+            tim.launch_steps = S->kh;
+            std::copy(r->live_cells, r->live_cells + 2, tim.live_cells);
+        }
         cf_opts o = r->opts;
         const bool ok = cfi::fill_result(*r->prob, r->chans, r->acc, {}, o, (r->t_done - r->t_admit) * 1e3, tim,
                                          r->st, out);

@@ -3,7 +3,9 @@
 
 #include <hip/hip_runtime.h>
 
+#include <array>
 #include <cmath>
+#include <memory>
 #include <new>
 #include <stdexcept>
 #include <string>
@@ -11,6 +13,7 @@
 
 #include "../../include/casimir_fdtd.h"
 #include "device.hpp"
+#include "patch2d_plan.hpp"
 #include "plan.hpp"
 
 namespace cfi {
@@ -128,6 +131,19 @@ struct ConvergenceStop {
         return calm >= 2;
     }
 };
+
+// 2D patch kernel: the lists of a problem (kept per problem and precision),
+// LDS sizes widened to the channels of `dev` (row length nx), the shapes of a
+// problem's polarizations (used: its channels per polarization slot; launched
+// together: `together`; false when one has none), and the lists and head of an
+// instance for given shapes (polarization slot q; -1: none), TM before TE,
+// with the lists at device address `at`.
+std::shared_ptr<const cf::Patch2DSet> cached_patches(const cf::Problem& p, int precision);
+void patch2d_sizes(const std::vector<cf::ChanDev>& dev, const std::vector<int32_t>& gidx, int nx, cf::Patch2DSizes& z);
+bool patch2d_pick(const cf::Patch2DSet& set, int precision, const int used[2], const int together[2],
+                  const cf::Patch2DSizes& z, std::array<int, 2>& shape);
+std::vector<cf::Patch2DCell> patch2d_cells(const cf::Patch2DSet& set, const std::array<int, 2>& shape);
+cf::Patch2DInst patch2d_head(const cf::Patch2DSet& set, const std::array<int, 2>& shape, const cf::Patch2DCell* at);
 
 // Stage the tables of one problem for the given channels and options.
 void stage(const cf::Problem& p, const cf_opts& o, const std::vector<cf::Channel>& chans, Staged& st);

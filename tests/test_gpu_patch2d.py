@@ -120,3 +120,26 @@ def test_batch(cf, graph, precision):
         for r, p in zip(cf.batch_solve(some, graph=graph, **o), some):
             b = p.solve(split=True, **o)
             assert r["fused"] and np.array_equal(r["per_channel"], b["per_channel"])
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_server(cf, precision):
+    """Requests on patches and on tiles, joining one after another, get what
+    their own split solves give; so does one that stops early."""
+    wls = [problem(13, 14, W), problem(97, 83, W, "filled"), problem(61, 37, W, "mixed"), problem(260, 200, W),
+           problem(61, 37, W), problem(24, 31, ("periodic", "pec", "periodic"))]
+    steps = [400, 61, 250, 90, 300, 77]
+    probs = [cf.Problem.from_workload(w) for w in wls]
+    o = [dict(sigma=0.9, courant=0.5, n_steps=n, pol="TM+TE", kernel="general", precision=precision) for n in steps]
+    o[4].update(stop_tol=1e6, stop_every=40)
+    srv = cf.Server(2 << 30, precision=precision)
+    for some in (range(3), range(6)):
+        tickets = [srv.submit(probs[k], **o[k]) for k in some]
+        for k, t in zip(some, tickets):
+            r = srv.wait(t, timeout=100)
+            ref = dict(sigma=0.9, courant=0.5, pol="TM+TE", kernel="general", precision=precision)
+            b = probs[k].solve(split=True, n_steps=r["n_steps_run"], **ref)
+            assert r["n_steps_run"] == steps[k] if k != 4 else 40 < r["n_steps_run"] < 300
+            assert r["fused"] and np.array_equal(r["per_channel"], b["per_channel"]), k
+            srv.release(t)
+    srv.close()
