@@ -290,10 +290,18 @@ std::vector<uint8_t> e_live_rows(const cf::Problem& p) {
     return rows;
 }
 
+// The fused 3D variants' plane ranges of a problem (stage_zranges).
+struct ZRanges {
+    std::vector<int32_t> zr;
+    int off[8];
+};
+std::map<uint64_t, ZRanges> g_zranges;
+
 void forget_plans(uint64_t uid) {
     std::lock_guard<std::mutex> lk(g_plan_mu);
     for (auto it = g_plans.begin(); it != g_plans.end();) it = (uint64_t)it->first[0] == uid ? g_plans.erase(it) : std::next(it);
     g_erows.erase(uid);
+    g_zranges.erase(uid);
     g_patches.erase(std::make_pair(uid, (int)CF_FP32));
     g_patches.erase(std::make_pair(uid, (int)CF_FP64));
 }
@@ -304,6 +312,15 @@ void forget_plans(uint64_t uid) {
 // nonzero coefficients, H only on kmin - 1..kmax (its z difference reads the
 // next plane); outside, every field stays 0 and the kernel skips the planes.
 void stage_zranges(const cf::Problem& p, Staged& st) {
+    {
+        std::lock_guard<std::mutex> lk(g_plan_mu);
+        auto it = g_zranges.find(p.uid);
+        if (it != g_zranges.end()) {
+            st.zr = it->second.zr;
+            std::copy(it->second.off, it->second.off + 8, st.zr_off);
+            return;
+        }
+    }
     const std::vector<uint8_t> rows = e_live_rows(p);
     const bool pery = p.grid.bc[1] == CF_BC_PERIODIC;
     st.zr.clear();
@@ -335,11 +352,17 @@ void stage_zranges(const cf::Problem& p, Staged& st) {
             st.zr.push_back(kmin < 0 ? 0 : kmax + 1);
         }
     }
+    ZRanges z{st.zr, {}};
+    std::copy(st.zr_off, st.zr_off + 8, z.off);
+    std::lock_guard<std::mutex> lk(g_plan_mu);
+    if (g_zranges.size() >= 64) g_zranges.clear();
+    g_zranges[p.uid] = std::move(z);
 }
 
 // Build host copies of every table a solve uploads.  Channels run in waves
 // of `resident` consecutive channels; channel c uses field block c % resident.
-void stage(const cf::Problem& p, const cf_opts& o, const std::vector<cf::Channel>& chans, Staged& st) {
+void stage(const cf::Problem& p, const cf_opts& o, const std::vector<cf::Channel>& chans, Staged& st,
+           bool sizes_only) {
     st.chans = chans;
     st.ncomp = cf::n_comp(p);
     const int C = (int)chans.size();
@@ -359,17 +382,46 @@ void stage(const cf::Problem& p, const cf_opts& o, const std::vector<cf::Channel
     }
     // concatenated gather / scatter tables for every (face, comp) pair used
     std::vector<int> g_goff(p.gathers.size(), -1), g_uoff(p.gathers.size(), -1);
+    int lo[3] = {p.nx, p.ny, p.nz}, hi[3] = {-1, -1, -1};   // 3D: box of their points
+    st.len = {};
+    if (!sizes_only) {
+        size_t gi = 0, us = 0;
+        for (const cf::Gather& g : p.gathers) {
+            gi += g.idx.size();
+            us += g.usamp.size();
+        }
+        st.gidx.reserve(gi);
+        st.gw.reserve(gi);
+        st.usamp.reserve(us);
+        st.uw.reserve(us);
+        size_t nb = 0;
+        for (const auto& b : p.basis) nb += b.size();
+        st.basis.reserve(nb);
+    }
     auto add_gather = [&](int gi) {
         if (g_goff[gi] >= 0) return;
         const cf::Gather& g = p.gathers[gi];
-        g_goff[gi] = (int)st.gidx.size();
+        g_goff[gi] = (int)st.len.gidx;
+        g_uoff[gi] = (int)st.len.uidx;
+        const int base = (int)st.len.usamp;
+        st.len.gidx += g.idx.size();
+        st.len.uidx += g.uidx.size() + 1;
+        st.len.uoff += g.uoff.size();
+        st.len.usamp += g.usamp.size();
+        if (p.grid.ndim == 3)
+            for (int32_t ix : g.idx) {
+                const int row = ix / p.nx, c[3] = {ix - row * p.nx, row % p.ny, row / p.ny};
+                for (int a = 0; a < 3; ++a) {
+                    lo[a] = std::min(lo[a], c[a]);
+                    hi[a] = std::max(hi[a], c[a]);
+                }
+            }
+        if (sizes_only) return;
         st.gidx.insert(st.gidx.end(), g.idx.begin(), g.idx.end());
         st.gw.insert(st.gw.end(), g.w.begin(), g.w.end());
-        g_uoff[gi] = (int)st.uidx.size();
-        const int base = (int)st.usamp.size();
-        st.uidx.insert(st.uidx.end(), g.uidx.begin(), g.uidx.end());
         // uoff holds one entry per distinct point plus a trailing one, offsets
         // global into usamp/uw; uidx gets a pad entry to stay index-aligned.
+        st.uidx.insert(st.uidx.end(), g.uidx.begin(), g.uidx.end());
         for (size_t k = 0; k < g.uoff.size(); ++k) st.uoff.push_back(base + g.uoff[k]);
         st.uidx.push_back(0);
         st.usamp.insert(st.usamp.end(), g.usamp.begin(), g.usamp.end());
@@ -377,8 +429,9 @@ void stage(const cf::Problem& p, const cf_opts& o, const std::vector<cf::Channel
     };
     std::vector<int> basis_face_off(p.faces.size());
     for (size_t f = 0; f < p.faces.size(); ++f) {
-        basis_face_off[f] = (int)st.basis.size();
-        st.basis.insert(st.basis.end(), p.basis[f].begin(), p.basis[f].end());
+        basis_face_off[f] = (int)st.len.basis;
+        st.len.basis += p.basis[f].size();
+        if (!sizes_only) st.basis.insert(st.basis.end(), p.basis[f].begin(), p.basis[f].end());
     }
     // waves: consecutive runs of `resident` channels; the split cylindrical
     // path groups the channels by azimuthal order first (one order per wave),
@@ -474,16 +527,8 @@ void stage(const cf::Problem& p, const cf_opts& o, const std::vector<cf::Channel
         } else {
             for (int v = 0; v < nv; ++v) st.f3d = st.f3d || usable(v);
         }
-        if (st.f3d && !st.gidx.empty()) {
-            // bounding box of every surface stencil point (all gathers)
-            int lo[3] = {p.nx, p.ny, p.nz}, hi[3] = {-1, -1, -1};
-            for (int32_t ix : st.gidx) {
-                const int c[3] = {(int)(ix % p.nx), (int)((ix / p.nx) % p.ny), (int)(ix / ((int64_t)p.nx * p.ny))};
-                for (int a = 0; a < 3; ++a) {
-                    lo[a] = std::min(lo[a], c[a]);
-                    hi[a] = std::max(hi[a], c[a]);
-                }
-            }
+        if (st.f3d && st.len.gidx > 0) {
+            // bounding box of every surface stencil point (all gathers used)
             cf::ShadowBox& b = st.sbox;
             b.x0 = lo[0];
             b.y0 = lo[1];
@@ -747,13 +792,13 @@ Layout layout_for(const cf::Problem& p, const cf_opts& o, const Staged& st) {
     L.pml = take((size_t)4 * p.nz * 8);
     L.chans = take(C * sizeof(cf::ChanDev));
     L.slots = take(st.slot_lists.size() * sizeof(int) + 4);
-    L.gidx = take(st.gidx.size() * 4 + 4);
-    L.gw = take(st.gw.size() * 8 + 8);
-    L.uidx = take(st.uidx.size() * 4 + 4);
-    L.uoff = take(st.uoff.size() * 4 + 4);
-    L.usamp = take(st.usamp.size() * 4 + 4);
-    L.uw = take(st.uw.size() * 8 + 8);
-    L.basis = take(st.basis.size() * 8 + 8);
+    L.gidx = take(st.len.gidx * 4 + 4);
+    L.gw = take(st.len.gidx * 8 + 8);
+    L.uidx = take(st.len.uidx * 4 + 4);
+    L.uoff = take(st.len.uoff * 4 + 4);
+    L.usamp = take(st.len.usamp * 4 + 4);
+    L.uw = take(st.len.usamp * 8 + 8);
+    L.basis = take(st.len.basis * 8 + 8);
     L.acc = take(C * 2 * 8);
     L.gamma = (o.flags & CF_FLAG_KEEP_GAMMA) ? take((size_t)t_max * C * 8) : off;
     L.fields = take(block);
@@ -1053,19 +1098,69 @@ cf::PatchSizes patch_sizes(const cf::Problem& p, const Staged& st) {
     return z;
 }
 
+// Uploads of a solve's tables.  They lie one behind another in the workspace, so
+// small ones are gathered and go up in one copy (a copy of pageable memory costs
+// about 10 us however small); large ones go up as they are.  Sources of `add`
+// have to live until `flush`, large ones until the stream has drained.
+class TableUpload {
+  public:
+    TableUpload(char* ws, hipStream_t s) : ws_(ws), s_(s) {}
+    hipError_t add(size_t off, const void* src, size_t bytes) {
+        if (!bytes) return hipSuccess;
+        if (bytes > kLarge) return hipMemcpyAsync(ws_ + off, src, bytes, hipMemcpyHostToDevice, s_);
+        pieces_.push_back({off, src, bytes});
+        return hipSuccess;
+    }
+    hipError_t zero(size_t off, size_t bytes) {
+        if (!bytes) return hipSuccess;
+        if (bytes > kLarge) return hipMemsetAsync(ws_ + off, 0, bytes, s_);
+        pieces_.push_back({off, nullptr, bytes});
+        return hipSuccess;
+    }
+    hipError_t flush() {
+        std::sort(pieces_.begin(), pieces_.end(), [](const Piece& a, const Piece& b) { return a.off < b.off; });
+        for (size_t i = 0; i < pieces_.size();) {
+            // a run of pieces with nothing but the alignment's padding between
+            size_t j = i + 1, end = pieces_[i].off + pieces_[i].bytes;
+            for (; j < pieces_.size() && pieces_[j].off >= end && pieces_[j].off <= align_up(end, 256); ++j)
+                end = pieces_[j].off + pieces_[j].bytes;
+            images_.emplace_back(end - pieces_[i].off, 0);
+            std::vector<char>& image = images_.back();
+            const size_t lo = pieces_[i].off;
+            for (size_t k = i; k < j; ++k)
+                if (pieces_[k].src) std::memcpy(image.data() + pieces_[k].off - lo, pieces_[k].src, pieces_[k].bytes);
+            const hipError_t e = hipMemcpyAsync(ws_ + lo, image.data(), image.size(), hipMemcpyHostToDevice, s_);
+            if (e != hipSuccess) return e;
+            i = j;
+        }
+        pieces_.clear();
+        return hipSuccess;
+    }
+
+  private:
+    static constexpr size_t kLarge = (size_t)1 << 20;
+    struct Piece {
+        size_t off;
+        const void* src;
+        size_t bytes;
+    };
+    char* ws_;
+    hipStream_t s_;
+    std::vector<Piece> pieces_;
+    std::deque<std::vector<char>> images_;
+};
+
 template <typename T>
 cf_status run_reduced(const cf::Problem& p, const cf_opts& o, const Staged& st, const Layout& L, char* ws,
                   hipStream_t s, std::vector<double>& acc_out, std::vector<double>& gamma_out, double* device_ms,
                   StencilTiming* timing) {
     const size_t C = st.chans.size();
     const int t_max = cf::max_steps(p, o);
+    TableUpload tables(ws, s);
+    auto up = [&](size_t off, const void* src, size_t bytes) { return tables.add(off, src, bytes); };
     std::vector<uint8_t> ids((size_t)cf::kNumComp * p.ncell);
     for (int c = 0; c < cf::kNumComp; ++c)
         std::memcpy(ids.data() + (size_t)c * p.ncell, p.ids[c].data(), p.ncell);
-    auto up = [&](size_t off, const void* src, size_t bytes) -> hipError_t {
-        if (!bytes) return hipSuccess;
-        return hipMemcpyAsync(ws + off, src, bytes, hipMemcpyHostToDevice, s);
-    };
     CF_HIP(up(L.ids, ids.data(), ids.size()));
     CF_HIP(up(L.chans, st.dev.data(), st.dev.size() * sizeof(cf::ChanDev)));
     CF_HIP(up(L.slots, st.slot_lists.data(), st.slot_lists.size() * sizeof(int)));
@@ -1076,7 +1171,7 @@ cf_status run_reduced(const cf::Problem& p, const cf_opts& o, const Staged& st, 
     CF_HIP(up(L.usamp, st.usamp.data(), st.usamp.size() * 4));
     CF_HIP(up(L.uw, st.uw.data(), st.uw.size() * 8));
     CF_HIP(up(L.basis, st.basis.data(), st.basis.size() * 8));
-    CF_HIP(hipMemsetAsync(ws + L.acc, 0, C * 2 * 8, s));
+    CF_HIP(tables.zero(L.acc, C * 2 * 8));
     const bool keep_gamma = (o.flags & CF_FLAG_KEEP_GAMMA) != 0;
     if (keep_gamma) CF_HIP(hipMemsetAsync(ws + L.gamma, 0, (size_t)t_max * C * 8, s));
 
@@ -1138,6 +1233,14 @@ cf_status run_reduced(const cf::Problem& p, const cf_opts& o, const Staged& st, 
         const double phi = p.bloch ? p.kxs[m] * p.nx / p.grid.res : 0.0;   // k_x L
         ord.ph_c[m] = std::cos(phi);
         ord.ph_s[m] = std::sin(phi);
+        // orders with one time step (every k_z point) share its tables
+        int same = 0;
+        while (same < m && !(ord.dt[same] == ord.dt[m] && ord.steps[same] == ord.steps[m])) ++same;
+        if (same < m) {
+            std::copy_n(luts.begin() + same * lut_len, lut_len, luts.begin() + m * lut_len);
+            std::copy_n(ktabs.begin() + (size_t)same * t_max, t_max, ktabs.begin() + (size_t)m * t_max);
+            continue;
+        }
         std::vector<double> l64 = cf::coefficient_lut(p, o.sigma, cm);
         std::copy(l64.begin(), l64.end(), luts.begin() + m * lut_len);
         cf::kernel_table(o.kernel, o.sigma, ord.dt[m], ord.steps[m], ktabs.data() + (size_t)m * t_max);
@@ -1203,8 +1306,9 @@ cf_status run_reduced(const cf::Problem& p, const cf_opts& o, const Staged& st, 
                 idw[k] |= uint32_t(id == cf::kWallId ? 15 : id) << (4 * c);
             }
         ord.idw = reinterpret_cast<const uint32_t*>(ws + L.idp);
-        return up(L.idp, idw.data(), idw.size() * 4);
+        return hipMemcpyAsync(ws + L.idp, idw.data(), idw.size() * 4, hipMemcpyHostToDevice, s);
     };
+    CF_HIP(tables.flush());
 
     hipEvent_t e0, e1;
     CF_HIP(hipEventCreate(&e0));
@@ -1359,9 +1463,6 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
     if (p.reduced()) return run_reduced<T>(p, o, st, L, ws, s, acc_out, gamma_out, device_ms, timing);
     const size_t C = st.chans.size();
     // ---- upload tables --------------------------------------------------
-    std::vector<uint8_t> ids((size_t)cf::kNumComp * p.ncell);
-    for (int c = 0; c < cf::kNumComp; ++c)
-        std::memcpy(ids.data() + (size_t)c * p.ncell, p.ids[c].data(), p.ncell);
     std::vector<double> lut64 = cf::coefficient_lut(p, o.sigma, o.courant);
     std::vector<T> lut(lut64.begin(), lut64.end());
     std::vector<double> ktab(o.n_steps);
@@ -1372,11 +1473,15 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
     pml.insert(pml.end(), chh.begin(), chh.end());
     pml.insert(pml.end(), be.begin(), be.end());
     pml.insert(pml.end(), ce.begin(), ce.end());
-    auto up = [&](size_t off, const void* src, size_t bytes) -> hipError_t {
-        if (!bytes) return hipSuccess;
-        return hipMemcpyAsync(ws + off, src, bytes, hipMemcpyHostToDevice, s);
-    };
-    CF_HIP(up(L.ids, ids.data(), ids.size()));
+    TableUpload tables(ws, s);
+    auto up = [&](size_t off, const void* src, size_t bytes) { return tables.add(off, src, bytes); };
+    for (int c = 0; c < cf::kNumComp; ++c) {
+        const size_t at = L.ids + (size_t)c * p.ncell;
+        // below 1 MB each the components still go up together
+        CF_HIP(p.ncell * cf::kNumComp > (1 << 20)
+                   ? hipMemcpyAsync(ws + at, p.ids[c].data(), p.ncell, hipMemcpyHostToDevice, s)
+                   : up(at, p.ids[c].data(), p.ncell));
+    }
     CF_HIP(up(L.lut, lut.data(), lut.size() * sizeof(T)));
     CF_HIP(up(L.ktab, ktab.data(), ktab.size() * 8));
     CF_HIP(up(L.pml, pml.data(), pml.size() * 8));
@@ -1389,19 +1494,8 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
     CF_HIP(up(L.usamp, st.usamp.data(), st.usamp.size() * 4));
     CF_HIP(up(L.uw, st.uw.data(), st.uw.size() * 8));
     CF_HIP(up(L.basis, st.basis.data(), st.basis.size() * 8));
-    std::vector<uint32_t> idp;
-    if (st.f3d) {
-        // material ids of the six components packed per cell for the fused 3D step
-        idp.resize((size_t)p.ncell * 2);
-        for (int64_t c = 0; c < p.ncell; ++c) {
-            idp[2 * c] = uint32_t(p.ids[CF_EX][c]) | (uint32_t(p.ids[CF_EY][c]) << 8) |
-                         (uint32_t(p.ids[CF_EZ][c]) << 16) | (uint32_t(p.ids[CF_HX][c]) << 24);
-            idp[2 * c + 1] = uint32_t(p.ids[CF_HY][c]) | (uint32_t(p.ids[CF_HZ][c]) << 8);
-        }
-        CF_HIP(up(L.idp, idp.data(), idp.size() * 4));
-        if (!st.zr.empty()) CF_HIP(up(L.zr, st.zr.data(), st.zr.size() * 4));
-    }
-    CF_HIP(hipMemsetAsync(ws + L.acc, 0, C * 2 * 8, s));
+    if (st.f3d && !st.zr.empty()) CF_HIP(up(L.zr, st.zr.data(), st.zr.size() * 4));
+    CF_HIP(tables.zero(L.acc, C * 2 * 8));
     const bool keep_gamma = (o.flags & CF_FLAG_KEEP_GAMMA) != 0;
     if (keep_gamma) CF_HIP(hipMemsetAsync(ws + L.gamma, 0, (size_t)o.n_steps * C * 8, s));
     std::vector<double> lor;
@@ -1409,6 +1503,10 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
         lor = lorentz_table(p, o.sigma, o.courant);
         CF_HIP(up(L.lor, lor.data(), lor.size() * 8));
     }
+    CF_HIP(tables.flush());
+    if (st.f3d)   // material ids of the six components packed per cell for the fused 3D step
+        CF_HIP(cf::launch_pack_ids(reinterpret_cast<const uint8_t*>(ws + L.ids), p.ncell,
+                                   reinterpret_cast<uint2*>(ws + L.idp), s));
 
     T* fields = reinterpret_cast<T*>(ws + L.fields);
     T* psi = st.psi_block > 0 ? reinterpret_cast<T*>(ws + L.psi) : nullptr;
@@ -2205,8 +2303,12 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
         std::vector<double> l64 = cf::coefficient_lut(p, o.sigma, o.courant);
         keepT.emplace_back(l64.begin(), l64.end());
         CF_HIP(up(L.lut + B.lut_off[i], keepT.back().data(), keepT.back().size() * sizeof(T)));
-        keepD.emplace_back(o.n_steps);
-        cf::kernel_table(o.kernel, o.sigma, o.courant / p.grid.res, o.n_steps, keepD.back().data());
+        // problems of one resolution share K(t_k)
+        int same = 0;
+        while (same < i && B.probs[same]->grid.res != p.grid.res) ++same;
+        if (same < i) keepD.push_back(keepD[same]);
+        else keepD.emplace_back(o.n_steps);
+        if (same == i) cf::kernel_table(o.kernel, o.sigma, o.courant / p.grid.res, o.n_steps, keepD.back().data());
         CF_HIP(up(L.ktab + B.ktab_off[i], keepD.back().data(), (size_t)o.n_steps * 8));
     }
     CF_HIP(up(L.chans, B.dev.data(), B.dev.size() * sizeof(cf::ChanDev)));
@@ -2579,7 +2681,7 @@ static cf_status cf_problem_info_impl(const cf_problem* h, const cf_opts* o, cf_
     auto all = cf::channel_table(p, o->pol);
     auto chans = selected_channels(p, *o, &e2);
     Staged sg;
-    stage(p, *o, chans, sg);
+    stage(p, *o, chans, sg, true);
     Layout L = layout_for(p, *o, sg);
     out->n_channels = (int)all.size();
     out->n_faces = (int)p.faces.size();

@@ -142,6 +142,8 @@ struct Grid3D {
     const int2* zr_tab;
     int zr_off[8];
 };
+// idp of a grid from its six id arrays (one behind another, ncell each).
+hipError_t launch_pack_ids(const uint8_t* ids, int64_t ncell, uint2* idp, hipStream_t s);
 // Shape of fused 3D variant v: waves W, rows per wave B, steps per launch.
 void f3d_shape(int variant, int* w, int* b, int* steps);
 

@@ -82,7 +82,6 @@ struct Req {
     size_t bytes = 0, off = 0;
     size_t o_ids, o_lut, o_ktab, o_pml, o_ch, o_slots, o_gidx, o_gw, o_uidx, o_uoff, o_usamp, o_uw, o_basis,
         o_acc, o_fa, o_fb, o_psi, o_psi2, o_idp, o_shadow, o_zr;
-    std::vector<uint32_t> idp;        // fused 3D: packed material ids
     std::vector<uint8_t> ids;
     std::vector<uint8_t> lut;     // field-precision bytes
     std::vector<double> ktab, pml;
@@ -116,7 +115,6 @@ void drop_tables(Req& r) {
     for (auto& v : r.own.ids) std::vector<uint8_t>().swap(v);
     std::vector<cf::Gather>().swap(r.own.gathers);
     r.own.gather_of.clear();
-    std::vector<uint32_t>().swap(r.idp);
     std::vector<uint8_t>().swap(r.ids);
     std::vector<uint8_t>().swap(r.lut);
     std::vector<cf::Patch2DCell>().swap(r.cells);
@@ -311,14 +309,6 @@ std::string prepare(cf_server* S, Req& r) {
     r.ids.resize((size_t)cf::kNumComp * p.ncell);
     for (int c = 0; c < cf::kNumComp; ++c)
         std::memcpy(r.ids.data() + (size_t)c * p.ncell, p.ids[c].data(), p.ncell);
-    if (r.v3 >= 0) {
-        r.idp.resize((size_t)p.ncell * 2);
-        for (int64_t c = 0; c < p.ncell; ++c) {
-            r.idp[2 * c] = uint32_t(p.ids[CF_EX][c]) | (uint32_t(p.ids[CF_EY][c]) << 8) |
-                           (uint32_t(p.ids[CF_EZ][c]) << 16) | (uint32_t(p.ids[CF_HX][c]) << 24);
-            r.idp[2 * c + 1] = uint32_t(p.ids[CF_HY][c]) | (uint32_t(p.ids[CF_HZ][c]) << 8);
-        }
-    }
     std::vector<double> l64 = cf::coefficient_lut(p, r.opts.sigma, r.opts.courant);
     if (S->precision == CF_FP64) {
         r.lut.resize(l64.size() * 8);
@@ -457,9 +447,11 @@ hipError_t admit(cf_server* S, Req& r) {
     UP(r.o_usamp, st.usamp.data(), st.usamp.size() * 4);
     UP(r.o_uw, st.uw.data(), st.uw.size() * 8);
     UP(r.o_basis, st.basis.data(), st.basis.size() * 8);
-    UP(r.o_idp, r.idp.data(), r.idp.size() * 4);
     if (r.v3 >= 0) UP(r.o_zr, st.zr.data(), st.zr.size() * 4);
 #undef UP
+    if (r.v3 >= 0 && (e = cf::launch_pack_ids(reinterpret_cast<const uint8_t*>(b + r.o_ids), r.prob->ncell,
+                                              reinterpret_cast<uint2*>(b + r.o_idp), s)) != hipSuccess)
+        return e;
     if ((e = hipMemsetAsync(b + r.o_acc, 0, (size_t)r.C * 2 * 8, s)) != hipSuccess) return e;
     r.wave = 0;
     r.start = S->clock;

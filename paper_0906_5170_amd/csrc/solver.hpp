@@ -82,6 +82,9 @@ struct Staged {
     std::vector<Wave> waves;
     std::vector<int32_t> gidx, uidx, uoff, usamp;
     std::vector<double> gw, uw, basis;
+    struct {
+        size_t gidx = 0, uidx = 0, uoff = 0, usamp = 0, basis = 0;
+    } len;                                 // their lengths (gw as gidx, uw as usamp)
     int max_uniq = 0;
     int resident = 0;                      // field blocks on the device
     int ncomp = 3;
@@ -145,8 +148,11 @@ bool patch2d_pick(const cf::Patch2DSet& set, int precision, const int used[2], c
 std::vector<cf::Patch2DCell> patch2d_cells(const cf::Patch2DSet& set, const std::array<int, 2>& shape);
 cf::Patch2DInst patch2d_head(const cf::Patch2DSet& set, const std::array<int, 2>& shape, const cf::Patch2DCell* at);
 
-// Stage the tables of one problem for the given channels and options.
-void stage(const cf::Problem& p, const cf_opts& o, const std::vector<cf::Channel>& chans, Staged& st);
+// Stage the tables of one problem for the given channels and options
+// (sizes_only: their lengths and everything a layout needs, but not the
+// interpolation tables and the basis themselves).
+void stage(const cf::Problem& p, const cf_opts& o, const std::vector<cf::Channel>& chans, Staged& st,
+           bool sizes_only = false);
 // XCD-balanced work list (see api.cpp).
 // Work list of the fused 2D launch: the tiles of each slot on one XCD
 // (channels balanced over the 8 XCDs, block b on XCD b mod 8), each slot's
