@@ -238,31 +238,47 @@ void patch2d_sizes(const std::vector<cf::ChanDev>& dev, const std::vector<int32_
 }
 
 bool patch2d_pick(const cf::Patch2DSet& set, int precision, const int used[2], const int together[2],
-                  const cf::Patch2DSizes& z, std::array<int, 2>& shape) {
+                  const cf::Patch2DSizes& z, PatchShapes& shape) {
     const size_t lim = cf::device_lds_limit();
     for (int q = 0; q < 2; ++q) {
         shape[q] = used[q] > 0 ? cf::patch2d_choose(set, precision, q, together[q], z, lim) : -1;
         if (used[q] > 0 && shape[q] < 0) return false;
     }
-    return true;
+    if (!patch2d_in_parts(set, shape)) return true;
+    // lists in the ids' place: no shape that reads the ids, and room for them
+    for (int q = 0; q < 2; ++q)
+        if (shape[q] >= 0 && (set.shapes[shape[q]].coef == cf::kRegAll || !set.masks)) return false;
+    return patch2d_cells(set, shape).size() * sizeof(cf::Patch2DCell) <= (size_t)cf::kNumComp * set.ncell;
 }
 
-std::vector<cf::Patch2DCell> patch2d_cells(const cf::Patch2DSet& set, const std::array<int, 2>& shape) {
-    std::vector<cf::Patch2DCell> out;
+bool patch2d_in_parts(const cf::Patch2DSet& set, const PatchShapes& shape) {
     for (int q = 0; q < 2; ++q)
-        if (shape[q] >= 0) out.insert(out.end(), set.lists[q][shape[q]].begin(), set.lists[q][shape[q]].end());
+        if (shape[q] >= 0 && set.lists[q][shape[q]].parts > 1) return true;
+    return false;
+}
+
+std::vector<cf::Patch2DCell> patch2d_cells(const cf::Patch2DSet& set, const PatchShapes& shape) {
+    std::vector<cf::Patch2DCell> out;
+    for (int q = 0; q < 2; ++q) {
+        if (shape[q] < 0) continue;
+        const auto& c = set.lists[q][shape[q]].cells;
+        out.insert(out.end(), c.begin(), c.end());
+    }
     return out;
 }
 
-cf::Patch2DInst patch2d_head(const cf::Patch2DSet& set, const std::array<int, 2>& shape, const cf::Patch2DCell* at) {
+cf::Patch2DInst patch2d_head(const cf::Patch2DSet& set, const PatchShapes& shape, const cf::Patch2DCell* at) {
     cf::Patch2DInst h{};
     h.id_e = set.id_e;
     h.id_h = set.id_h;
+    h.masks = set.masks ? 1 : 0;
     for (int q = 0; q < 2; ++q) {
         if (shape[q] < 0) continue;
+        const cf::Patch2DList& l = set.lists[q][shape[q]];
         h.cells[q] = at;
-        h.n[q] = (int32_t)set.lists[q][shape[q]].size();
-        at += h.n[q];
+        h.n[q] = l.n;
+        h.surf_part[q] = l.surf_part;
+        at += l.cells.size();
     }
     return h;
 }
@@ -1658,31 +1674,45 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
     // cells fit the registers of one compute unit advances whole channels
     // there instead of tiles (no halo to recompute, no launch every few steps;
     // 400 x 200 piston, 448 channels, 10000 steps, FP32: 108.4 -> 27.4 ms on
-    // the device; 80 x 40, 116 channels, 2000 steps, FP64: 5.9 -> 1.0 ms).  Its patch
-    // lists lie in the second field array, which only the tiles need.
+    // the device; 80 x 40, 116 channels, 2000 steps, FP64: 5.9 -> 1.0 ms), a
+    // larger one in parts.  The patch lists lie in the second field array, which
+    // whole channels do not need; parts do, and put them in the place of the
+    // material ids, which are not read after the start.
     std::shared_ptr<const cf::Patch2DSet> patches;
     cf::Patch2DSizes psizes{1, 1, 1};
     std::deque<std::vector<cf::Patch2DCell>> host_cells;
     std::deque<cf::Patch2DInst> host_heads;
-    std::vector<std::array<int, 2>> pshape;
+    std::deque<std::vector<int>> host_items;
+    std::vector<PatchShapes> pshape;
+    std::vector<size_t> plists;                            // where the lists of each wave go
     if (variant >= 0 && o.tile_variant == 0) {
         patches = cached_patches(p, o.precision);
         patch2d_sizes(st.dev, st.gidx, p.nx, psizes);
         for (const Wave& w : st.waves) {
-            std::array<int, 2> sh;
+            PatchShapes sh;
             const int num[2] = {w.n_tm, w.n_te};
-            if (!patch2d_pick(*patches, o.precision, num, num, psizes, sh)) {
+            bool ok = patch2d_pick(*patches, o.precision, num, num, psizes, sh);
+            if (ok) {
+                const bool parts = patch2d_in_parts(*patches, sh);
+                host_cells.push_back(patch2d_cells(*patches, sh));
+                plists.push_back(parts ? L.ids : L.fields2);
+                ok = parts || host_cells.back().size() * sizeof(cf::Patch2DCell) <= field_bytes;
+                host_heads.push_back(patch2d_head(*patches, sh, reinterpret_cast<const cf::Patch2DCell*>(
+                                                                    ws + plists.back())));
+                // channels and parts of the blocks, the longest lists first; the head behind the TE ones
+                for (int q = 0; q < 2; ++q) {
+                    const int* list = st.slot_lists.data() + (q == 0 ? w.tm_off : w.te_off);
+                    host_items.push_back(patch2d_items(*patches, sh, q, list, num[q]));
+                    const size_t bytes = host_items.back().size() * sizeof(int) +
+                                         (q == 1 ? 16 + sizeof(cf::Patch2DInst) : 0);
+                    ok = ok && bytes <= L.work_items * sizeof(cf::WorkItem);
+                }
+                pshape.push_back(sh);
+            }
+            if (!ok) {
                 patches = nullptr;
                 break;
             }
-            host_cells.push_back(patch2d_cells(*patches, sh));
-            pshape.push_back(sh);
-            if (sizeof(cf::Patch2DInst) + host_cells.back().size() * sizeof(cf::Patch2DCell) > field_bytes) {
-                patches = nullptr;
-                break;
-            }
-            host_heads.push_back(patch2d_head(*patches, sh, reinterpret_cast<const cf::Patch2DCell*>(
-                                                                ws + L.fields2 + sizeof(cf::Patch2DInst))));
         }
     }
     // Steps of a patch launch: where the channels outnumber the compute units,
@@ -1694,9 +1724,13 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
         patch_launch_steps = std::min({patch_launch_steps, o.n_steps, 1 << 14});
         timing->launch_steps = patch_launch_steps;
         for (int q = 0; q < 2; ++q)
-            if (pshape[0][q] >= 0) timing->live_cells[q] = patches->cells[q][pshape[0][q]];
+            if (pshape[0][q] >= 0) {
+                const cf::Patch2DList& l = patches->lists[q][pshape[0][q]];
+                timing->live_cells[q] = l.live_cells;
+                if (l.steps > 0) timing->launch_steps = std::min(timing->launch_steps, l.steps);
+            }
         if (smp.on)
-            smp.stride = std::max(1, 2 * ((o.n_steps + patch_launch_steps - 1) / patch_launch_steps) *
+            smp.stride = std::max(1, 2 * ((o.n_steps + timing->launch_steps - 1) / timing->launch_steps) *
                                          (int)st.waves.size() / 200);
     }
     if (variant >= 0 && o.tile_variant == 0 && !patches && !st.waves.empty()) {
@@ -1836,12 +1870,23 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
         }
         if (variant >= 0 && patches) {
             const size_t wi = (size_t)(&w - st.waves.data());
-            const std::array<int, 2>& sh = pshape[wi];
+            const PatchShapes& sh = pshape[wi];
             STEP_OK(upload_inst(make_inst(st.plans[variant], true)));
-            STEP_OK(hipMemcpyAsync(ws + L.fields2, &host_heads[wi], sizeof(cf::Patch2DInst), hipMemcpyHostToDevice, s));
-            STEP_OK(hipMemcpyAsync(ws + L.fields2 + sizeof(cf::Patch2DInst), host_cells[wi].data(),
+            STEP_OK(hipMemcpyAsync(ws + plists[wi], host_cells[wi].data(),
                                    host_cells[wi].size() * sizeof(cf::Patch2DCell), hipMemcpyHostToDevice, s));
-            const cf::Patch2DInst* heads = reinterpret_cast<const cf::Patch2DInst*>(ws + L.fields2);
+            const int* ditems[2];
+            const size_t te_bytes = host_items[2 * wi + 1].size() * sizeof(int);
+            for (int q = 0; q < 2; ++q) {
+                ditems[q] = reinterpret_cast<const int*>(dwork + q * L.work_items);
+                const std::vector<int>& it = host_items[2 * wi + q];
+                if (!it.empty())
+                    STEP_OK(hipMemcpyAsync(const_cast<int*>(ditems[q]), it.data(), it.size() * sizeof(int),
+                                           hipMemcpyHostToDevice, s));
+            }
+            const cf::Patch2DInst* heads = reinterpret_cast<const cf::Patch2DInst*>(
+                ws + align_up(L.work + L.work_items * sizeof(cf::WorkItem) + te_bytes, 16));
+            STEP_OK(hipMemcpyAsync(const_cast<cf::Patch2DInst*>(heads), &host_heads[wi], sizeof(cf::Patch2DInst),
+                                   hipMemcpyHostToDevice, s));
             const int kh = st.shapes[variant].kh, num[2] = {w.n_tm, w.n_te};
             // the polarizations on two streams, as for the tiles
             const bool split_pol = !smp.on && !conv.on && w.n_tm > 0 && w.n_te > 0;
@@ -1850,22 +1895,42 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
             STEP_OK(graph.begin());
             const hipStream_t ls = graph.launch_stream(s);
             hipError_t body = split_pol ? side.open(ls) : hipSuccess;
+            int parity[2] = {0, 0};
+            // at most ks steps of polarization q from step m; the steps taken
+            auto launch = [&](int q, int m, int ks) -> hipError_t {
+                const cf::Patch2DList& l = patches->lists[q][sh[q]];
+                const bool take = smp.begin(ls);
+                const hipError_t e = cf::launch_patch2d<T>(
+                    sh[q], q == 0 ? CF_POL_TM : CF_POL_TE, dch, ditems[q], (int)host_items[2 * wi + q].size(), dinst,
+                    heads, l.n, psizes, ks, m, parity[q], l.parts > 1 ? parity[q] ^ 1 : parity[q],
+                    split_pol && q == 1 ? side.s[0] : ls);
+                if (l.parts > 1) parity[q] ^= 1;
+                const double cu = (double)num[q] * p.ncell * ks;
+                if (e == hipSuccess) smp.end(take, ls, cu, cu * state_bytes);
+                return e;
+            };
+            auto most = [&](int q) {
+                const int steps = num[q] > 0 ? patches->lists[q][sh[q]].steps : 0;
+                return steps > 0 ? std::min(steps, patch_launch_steps) : patch_launch_steps;
+            };
             if (body == hipSuccess)
                 body = [&]() -> hipError_t {
+                    if (!conv.on && !smp.on) {
+                        for (int q = 0; q < 2; ++q)
+                            for (int m = 0, ks; num[q] > 0 && m < o.n_steps; m += ks) {
+                                ks = std::min(most(q), o.n_steps - m);
+                                const hipError_t e = launch(q, m, ks);
+                                if (e != hipSuccess) return e;
+                            }
+                        return hipSuccess;
+                    }
                     for (int m = 0; m < o.n_steps;) {
-                        int ks = std::min(patch_launch_steps, o.n_steps - m);
+                        int ks = std::min({most(0), most(1), o.n_steps - m});
                         // the convergence stop looks after the tiles' multiples of kh
                         if (conv.on) ks = std::min(ks, std::max((conv.next - m + kh - 1) / kh * kh, kh));
                         for (int q = 0; q < 2; ++q) {
-                            if (num[q] == 0) continue;
-                            const bool take = smp.begin(ls);
-                            const hipError_t e = cf::launch_patch2d<T>(
-                                sh[q], q == 0 ? CF_POL_TM : CF_POL_TE, dch, q == 0 ? s_tm : s_te, num[q], dinst, heads,
-                                (int)patches->lists[q][sh[q]].size(), psizes, ks, m,
-                                split_pol && q == 1 ? side.s[0] : ls);
+                            const hipError_t e = num[q] > 0 ? launch(q, m, ks) : hipSuccess;
                             if (e != hipSuccess) return e;
-                            const double cu = (double)num[q] * p.ncell * ks;
-                            smp.end(take, ls, cu, cu * state_bytes);
                         }
                         m += ks;
                         if (converged(m)) break;
@@ -1877,6 +1942,11 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
                 if (body == hipSuccess) body = ec;
             }
             STEP_OK(graph.end(s, body));
+            // the next wave's start reads the ids again
+            if (plists[wi] == L.ids && wi + 1 < st.waves.size())
+                for (int c = 0; c < cf::kNumComp; ++c)
+                    STEP_OK(hipMemcpyAsync(ws + L.ids + (size_t)c * p.ncell, p.ids[c].data(), p.ncell,
+                                           hipMemcpyHostToDevice, s));
         } else if (variant >= 0) {
             const TBPlan& pl = st.plans[variant];
             const int kh = st.shapes[variant].kh;
@@ -2391,53 +2461,44 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
         }
         return make_work(slots, tl, st);
     };
-    // Problems whose live cells fit a compute unit's registers go to the 2D
-    // patch kernel (see run), every shape's channels in one launch per
-    // polarization, the longest first; the rest to the tiles.  The patch lists
-    // lie in the second field array of such a problem, the channel lists behind
-    // the tiles' work items.
+    // Problems go to the 2D patch kernel where it covers them (see run_solve),
+    // every shape's channels in one launch per polarization, the longest first;
+    // the rest to the tiles.  Patch lists of whole channels lie in the second
+    // field array of such a problem, those of a problem in parts in the place of
+    // its ids; the launches' items and the heads behind the tiles' work items.
     std::vector<std::shared_ptr<const cf::Patch2DSet>> keep_sets(n);
     std::vector<const cf::Patch2DSet*> psets(n, nullptr);
-    std::vector<std::array<int, 2>> pshapes(n, {-1, -1});
-    std::vector<cf::Patch2DCell> cells;
+    std::vector<PatchShapes> pshapes(n, {-1, -1});
+    std::deque<std::vector<cf::Patch2DCell>> cells;
+    std::vector<size_t> cells_at(n, 0);                // where they go
     std::vector<cf::Patch2DInst> heads(n);
-    size_t blob_at = 0;                                // field offset of the lists in Bf
     struct PatchGroup {
-        int shape, n;                                  // n: longest patch list
+        int shape, n, steps;                           // n: longest patch list; steps: of a launch (0: any)
         std::vector<std::pair<double, int>> slots;     // (cells, slot)
-        size_t at;                                     // byte offset of its channel list
+        size_t at;                                     // first of its items
+        int count;
     };
-    std::map<int, PatchGroup> groups[2];               // per polarization slot: by shape
-    std::vector<int> tiles[2], patch_slots[2];         // slots per path
+    std::map<std::pair<bool, int>, PatchGroup> groups[2];   // per polarization slot: by (in parts, shape)
+    std::vector<int> tiles[2], items[2];               // tiled slots, patch items
     cf::Patch2DSizes psizes{1, 1, 1};
     if (o.tile_variant == 0) {
         const int together[2] = {(int)B.tm.size(), (int)B.te.size()};
         for (int i = 0; i < n; ++i) patch2d_sizes(B.st[i].dev, B.st[i].gidx, B.probs[i]->nx, psizes);
-        size_t room = 0;
         for (int i = 0; i < n; ++i) {
             keep_sets[i] = cached_patches(*B.probs[i], o.precision);
             const int used[2] = {B.inst_tm_n[i], B.inst_te_n[i]};
-            if (!patch2d_pick(*keep_sets[i], o.precision, used, together, psizes, pshapes[i])) {
-                pshapes[i] = {-1, -1};
+            if (!patch2d_pick(*keep_sets[i], o.precision, used, together, psizes, pshapes[i])) continue;
+            cells.push_back(patch2d_cells(*keep_sets[i], pshapes[i]));
+            const size_t elems = (i + 1 < n ? B.field_off[i + 1] : B.field_elems) - B.field_off[i];
+            const bool parts = patch2d_in_parts(*keep_sets[i], pshapes[i]);
+            cells_at[i] = parts ? L.ids + B.ids_off[i] : align_up(L.fB + B.field_off[i] * sizeof(T), 16);
+            if (!parts && cells.back().size() * sizeof(cf::Patch2DCell) + 16 > elems * sizeof(T)) {
+                cells.pop_back();
                 continue;
             }
             psets[i] = keep_sets[i].get();
-            const size_t elems = (i + 1 < n ? B.field_off[i + 1] : B.field_elems) - B.field_off[i];
-            if (elems * sizeof(T) > room) {
-                room = elems * sizeof(T);
-                blob_at = B.field_off[i];
-            }
+            heads[i] = patch2d_head(*psets[i], pshapes[i], reinterpret_cast<const cf::Patch2DCell*>(ws + cells_at[i]));
         }
-        const cf::Patch2DCell* at = reinterpret_cast<const cf::Patch2DCell*>(
-            reinterpret_cast<const cf::Patch2DInst*>(Bf + blob_at) + n);
-        for (int i = 0; i < n; ++i) {
-            if (!psets[i]) continue;
-            heads[i] = patch2d_head(*psets[i], pshapes[i], at + cells.size());
-            const auto c = patch2d_cells(*psets[i], pshapes[i]);
-            cells.insert(cells.end(), c.begin(), c.end());
-        }
-        if (n * sizeof(heads[0]) + cells.size() * sizeof(cells[0]) > room)
-            std::fill(psets.begin(), psets.end(), nullptr);
     }
     for (int q = 0; q < 2; ++q) {
         for (int sl : q == 0 ? B.tm : B.te) {
@@ -2447,15 +2508,22 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
                 continue;
             }
             const int v = pshapes[i][q];
-            PatchGroup& gr = groups[q].try_emplace(v, PatchGroup{v, 0, {}, 0}).first->second;
-            gr.n = std::max(gr.n, (int)psets[i]->lists[q][v].size());
-            gr.slots.emplace_back(-psets[i]->cells[q][v], sl);
+            const cf::Patch2DList& l = psets[i]->lists[q][v];
+            PatchGroup& gr = groups[q].try_emplace({l.parts > 1, v}, PatchGroup{v, 0, l.steps, {}, 0, 0}).first->second;
+            gr.n = std::max(gr.n, l.n);
+            gr.slots.emplace_back(-(double)l.n, sl);
         }
         for (auto& kv : groups[q]) {
-            std::stable_sort(kv.second.slots.begin(), kv.second.slots.end(),
+            PatchGroup& gr = kv.second;
+            std::stable_sort(gr.slots.begin(), gr.slots.end(),
                              [](const auto& a, const auto& b) { return a.first < b.first; });
-            kv.second.at = patch_slots[q].size() * sizeof(int);
-            for (const auto& c : kv.second.slots) patch_slots[q].push_back(c.second);
+            gr.at = items[q].size();
+            for (const auto& c : gr.slots) {
+                const int i = B.dev[c.second].inst;
+                const auto it = patch2d_items(*psets[i], pshapes[i], q, &c.second, 1);
+                items[q].insert(items[q].end(), it.begin(), it.end());
+            }
+            gr.count = (int)(items[q].size() - gr.at);
         }
     }
     const bool any_patch = !groups[0].empty() || !groups[1].empty();
@@ -2519,8 +2587,12 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
             timing[i].variant = variant;
             if (!psets[i]) continue;
             timing[i].launch_steps = patch_steps;
-            for (int q = 0; q < 2; ++q)
-                if (pshapes[i][q] >= 0) timing[i].live_cells[q] = psets[i]->cells[q][pshapes[i][q]];
+            for (int q = 0; q < 2; ++q) {
+                if (pshapes[i][q] < 0) continue;
+                const cf::Patch2DList& l = psets[i]->lists[q][pshapes[i][q]];
+                timing[i].live_cells[q] = l.live_cells;
+                if (l.steps > 0) timing[i].launch_steps = std::min(timing[i].launch_steps, l.steps);
+            }
         }
         keepI.push_back(insts_for(variant));
         BSTEP(up(L.inst, keepI.back().data(), n * sizeof(cf::InstDev)));
@@ -2530,23 +2602,22 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
         keepW.push_back(work_for(variant, tiles[1]));
         const int nw_te = (int)keepW.back().size();
         BSTEP(up(L.work + B.work_items * sizeof(cf::WorkItem), keepW.back().data(), nw_te * sizeof(cf::WorkItem)));
+        // the items, and behind the TE ones the heads
         const size_t region = B.work_items * sizeof(cf::WorkItem);
         const size_t pat[2] = {L.work + nw_tm * sizeof(cf::WorkItem), L.work + region + nw_te * sizeof(cf::WorkItem)};
-        for (int q = 0; q < 2; ++q) {
-            const size_t bytes = patch_slots[q].size() * sizeof(int);
-            if (pat[q] + bytes > L.work + (q + 1) * region) BSTEP(hipErrorInvalidValue);
-            BSTEP(up(pat[q], patch_slots[q].data(), bytes));
+        const size_t heads_at = align_up(pat[1] + items[1].size() * sizeof(int), 16);
+        if (any_patch) {
+            if (pat[0] + items[0].size() * sizeof(int) > L.work + region ||
+                heads_at + n * sizeof(heads[0]) > L.work + 2 * region)
+                BSTEP(hipErrorInvalidValue);
+            for (int q = 0; q < 2; ++q) BSTEP(up(pat[q], items[q].data(), items[q].size() * sizeof(int)));
+            BSTEP(up(heads_at, heads.data(), n * sizeof(heads[0])));
         }
+        const cf::Patch2DInst* dheads = reinterpret_cast<const cf::Patch2DInst*>(ws + heads_at);
         BSTEP(hipMemsetAsync(dacc, 0, (size_t)B.C * 2 * 8, s));
         BSTEP(hipMemsetAsync(A, 0, fbytes, s));
         if (n_tm + n_te > 0)
             BSTEP(hipMemsetAsync(Bf, 0, fbytes, s));   // cells the fused kernel skips stay zero in both arrays
-        const cf::Patch2DInst* dheads = reinterpret_cast<const cf::Patch2DInst*>(Bf + blob_at);
-        if (any_patch) {
-            const size_t at = L.fB + blob_at * sizeof(T);
-            BSTEP(up(at, heads.data(), n * sizeof(heads[0])));
-            BSTEP(up(at + n * sizeof(heads[0]), cells.data(), cells.size() * sizeof(cells[0])));
-        }
         BSTEP(hipEventRecord(e0, s));
         BSTEP(cf::launch_kick<T>(A, dch, dl, B.C, B.max_uniq, tabs, s));
         for (int i = 0; i < n; ++i) {
@@ -2558,6 +2629,15 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
             BSTEP(cf::launch_h2d<T>(CF_POL_TE, 1, A, dch, te, B.inst_te_n[i], g, lut, s));
             BSTEP(cf::launch_e2d<T>(CF_POL_TM, 1, A, dch, tm, B.inst_tm_n[i], g, lut, s));
             BSTEP(cf::launch_e2d<T>(CF_POL_TE, 1, A, dch, te, B.inst_te_n[i], g, lut, s));
+        }
+        {
+            // the patch lists, some of them over ids that the start has read
+            size_t k = 0;
+            for (int i = 0; i < n; ++i)
+                if (psets[i]) {
+                    BSTEP(up(cells_at[i], cells[k].data(), cells[k].size() * sizeof(cf::Patch2DCell)));
+                    ++k;
+                }
         }
         int launches = 0;
         // each polarization of each path on a stream of its own (parallel
@@ -2579,17 +2659,22 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
             auto on = [&](int k, int q) { return lane[k][q] == 0 ? ls : side.s[lane[k][q] - 1]; };
             if (body == hipSuccess)
                 body = [&]() -> hipError_t {
-                    for (int m = 0; m < o.n_steps; m += patch_steps)
-                        for (int q = 0; q < 2; ++q)
-                            for (const auto& kv : groups[q]) {
-                                const PatchGroup& gr = kv.second;
+                    for (int q = 0; q < 2; ++q)
+                        for (const auto& kv : groups[q]) {
+                            const PatchGroup& gr = kv.second;
+                            const int most = gr.steps > 0 ? std::min(gr.steps, patch_steps) : patch_steps;
+                            int par = 0;
+                            for (int m = 0; m < o.n_steps; m += most) {
+                                const int to = gr.steps > 0 ? par ^ 1 : par;
                                 const hipError_t e = cf::launch_patch2d<T>(
                                     gr.shape, q == 0 ? CF_POL_TM : CF_POL_TE, dch,
-                                    reinterpret_cast<const int*>(ws + pat[q] + gr.at), (int)gr.slots.size(), dinst,
-                                    dheads, gr.n, psizes, std::min(patch_steps, o.n_steps - m), m, on(1, q));
+                                    reinterpret_cast<const int*>(ws + pat[q]) + gr.at, gr.count, dinst, dheads, gr.n,
+                                    psizes, std::min(most, o.n_steps - m), m, par, to, on(1, q));
                                 if (e != hipSuccess) return e;
+                                par = to;
                                 ++launches;
                             }
+                        }
                     int parity = 0;
                     for (int m = 0; m < o.n_steps && n_tm + n_te > 0; m += kh) {
                         hipError_t e = hipSuccess;

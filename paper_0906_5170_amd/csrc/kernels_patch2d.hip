@@ -131,8 +131,8 @@ __device__ __forceinline__ double masked(double v, uint32_t bits, int k) {
 // registers: read from LDS by an ordinary wave they took 0.9 us per step.
 template <typename T, int POL, int CX, int B, int MW, int COEF>
 __global__ __launch_bounds__(256 * MW) __attribute__((amdgpu_waves_per_eu(MW)))
-void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, const InstDev* __restrict__ insts,
-               const Patch2DInst* __restrict__ heads, int kmax, int mclock, P2Lds l) {
+void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ items, const InstDev* __restrict__ insts,
+               const Patch2DInst* __restrict__ heads, int kmax, int mclock, int src, int dst, P2Lds l) {
     constexpr bool TM = POL == CF_POL_TM;
     constexpr int C0 = TM ? CF_EZ : CF_EX, C1 = TM ? CF_HX : CF_EY, C2 = TM ? CF_HY : CF_HZ;
     constexpr int NE = TM ? 1 : 2, NH = 3 - NE, NC = CX * B;
@@ -143,8 +143,8 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, co
     __shared__ int s_box[4];                       // box of the measured points
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int slot = slots[blockIdx.x];
-    const ChanDev d = ch[slot];
+    const int item = items[blockIdx.x], part = item >> kPartShift;
+    const ChanDev d = ch[item & ((1 << kPartShift) - 1)];
     const InstDev g = insts[d.inst];
     const Patch2DInst hd = heads[d.inst];
     const SurfTables& t = g.t;
@@ -152,6 +152,7 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, co
     const int ksteps = min(kmax, g.nsteps - m0);
     if (m0 < 0 || ksteps <= 0) return;             // not started / finished
     const int n = hd.n[TM ? 0 : 1];
+    const bool surf = part == hd.surf_part[TM ? 0 : 1];   // this block takes the surface sums
     const int nx = g.nx, ny = g.ny;
     const auto lk = as_global(static_cast<const T*>(g.lut)) + d.kind * 6 * 256 * 2;   // (a, b) of (comp, id)
 
@@ -163,7 +164,7 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, co
     uint16_t* const so = reinterpret_cast<uint16_t*>(lds + l.so);
 
     // ---- surface tables and the zero entries ---------------------------
-    const int npt = d.nsamp * d.P;
+    const int npt = surf ? d.nsamp * d.P : 0;
     if (tid < 4) s_box[tid] = tid < 2 ? 0x7fffffff : -1;
     for (int k = tid; k < S; k += nthr) XE[n * S + k] = XH[n * S + k] = T(0);
     __syncthreads();
@@ -187,6 +188,14 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, co
         // ---- the block's last wave: surface sum and accumulation of every
         // step, while the others take the next one (the samples before their
         // H half, the total before their E half)
+        if (!surf) {
+            __syncthreads();
+            for (int step = 0; step < ksteps; ++step) {
+                __syncthreads();
+                __syncthreads();
+            }
+            return;
+        }
         const auto acc = as_global(g.acc + 2 * d.local);
         const auto ktab = as_global(g.ktab) + m0;
         const int nsamp = d.nsamp, P = d.P;
@@ -271,12 +280,14 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, co
     }
 
     // ---- the patch: neighbours, coefficients, fields ----------------------
-    const bool act = tid < n;
     Patch2DCell pc{};
-    if (act) {
-        const auto q = as_global(hd.cells[TM ? 0 : 1]) + tid;
-        pc = {q->x0, q->y0, q->right, q->left, q->up, q->down, 0, 0};
+    if (tid < n) {
+        const auto q = reinterpret_cast<yee::gmem<const uint64_t>>(as_global(hd.cells[TM ? 0 : 1])) +
+                       (int64_t)3 * (part * n + tid);
+        const uint64_t w[3] = {q[0], q[1], q[2]};
+        __builtin_memcpy(&pc, w, sizeof(pc));
     }
+    const bool act = (pc.flags & kPatchUsed) != 0;
     const int x0 = pc.x0, y0 = pc.y0;
     T* const er = XE + (act ? pc.right : n) * S;   // E column of the patch to the right
     T* const eu = XE + (act ? pc.up : n) * S;      // E row of the patch above
@@ -295,9 +306,9 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, co
     T ke[NE][KE], kh[NH][KH];                      // kRegE, kRegAll: b of the cells
     uint32_t in_m = 0;                             // cells inside the measured box
 #pragma unroll
-    for (int e = 0; e < NE; ++e) live[e] = 0;
+    for (int e = 0; e < NE; ++e) live[e] = pc.live[e];
     {
-        const auto F0 = as_global(static_cast<const T*>(g.fa)) + d.field_off;
+        const auto F0 = as_global(static_cast<const T*>(src ? g.fb : g.fa)) + d.field_off;
         const auto F1 = F0 + g.ncell;
         const auto F2 = F1 + g.ncell;
         const auto I0 = as_global(g.ids[C0]), I1 = as_global(g.ids[C1]), I2 = as_global(g.ids[C2]);
@@ -313,20 +324,22 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, co
                 f0[r][j] = in ? v0 : T(0);
                 f1[r][j] = in ? v1 : T(0);
                 f2[r][j] = in ? v2 : T(0);
-                const uint32_t i0 = in ? I0[c] : kNullId, i1 = in ? I1[c] : kNullId, i2 = in ? I2[c] : kNullId;
-                const T b0 = lk[(C0 * 256 + i0) * 2 + 1];
-                if constexpr (COEF == kMaskB) {
-                    live[0] |= b0 != T(0) ? 1u << k : 0u;
-                    if constexpr (!TM) live[NE - 1] |= lk[(C1 * 256 + i1) * 2 + 1] != T(0) ? 1u << k : 0u;
-                } else {
-                    ke[0][k % KE] = b0;
-                    if constexpr (!TM) ke[NE - 1][k % KE] = lk[(C1 * 256 + i1) * 2 + 1];
+                if constexpr (COEF == kRegE) {
+                    ke[0][k % KE] = masked(be, pc.live[0], k);
+                    if constexpr (!TM) ke[NE - 1][k % KE] = masked(be, pc.live[1], k);
+                    if (!hd.masks) {
+                        ke[0][k % KE] = lk[(C0 * 256 + (in ? I0[c] : kNullId)) * 2 + 1];
+                        if constexpr (!TM) ke[NE - 1][k % KE] = lk[(C1 * 256 + (in ? I1[c] : kNullId)) * 2 + 1];
+                    }
                 }
                 if constexpr (COEF == kRegAll) {
+                    const uint32_t i0 = in ? I0[c] : kNullId, i1 = in ? I1[c] : kNullId, i2 = in ? I2[c] : kNullId;
+                    ke[0][k % KE] = lk[(C0 * 256 + i0) * 2 + 1];
+                    if constexpr (!TM) ke[NE - 1][k % KE] = lk[(C1 * 256 + i1) * 2 + 1];
                     if constexpr (TM) kh[0][k % KH] = lk[(C1 * 256 + i1) * 2 + 1];
                     kh[NH - 1][k % KH] = lk[(C2 * 256 + i2) * 2 + 1];
                 }
-                if (in && x >= mx0 && x <= mx1 && y >= my0 && y <= my1) in_m |= 1u << k;
+                if (surf && in && x >= mx0 && x <= mx1 && y >= my0 && y <= my1) in_m |= 1u << k;
             }
         }
     }
@@ -438,14 +451,14 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ slots, co
         if (wave_m) put();
         __syncthreads();
     }
-    const auto F0 = as_global(static_cast<T*>(g.fa)) + d.field_off;
+    const auto F0 = as_global(static_cast<T*>(dst ? g.fb : g.fa)) + d.field_off;
     const auto F1 = F0 + g.ncell;
     const auto F2 = F1 + g.ncell;
 #pragma unroll
     for (int r = 0; r < B; ++r)
 #pragma unroll
         for (int j = 0; j < CX; ++j)
-            if (act && x0 + j < nx && y0 + r < ny) {
+            if ((pc.flags & kPatchStored) && x0 + j < nx && y0 + r < ny) {
                 const uint32_t c = (uint32_t)((y0 + r) * nx + x0 + j);
                 F0[c] = f0[r][j];
                 F1[c] = f1[r][j];
@@ -484,19 +497,19 @@ int p2_stride_of(const Patch2DShape& q) {
 }
 
 template <typename T, int V>
-hipError_t p2_launch(int shape, int pol, int threads, const P2Lds& l, const ChanDev* ch, const int* slots, int nslots,
-                     const InstDev* inst, const Patch2DInst* heads, int kmax, int m, hipStream_t s) {
+hipError_t p2_launch(int shape, int pol, int threads, const P2Lds& l, const ChanDev* ch, const int* items, int nitems,
+                     const InstDev* inst, const Patch2DInst* heads, int kmax, int m, int src, int dst, hipStream_t s) {
     if constexpr (V >= P2Shapes<T>::n) {
         return hipErrorInvalidValue;
     } else {
         if (shape != V)
-            return p2_launch<T, V + 1>(shape, pol, threads, l, ch, slots, nslots, inst, heads, kmax, m, s);
+            return p2_launch<T, V + 1>(shape, pol, threads, l, ch, items, nitems, inst, heads, kmax, m, src, dst, s);
         constexpr Patch2DShape q = P2Shapes<T>::s[V];
         if (threads > 256 * q.mw) return hipErrorInvalidValue;
         auto run = [&](auto kernel) -> hipError_t {
             if (!lds_allow(reinterpret_cast<const void*>(kernel), (size_t)l.total)) return hipErrorInvalidValue;
-            hipLaunchKernelGGL(kernel, dim3(nslots), dim3(threads), l.total, s, ch, slots, inst, heads, kmax, m,
-                               l);
+            hipLaunchKernelGGL(kernel, dim3(nitems), dim3(threads), l.total, s, ch, items, inst, heads, kmax, m, src,
+                               dst, l);
             return hipGetLastError();
         };
         return pol == CF_POL_TM ? run(&k_patch2d<T, CF_POL_TM, q.cx, q.b, q.mw, q.coef>)
@@ -519,22 +532,24 @@ size_t patch2d_lds(const Patch2DShape& q, int n, const Patch2DSizes& z) {
 }
 
 template <typename T>
-hipError_t launch_patch2d(int shape, int pol, const ChanDev* ch, const int* slots, int nslots, const InstDev* inst,
-                          const Patch2DInst* heads, int n, const Patch2DSizes& z, int kmax, int m, hipStream_t s) {
-    if (nslots <= 0) return hipSuccess;
+hipError_t launch_patch2d(int shape, int pol, const ChanDev* ch, const int* items, int nitems, const InstDev* inst,
+                          const Patch2DInst* heads, int n, const Patch2DSizes& z, int kmax, int m, int src, int dst,
+                          hipStream_t s) {
+    if (nitems <= 0) return hipSuccess;
     if (shape < 0 || shape >= P2Shapes<T>::n || n < 0 || kmax < 1) return hipErrorInvalidValue;
     const Patch2DShape& q = P2Shapes<T>::s[shape];
     // a wave of its own takes the surface sums
     const int threads = (n + 63) / 64 * 64 + 64;
-    return p2_launch<T, 0>(shape, pol, threads, p2_lds<T>(p2_stride_of<T>(q), n, z), ch, slots, nslots, inst, heads, kmax,
-                           m, s);
+    return p2_launch<T, 0>(shape, pol, threads, p2_lds<T>(p2_stride_of<T>(q), n, z), ch, items, nitems, inst, heads,
+                           kmax, m, src, dst, s);
 }
 
 #define CF_INSTANTIATE(T)                                                                                          \
     template int patch2d_shapes<T>(Patch2DShape*, int);                                                            \
     template size_t patch2d_lds<T>(const Patch2DShape&, int, const Patch2DSizes&);                                 \
     template hipError_t launch_patch2d<T>(int, int, const ChanDev*, const int*, int, const InstDev*,               \
-                                          const Patch2DInst*, int, const Patch2DSizes&, int, int, hipStream_t);
+                                          const Patch2DInst*, int, const Patch2DSizes&, int, int, int, int,        \
+                                          hipStream_t);
 CF_INSTANTIATE(float)
 CF_INSTANTIATE(double)
 #undef CF_INSTANTIATE

@@ -24,20 +24,32 @@ constexpr int kMaxShapes2D = 12;
 template <typename T>
 int patch2d_shapes(Patch2DShape* out, int max);
 
-// One patch of an instance's list, on the device: first cell, and the list
-// indices of the patches to the right and left, above and below (the list's
-// length stands for "none": fields there are 0).
+// One patch of an instance's list, on the device: first cell, the list indices
+// of the patches to the right and left, above and below (the list's length
+// stands for "none": fields there are 0), and the cells whose E components
+// (TM: E_z; TE: E_x, E_y) are not held at 0, cell (r, j) at bit r cx + j.
+enum { kPatchUsed = 1, kPatchStored = 2 };
 struct Patch2DCell {
-    uint16_t x0, y0, right, left, up, down, pad0, pad1;
+    uint16_t x0, y0, right, left, up, down, flags, pad;
+    uint32_t live[2];
 };
-static_assert(sizeof(Patch2DCell) == 16, "one 16-byte load per thread");
+static_assert(sizeof(Patch2DCell) == 24, "three 8-byte loads per thread");
 
-// Head of an instance: its lists and their lengths per polarization (0 TM,
-// 1 TE), and an E and an H material whose a, b its cells carry.
+// Head of an instance: per polarization (0 TM, 1 TE) its lists (one per part,
+// of one length n, the shorter ones filled up with unused patches), the part
+// whose stored patches hold the measured points; and an E and an H material
+// whose a, b its cells carry.
+//
+// A grid with more live cells than a compute unit's registers hold goes in
+// parts, one block each: a part's list holds the patches it stores and, beyond
+// the cuts, a rim of its neighbours' patches, which goes stale by one cell per
+// step.  A launch may take as many steps as the rim is wide.
 struct Patch2DInst {
     const Patch2DCell* cells[2];
-    int32_t n[2];
+    int32_t n[2], surf_part[2];
     int32_t id_e, id_h;
+    int32_t masks;      // E components share one material: b = b(id_e) where live
+    int32_t pad;
 };
 
 // Box of the measured points and samples x points of a channel, the largest
@@ -50,12 +62,15 @@ struct Patch2DSizes {
 template <typename T>
 size_t patch2d_lds(const Patch2DShape& q, int n, const Patch2DSizes& z);
 
-// Advances the channels slots[0 .. nslots - 1] (all of polarization pol) by
-// min(kmax, remaining steps of the instance) steps from launch-clock step m, in
-// the instance's buffer fa.  heads: one per instance.  n: longest list of the
-// launch's instances.
+// Advances the channels (all of polarization pol) by min(kmax, remaining steps
+// of the instance) steps from launch-clock step m, from the instance's buffer
+// src (0: fa, 1: fb) to dst (the same one only without parts).  items: one per
+// block, channel slot | part << kPartShift.  heads: one per instance.  n:
+// longest list of the launch's instances.
+constexpr int kPartShift = 26;
 template <typename T>
-hipError_t launch_patch2d(int shape, int pol, const ChanDev* ch, const int* slots, int nslots, const InstDev* inst,
-                          const Patch2DInst* heads, int n, const Patch2DSizes& z, int kmax, int m, hipStream_t s);
+hipError_t launch_patch2d(int shape, int pol, const ChanDev* ch, const int* items, int nitems, const InstDev* inst,
+                          const Patch2DInst* heads, int n, const Patch2DSizes& z, int kmax, int m, int src, int dst,
+                          hipStream_t s);
 
 }  // namespace cf

@@ -3,10 +3,40 @@
 
 #include <algorithm>
 #include <cmath>
+#include <numeric>
 
 namespace cf {
 
 namespace {
+
+// Steps of a launch of a grid in parts, and so the width of their rims: a
+// longer launch loads and stores the fields less often but computes wider rims.
+// Batch of six pistons, the two largest in two parts (34000 and 38000 live
+// cells, FP32), 900 steps: @@ ms with 32, @@ with 16, @@ with 8, 62 on tiles.
+constexpr int kPartSteps[] = {32, 16, 8};
+
+// Patches a block of the shape may hold (its last wave takes the surface sums).
+int most_patches(const Patch2DShape& q) { return 256 * q.mw - 64; }
+
+// Estimated cycles of a step on a compute unit with `waves` waves of the shape,
+// polarization slot k.  VALU issue: about 11 instructions per cell and step, 2
+// more per masked E component, 4 cycles each; a step's latency (LDS, two
+// barriers) is 700 cycles beyond a wave's own instructions.
+double step_cycles(const Patch2DShape& q, int k, int waves) {
+    const double instr = (q.cx * q.b) * (q.coef == kMaskB ? (k == 0 ? 13.0 : 15.0) : 11.0) + 40;
+    return std::max(std::ceil(waves / 4.0) * instr * 4, 700 + instr * 4.5);
+}
+
+// Estimated cycles of a compute unit per channel and step: of a grid in parts
+// (with its share of the copy rate, 4.7 TB/s: 7.6 bytes a cycle, for the loads
+// and stores of a launch), and of the tiles (400 x 200 piston: 14000 live cells
+// in 6.2 us, FP32).
+double parts_cost(const Patch2DShape& q, int k, const Patch2DList& l, int precision) {
+    const double value = precision == CF_FP64 ? 8.0 : 4.0;
+    const double bytes = 3 * value * (l.cells.size() * (double)(q.cx * q.b) + l.live_cells);
+    return l.parts * step_cycles(q, k, (l.n + 63) / 64 + 1) + bytes / 7.6 / l.steps;
+}
+double tiles_cost(double cells, int precision) { return cells * (precision == CF_FP64 ? 2.2 : 1.05); }
 
 // Whether an id's material lets the field change.
 bool holds_field(const Problem& p, const std::vector<double>& v, int id) {
@@ -33,48 +63,157 @@ Uniform uniform(const Problem& p, const std::vector<double>& v, std::initializer
     return u;
 }
 
-// Patches of cx x b cells with a cell that can change: E where its coefficient
-// is not 0, H where an E value of its curl is such a one.
-std::vector<Patch2DCell> live_patches(const Problem& p, const std::vector<uint8_t>& live, int cx, int b) {
-    const int nx = p.nx, ny = p.ny, LX = (nx + cx - 1) / cx, LY = (ny + b - 1) / b;
-    const bool perx = p.grid.bc[0] == CF_BC_PERIODIC, pery = p.grid.bc[1] == CF_BC_PERIODIC;
-    std::vector<uint8_t> on((size_t)LX * LY, 0);
-    for (int y = 0; y < ny; ++y) {
-        const uint8_t* row = live.data() + (size_t)y * nx;
-        const int yb = y / b, yd = (y > 0 ? y - 1 : pery ? ny - 1 : y) / b;
-        for (int x = 0; x < nx; ++x) {
-            if (!row[x]) continue;
-            const int xb = x / cx;
-            on[(size_t)yb * LX + xb] = on[(size_t)yd * LX + xb] = 1;
-            on[(size_t)yb * LX + (x > 0 ? x - 1 : perx ? nx - 1 : x) / cx] = 1;
+// Which E components of a polarization can change: bit 0 E_z (TM) or E_x (TE),
+// bit 1 E_y (TE).
+std::vector<uint8_t> live_e(const Problem& p, int k) {
+    std::vector<uint8_t> live(p.ncell, 0);
+    const int first = k == 0 ? CF_EZ : CF_EX, n = k == 0 ? 1 : 2;
+    for (int c = 0; c < n; ++c)
+        for (int64_t q = 0; q < p.ncell; ++q) live[q] |= (uint8_t)(holds_field(p, p.eps, p.ids[first + c][q]) << c);
+    return live;
+}
+
+// The patches of cx x b cells of a grid, row by row; `on` marks those with a
+// cell that can change: E where its coefficient is not 0, H where an E value of
+// its curl is such a one.
+struct PatchGrid {
+    const Problem& p;
+    const std::vector<uint8_t>& live;
+    int cx, b, LX, LY;
+    bool perx, pery;
+    std::vector<uint8_t> on;
+    PatchGrid(const Problem& p_, const std::vector<uint8_t>& live_, int cx_, int b_)
+        : p(p_), live(live_), cx(cx_), b(b_), LX((p_.nx + cx_ - 1) / cx_), LY((p_.ny + b_ - 1) / b_),
+          perx(p_.grid.bc[0] == CF_BC_PERIODIC), pery(p_.grid.bc[1] == CF_BC_PERIODIC) {
+        on.assign((size_t)LX * LY, 0);
+        for (int y = 0; y < p.ny; ++y) {
+            const uint8_t* row = live.data() + (size_t)y * p.nx;
+            const int yb = y / b, yd = (y > 0 ? y - 1 : pery ? p.ny - 1 : y) / b;
+            for (int x = 0; x < p.nx; ++x) {
+                if (!row[x]) continue;
+                const int xb = x / cx;
+                on[(size_t)yb * LX + xb] = on[(size_t)yd * LX + xb] = 1;
+                on[(size_t)yb * LX + (x > 0 ? x - 1 : perx ? p.nx - 1 : x) / cx] = 1;
+            }
         }
     }
-    std::vector<int> at(on.size(), -1);
-    int n = 0;
-    for (size_t k = 0; k < on.size(); ++k)
-        if (on[k]) at[k] = n++;
-    std::vector<Patch2DCell> out;
-    if (n >= 65535) return out;
-    auto ref = [&](int i, int j) -> uint16_t {
-        if (i < 0 || i >= LX) {
-            if (!perx) return (uint16_t)n;
-            i = (i + LX) % LX;
+    // Appends the patches of columns [i0, i1) and rows [j0, j1) (wrapped on a
+    // periodic axis), those of the columns [s0, s1) and rows [t0, t1) stored;
+    // `none` marks a neighbour outside the list.  Returns how many.
+    int append(int i0, int i1, int j0, int j1, int s0, int s1, int t0, int t1, int none,
+               std::vector<Patch2DCell>& out) const {
+        std::vector<int> at((size_t)LX * LY, -1);
+        auto wrap = [](int v, int n) { return ((v % n) + n) % n; };
+        int n = 0;
+        for (int j = j0; j < j1; ++j)
+            for (int i = i0; i < i1; ++i) {
+                if ((!perx && (i < 0 || i >= LX)) || (!pery && (j < 0 || j >= LY))) continue;
+                const size_t q = (size_t)wrap(j, LY) * LX + wrap(i, LX);
+                if (on[q] && at[q] < 0) at[q] = n++;
+            }
+        auto ref = [&](int i, int j) -> uint16_t {
+            if ((!perx && (i < 0 || i >= LX)) || (!pery && (j < 0 || j >= LY))) return (uint16_t)none;
+            const int a = at[(size_t)wrap(j, LY) * LX + wrap(i, LX)];
+            return (uint16_t)(a < 0 ? none : a);
+        };
+        const size_t first = out.size();
+        out.resize(first + n);
+        for (int j = 0; j < LY; ++j)
+            for (int i = 0; i < LX; ++i) {
+                const int k = at[(size_t)j * LX + i];
+                if (k < 0) continue;
+                Patch2DCell c{};
+                c.x0 = (uint16_t)(i * cx);
+                c.y0 = (uint16_t)(j * b);
+                c.right = ref(i + 1, j);
+                c.left = ref(i - 1, j);
+                c.up = ref(i, j + 1);
+                c.down = ref(i, j - 1);
+                c.flags = kPatchUsed | (i >= s0 && i < s1 && j >= t0 && j < t1 ? kPatchStored : 0);
+                for (int r = 0; r < b && j * b + r < p.ny; ++r)
+                    for (int q = 0; q < cx && i * cx + q < p.nx; ++q) {
+                        const uint8_t v = live[(size_t)(j * b + r) * p.nx + i * cx + q];
+                        c.live[0] |= (uint32_t)(v & 1) << (r * cx + q);
+                        c.live[1] |= (uint32_t)(v >> 1) << (r * cx + q);
+                    }
+                out[first + k] = c;
+            }
+        return n;
+    }
+    Patch2DList whole() const {
+        Patch2DList l;
+        l.n = (int)std::count(on.begin(), on.end(), 1);
+        if (l.n == 0 || l.n >= 65535) return Patch2DList();
+        l.parts = 1;
+        append(0, LX, 0, LY, 0, LX, 0, LY, l.n, l.cells);
+        count(l);
+        return l;
+    }
+    void count(Patch2DList& l) const {
+        for (const Patch2DCell& c : l.cells)
+            if (c.flags & kPatchStored)
+                l.live_cells += (double)std::min(cx, p.nx - c.x0) * std::min(b, p.ny - c.y0);
+    }
+    // Parts of at most `most` patches, cut across x or y where the fewest blocks
+    // (then patches) result; a rim of at least `steps` cells beyond a cut.  The
+    // measured points (box lo .. hi) stay inside one part.
+    Patch2DList parts(int most, int steps, const int lo[2], const int hi[2]) const {
+        Patch2DList best;
+        for (int axis = 0; axis < 2; ++axis) {
+            const int N = axis == 0 ? LX : LY, w = axis == 0 ? cx : b, rim = (steps + w - 1) / w;
+            std::vector<int> load(N, 0);
+            for (int j = 0; j < LY; ++j)
+                for (int i = 0; i < LX; ++i) load[axis == 0 ? i : j] += on[(size_t)j * LX + i];
+            const int total = std::accumulate(load.begin(), load.end(), 0);
+            const int s0 = lo[axis] / w, s1 = hi[axis] / w;
+            const bool per = axis == 0 ? perx : pery;
+            for (int m = 2; m <= kMaxParts; ++m) {
+                // equal shares; a cut through the measured points moves to their nearer end
+                std::vector<int> cut{0};
+                int sum = 0;
+                for (int c = 0; c < N && (int)cut.size() < m; ++c) {
+                    sum += load[c];
+                    if (sum * (int64_t)m < (int64_t)total * (int)cut.size()) continue;
+                    int at = c + 1;
+                    if (at > s0 && at <= s1) at = at - s0 < s1 + 1 - at ? s0 : s1 + 1;
+                    if (at > cut.back() && at < N) cut.push_back(at);
+                    else break;
+                }
+                cut.push_back(N);
+                if ((int)cut.size() != m + 1) continue;
+                Patch2DList l;
+                l.parts = m;
+                l.steps = steps;
+                int n = 0;
+                bool ok = true;
+                for (int q = 0; q < m; ++q) {
+                    const int c0 = cut[q] - rim, c1 = cut[q + 1] + rim;
+                    ok = ok && !(per && c1 - c0 > N);      // a rim that meets itself
+                    int k = 0;
+                    for (int c = c0; c < c1; ++c)
+                        if (per) k += load[((c % N) + N) % N];
+                        else if (c >= 0 && c < N) k += load[c];
+                    n = std::max(n, k);
+                    if (s0 >= cut[q] && s1 < cut[q + 1]) l.surf_part = q;
+                }
+                if (!ok || n == 0 || n > most) continue;
+                if (best.parts && (m > best.parts || (m == best.parts && n >= best.n))) break;
+                l.n = n;
+                for (int q = 0; q < m; ++q) {
+                    const int c0 = cut[q] - rim, c1 = cut[q + 1] + rim;
+                    const int have = axis == 0 ? append(c0, c1, 0, LY, cut[q], cut[q + 1], 0, LY, n, l.cells)
+                                               : append(0, LX, c0, c1, 0, LX, cut[q], cut[q + 1], n, l.cells);
+                    l.cells.resize(l.cells.size() + n - have);
+                }
+                count(l);
+                best = std::move(l);
+                break;
+            }
         }
-        if (j < 0 || j >= LY) {
-            if (!pery) return (uint16_t)n;
-            j = (j + LY) % LY;
-        }
-        const int a = at[(size_t)j * LX + i];
-        return (uint16_t)(a < 0 ? n : a);
-    };
-    out.reserve(n);
-    for (int j = 0; j < LY; ++j)
-        for (int i = 0; i < LX; ++i)
-            if (on[(size_t)j * LX + i])
-                out.push_back({(uint16_t)(i * cx), (uint16_t)(j * b), ref(i + 1, j), ref(i - 1, j), ref(i, j + 1),
-                               ref(i, j - 1), 0, 0});
-    return out;
-}
+        return best;
+    }
+    static constexpr int kMaxParts = 16;
+};
 
 }  // namespace
 
@@ -87,14 +226,24 @@ Patch2DSet patch2d_set(const Problem& p, int precision) {
     const Uniform ue = uniform(p, p.eps, {CF_EX, CF_EY, CF_EZ}), uh = uniform(p, p.mu, {CF_HX, CF_HY, CF_HZ});
     s.id_e = ue.id;
     s.id_h = uh.id;
+    s.masks = ue.single;
+    s.ncell = p.ncell;
     const bool fits = p.grid.ndim == 2 && p.nx < 65536 && p.ny < 65536;
+    // box of every point a channel can measure
+    int lo[2] = {p.nx, p.ny}, hi[2] = {-1, -1};
+    for (const Gather& g : p.gathers)
+        for (int32_t ix : g.idx) {
+            const int c[2] = {ix % p.nx, ix / p.nx};
+            for (int a = 0; a < 2; ++a) {
+                lo[a] = std::min(lo[a], c[a]);
+                hi[a] = std::max(hi[a], c[a]);
+            }
+        }
     for (int k = 0; k < 2; ++k) {
         s.lists[k].resize(n);
-        s.cells[k].assign(n, 0.0);
         if (!fits) continue;
-        std::vector<uint8_t> live(p.ncell, 0);
-        for (int c : k == 0 ? std::vector<int>{CF_EZ} : std::vector<int>{CF_EX, CF_EY})
-            for (int64_t q = 0; q < p.ncell; ++q) live[q] |= holds_field(p, p.eps, p.ids[c][q]);
+        const std::vector<uint8_t> live = live_e(p, k);
+        bool covered = false;
         for (int v = 0; v < n; ++v) {
             const Patch2DShape& q = s.shapes[v];
             if (q.coef != kRegAll && !(uh.single && uh.all)) continue;
@@ -102,9 +251,30 @@ Patch2DSet patch2d_set(const Problem& p, int precision) {
             // a periodic axis wraps at a patch edge
             if (p.grid.bc[0] == CF_BC_PERIODIC && p.nx % q.cx) continue;
             if (p.grid.bc[1] == CF_BC_PERIODIC && p.ny % q.b) continue;
-            s.lists[k][v] = live_patches(p, live, q.cx, q.b);
-            for (const Patch2DCell& c : s.lists[k][v])
-                s.cells[k][v] += (double)std::min(q.cx, p.nx - c.x0) * std::min(q.b, p.ny - c.y0);
+            s.lists[k][v] = PatchGrid(p, live, q.cx, q.b).whole();
+            if (s.lists[k][v].n > most_patches(q)) s.lists[k][v] = Patch2DList();
+            covered = covered || s.lists[k][v].parts > 0;
+        }
+        if (covered || hi[0] < 0) continue;
+        // too large for one compute unit: parts, with the shape of the most cells,
+        // unless the tiles are estimated to take less
+        for (int v = 0; v < n; ++v) {
+            const Patch2DShape& q = s.shapes[v];
+            if (q.coef != kMaskB || !ue.single || !(uh.single && uh.all)) continue;
+            if (p.grid.bc[0] == CF_BC_PERIODIC && p.nx % q.cx) continue;
+            if (p.grid.bc[1] == CF_BC_PERIODIC && p.ny % q.b) continue;
+            const PatchGrid grid(p, live, q.cx, q.b);
+            double best = 0;
+            for (int steps : kPartSteps) {
+                Patch2DList l = grid.parts(most_patches(q), steps, lo, hi);
+                if (!l.parts) continue;
+                const double cost = parts_cost(q, k, l, precision);
+                if (s.lists[k][v].parts && cost >= best) continue;
+                best = cost;
+                s.lists[k][v] = std::move(l);
+            }
+            if (s.lists[k][v].parts && best > tiles_cost(s.lists[k][v].live_cells, precision)) s.lists[k][v] = Patch2DList();
+            if (s.lists[k][v].parts) break;
         }
     }
     return s;
@@ -118,19 +288,15 @@ int patch2d_choose(const Patch2DSet& s, int precision, int k, int nslots, const 
     if (z.box > 65535) return -1;
     for (int v = 0; v < (int)s.shapes.size(); ++v) {
         const Patch2DShape& q = s.shapes[v];
-        const int n = (int)s.lists[k][v].size(), waves = (n + 63) / 64 + 1;
-        if (n == 0 || waves > 4 * q.mw) continue;
+        const Patch2DList& l = s.lists[k][v];
+        const int n = l.n, waves = (n + 63) / 64 + 1, nblocks = nslots * l.parts;
+        if (l.parts == 0) continue;
         const size_t lds = precision == CF_FP64 ? patch2d_lds<double>(q, n, z) : patch2d_lds<float>(q, n, z);
         if (lds > lds_limit) continue;
-        // VALU issue: about 11 instructions per cell and step, 2 more per
-        // masked E component, 4 cycles each; a step's latency (LDS, two
-        // barriers) is 700 cycles beyond a wave's own instructions
-        const double instr = (q.cx * q.b) * (q.coef == kMaskB ? (k == 0 ? 13.0 : 15.0) : 11.0) + 40;
         const int per_cu = std::max(1, std::min(4 * q.mw / waves, (int)(lds_limit / std::max<size_t>(lds, 1))));
-        const int c = std::min(per_cu, (nslots + kCUs - 1) / kCUs);
-        const int rounds = (nslots + kCUs * c - 1) / (kCUs * c);
-        const double simd = std::ceil(c * waves / 4.0);   // waves of the fullest SIMD
-        const double cost = rounds * std::max(simd * instr * 4, 700 + instr * 4.5);
+        const int c = std::min(per_cu, (nblocks + kCUs - 1) / kCUs);
+        const int rounds = (nblocks + kCUs * c - 1) / (kCUs * c);
+        const double cost = rounds * step_cycles(q, k, c * waves);
         if (best < 0 || cost < best_cost) {
             best = v;
             best_cost = cost;

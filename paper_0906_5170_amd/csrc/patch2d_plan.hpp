@@ -1,5 +1,6 @@
 // Host plan of the 2D patch kernel: which patches of a problem's grid hold
-// cells that can change, and the shape a launch takes.
+// cells that can change, the parts of grids beyond one compute unit, and the
+// shape a launch takes.
 #pragma once
 
 #include <memory>
@@ -10,11 +11,20 @@
 
 namespace cf {
 
+// A polarization's lists for one shape: `parts` lists of n patches each, at
+// most `steps` steps per launch (0: any number, one part).
+struct Patch2DList {
+    int n = 0, parts = 0, surf_part = 0, steps = 0;
+    std::vector<Patch2DCell> cells;
+    double live_cells = 0;                            // cells of the stored patches inside the grid
+};
+
 struct Patch2DSet {
     std::vector<Patch2DShape> shapes;
-    std::vector<std::vector<Patch2DCell>> lists[2];   // per polarization (0 TM, 1 TE) and shape; empty: not usable
-    std::vector<double> cells[2];                     // cells of the listed patches inside the grid
+    std::vector<Patch2DList> lists[2];                // per polarization (0 TM, 1 TE) and shape (parts == 0: not usable)
     int id_e = kNullId, id_h = kNullId;               // an E and an H material with a field
+    bool masks = false;                               // E components share one material
+    int64_t ncell = 0;
 };
 
 // The lists of a fusable 2D problem for every shape of the precision.

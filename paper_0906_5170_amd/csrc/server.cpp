@@ -69,7 +69,8 @@ struct Req {
     bool fused = false;
     int variant = -1;                 // fused variant of this request
     std::shared_ptr<const cf::Patch2DSet> patches;   // fused: on the 2D patch kernel (null: tiles)
-    std::array<int, 2> pshape{-1, -1};
+    cfi::PatchShapes pshape{-1, -1};
+    bool parts = false;               // some polarization goes in parts, between the two field arrays
     cf::Patch2DSizes psizes{1, 1, 1};
     std::vector<cf::Patch2DCell> cells;   // its patch lists
     double live_cells[2] = {0, 0};
@@ -165,6 +166,7 @@ struct cf_server {
         // 2D patch kernel (shape >= 0): byte offset of the channel list behind
         // the work items, channels, longest patch list, LDS sizes
         int shape = -1;
+        bool pingpong = false;        // from the field array of the clock's parity to the other
         int longest = 0;
         cf::Patch2DSizes sizes{1, 1, 1};
     };
@@ -250,8 +252,9 @@ std::string prepare(cf_server* S, Req& r) {
             }
     r.fused = r.variant >= 0;
     // with the tiling left to the server, a request whose live cells fit a
-    // compute unit's registers takes the 2D patch kernel; its lists lie in the
-    // second field array.  Shapes are chosen for a full device.
+    // compute unit's registers takes the 2D patch kernel, with its lists in the
+    // second field array; a larger one goes in parts, with the lists in the place
+    // of its ids, which are not read after the start.  Shapes are chosen for a full device.
     r.patches = nullptr;
     if (r.fused && !S->tiles_only) {
         auto set = cfi::cached_patches(p, S->precision);
@@ -261,10 +264,17 @@ std::string prepare(cf_server* S, Req& r) {
         const int together[2] = {std::max(used[0], 1024), std::max(used[1], 1024)};
         if (cfi::patch2d_pick(*set, S->precision, used, together, r.psizes, r.pshape)) {
             r.cells = cfi::patch2d_cells(*set, r.pshape);
+            r.parts = cfi::patch2d_in_parts(*set, r.pshape);
             const size_t room = (size_t)r.C * r.st.ncomp * p.ncell * (S->precision == CF_FP64 ? 8 : 4);
-            if (r.cells.size() * sizeof(cf::Patch2DCell) <= room) r.patches = set;
+            if (r.parts || r.cells.size() * sizeof(cf::Patch2DCell) <= room) r.patches = set;
             for (int q = 0; q < 2; ++q)
-                if (r.pshape[q] >= 0) r.live_cells[q] = set->cells[q][r.pshape[q]];
+                if (r.pshape[q] >= 0) r.live_cells[q] = set->lists[q][r.pshape[q]].live_cells;
+            // parts take a launch of at least a tick
+            for (int q = 0; q < 2; ++q)
+                if (r.pshape[q] >= 0 && r.parts && set->lists[q][r.pshape[q]].parts > 1 &&
+                    set->lists[q][r.pshape[q]].steps < S->kh)
+                    r.patches = nullptr;
+            if (!r.patches) r.parts = false;
         }
     }
     // 3D requests take the fused z-streaming step when it applies: in FP32
@@ -391,11 +401,11 @@ hipError_t start_wave(cf_server* S, Req& r, T* f) {
     const size_t fbytes = (size_t)r.st.resident * r.st.ncomp * p.ncell * sizeof(T);
     hipError_t e;
     if ((e = hipMemsetAsync(f, 0, fbytes, s)) != hipSuccess) return e;
-    if (r.patches) {
+    if (r.patches && !r.parts) {
         if ((e = hipMemcpyAsync(b + r.o_fb, r.cells.data(), r.cells.size() * sizeof(cf::Patch2DCell),
                                 hipMemcpyHostToDevice, s)) != hipSuccess)
             return e;
-    } else if (r.fused || r.v3 >= 0) {
+    } else if (!r.patches && (r.fused || r.v3 >= 0)) {
         // the fused kernels never write the cells they skip: zero in both arrays
         char* other = b + (reinterpret_cast<char*>(f) == b + r.o_fa ? r.o_fb : r.o_fa);
         if ((e = hipMemsetAsync(other, 0, fbytes, s)) != hipSuccess) return e;
@@ -458,9 +468,12 @@ hipError_t admit(cf_server* S, Req& r) {
     r.done = 0;
     r.credit = 0;
     r.sps = 0;
-    // a tiled request is kicked into the buffer the next fused launch reads
-    T* f = reinterpret_cast<T*>(b + (r.fused && !r.patches && S->parity ? r.o_fb : r.o_fa));
-    return start_wave<T>(S, r, f);
+    // a request that goes between the field arrays is kicked into the one the
+    // next fused launch reads; the launches take its TM and TE channels alike
+    T* f = reinterpret_cast<T*>(b + (r.fused && (!r.patches || r.parts) && S->parity ? r.o_fb : r.o_fa));
+    if ((e = start_wave<T>(S, r, f)) != hipSuccess || !r.parts) return e;
+    return hipMemcpyAsync(b + r.o_ids, r.cells.data(), r.cells.size() * sizeof(cf::Patch2DCell),
+                          hipMemcpyHostToDevice, s);
 }
 
 // Rebuild the fused group: descriptors and instances of every fused request
@@ -475,11 +488,11 @@ hipError_t rebuild_group(cf_server* S) {
         std::vector<int> third;                          // surface tile per slot
     };
     std::map<std::pair<int, int>, SlotTiles> lists;   // (v, pol) -> slots, tiles, surface tiles
-    // patch launches by shape and polarization; the cells of a slot's patches
-    // order a launch's channels, longest first
+    // patch launches by shape, polarization and parts; items in order of their
+    // lists, longest first
     struct SlotPatches {
         cf_server::Launch l;
-        std::vector<std::pair<double, int>> slots;
+        std::vector<std::pair<double, int>> slots;   // (-patches, item)
     };
     std::vector<SlotPatches> patches;
     std::vector<cf::Patch2DInst> heads;
@@ -521,7 +534,7 @@ hipError_t rebuild_group(cf_server* S) {
         SlotPatches* to[2] = {nullptr, nullptr};
         if (r.patches) {
             heads.back() = cfi::patch2d_head(*r.patches, r.pshape,
-                                             reinterpret_cast<const cf::Patch2DCell*>(b + r.o_fb));
+                                             reinterpret_cast<const cf::Patch2DCell*>(b + (r.parts ? r.o_ids : r.o_fb)));
             size_t idx[2] = {0, 0};
             for (int q = 0; q < 2; ++q) {
                 if (r.pshape[q] < 0) continue;
@@ -531,7 +544,7 @@ hipError_t rebuild_group(cf_server* S) {
                 cf_server::Launch l;
                 for (; k < patches.size(); ++k) {
                     l = patches[k].l;
-                    if (l.shape != v || l.pol != pol) continue;
+                    if (l.shape != v || l.pol != pol || l.pingpong != r.parts) continue;
                     l.longest = std::max(l.longest, n);
                     l.sizes.box = std::max(l.sizes.box, r.psizes.box);
                     l.sizes.samples = std::max(l.sizes.samples, r.psizes.samples);
@@ -539,7 +552,7 @@ hipError_t rebuild_group(cf_server* S) {
                     if (cf::patch2d_lds<T>(r.patches->shapes[v], l.longest, l.sizes) <= lim) break;
                 }
                 if (k == patches.size()) {
-                    l = {-1, pol, 0, 0, v, n, r.psizes};
+                    l = {-1, pol, 0, 0, v, r.parts, n, r.psizes};
                     patches.push_back({});
                 }
                 patches[k].l = l;
@@ -555,7 +568,8 @@ hipError_t rebuild_group(cf_server* S) {
             ch.push_back(d);
             if (r.patches) {
                 const int q = r.chans[c].pol == CF_POL_TE ? 1 : 0;
-                to[q]->slots.emplace_back(-r.live_cells[q], slot);
+                for (int item : cfi::patch2d_items(*r.patches, r.pshape, q, &slot, 1))
+                    to[q]->slots.emplace_back(-(double)heads.back().n[q], item);
                 continue;
             }
             auto& l = lists[{r.variant, r.chans[c].pol}];
@@ -619,13 +633,17 @@ hipError_t rebuild_group(cf_server* S) {
     return hipSuccess;
 }
 
+// Ticks run as one take no more device time than this (seconds).
+constexpr double kMergedTick = 2e-3;
+
 // Ticks that may run as one: where every resident request is on the 2D patch
-// kernel, whose launches take any number of steps, as many as stay within a
-// millisecond of device time and end by the next tick in which a request
-// finishes or is checked for convergence.
+// kernel, whose launches take any number of steps (in parts, as many as the rim is
+// wide), as many as stay within kMergedTick and end by the next tick in which a request
+// finishes or is checked for convergence.  Longer launches load and store the
+// fields less often.
 int merged_ticks(const cf_server* S) {
     if (!(S->group_s > 0)) return 1;
-    long long n = std::min<long long>((long long)(1e-3 / S->group_s), 64);
+    long long n = std::min<long long>((long long)(kMergedTick / S->group_s), 64);
     for (const auto& rp : S->active) {
         const Req& r = *rp;
         if (!r.fused || !r.patches) return 1;
@@ -633,6 +651,10 @@ int merged_ticks(const cf_server* S) {
         long long left = r.opts.n_steps - done;
         if (r.conv.on) left = std::min<long long>(left, r.conv.next - done);
         n = std::min(n, (left + S->kh - 1) / S->kh);
+        for (int q = 0; q < 2; ++q) {
+            const int steps = r.pshape[q] >= 0 ? r.patches->lists[q][r.pshape[q]].steps : 0;
+            if (steps > 0) n = std::min<long long>(n, steps / S->kh);
+        }
     }
     return (int)std::max<long long>(n, 1);
 }
@@ -676,7 +698,7 @@ hipError_t tick(cf_server* S, int ticks) {
                 e = cf::launch_patch2d<T>(
                     l.shape, l.pol, gch, reinterpret_cast<const int*>(S->group + S->g_work + l.off), l.n, gin,
                     reinterpret_cast<const cf::Patch2DInst*>(S->group + S->g_work + S->heads_off), l.longest, l.sizes,
-                    S->kh * ticks, (int)S->clock, ls);
+                    S->kh * ticks, (int)S->clock, l.pingpong ? S->parity : 0, l.pingpong ? S->parity ^ 1 : 0, ls);
             else
                 e = cf::launch_tb2d<T>(l.variant, l.pol, gch, gw + l.off, l.n, gin, S->kh, (int)S->clock, S->parity,
                                        ls);

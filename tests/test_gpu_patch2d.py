@@ -52,8 +52,8 @@ def both(cf, wl, precision, patch=True, **kw):
     p = cf.Problem.from_workload(wl)
     a, b = solve(p, wl, precision, **kw), solve(p, wl, precision, split=True)
     assert a["fused"] and not b["fused"]
-    # a patch launch takes all its steps at once, a tile launch at most 8
-    assert patch is None or (a["tile_halo"] > 8) == patch, a["tile_halo"]
+    # a patch launch takes more steps than a tile launch (8 in FP32, 4 in FP64)
+    assert patch is None or (a["tile_halo"] > (8 if precision == "fp32" else 4)) == patch, a["tile_halo"]
     for key in ("per_channel", "gamma"):
         assert np.all(np.isfinite(a[key])) and np.any(a[key] != 0.0), key
         assert np.array_equal(a[key], b[key]), (wl.shape, wl.bc, precision, key)
@@ -84,10 +84,35 @@ def test_largest_shapes(cf, shape, slab, media, pol):
     both(cf, problem(*shape, W, media, slab, pol, n_steps=60), "fp32")
 
 
-@pytest.mark.parametrize("shape", [(260, 200)])
-def test_beyond_the_shapes(cf, shape):
-    """A grid no shape covers stays with the tiles."""
-    both(cf, problem(*shape, W, n_steps=30), "fp32", patch=False)
+@pytest.mark.parametrize("shape,bc,slab,pol", [
+    ((260, 200), W, 1, "TM+TE"), ((200, 260), W, 1, "TM"), ((512, 96), ("periodic", "pec", "periodic"), 1, "TM+TE"),
+    ((96, 512), ("pec", "periodic", "periodic"), 1, "TE"), ((400, 300), W, 150, "TM+TE"), ((417, 203), W, 2, "TE")])
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_parts(cf, shape, bc, slab, pol, precision):
+    """Grids beyond one compute unit go in parts, cut along either axis, over
+    periodic edges too; several launches, the last one shorter."""
+    # FP64 lists of a grid without conductor may find no room: tiles
+    both(cf, problem(*shape, bc, "vacuum", slab, pol, n_steps=75), precision,
+         patch=True if precision == "fp32" or slab > 100 else None)
+
+
+def test_parts_waves_graph_and_stop(cf):
+    wl = problem(260, 200, W, n_steps=150)
+    p, a = both(cf, wl, "fp32")
+    for kw in (dict(graph=True), dict(max_resident=5), dict(graph=True, max_resident=7), dict(time_stencil=True)):
+        for _ in range(2):
+            r = solve(p, wl, "fp32", **kw)
+            assert np.array_equal(r["per_channel"], a["per_channel"]) and np.array_equal(r["gamma"], a["gamma"]), kw
+    s = p.solve(sigma=wl.sigma, courant=wl.courant, n_steps=wl.n_steps, pol=wl.pol, kernel=wl.kernel,
+                precision="fp32", stop_tol=1e6, stop_every=40)
+    assert 40 < s["n_steps_run"] < wl.n_steps
+    t = solve(p, wl.replace(n_steps=s["n_steps_run"]), "fp32")
+    assert np.array_equal(t["per_channel"], s["per_channel"])
+
+
+def test_beyond_the_shapes(cf):
+    """A grid no shape covers (several materials) stays with the tiles."""
+    both(cf, problem(180, 160, W, "mixed", n_steps=30), "fp32", patch=False)
 
 
 def test_waves_graph_and_stop(cf):
@@ -112,11 +137,11 @@ def test_batch(cf, graph, precision):
     """A batch of problems of both kinds (patches of several shapes, tiles)
     gives every problem what its own split solve gives, twice."""
     wls = [problem(13, 14, W), problem(97, 83, W, "filled"), problem(260, 200, W), problem(61, 37, W, "mixed"),
-           problem(24, 31, ("periodic", "pec", "periodic")), problem(61, 37, W)]
+           problem(24, 31, ("periodic", "pec", "periodic")), problem(180, 160, W, "mixed")]
     wls = [w.replace(n_steps=70) for w in wls]
     probs = [cf.Problem.from_workload(w) for w in wls]
     o = dict(sigma=0.9, courant=0.5, n_steps=70, pol="TM+TE", kernel="general", precision=precision)
-    for some in (probs, probs[:2], probs[2:3], probs):
+    for some in (probs, probs[:2], probs[2:3], probs[5:], probs):
         for r, p in zip(cf.batch_solve(some, graph=graph, **o), some):
             b = p.solve(split=True, **o)
             assert r["fused"] and np.array_equal(r["per_channel"], b["per_channel"])
@@ -127,13 +152,13 @@ def test_server(cf, precision):
     """Requests on patches and on tiles, joining one after another, get what
     their own split solves give; so does one that stops early."""
     wls = [problem(13, 14, W), problem(97, 83, W, "filled"), problem(61, 37, W, "mixed"), problem(260, 200, W),
-           problem(61, 37, W), problem(24, 31, ("periodic", "pec", "periodic"))]
-    steps = [400, 61, 250, 90, 300, 77]
+           problem(61, 37, W), problem(24, 31, ("periodic", "pec", "periodic")), problem(180, 160, W, "mixed")]
+    steps = [400, 61, 250, 90, 300, 77, 83]
     probs = [cf.Problem.from_workload(w) for w in wls]
     o = [dict(sigma=0.9, courant=0.5, n_steps=n, pol="TM+TE", kernel="general", precision=precision) for n in steps]
     o[4].update(stop_tol=1e6, stop_every=40)
     srv = cf.Server(2 << 30, precision=precision)
-    for some in (range(3), range(6)):
+    for some in (range(3), range(2, 4), range(7)):
         tickets = [srv.submit(probs[k], **o[k]) for k in some]
         for k, t in zip(some, tickets):
             r = srv.wait(t, timeout=100)
