@@ -219,21 +219,25 @@ std::shared_ptr<const cf::Patch2DSet> cached_patches(const cf::Problem& p, int p
     return set;
 }
 
-void patch2d_sizes(const std::vector<cf::ChanDev>& dev, const std::vector<int32_t>& gidx, int nx, cf::Patch2DSizes& z) {
-    std::map<int, bool> seen;   // channels of a face share their tables
-    for (const cf::ChanDev& d : dev) {
-        z.samples = std::max(z.samples, d.nsamp);
-        z.points = std::max(z.points, d.P);
-        if (!seen.emplace(d.g_off, true).second) continue;
+void patch2d_sizes(const Staged& st, int nx, cf::Patch2DSizes& z) {
+    auto box = [&](const int32_t* idx, int n) {
         int x0 = nx, x1 = -1, y0 = INT32_MAX, y1 = -1;
-        for (int k = 0; k < d.nsamp * d.P; ++k) {
-            const int x = gidx[d.g_off + k] % nx, y = gidx[d.g_off + k] / nx;
+        for (int k = 0; k < n; ++k) {
+            const int x = idx[k] % nx, y = idx[k] / nx;
             x0 = std::min(x0, x);
             x1 = std::max(x1, x);
             y0 = std::min(y0, y);
             y1 = std::max(y1, y);
         }
         if (x1 >= x0) z.box = std::max(z.box, (x1 - x0 + 1) * (y1 - y0 + 1));
+    };
+    std::map<std::pair<int, int>, bool> seen;   // channels of a face share their tables
+    for (const cf::ChanDev& d : st.dev) {
+        z.samples = std::max(z.samples, d.nsamp);
+        z.points = std::max(z.points, d.P);
+        if (!seen.emplace(std::make_pair(d.g_off, d.u_off), true).second) continue;
+        box(st.gidx.data() + d.g_off, d.nsamp * d.P);
+        box(st.uidx.data() + d.u_off, d.n_uniq);
     }
 }
 
@@ -257,6 +261,16 @@ bool patch2d_in_parts(const cf::Patch2DSet& set, const PatchShapes& shape) {
     return false;
 }
 
+bool patch2d_own_start(const cf::Patch2DSet& set, const PatchShapes& shape, int precision) {
+    for (int q = 0; q < 2; ++q) {
+        if (shape[q] < 0) continue;
+        const cf::Patch2DShape& s = set.shapes[shape[q]];
+        if (set.lists[q][shape[q]].parts != 1 || !cf::patch2d_small(s.cx * s.b, precision == CF_FP64 ? 8 : 4))
+            return false;
+    }
+    return true;
+}
+
 std::vector<cf::Patch2DCell> patch2d_cells(const cf::Patch2DSet& set, const PatchShapes& shape) {
     std::vector<cf::Patch2DCell> out;
     for (int q = 0; q < 2; ++q) {
@@ -267,11 +281,13 @@ std::vector<cf::Patch2DCell> patch2d_cells(const cf::Patch2DSet& set, const Patc
     return out;
 }
 
-cf::Patch2DInst patch2d_head(const cf::Patch2DSet& set, const PatchShapes& shape, const cf::Patch2DCell* at) {
+cf::Patch2DInst patch2d_head(const cf::Patch2DSet& set, const PatchShapes& shape, const cf::Patch2DCell* at,
+                             bool start) {
     cf::Patch2DInst h{};
     h.id_e = set.id_e;
     h.id_h = set.id_h;
     h.masks = set.masks ? 1 : 0;
+    h.start = start ? 1 : 0;
     for (int q = 0; q < 2; ++q) {
         if (shape[q] < 0) continue;
         const cf::Patch2DList& l = set.lists[q][shape[q]];
@@ -1683,30 +1699,40 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
     std::deque<std::vector<cf::Patch2DCell>> host_cells;
     std::deque<cf::Patch2DInst> host_heads;
     std::deque<std::vector<int>> host_items;
+    std::deque<TableUpload> ptables;
     std::vector<PatchShapes> pshape;
+    std::vector<char> pmixed;                              // whether a wave's launch takes both polarizations
     std::vector<size_t> plists;                            // where the lists of each wave go
     if (variant >= 0 && o.tile_variant == 0) {
         patches = cached_patches(p, o.precision);
-        patch2d_sizes(st.dev, st.gidx, p.nx, psizes);
+        patch2d_sizes(st, p.nx, psizes);
         for (const Wave& w : st.waves) {
             PatchShapes sh;
             const int num[2] = {w.n_tm, w.n_te};
-            bool ok = patch2d_pick(*patches, o.precision, num, num, psizes, sh);
+            // both polarizations in one launch where the device takes every block at once
+            const int both = num[0] > 0 && num[1] > 0
+                                 ? cf::patch2d_choose_mixed(*patches, o.precision, w.n_all, psizes,
+                                                            cf::device_lds_limit())
+                                 : -1;
+            if (both >= 0) sh = {both, both};
+            bool ok = both >= 0 || patch2d_pick(*patches, o.precision, num, num, psizes, sh);
             if (ok) {
+                pmixed.push_back(both >= 0);
                 const bool parts = patch2d_in_parts(*patches, sh);
                 host_cells.push_back(patch2d_cells(*patches, sh));
                 plists.push_back(parts ? L.ids : L.fields2);
                 ok = parts || host_cells.back().size() * sizeof(cf::Patch2DCell) <= field_bytes;
-                host_heads.push_back(patch2d_head(*patches, sh, reinterpret_cast<const cf::Patch2DCell*>(
-                                                                    ws + plists.back())));
-                // channels and parts of the blocks, the longest lists first; the head behind the TE ones
+                host_heads.push_back(patch2d_head(*patches, sh,
+                                                  reinterpret_cast<const cf::Patch2DCell*>(ws + plists.back()),
+                                                  patch2d_own_start(*patches, sh, o.precision)));
+                // the blocks' items, TM before TE, in the work list's place; the head behind them
+                size_t bytes = 16 + sizeof(cf::Patch2DInst);
                 for (int q = 0; q < 2; ++q) {
                     const int* list = st.slot_lists.data() + (q == 0 ? w.tm_off : w.te_off);
                     host_items.push_back(patch2d_items(*patches, sh, q, list, num[q]));
-                    const size_t bytes = host_items.back().size() * sizeof(int) +
-                                         (q == 1 ? 16 + sizeof(cf::Patch2DInst) : 0);
-                    ok = ok && bytes <= L.work_items * sizeof(cf::WorkItem);
+                    bytes += host_items.back().size() * sizeof(int);
                 }
+                ok = ok && bytes <= 2 * L.work_items * sizeof(cf::WorkItem);
                 pshape.push_back(sh);
             }
             if (!ok) {
@@ -1855,14 +1881,15 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
             continue;
         }
         // batched: kick and consistent start for the whole wave
-        STEP_OK(hipMemsetAsync(fields, 0, field_bytes, s));
+        const bool own_start = patches && host_heads[(size_t)(&w - st.waves.data())].start != 0;
+        if (!own_start) STEP_OK(hipMemsetAsync(fields, 0, field_bytes, s));
         if (psi) STEP_OK(hipMemsetAsync(psi, 0, psi_bytes, s));
         if (aux_bytes) STEP_OK(hipMemsetAsync(ws + L.aux, 0, aux_bytes, s));
-        STEP_OK(cf::launch_kick<T>(fields, dch, s_all, w.n_all, st.max_uniq, tabs, s));
+        if (!own_start) STEP_OK(cf::launch_kick<T>(fields, dch, s_all, w.n_all, st.max_uniq, tabs, s));
         if (three) {
             STEP_OK(cf::launch_h3d<T>(1, fields, psi, dch, s_3d, w.n_3d, g3, dlut, s));
             STEP_OK(cf::launch_e3d<T>(1, fields, psi, dch, s_3d, w.n_3d, g3, dlut, s));
-        } else {
+        } else if (!own_start) {
             STEP_OK(cf::launch_h2d<T>(CF_POL_TM, 1, fields, dch, s_tm, w.n_tm, g, dlut, s));
             STEP_OK(cf::launch_h2d<T>(CF_POL_TE, 1, fields, dch, s_te, w.n_te, g, dlut, s));
             STEP_OK(cf::launch_e2d<T>(CF_POL_TM, 1, fields, dch, s_tm, w.n_tm, g, dlut, s));
@@ -1871,41 +1898,43 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
         if (variant >= 0 && patches) {
             const size_t wi = (size_t)(&w - st.waves.data());
             const PatchShapes& sh = pshape[wi];
-            STEP_OK(upload_inst(make_inst(st.plans[variant], true)));
-            STEP_OK(hipMemcpyAsync(ws + plists[wi], host_cells[wi].data(),
-                                   host_cells[wi].size() * sizeof(cf::Patch2DCell), hipMemcpyHostToDevice, s));
-            const int* ditems[2];
-            const size_t te_bytes = host_items[2 * wi + 1].size() * sizeof(int);
-            for (int q = 0; q < 2; ++q) {
-                ditems[q] = reinterpret_cast<const int*>(dwork + q * L.work_items);
-                const std::vector<int>& it = host_items[2 * wi + q];
-                if (!it.empty())
-                    STEP_OK(hipMemcpyAsync(const_cast<int*>(ditems[q]), it.data(), it.size() * sizeof(int),
-                                           hipMemcpyHostToDevice, s));
-            }
-            const cf::Patch2DInst* heads = reinterpret_cast<const cf::Patch2DInst*>(
-                ws + align_up(L.work + L.work_items * sizeof(cf::WorkItem) + te_bytes, 16));
-            STEP_OK(hipMemcpyAsync(const_cast<cf::Patch2DInst*>(heads), &host_heads[wi], sizeof(cf::Patch2DInst),
-                                   hipMemcpyHostToDevice, s));
+            host_inst.push_back(make_inst(st.plans[variant], true));
+            const std::vector<int>* const pitems[2] = {&host_items[2 * wi], &host_items[2 * wi + 1]};
+            const size_t te_at = L.work + pitems[0]->size() * sizeof(int);
+            const size_t head_at = align_up(te_at + pitems[1]->size() * sizeof(int), 16);
+            ptables.emplace_back(ws, s);
+            TableUpload& pt = ptables.back();
+            STEP_OK(pt.add(L.inst, &host_inst.back(), sizeof(cf::InstDev)));
+            STEP_OK(pt.add(L.work, pitems[0]->data(), pitems[0]->size() * sizeof(int)));
+            STEP_OK(pt.add(te_at, pitems[1]->data(), pitems[1]->size() * sizeof(int)));
+            STEP_OK(pt.add(head_at, &host_heads[wi], sizeof(cf::Patch2DInst)));
+            STEP_OK(pt.add(plists[wi], host_cells[wi].data(), host_cells[wi].size() * sizeof(cf::Patch2DCell)));
+            STEP_OK(pt.flush());
+            const int* ditems[2] = {reinterpret_cast<const int*>(ws + L.work), reinterpret_cast<const int*>(ws + te_at)};
+            const cf::Patch2DInst* heads = reinterpret_cast<const cf::Patch2DInst*>(ws + head_at);
             const int kh = st.shapes[variant].kh, num[2] = {w.n_tm, w.n_te};
-            // the polarizations on two streams, as for the tiles
-            const bool split_pol = !smp.on && !conv.on && w.n_tm > 0 && w.n_te > 0;
+            // the polarizations in one launch, or on two streams, as for the tiles
+            const bool mixed = pmixed[wi] != 0;
+            const bool split_pol = !mixed && !smp.on && !conv.on && w.n_tm > 0 && w.n_te > 0;
             SideStreams side;
             if (split_pol) STEP_OK(side.create(1));
             STEP_OK(graph.begin());
             const hipStream_t ls = graph.launch_stream(s);
             hipError_t body = split_pol ? side.open(ls) : hipSuccess;
             int parity[2] = {0, 0};
-            // at most ks steps of polarization q from step m; the steps taken
+            // ks steps of polarization q (of both in a mixed launch) from step m
             auto launch = [&](int q, int m, int ks) -> hipError_t {
+                if (mixed && q == 1) return hipSuccess;
                 const cf::Patch2DList& l = patches->lists[q][sh[q]];
+                const int longest = mixed ? std::max(l.n, patches->lists[1][sh[1]].n) : l.n;
+                const size_t blocks = pitems[q]->size() + (mixed ? pitems[1]->size() : 0);
                 const bool take = smp.begin(ls);
                 const hipError_t e = cf::launch_patch2d<T>(
-                    sh[q], q == 0 ? CF_POL_TM : CF_POL_TE, dch, ditems[q], (int)host_items[2 * wi + q].size(), dinst,
-                    heads, l.n, psizes, ks, m, parity[q], l.parts > 1 ? parity[q] ^ 1 : parity[q],
+                    sh[q], mixed ? 0 : q == 0 ? CF_POL_TM : CF_POL_TE, dch, ditems[q], (int)blocks, dinst, heads, longest,
+                    psizes, ks, m, parity[q], l.parts > 1 ? parity[q] ^ 1 : parity[q],
                     split_pol && q == 1 ? side.s[0] : ls);
                 if (l.parts > 1) parity[q] ^= 1;
-                const double cu = (double)num[q] * p.ncell * ks;
+                const double cu = (double)(mixed ? w.n_all : num[q]) * p.ncell * ks;
                 if (e == hipSuccess) smp.end(take, ls, cu, cu * state_bytes);
                 return e;
             };
@@ -2478,12 +2507,12 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
         size_t at;                                     // first of its items
         int count;
     };
-    std::map<std::pair<bool, int>, PatchGroup> groups[2];   // per polarization slot: by (in parts, shape)
+    std::map<std::pair<int, int>, PatchGroup> groups[2];   // per polarization slot: by (steps of a launch, shape)
     std::vector<int> tiles[2], items[2];               // tiled slots, patch items
     cf::Patch2DSizes psizes{1, 1, 1};
     if (o.tile_variant == 0) {
         const int together[2] = {(int)B.tm.size(), (int)B.te.size()};
-        for (int i = 0; i < n; ++i) patch2d_sizes(B.st[i].dev, B.st[i].gidx, B.probs[i]->nx, psizes);
+        for (int i = 0; i < n; ++i) patch2d_sizes(B.st[i], B.probs[i]->nx, psizes);
         for (int i = 0; i < n; ++i) {
             keep_sets[i] = cached_patches(*B.probs[i], o.precision);
             const int used[2] = {B.inst_tm_n[i], B.inst_te_n[i]};
@@ -2497,7 +2526,8 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
                 continue;
             }
             psets[i] = keep_sets[i].get();
-            heads[i] = patch2d_head(*psets[i], pshapes[i], reinterpret_cast<const cf::Patch2DCell*>(ws + cells_at[i]));
+            heads[i] = patch2d_head(*psets[i], pshapes[i], reinterpret_cast<const cf::Patch2DCell*>(ws + cells_at[i]),
+                                    false);
         }
     }
     for (int q = 0; q < 2; ++q) {
@@ -2509,7 +2539,7 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
             }
             const int v = pshapes[i][q];
             const cf::Patch2DList& l = psets[i]->lists[q][v];
-            PatchGroup& gr = groups[q].try_emplace({l.parts > 1, v}, PatchGroup{v, 0, l.steps, {}, 0, 0}).first->second;
+            PatchGroup& gr = groups[q].try_emplace({l.steps, v}, PatchGroup{v, 0, l.steps, {}, 0, 0}).first->second;
             gr.n = std::max(gr.n, l.n);
             gr.slots.emplace_back(-(double)l.n, sl);
         }

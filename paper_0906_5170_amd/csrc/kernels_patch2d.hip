@@ -1,6 +1,7 @@
 // Patch kernel of the Cartesian 2D problems: one block advances one channel,
 // every field value in a register.
 #include <algorithm>
+#include <type_traits>
 
 #include "../../include/casimir_fdtd.h"
 #include "lds.hpp"
@@ -107,6 +108,18 @@ __device__ __forceinline__ double masked(double v, uint32_t bits, int k) {
     return __hiloint2double(__double2hiint(v) & m, __double2loint(v) & m);
 }
 
+// x <- a x - b d and x <- a x + b d, or (START) the consistent start's (b / 2) d
+template <bool START, typename T>
+__device__ __forceinline__ void p2_sub(T& x, T a, T b, T v) {
+    if constexpr (START) x = yee::half(b, v);
+    else yee::sub_into(x, a, b, v);
+}
+template <bool START, typename T>
+__device__ __forceinline__ void p2_add(T& x, T a, T b, T v) {
+    if constexpr (START) x = yee::half(b, v);
+    else yee::add_into(x, a, b, v);
+}
+
 // One block advances one channel; thread k holds patch k of the channel's list,
 // CX x B cells with every field value in registers, over all steps of the
 // launch.  Only patches with a cell that can change are listed, so conductors
@@ -129,10 +142,9 @@ __device__ __forceinline__ double masked(double v, uint32_t bits, int k) {
 // live cells, FP64) 2.9 -> 0.5 us per step.  The surface sum has a wave of its
 // own, a step behind the others, with the lane's offsets and weights in
 // registers: read from LDS by an ordinary wave they took 0.9 us per step.
-template <typename T, int POL, int CX, int B, int MW, int COEF>
-__global__ __launch_bounds__(256 * MW) __attribute__((amdgpu_waves_per_eu(MW)))
-void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ items, const InstDev* __restrict__ insts,
-               const Patch2DInst* __restrict__ heads, int kmax, int mclock, int src, int dst, P2Lds l) {
+template <typename T, int POL, int CX, int B, int COEF>
+__device__ __forceinline__ void p2_advance(const ChanDev& d, const InstDev& g, const Patch2DInst& hd, int part, int m0,
+                                           int ksteps, int src, int dst, const P2Lds& l) {
     constexpr bool TM = POL == CF_POL_TM;
     constexpr int C0 = TM ? CF_EZ : CF_EX, C1 = TM ? CF_HX : CF_EY, C2 = TM ? CF_HY : CF_HZ;
     constexpr int NE = TM ? 1 : 2, NH = 3 - NE, NC = CX * B;
@@ -140,18 +152,14 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ items, co
     constexpr int S = X::stride;
     static_assert(NC <= 32, "one mask bit per cell of the patch");
     extern __shared__ __align__(16) char lds[];
-    __shared__ int s_box[4];                       // box of the measured points
+    __shared__ int s_box[8];                       // box of the measured points (x0, y0, x1, y1), of the kicked ones
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int item = items[blockIdx.x], part = item >> kPartShift;
-    const ChanDev d = ch[item & ((1 << kPartShift) - 1)];
-    const InstDev g = insts[d.inst];
-    const Patch2DInst hd = heads[d.inst];
     const SurfTables& t = g.t;
-    const int m0 = mclock - g.start;               // instance's own step
-    const int ksteps = min(kmax, g.nsteps - m0);
-    if (m0 < 0 || ksteps <= 0) return;             // not started / finished
     const int n = hd.n[TM ? 0 : 1];
+    // small shapes: the block's own kick and consistent start at step 0; else the
+    // fields are in memory
+    const bool start = patch2d_small(NC, sizeof(T)) && hd.start != 0 && m0 == 0;
     const bool surf = part == hd.surf_part[TM ? 0 : 1];   // this block takes the surface sums
     const int nx = g.nx, ny = g.ny;
     const auto lk = as_global(static_cast<const T*>(g.lut)) + d.kind * 6 * 256 * 2;   // (a, b) of (comp, id)
@@ -165,7 +173,7 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ items, co
 
     // ---- surface tables and the zero entries ---------------------------
     const int npt = surf ? d.nsamp * d.P : 0;
-    if (tid < 4) s_box[tid] = tid < 2 ? 0x7fffffff : -1;
+    if (tid < 8) s_box[tid] = (tid & 2) ? -1 : 0x7fffffff;
     for (int k = tid; k < S; k += nthr) XE[n * S + k] = XH[n * S + k] = T(0);
     __syncthreads();
     for (int k = tid; k < npt; k += nthr) {
@@ -175,6 +183,14 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ items, co
         atomicMax(&s_box[2], i);
         atomicMax(&s_box[3], j);
     }
+    if (start)
+        for (int u = tid; u < d.n_uniq; u += nthr) {
+            const int c = as_global(t.uidx)[d.u_off + u], i = c % nx, j = c / nx;
+            atomicMin(&s_box[4], i);
+            atomicMin(&s_box[5], j);
+            atomicMax(&s_box[6], i);
+            atomicMax(&s_box[7], j);
+        }
     __syncthreads();
     const int mx0 = s_box[0], my0 = s_box[1], mx1 = s_box[2], my1 = s_box[3], mbw = mx1 - mx0 + 1;
     for (int k = tid; k < npt; k += nthr) {
@@ -184,7 +200,27 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ items, co
     }
     for (int k = tid; k < d.nsamp; k += nthr) sb[k] = as_global(t.basis)[d.basis_off + k];
 
+    // ---- the kick (as k_kick), in the stage array -------------------------
+    const int kx0 = s_box[4], ky0 = s_box[5], kx1 = s_box[6], ky1 = s_box[7], kbw = kx1 - kx0 + 1;
+    if (start) {
+        for (int k = tid; k < kbw * (ky1 - ky0 + 1); k += nthr) stage[k] = T(0);
+        __syncthreads();
+        for (int u = tid; u < d.n_uniq; u += nthr) {
+            const int k0 = as_global(t.uoff)[d.u_off + u], k1 = as_global(t.uoff)[d.u_off + u + 1];
+            double v = 0.0;
+            for (int k = k0; k < k1; ++k)
+                v += as_global(t.uw)[k] * as_global(t.basis)[d.basis_off + as_global(t.usamp)[k]];
+            const int c = as_global(t.uidx)[d.u_off + u];
+            stage[(c / nx - ky0) * kbw + c % nx - kx0] = T(d.kick_scale * v);
+        }
+        __syncthreads();
+    }
+
     if (wave == (nthr >> 6) - 1) {
+        if (start) {                               // the barriers of the others' start
+            __syncthreads();
+            __syncthreads();
+        }
         // ---- the block's last wave: surface sum and accumulation of every
         // step, while the others take the next one (the samples before their
         // H half, the total before their E half)
@@ -311,6 +347,7 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ items, co
         const auto F0 = as_global(static_cast<const T*>(src ? g.fb : g.fa)) + d.field_off;
         const auto F1 = F0 + g.ncell;
         const auto F2 = F1 + g.ncell;
+        const int kick = (int)((d.src_off - d.field_off) / g.ncell);   // slot of the kicked component
         const auto I0 = as_global(g.ids[C0]), I1 = as_global(g.ids[C1]), I2 = as_global(g.ids[C2]);
 #pragma unroll
         for (int r = 0; r < B; ++r) {
@@ -320,10 +357,18 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ items, co
                 const int x = x0 + j, y = y0 + r, k = r * CX + j;
                 const bool in = act && x < nx && y < ny;
                 const uint32_t c = in ? (uint32_t)(y * nx + x) : 0u;
-                const T v0 = F0[c], v1 = F1[c], v2 = F2[c];
-                f0[r][j] = in ? v0 : T(0);
-                f1[r][j] = in ? v1 : T(0);
-                f2[r][j] = in ? v2 : T(0);
+                if (start) {
+                    const bool at = in && x >= kx0 && x <= kx1 && y >= ky0 && y <= ky1;
+                    const T v = at ? stage[(y - ky0) * kbw + x - kx0] : T(0);
+                    f0[r][j] = kick == 0 ? v : T(0);
+                    f1[r][j] = kick == 1 ? v : T(0);
+                    f2[r][j] = kick == 2 ? v : T(0);
+                } else {
+                    const T v0 = F0[c], v1 = F1[c], v2 = F2[c];
+                    f0[r][j] = in ? v0 : T(0);
+                    f1[r][j] = in ? v1 : T(0);
+                    f2[r][j] = in ? v2 : T(0);
+                }
                 if constexpr (COEF == kRegE) {
                     ke[0][k % KE] = masked(be, pc.live[0], k);
                     if constexpr (!TM) ke[NE - 1][k % KE] = masked(be, pc.live[1], k);
@@ -359,12 +404,17 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ items, co
         if constexpr (COEF == kRegAll) return kh[h][k % KH];
         else return bh;
     };
-    auto half_h = [&]() __attribute__((always_inline)) {
+    // large patches take their rows in turn, so that the registers hold one row's
+    // temporaries; small ones interleave them to hide the arithmetic's latency
+    constexpr bool rows_in_turn = NC > 8;
+    // a half step, or (START) its part of the consistent start, the (b / 2) curl
+    auto half_h = [&](auto mode) __attribute__((always_inline)) {
+        constexpr bool START = decltype(mode)::value;
         T eR[B], eU[CX];
         p2_col<false, X>(er, eR);
 #pragma unroll
         for (int r = 0; r < B; ++r) {
-            __builtin_amdgcn_sched_barrier(0);     // rows in turn: the registers hold one row's temporaries
+            if (rows_in_turn) __builtin_amdgcn_sched_barrier(0);
             if (r + 2 == B || B == 1)
                 p2_row<false, X>(eu, eU);
 #pragma unroll
@@ -374,18 +424,19 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ items, co
                     const T ez = f0[r][j];
                     const T ezr = j + 1 < CX ? f0[r][(j + 1) % CX] : eR[r];
                     const T ezu = r + 1 < B ? f0[(r + 1) % B][j] : eU[j];
-                    yee::sub_into(f1[r][j], a_h, b_h(0, k), ezu - ez);
-                    yee::sub_into(f2[r][j], a_h, b_h(NH - 1, k), ez - ezr);
+                    p2_sub<START>(f1[r][j], a_h, b_h(0, k), ezu - ez);
+                    p2_sub<START>(f2[r][j], a_h, b_h(NH - 1, k), ez - ezr);
                 } else {
                     const T ex = f0[r][j], ey = f1[r][j];
                     const T eyr = j + 1 < CX ? f1[r][(j + 1) % CX] : eR[r];
                     const T exu = r + 1 < B ? f0[(r + 1) % B][j] : eU[j];
-                    yee::sub_into(f2[r][j], a_h, b_h(0, k), (eyr - ey) - (exu - ex));
+                    p2_sub<START>(f2[r][j], a_h, b_h(0, k), (eyr - ey) - (exu - ex));
                 }
             }
         }
     };
-    auto half_e = [&]() __attribute__((always_inline)) {
+    auto half_e = [&](auto mode) __attribute__((always_inline)) {
+        constexpr bool START = decltype(mode)::value;
         if constexpr (COEF == kMaskB)   // no b values kept across steps
 #pragma unroll
             for (int e = 0; e < NE; ++e) asm volatile("" : "+v"(live[e]));
@@ -395,7 +446,7 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ items, co
         // the row and column that wait for the neighbours' values last
 #pragma unroll
         for (int r = B - 1; r >= 0; --r) {
-            __builtin_amdgcn_sched_barrier(0);
+            if (rows_in_turn) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = CX - 1; j >= 0; --j) {
                 const int k = r * CX + j;
@@ -403,13 +454,14 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ items, co
                     const T hx = f1[r][j], hy = f2[r][j];
                     const T hyl = j > 0 ? f2[r][(j + CX - 1) % CX] : hL[r];
                     const T hxd = r > 0 ? f1[(r + B - 1) % B][j] : hD[j];
-                    yee::add_into(f0[r][j], a_e, b_e(0, k), (hy - hyl) - (hx - hxd));
+                    p2_add<START>(f0[r][j], a_e, b_e(0, k), (hy - hyl) - (hx - hxd));
                 } else {
                     const T hz = f2[r][j];
                     const T hzl = j > 0 ? f2[r][(j + CX - 1) % CX] : hL[r];
                     const T hzd = r > 0 ? f2[(r + B - 1) % B][j] : hD[j];
-                    yee::add_into(f0[r][j], a_e, b_e(0, k), hz - hzd);
-                    yee::sub_into(f1[r][j], a_e, b_e(NE - 1, k), hz - hzl);
+                    p2_add<START>(f0[r][j], a_e, b_e(0, k), hz - hzd);
+                    p2_sub<START>(f1[r][j], a_e, b_e(NE - 1, k), hz - hzl);
+                    if (START) f1[r][j] = -f1[r][j];   // E_y <- -(b / 2) d
                 }
             }
         }
@@ -440,13 +492,24 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ items, co
                     if ((in_m >> (r * CX + j)) & 1u) stage[mbase + r * mbw + j] = ms == 0 ? a : ms == 1 ? b : c;
                 }
     };
+    using Step = std::false_type;
+    using Start = std::true_type;
+    if (start) {
+        // E-current runs set H^{-1/2}, H-current runs E^{+1/2}
+        if (d.kind == 0) publish_e();
+        else publish_h();
+        __syncthreads();
+        if (d.kind == 0) half_h(Start{});
+        else half_e(Start{});
+        __syncthreads();
+    }
     publish_e();
     __syncthreads();
     for (int step = 0; step < ksteps; ++step) {
-        half_h();
+        half_h(Step{});
         publish_h();
         __syncthreads();
-        half_e();
+        half_e(Step{});
         publish_e();
         if (wave_m) put();
         __syncthreads();
@@ -466,6 +529,24 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ items, co
             }
 }
 
+// POL 0: items of both polarizations (small shapes only: the registers of the
+// larger ones leave no room for two bodies)
+template <typename T, int POL, int CX, int B, int MW, int COEF>
+__global__ __launch_bounds__(256 * MW) __attribute__((amdgpu_waves_per_eu(MW)))
+void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ items, const InstDev* __restrict__ insts,
+               const Patch2DInst* __restrict__ heads, int kmax, int mclock, int src, int dst, P2Lds l) {
+    const int item = items[blockIdx.x], part = item >> kPartShift;
+    const ChanDev d = ch[item & ((1 << kPartShift) - 1)];
+    const InstDev g = insts[d.inst];
+    const Patch2DInst hd = heads[d.inst];
+    const int m0 = mclock - g.start;               // instance's own step
+    const int ksteps = min(kmax, g.nsteps - m0);
+    if (m0 < 0 || ksteps <= 0) return;             // not started / finished
+    if constexpr (POL != 0) p2_advance<T, POL, CX, B, COEF>(d, g, hd, part, m0, ksteps, src, dst, l);
+    else if (d.pol == CF_POL_TM) p2_advance<T, CF_POL_TM, CX, B, COEF>(d, g, hd, part, m0, ksteps, src, dst, l);
+    else p2_advance<T, CF_POL_TE, CX, B, COEF>(d, g, hd, part, m0, ksteps, src, dst, l);
+}
+
 // Shapes (columns, rows, waves per SIMD of the register budget, coefficients).
 // None spills in the step loop; 128 registers hold up to 32 cells with masks,
 // 20 with E values, 12 with all values (12, 8, 6 in FP64).
@@ -473,16 +554,17 @@ template <typename T>
 struct P2Shapes;
 template <>
 struct P2Shapes<float> {
-    static constexpr int n = 10;
+    static constexpr int n = 11;
     static constexpr Patch2DShape s[n] = {{8, 4, 4, kMaskB},  {6, 5, 4, kMaskB}, {5, 5, 4, kMaskB}, {5, 4, 4, kRegE},
                                           {4, 4, 4, kRegE},   {4, 2, 4, kRegE},  {2, 2, 4, kRegE},  {4, 3, 4, kRegAll},
-                                          {3, 2, 4, kRegAll}, {2, 2, 4, kRegAll}};
+                                          {3, 2, 4, kRegAll}, {2, 2, 4, kRegAll}, {2, 1, 4, kRegE}};
 };
 template <>
 struct P2Shapes<double> {
-    static constexpr int n = 6;
+    static constexpr int n = 7;
     static constexpr Patch2DShape s[n] = {{4, 3, 4, kMaskB}, {4, 2, 4, kRegE},   {3, 2, 4, kRegE},
-                                          {2, 2, 4, kRegE},  {3, 2, 4, kRegAll}, {2, 2, 4, kRegAll}};
+                                          {2, 2, 4, kRegE},  {3, 2, 4, kRegAll}, {2, 2, 4, kRegAll},
+                                         {2, 1, 4, kRegE}};
 };
 
 template <typename T, int V = 0>
@@ -512,8 +594,10 @@ hipError_t p2_launch(int shape, int pol, int threads, const P2Lds& l, const Chan
                                dst, l);
             return hipGetLastError();
         };
-        return pol == CF_POL_TM ? run(&k_patch2d<T, CF_POL_TM, q.cx, q.b, q.mw, q.coef>)
-                                : run(&k_patch2d<T, CF_POL_TE, q.cx, q.b, q.mw, q.coef>);
+        if (pol == CF_POL_TM) return run(&k_patch2d<T, CF_POL_TM, q.cx, q.b, q.mw, q.coef>);
+        if (pol == CF_POL_TE) return run(&k_patch2d<T, CF_POL_TE, q.cx, q.b, q.mw, q.coef>);
+        if constexpr (patch2d_small(q.cx * q.b, sizeof(T))) return run(&k_patch2d<T, 0, q.cx, q.b, q.mw, q.coef>);
+        return hipErrorInvalidValue;
     }
 }
 

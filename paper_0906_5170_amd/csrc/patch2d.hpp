@@ -21,6 +21,10 @@ struct Patch2DShape {
     int cx, b, mw, coef;
 };
 constexpr int kMaxShapes2D = 12;
+// Small shapes, of grids whose solve takes a fraction of a millisecond: a launch
+// may hold both polarizations, and a block can start its channel itself.  (The
+// registers of the larger ones have no room for either.)
+constexpr bool patch2d_small(int cells, int value_bytes) { return cells * value_bytes <= 32; }
 template <typename T>
 int patch2d_shapes(Patch2DShape* out, int max);
 
@@ -49,11 +53,11 @@ struct Patch2DInst {
     int32_t n[2], surf_part[2];
     int32_t id_e, id_h;
     int32_t masks;      // E components share one material: b = b(id_e) where live
-    int32_t pad;
+    int32_t start;      // the block of step 0 kicks and starts its channel itself (whole channels only)
 };
 
-// Box of the measured points and samples x points of a channel, the largest
-// of a launch: they size the block's LDS tables.
+// Box of the measured or the kicked points and samples x points of a channel,
+// the largest of a launch: they size the block's LDS tables.
 struct Patch2DSizes {
     int box, samples, points;
 };
@@ -62,11 +66,11 @@ struct Patch2DSizes {
 template <typename T>
 size_t patch2d_lds(const Patch2DShape& q, int n, const Patch2DSizes& z);
 
-// Advances the channels (all of polarization pol) by min(kmax, remaining steps
-// of the instance) steps from launch-clock step m, from the instance's buffer
-// src (0: fa, 1: fb) to dst (the same one only without parts).  items: one per
-// block, channel slot | part << kPartShift.  heads: one per instance.  n:
-// longest list of the launch's instances.
+// Advances the channels (of polarization pol; 0: of both, for a small shape) by
+// min(kmax, remaining steps of the instance) steps from launch-clock step m, from
+// the instance's buffer src (0: fa, 1: fb) to dst (the same one only without
+// parts).  items: one per block, channel slot | part << kPartShift.  heads: one
+// per instance.  n: longest list of the launch's instances.
 constexpr int kPartShift = 26;
 template <typename T>
 hipError_t launch_patch2d(int shape, int pol, const ChanDev* ch, const int* items, int nitems, const InstDev* inst,

@@ -13,7 +13,7 @@ namespace {
 // longer launch loads and stores the fields less often but computes wider rims.
 // Batch of six pistons, the two largest in two parts (34000 and 38000 live
 // cells, FP32), 900 steps: @@ ms with 32, @@ with 16, @@ with 8, 62 on tiles.
-constexpr int kPartSteps[] = {32, 16, 8};
+constexpr int kPartSteps[] = {48, 32, 24, 16, 8};
 
 // Patches a block of the shape may hold (its last wave takes the surface sums).
 int most_patches(const Patch2DShape& q) { return 256 * q.mw - 64; }
@@ -37,6 +37,8 @@ double parts_cost(const Patch2DShape& q, int k, const Patch2DList& l, int precis
     return l.parts * step_cycles(q, k, (l.n + 63) / 64 + 1) + bytes / 7.6 / l.steps;
 }
 double tiles_cost(double cells, int precision) { return cells * (precision == CF_FP64 ? 2.2 : 1.05); }
+
+constexpr int kCUs = 256;
 
 // Whether an id's material lets the field change.
 bool holds_field(const Problem& p, const std::vector<double>& v, int id) {
@@ -281,7 +283,6 @@ Patch2DSet patch2d_set(const Problem& p, int precision) {
 }
 
 int patch2d_choose(const Patch2DSet& s, int precision, int k, int nslots, const Patch2DSizes& z, size_t lds_limit) {
-    constexpr int kCUs = 256;
     int best = -1;
     double best_cost = 0;
     // the surface wave addresses the box by 16-bit offsets
@@ -297,6 +298,26 @@ int patch2d_choose(const Patch2DSet& s, int precision, int k, int nslots, const 
         const int c = std::min(per_cu, (nblocks + kCUs - 1) / kCUs);
         const int rounds = (nblocks + kCUs * c - 1) / (kCUs * c);
         const double cost = rounds * step_cycles(q, k, c * waves);
+        if (best < 0 || cost < best_cost) {
+            best = v;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+int patch2d_choose_mixed(const Patch2DSet& s, int precision, int nslots, const Patch2DSizes& z, size_t lds_limit) {
+    int best = -1;
+    double best_cost = 0;
+    if (nslots > kCUs || z.box > 65535) return -1;
+    for (int v = 0; v < (int)s.shapes.size(); ++v) {
+        const Patch2DShape& q = s.shapes[v];
+        const Patch2DList &tm = s.lists[0][v], &te = s.lists[1][v];
+        if (!patch2d_small(q.cx * q.b, precision == CF_FP64 ? 8 : 4) || tm.parts != 1 || te.parts != 1) continue;
+        const int n = std::max(tm.n, te.n);
+        const size_t lds = precision == CF_FP64 ? patch2d_lds<double>(q, n, z) : patch2d_lds<float>(q, n, z);
+        if (lds > lds_limit) continue;
+        const double cost = step_cycles(q, 1, (n + 63) / 64 + 1);
         if (best < 0 || cost < best_cost) {
             best = v;
             best_cost = cost;

@@ -34,4 +34,8 @@ Patch2DSet patch2d_set(const Problem& p, int precision);
 // slot k, or -1 when none covers the problem.
 int patch2d_choose(const Patch2DSet& s, int precision, int k, int nslots, const Patch2DSizes& z, size_t lds_limit);
 
+// The small shape with the least time for a launch of whole channels of both
+// polarizations (nslots in all) that the device takes at once, or -1.
+int patch2d_choose_mixed(const Patch2DSet& s, int precision, int nslots, const Patch2DSizes& z, size_t lds_limit);
+
 }  // namespace cf

@@ -258,7 +258,7 @@ std::string prepare(cf_server* S, Req& r) {
     r.patches = nullptr;
     if (r.fused && !S->tiles_only) {
         auto set = cfi::cached_patches(p, S->precision);
-        cfi::patch2d_sizes(r.st.dev, r.st.gidx, p.nx, r.psizes);
+        cfi::patch2d_sizes(r.st, p.nx, r.psizes);
         int used[2] = {0, 0};
         for (const cf::Channel& c : r.chans) ++used[c.pol == CF_POL_TE ? 1 : 0];
         const int together[2] = {std::max(used[0], 1024), std::max(used[1], 1024)};
@@ -534,7 +534,8 @@ hipError_t rebuild_group(cf_server* S) {
         SlotPatches* to[2] = {nullptr, nullptr};
         if (r.patches) {
             heads.back() = cfi::patch2d_head(*r.patches, r.pshape,
-                                             reinterpret_cast<const cf::Patch2DCell*>(b + (r.parts ? r.o_ids : r.o_fb)));
+                                             reinterpret_cast<const cf::Patch2DCell*>(b + (r.parts ? r.o_ids : r.o_fb)),
+                                             false);
             size_t idx[2] = {0, 0};
             for (int q = 0; q < 2; ++q) {
                 if (r.pshape[q] < 0) continue;

@@ -136,19 +136,23 @@ struct ConvergenceStop {
 };
 
 // 2D patch kernel: the lists of a problem (kept per problem and precision),
-// LDS sizes widened to the channels of `dev` (row length nx), the shapes of a
+// LDS sizes widened to the channels of `st` (row length nx), the shapes of a
 // problem's polarizations (slot q; -1: no channel; used: its channels, launched
-// with `together`; false when one has none), whether one goes in parts, the
+// with `together`; false when one has none), whether one goes in parts, whether
+// all are small and whole (the blocks then start their channels themselves), the
 // lists and head of an instance, TM before TE, with the lists at device address
 // `at`, and the work items of n channels.
 using PatchShapes = std::array<int, 2>;
 std::shared_ptr<const cf::Patch2DSet> cached_patches(const cf::Problem& p, int precision);
-void patch2d_sizes(const std::vector<cf::ChanDev>& dev, const std::vector<int32_t>& gidx, int nx, cf::Patch2DSizes& z);
+struct Staged;
+void patch2d_sizes(const Staged& st, int nx, cf::Patch2DSizes& z);
 bool patch2d_pick(const cf::Patch2DSet& set, int precision, const int used[2], const int together[2],
                   const cf::Patch2DSizes& z, PatchShapes& shape);
 bool patch2d_in_parts(const cf::Patch2DSet& set, const PatchShapes& shape);
+bool patch2d_own_start(const cf::Patch2DSet& set, const PatchShapes& shape, int precision);
 std::vector<cf::Patch2DCell> patch2d_cells(const cf::Patch2DSet& set, const PatchShapes& shape);
-cf::Patch2DInst patch2d_head(const cf::Patch2DSet& set, const PatchShapes& shape, const cf::Patch2DCell* at);
+cf::Patch2DInst patch2d_head(const cf::Patch2DSet& set, const PatchShapes& shape, const cf::Patch2DCell* at,
+                             bool start);
 inline std::vector<int> patch2d_items(const cf::Patch2DSet& set, const PatchShapes& shape, int q, const int* slots,
                                       int n) {
     std::vector<int> out;

@@ -75,6 +75,16 @@ def test_bitwise(cf, shape, bc, media, precision):
     both(cf, problem(*shape, bc, media), precision, patch=True if shape[0] < 80 else None)
 
 
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("pol", ["TM", "TE"])
+@pytest.mark.parametrize("media", ["vacuum", "mixed"])
+def test_small_one_polarization(cf, media, pol, precision):
+    """Small grids start their channels in the patch kernel; one polarization
+    alone, and enough channels that both do not share a launch."""
+    both(cf, problem(29, 23, W, media, pol=pol), precision)
+    both(cf, problem(29, 23, W, media).replace(n_harm=20), precision)
+
+
 @pytest.mark.parametrize("pol", ["TM", "TE"])
 @pytest.mark.parametrize("shape,slab,media", [((150, 120), 1, "vacuum"), ((180, 160), 1, "vacuum"),
                                               ((176, 170), 1, "filled"), ((400, 200), 150, "vacuum"),
@@ -168,3 +178,22 @@ def test_server(cf, precision):
             assert r["fused"] and np.array_equal(r["per_channel"], b["per_channel"]), k
             srv.release(t)
     srv.close()
+
+
+def test_batch_of_parts(cf):
+    """Problems whose rims differ do not share launches;
+    enough steps for waves to cross the cuts and return."""
+    wls = [problem(400, 300, W, slab=150, n_steps=500), problem(260, 200, W, n_steps=500)]
+    probs = [cf.Problem.from_workload(w) for w in wls]
+    o = dict(sigma=0.9, courant=0.5, n_steps=500, pol="TM+TE", kernel="general", precision="fp32")
+    halos = {p.solve(**o)["tile_halo"] for p in probs}
+    assert len(halos) == 2, halos
+    for some in (probs, probs[::-1]):
+        for r, p in zip(cf.batch_solve(some, **o), some):
+            assert np.array_equal(r["per_channel"], p.solve(split=True, **o)["per_channel"])
+
+
+def test_parts_long(cf):
+    """Waves that cross the cuts many times."""
+    for shape, slab in (((260, 200), 1), ((400, 300), 150)):
+        both(cf, problem(*shape, W, slab=slab, n_steps=1500).replace(n_harm=1), "fp32")
