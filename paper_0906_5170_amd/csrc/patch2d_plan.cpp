@@ -11,9 +11,10 @@ namespace {
 
 // Steps of a launch of a grid in parts, and so the width of their rims: a
 // longer launch loads and stores the fields less often but computes wider rims.
-// Batch of six pistons, the two largest in two parts (34000 and 38000 live
-// cells, FP32), 900 steps: @@ ms with 32, @@ with 16, @@ with 8, 62 on tiles.
-constexpr int kPartSteps[] = {48, 32, 24, 16, 8};
+// Pistons of 34000 and 38000 live cells in two parts (FP32, 448 channels, 900
+// steps): 12.6 and 17.3 ms with at most 32 steps, 10.8 and 11.9 with 48, 9.9
+// and 10.4 with 64 and 96 (about 23 and 25 on tiles).
+constexpr int kPartSteps[] = {96, 64, 48, 32, 24, 16, 8};
 
 // Patches a block of the shape may hold (its last wave takes the surface sums).
 int most_patches(const Patch2DShape& q) { return 256 * q.mw - 64; }
