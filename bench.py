@@ -86,6 +86,32 @@ def measured_valu(variant):
     return rec["valu_wave_instr_per_launch"], rec.get("command", "")
 
 
+PATCH_RECORD = os.path.join(ROOT, "profiles", "counters_k_patch2d_piston2d_400x200_tetm_fp32.json")
+# the 2D patch kernel's lane-level VALU instructions of a cell-update (TM and TE
+# alike: the differences, and a multiply and an FMA per updated component;
+# neighbours come from registers and LDS)
+PATCH_LANE_INSTR = 11
+
+
+def measured_patch(steps_per_launch):
+    """VALU instructions and HBM bytes per launch of the 2D patch kernel (mean
+    over the TM and TE launches) from the committed counter record, or None
+    when it does not match the source or the launch length."""
+    import hashlib
+    if not os.path.exists(PATCH_RECORD):
+        return None, None, "no counter record"
+    rec = json.load(open(PATCH_RECORD))
+    h = hashlib.sha256()
+    for name in ("kernels_patch2d.hip", "patch2d.hpp", "device.hpp", "yee_common.hpp"):
+        with open(os.path.join(ROOT, "paper_0906_5170_amd", "csrc", name), "rb") as f:
+            h.update(f.read())
+    if rec.get("source_sha256") != h.hexdigest():
+        return None, None, "kernel source changed since the counters were taken"
+    if rec.get("steps_per_launch") != steps_per_launch:
+        return None, None, f"counters taken with {rec.get('steps_per_launch')} steps per launch, not {steps_per_launch}"
+    return rec["valu_wave_instr_per_launch"], rec["hbm_bytes_per_launch"], rec.get("command", "")
+
+
 TRAFFIC_RECORD_3D = os.path.join(ROOT, "profiles", "traffic_k_f3d2_sphere_plate_192_fp32.json")
 
 
@@ -908,11 +934,22 @@ def main():
     rt = prob.solve(workspace=ws, time_stencil=True, **opts)
     avg_s = rt["stencil_ms_avg"] * 1e-3
     alg_bytes = rt["stencil_alg_bytes"]
-    # cells the kernel advances per launch (waves holding only conductor skipped)
+    # cells the kernel advances per launch (conductor skipped)
     adv_cells = rt["stencil_cell_updates"] * rt["advanced_cell_updates"] / rt["cell_updates"]
-    traffic, traffic_note = measured_traffic(rt["tile_variant"])
-    valu, valu_note = measured_valu(rt["tile_variant"])
-    # The kernel keeps several steps per launch in registers and skips rows of
+    # a launch of the patch kernel takes hundreds of steps, one of the tiles at most 8
+    patches = rt["tile_halo"] > 8
+    if patches:
+        valu, traffic, valu_note = measured_patch(rt["tile_halo"])
+        traffic_note, step_instr = valu_note, PATCH_LANE_INSTR
+        kernel = ("k_patch2d: all TM (or TE) channels, one block per channel with its live cells in registers, "
+                  "steps_per_launch time steps per launch")
+    else:
+        traffic, traffic_note = measured_traffic(rt["tile_variant"])
+        valu, valu_note = measured_valu(rt["tile_variant"])
+        step_instr = STEP_LANE_INSTR
+        kernel = ("k_rb2d: fused register-blocked 2D update of all TM (or TE) channels, "
+                  "steps_per_launch time steps per launch")
+    # The kernel keeps its fields in registers over a launch and skips
     # conductor, so its algorithmic bytes exceed what HBM could deliver in the
     # launch time: the binding resource is vector-instruction issue (VALU),
     # reported against the issue ceiling with the counter record's
@@ -922,24 +959,25 @@ def main():
                 "peak": VALU_PEAK_WAVE_INSTR, "unit": "VALU wave-instructions/s",
                 "frac": valu / avg_s / VALU_PEAK_WAVE_INSTR if (valu and avg_s > 0) else None,
                 "valu_instr_per_launch": valu, "valu_note": valu_note,
-                "useful_valu_frac": (STEP_LANE_INSTR * adv_cells / 64.0) / avg_s / VALU_PEAK_WAVE_INSTR
+                "useful_valu_frac": (step_instr * adv_cells / 64.0) / avg_s / VALU_PEAK_WAVE_INSTR
                 if avg_s > 0 else None,
-                "step_lane_instr_per_cell_update": STEP_LANE_INSTR,
+                "step_lane_instr_per_cell_update": step_instr,
                 "advanced_cells_per_launch": adv_cells,
                 "traffic": traffic, "traffic_note": traffic_note,
                 "hbm_real_frac": traffic / avg_s / (HBM_PEAK_GBS * 1e9) if (traffic and avg_s > 0) else None,
                 "alg_bytes_per_launch": alg_bytes,
                 "alg_bytes_per_cell_update": alg_bytes / rt["stencil_cell_updates"],
                 "alg_hbm_ratio": alg_bytes / avg_s / (HBM_PEAK_GBS * 1e9) if avg_s > 0 else None,
-                "kernel": "k_rb2d: fused register-blocked 2D update of all TM (or TE) channels, "
-                          "steps_per_launch time steps per launch",
+                "kernel": kernel,
                 "avg_launch_ms": rt["stencil_ms_avg"], "launches_timed": rt["stencil_samples"],
                 "tile_variant": rt["tile_variant"], "steps_per_launch": rt["tile_halo"],
                 "launches_per_solve": rt["stencil_launches"],
                 # the timed solves run the TM and the TE launches on two streams, so that
                 # each polarization's launch tail overlaps the other's; over a whole solve
                 # the VALU issue rate is (instructions per launch x launches) / device time
-                "solve_valu_frac": (valu * rt["stencil_launches"] / (r["device_ms"] * 1e-3) / VALU_PEAK_WAVE_INSTR
+                "solve_valu_frac": (valu / rt["tile_halo"] * (2 * wl.n_steps if patches else
+                                                              rt["stencil_launches"] * rt["tile_halo"])
+                                    / (r["device_ms"] * 1e-3) / VALU_PEAK_WAVE_INSTR
                                     if valu and r["device_ms"] > 0 else None),
                 "solve_valu_note": "per-launch figures (frac, traffic) come from a solve whose launches run "
                                    "one at a time (launch sampling turns the two streams off)"}
