@@ -1306,10 +1306,19 @@ cf_status run_reduced(const cf::Problem& p, const cf_opts& o, const Staged& st, 
     cf::PatchClasses classes{};
     std::vector<uint16_t> cls;
     cf::PatchSizes psizes{};
+    std::deque<std::vector<uint16_t>> live_lists;
+    cf::PatchLive live{nullptr, nullptr, 0, &live_lists};
     if (st.red_res && o.tile_variant != 2 && patch_classes(p, cls, classes)) {
         CF_HIP(up(L.idp, cls.data(), cls.size() * 2));
         classes.cls = reinterpret_cast<const uint16_t*>(ws + L.idp);
         psizes = patch_sizes(p, st);
+        // the patch lists go behind the classes
+        const size_t at = align_up(cls.size() * 2, 16);
+        if (at < (size_t)p.ncell * 4) {
+            live.dev = ws + L.idp + at;
+            live.room = (size_t)p.ncell * 4 - at;
+        }
+        live.cls = cls.data();
     }
     // an open or dispersive k_z run on the patch kernel needs no field blocks:
     // their region holds the classes and the blocks' CPML values
@@ -1377,7 +1386,7 @@ cf_status run_reduced(const cf::Problem& p, const cf_opts& o, const Staged& st, 
         const cf::RedSpan span = cf::red_span(ord, n_ord, 0, o.n_steps, o.n_steps);
         const double cu = (double)C * p.ncell * o.n_steps;
         const bool take = smp.begin(s);
-        STEP_OK(cf::launch_red_patch<T>(fields, dch, nullptr, (int)C, g, ord, span, tabs, classes, psizes, &open, dA,
+        STEP_OK(cf::launch_red_patch<T>(fields, dch, nullptr, (int)C, g, ord, span, tabs, classes, psizes, &open, nullptr, dA,
                                         dacc, dgam, (int)C, s, &opened));
         if (opened) smp.end(take, s, cu, cu * state_bytes);
     }
@@ -1398,7 +1407,7 @@ cf_status run_reduced(const cf::Problem& p, const cf_opts& o, const Staged& st, 
                 int used = 0;
                 bool patched = false;
                 STEP_OK(cf::launch_red_patch<T>(fields, dch, sl, w.n_all, g, ord, span, tabs, classes, psizes,
-                                                nullptr, dA, dacc, dgam, (int)C, s, &patched));
+                                                nullptr, &live, dA, dacc, dgam, (int)C, s, &patched));
                 if (patched) {
                     used = cf::red_regs_covers<T>(g, ord.cplx) ? 1 : 2;
                 } else {

@@ -2,6 +2,9 @@
 // points): launch interface.
 #pragma once
 
+#include <deque>
+#include <vector>
+
 #include "device.hpp"
 #include "lds.hpp"
 #include "red_span.hpp"
@@ -40,15 +43,25 @@ struct PatchOpen {
     int64_t scratch_bytes;
 };
 
+// Patches without a cell that can change are left out: host copy of the
+// classes, device memory for the list of the others, and the host lists, which
+// live until the stream has drained.
+struct PatchLive {
+    const uint16_t* cls;
+    char* dev;
+    size_t room;
+    std::deque<std::vector<uint16_t>>* keep;
+};
+
 // As launch_red_resident_span, for grids a patch shape covers: *launched
 // tells whether one did (nothing is launched otherwise).  slots == nullptr:
 // the channels 0 .. nslots - 1.  op: an open or dispersive run (whole span
 // only, the grid's CPML set as for the split kernels); it uses no field
-// blocks.
+// blocks.  live: as above, or null (every patch of the grid).
 template <typename T>
 hipError_t launch_red_patch(T* fields, const ChanDev* ch, const int* slots, int nslots, const Grid2D& g,
                             const RedOrders& ord, const RedSpan& span, const SurfTables& t, const PatchClasses& pc,
-                            const PatchSizes& ps, const PatchOpen* op, double dA, double* acc, double* gamma,
+                            const PatchSizes& ps, const PatchOpen* op, const PatchLive* live, double dA, double* acc, double* gamma,
                             int gamma_stride, hipStream_t s, bool* launched);
 
 }  // namespace cf

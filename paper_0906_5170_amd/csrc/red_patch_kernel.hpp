@@ -3,8 +3,9 @@
 // kick, start and all its steps in a single launch, with every field value in
 // a register.
 //
-// A thread owns a patch of CX x B cells (columns x rows); LX x LY threads
-// cover the grid.  Inside the patch a neighbour is a register; the patch's
+// A thread owns a patch of CX x B cells (columns x rows); LX x LY patches
+// cover the grid, of which those with a cell that can change are listed (open
+// runs: all).  Inside the patch a neighbour is a register; the patch's
 // lowest row and first column of E and highest row and last column of H go
 // through LDS, one entry of S values per thread, read by the threads below /
 // left (E) and above / right (H).  A neighbour index is formed once per
@@ -27,9 +28,10 @@
 // and recomputes every cell's coordinates; a patch of 5 x 5 cells reads and
 // writes 1.6 and computes none.  k_z piston (80 x 40, 1856 channels, 2000
 // steps, FP32): 56.5 -> 14.7 ms on the device (17.3 with the H coefficients
-// looked up, see HU; 15.4 with copies of updated fields, see upd_h); Bloch
-// grating (48 x 60, 4096 complex channels, 2000 steps, FP32): 177.7 -> 54.4 ms
-// (59.7 with the copies).
+// looked up, see HU; 15.4 with copies of updated fields, see upd_h), 8.8 with the
+// patches left out that hold only conductor (half of this grid); Bloch grating
+// (48 x 60, 4096 complex channels, 2000 steps, FP32): 177.7 -> 54.4 ms (59.7 with
+// the copies).
 #pragma once
 
 #include <algorithm>
@@ -107,6 +109,10 @@ constexpr int patch_zs(int CX, int B) { return (CX * B) | 1; }
 
 struct PatchArgs {
     int LX, LY;
+    // patches in use, and their list [patch column and row, list indices of the
+    // patches right, left, above, below (np: none)], or null: all LX LY of them
+    int np;
+    const uint16_t* list;
     PatchLds lds;
     // open: patch columns [0, xlo) and [xhi, LX), rows [0, ylo) and [yhi, LY)
     // hold layer cells; psi of the y differences in memory, a region of
@@ -208,8 +214,17 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
     const double dt = ord.dt[m];
     const auto ktab = as_global(ord.ktab + m * ord.ktab_stride);
     const int nx = g.nx, ny = g.ny;
-    const bool act = tid < LX * LY;
+    const bool act = tid < pa.np;
     int tx = tid % LX, ty = tid / LX;
+    const bool listed = !OPEN && pa.list != nullptr;
+    uint32_t link[2] = {0, 0};                     // right | left << 16, above | below << 16
+    if (listed && act) {
+        const auto q = reinterpret_cast<yee::gmem<const uint32_t>>(as_global(pa.list)) + 3 * tid;
+        tx = q[0] & 0xffff;
+        ty = q[0] >> 16;
+        link[0] = q[1];
+        link[1] = q[2];
+    }
     // Open runs: the threads are sorted by what their patches hold, corners
     // of both layers first, then x layers, y layers and the rest, so that few
     // waves carry CPML work, the heaviest one on each SIMD beside a light one.
@@ -224,13 +239,13 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
         tx = in_x ? (cx < pa.xlo ? cx : pa.xhi + cx - pa.xlo) : pa.xlo + cx;
         ty = in_y ? (cy < pa.ylo ? cy : pa.yhi + cy - pa.ylo) : pa.ylo + cy;
     }
-    const int patch = ty * LX + tx;
+    const int patch = OPEN ? ty * LX + tx : tid;   // its exchange entry
     const int x0 = tx * CX, y0 = ty * B;
 
     T* const XE = reinterpret_cast<T*>(lds + pa.lds.xe);
     T* const XH = reinterpret_cast<T*>(lds + pa.lds.xh);
     T* const EZ = reinterpret_cast<T*>(lds + pa.lds.ez);
-    const int zero = LX * LY;                      // the entry of zeros
+    const int zero = pa.np;                        // the entry of zeros
     T* const stage = reinterpret_cast<T*>(lds + pa.lds.stage);
     T* const rows = reinterpret_cast<T*>(lds + pa.lds.rows);
     double* const sw = reinterpret_cast<double*>(lds + pa.lds.sw);
@@ -298,7 +313,8 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
     // ---- the patch's classes, neighbours and masks ---------------------
     // the cells' classes, H and E in 16 bits; where the registers are short (LZ)
     // and one H class needs no lookup, 4 bits of E class each (cylindrical
-    // piston, 400 x 21, FP64: 62.5 -> 57.3 ms; elsewhere the words cost less than
+    // piston, 400 x 21, FP64: 62.5 -> 57.3 ms, 56.3 with its 7 % of conductor left
+    // out; elsewhere the words cost less than
     // their extraction: k_z piston 14.7 against 15.3 ms)
     constexpr bool C4 = HU && patch_packs(LZ, OPEN);
     constexpr int CPW = C4 ? 8 : 2, CB = 32 / CPW, NW = (NC + CPW - 1) / CPW;
@@ -320,10 +336,10 @@ void k_red_patch(T* __restrict__ fields, const ChanDev* __restrict__ ch, const i
                 if (x >= sx0 && x <= s_box[2] && y >= sy0 && y <= s_box[3]) in_s |= 1u << k;
             }
         }
-    const int n_r = !act ? zero : tx + 1 < LX ? patch + 1 : g.perx ? patch + 1 - LX : zero;
-    const int n_l = !act ? zero : tx > 0 ? patch - 1 : g.perx ? patch + LX - 1 : zero;
-    const int n_u = !act ? zero : ty + 1 < LY ? patch + LX : !CYL && g.pery ? tx : zero;
-    const int n_d = !act ? zero : ty > 0 ? patch - LX : !CYL && g.pery ? tx + (LY - 1) * LX : zero;
+    const int n_r = !act ? zero : listed ? link[0] & 0xffff : tx + 1 < LX ? patch + 1 : g.perx ? patch + 1 - LX : zero;
+    const int n_l = !act ? zero : listed ? link[0] >> 16 : tx > 0 ? patch - 1 : g.perx ? patch + LX - 1 : zero;
+    const int n_u = !act ? zero : listed ? link[1] & 0xffff : ty + 1 < LY ? patch + LX : !CYL && g.pery ? tx : zero;
+    const int n_d = !act ? zero : listed ? link[1] >> 16 : ty > 0 ? patch - LX : !CYL && g.pery ? tx + (LY - 1) * LX : zero;
     const T* const er = XE + n_r * S;             // E columns of the patch to the right
     const T* const eu = XE + n_u * S;             // E rows of the patch above
     const T* const hl = XH + n_l * S + 2 * CX;    // H_y, H_z columns of the patch to the left
@@ -1055,9 +1071,45 @@ inline bool plan_open(const PatchShape& q, const Grid2D& g, const PatchOpen& op,
 // The shape that takes the least modelled time for nslots channels on an
 // nx x ny grid: steps of a CU's resident blocks at the waves its fullest SIMD
 // holds, times the rounds of blocks.  shape -1 when none covers the grid.
+// The list (see PatchArgs) of the patches of cx x b cells with a cell that can
+// change: E of a class that holds a field, H where an E value of its curl is of
+// such a one.
+inline std::vector<uint16_t> live_list(const uint16_t* cls, const Grid2D& g, bool pery, int cx, int b) {
+    const int LX = (g.nx + cx - 1) / cx, LY = (g.ny + b - 1) / b;
+    std::vector<int> at((size_t)LX * LY, -1);
+    for (int y = 0; y < g.ny; ++y)
+        for (int x = 0; x < g.nx; ++x) {
+            if ((cls[(size_t)y * g.nx + x] >> 8) == 0) continue;
+            const int xl = (x > 0 ? x - 1 : g.perx ? g.nx - 1 : x) / cx, yd = (y > 0 ? y - 1 : pery ? g.ny - 1 : y) / b;
+            at[(y / b) * LX + x / cx] = at[(y / b) * LX + xl] = at[yd * LX + x / cx] = 0;
+        }
+    int n = 0;
+    for (int& v : at)
+        if (v == 0) v = n++;
+    auto ref = [&](int i, int j) -> uint16_t {
+        if (i < 0 || i >= LX) {
+            if (!g.perx) return (uint16_t)n;
+            i = (i + LX) % LX;
+        }
+        if (j < 0 || j >= LY) {
+            if (!pery) return (uint16_t)n;
+            j = (j + LY) % LY;
+        }
+        return (uint16_t)(at[j * LX + i] < 0 ? n : at[j * LX + i]);
+    };
+    std::vector<uint16_t> out;
+    for (int j = 0; j < LY; ++j)
+        for (int i = 0; i < LX; ++i)
+            if (at[j * LX + i] >= 0)
+                for (uint16_t v : {(uint16_t)i, (uint16_t)j, ref(i + 1, j), ref(i - 1, j), ref(i, j + 1), ref(i, j - 1)})
+                    out.push_back(v);
+    return out;
+}
+
+// live: the list of the best shape lands in `list` (empty: every patch).
 template <typename T, bool CPLX, bool OPEN>
 PatchPlan plan_patch(bool cyl, const Grid2D& g, int nslots, const PatchClasses& pc, const PatchSizes& z,
-                     const PatchOpen* op, size_t lds_cap) {
+                     const PatchOpen* op, size_t lds_cap, const PatchLive* live, std::vector<uint16_t>& list) {
     using SH = PatchShapes<T, CPLX, OPEN>;
     constexpr int np = CPLX ? 2 : 1;
     PatchPlan best;
@@ -1069,8 +1121,14 @@ PatchPlan plan_patch(bool cyl, const Grid2D& g, int nslots, const PatchClasses& 
         PatchArgs a{};
         a.LX = (g.nx + q.cx - 1) / q.cx;
         a.LY = (g.ny + q.b - 1) / q.b;
-        const int64_t need = (int64_t)a.LX * a.LY;
+        int64_t need = (int64_t)a.LX * a.LY;
+        std::vector<uint16_t> l;
+        if (live && need <= 4 * 1024) l = live_list(live->cls, g, !cyl && g.pery, q.cx, q.b);
+        // without room for it, or with nothing to leave out, no list
+        if (l.size() * sizeof(l[0]) > (live ? live->room : 0) || (int64_t)l.size() == 6 * need) l.clear();
+        if (!l.empty()) need = (int64_t)l.size() / 6;
         if (need > 256 * q.mw || need > 1024) continue;
+        a.np = (int)need;
         const int threads = (int)((need + 63) / 64) * 64, waves = threads / 64;
         OpenSizes os;
         if (OPEN) plan_open(q, g, *op, a, os);
@@ -1092,6 +1150,7 @@ PatchPlan plan_patch(bool cyl, const Grid2D& g, int nslots, const PatchClasses& 
             best.threads = threads;
             best.blocks = blocks;
             best.cost = cost;
+            list = std::move(l);
         }
     }
     return best;
@@ -1100,13 +1159,21 @@ PatchPlan plan_patch(bool cyl, const Grid2D& g, int nslots, const PatchClasses& 
 template <typename T, bool CYL, bool CPLX, bool OPEN>
 hipError_t patch_dispatch(T* fields, const ChanDev* ch, const int* slots, int nslots, const Grid2D& g,
                           const RedOrders& ord, const RedSpan& sp, const SurfTables& t, const PatchClasses& pc,
-                          const PatchSizes& z, const PatchOpen* op, double dA, double* acc, double* gamma,
-                          int gamma_stride, hipStream_t s, bool* launched) {
+                          const PatchSizes& z, const PatchOpen* op, const PatchLive* live, double dA, double* acc,
+                          double* gamma, int gamma_stride, hipStream_t s, bool* launched) {
     using SH = PatchShapes<T, CPLX, OPEN>;
-    PatchPlan pl = plan_patch<T, CPLX, OPEN>(CYL, g, nslots, pc, z, op, device_lds_limit());
+    std::vector<uint16_t> list;
+    PatchPlan pl = plan_patch<T, CPLX, OPEN>(CYL, g, nslots, pc, z, op, device_lds_limit(), OPEN ? nullptr : live, list);
     if (pl.shape < 0) return hipSuccess;
     if (OPEN) pl.args.scratch = op->scratch;
     hipError_t e = hipSuccess;
+    if (!list.empty()) {
+        live->keep->push_back(std::move(list));
+        const std::vector<uint16_t>& l = live->keep->back();
+        pl.args.list = reinterpret_cast<const uint16_t*>(live->dev);
+        e = hipMemcpyAsync(live->dev, l.data(), l.size() * sizeof(l[0]), hipMemcpyHostToDevice, s);
+        if (e != hipSuccess) return e;
+    }
     auto attempt = [&](auto v) {
         constexpr int V = decltype(v)::value;
         if constexpr (V < SH::n) {
@@ -1143,22 +1210,22 @@ hipError_t patch_dispatch(T* fields, const ChanDev* ch, const int* slots, int ns
 template <typename T>
 hipError_t launch_red_patch(T* fields, const ChanDev* ch, const int* slots, int nslots, const Grid2D& g,
                             const RedOrders& ord, const RedSpan& span, const SurfTables& t, const PatchClasses& pc,
-                            const PatchSizes& ps, const PatchOpen* op, double dA, double* acc, double* gamma,
-                            int gamma_stride, hipStream_t s, bool* launched) {
+                            const PatchSizes& ps, const PatchOpen* op, const PatchLive* live, double dA, double* acc,
+                            double* gamma, int gamma_stride, hipStream_t s, bool* launched) {
     *launched = false;
     if (nslots <= 0 || pc.cls == nullptr) return hipSuccess;
     if (op) {
         if (ord.axis || ord.cplx) return hipSuccess;
-        return patch_dispatch<T, false, false, true>(fields, ch, slots, nslots, g, ord, span, t, pc, ps, op, dA, acc,
+        return patch_dispatch<T, false, false, true>(fields, ch, slots, nslots, g, ord, span, t, pc, ps, op, live, dA, acc,
                                                      gamma, gamma_stride, s, launched);
     }
     if (ord.axis)
-        return patch_dispatch<T, true, false, false>(fields, ch, slots, nslots, g, ord, span, t, pc, ps, op, dA, acc,
+        return patch_dispatch<T, true, false, false>(fields, ch, slots, nslots, g, ord, span, t, pc, ps, op, live, dA, acc,
                                                      gamma, gamma_stride, s, launched);
     if (ord.cplx)
-        return patch_dispatch<T, false, true, false>(fields, ch, slots, nslots, g, ord, span, t, pc, ps, op, dA, acc,
+        return patch_dispatch<T, false, true, false>(fields, ch, slots, nslots, g, ord, span, t, pc, ps, op, live, dA, acc,
                                                      gamma, gamma_stride, s, launched);
-    return patch_dispatch<T, false, false, false>(fields, ch, slots, nslots, g, ord, span, t, pc, ps, op, dA, acc,
+    return patch_dispatch<T, false, false, false>(fields, ch, slots, nslots, g, ord, span, t, pc, ps, op, live, dA, acc,
                                                   gamma, gamma_stride, s, launched);
 }
 

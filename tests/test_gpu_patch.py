@@ -115,3 +115,20 @@ def test_open_along_one_axis(cf, precision):
 def test_dispersive_without_layers(cf, precision):
     wl = block_problem(37, 29, WALLS)
     both(cf, wl.replace(lorentz={2: POLES}), precision)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("kx", [(), (0.3, 0.9)])
+@pytest.mark.parametrize("shape,bc,rows", [((48, 60), ("periodic", "pec", "periodic"), 31),
+                                           ((72, 48), ("periodic", "periodic", "periodic"), 17),
+                                           ((80, 40), WALLS, 20), ((150, 77), WALLS, 50)])
+def test_conductor_holes(cf, shape, bc, rows, kx, precision):
+    """A slab of conductor and one in a corner: patches without a cell that can
+    change are left out of the list, across periodic edges too."""
+    if kx and bc[0] != "periodic":
+        pytest.skip("Bloch runs need a periodic x axis")
+    nx, ny = shape
+    wl = block_problem(nx, ny, bc, kx=kx, n_steps=220)
+    prims = [Box((-BIG, 14, -BIG), (BIG, 14 + min(rows, ny - 22), BIG), 1), Box((nx - 13, ny - 6, -BIG), (BIG, BIG, BIG), 1),
+             Box((5, 5, -BIG), (7, 7, BIG), 2)]
+    both(cf, wl.replace(comp_ids=rasterize((nx, ny, 1), prims)), precision)
