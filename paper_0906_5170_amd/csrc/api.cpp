@@ -286,6 +286,7 @@ cf::Patch2DInst patch2d_head(const cf::Patch2DSet& set, const PatchShapes& shape
     cf::Patch2DInst h{};
     h.id_e = set.id_e;
     h.id_h = set.id_h;
+    h.id_h2 = set.id_h2;
     h.masks = set.masks ? 1 : 0;
     h.start = start ? 1 : 0;
     for (int q = 0; q < 2; ++q) {

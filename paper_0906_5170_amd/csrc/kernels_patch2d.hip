@@ -108,6 +108,21 @@ __device__ __forceinline__ double masked(double v, uint32_t bits, int k) {
     return __hiloint2double(__double2hiint(v) & m, __double2loint(v) & m);
 }
 
+// v where bit k of `bits` is set, else w: an extract and a bit-field insert (as
+// asm: the compiler makes a test and a conditional move of it, one more)
+__device__ __forceinline__ int bfi(int m, int v, int w) {
+    int r;
+    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(m), "v"(v), "v"(w));
+    return r;
+}
+__device__ __forceinline__ float selected(float v, float w, uint32_t bits, int k) {
+    return __int_as_float(bfi(__builtin_amdgcn_sbfe((int)bits, k, 1), __float_as_int(v), __float_as_int(w)));
+}
+__device__ __forceinline__ double selected(double v, double w, uint32_t bits, int k) {
+    const int m = __builtin_amdgcn_sbfe((int)bits, k, 1);
+    return __hiloint2double(bfi(m, __double2hiint(v), __double2hiint(w)), bfi(m, __double2loint(v), __double2loint(w)));
+}
+
 // x <- a x - b d and x <- a x + b d, or (START) the consistent start's (b / 2) d
 template <bool START, typename T>
 __device__ __forceinline__ void p2_sub(T& x, T a, T b, T v) {
@@ -133,7 +148,7 @@ __device__ __forceinline__ void p2_add(T& x, T a, T b, T v) {
 // Patch2DCoef says where b comes from.
 //
 // What bounds it: VALU issue (11 instructions per cell-update, 2 more per
-// masked E component) and the register file, which caps a channel's cells: 3
+// masked component) and the register file, which caps a channel's cells: 3
 // to 6 values per cell of 512 KB.  The tiles (k_rb2d) compute 64 x 64 cells
 // for 52 x 52, whole waves of conductor but not less, and reload everything
 // every 6 steps.  400 x 200 piston (14000 live cells, 448 channels, 10000
@@ -319,8 +334,8 @@ __device__ __forceinline__ void p2_advance(const ChanDev& d, const InstDev& g, c
     Patch2DCell pc{};
     if (tid < n) {
         const auto q = reinterpret_cast<yee::gmem<const uint64_t>>(as_global(hd.cells[TM ? 0 : 1])) +
-                       (int64_t)3 * (part * n + tid);
-        const uint64_t w[3] = {q[0], q[1], q[2]};
+                       (int64_t)4 * (part * n + tid);
+        const uint64_t w[4] = {q[0], q[1], q[2], q[3]};
         __builtin_memcpy(&pc, w, sizeof(pc));
     }
     const bool act = (pc.flags & kPatchUsed) != 0;
@@ -336,13 +351,18 @@ __device__ __forceinline__ void p2_advance(const ChanDev& d, const InstDev& g, c
     const T be = yee::lane_value(lk[(C0 * 256 + hd.id_e) * 2 + 1], 0);
     const T bh = yee::lane_value(lk[(C2 * 256 + hd.id_h) * 2 + 1], 0);
 
+    const T bh2 = yee::lane_value(lk[(C2 * 256 + hd.id_h2) * 2 + 1], 0);   // kMaskH
+    constexpr bool MASK_E = COEF == kMaskB || COEF == kMaskH, MASK_H = COEF == kMaskH;
+
     T f0[B][CX], f1[B][CX], f2[B][CX];
-    uint32_t live[NE];                             // kMaskB: the E components that are not held at 0
-    constexpr int KE = COEF == kMaskB ? 1 : NC, KH = COEF == kRegAll ? NC : 1;
+    uint32_t live[NE], high[NH];                   // the masks of kMaskB and kMaskH
+    constexpr int KE = MASK_E ? 1 : NC, KH = COEF == kRegAll ? NC : 1;
     T ke[NE][KE], kh[NH][KH];                      // kRegE, kRegAll: b of the cells
     uint32_t in_m = 0;                             // cells inside the measured box
 #pragma unroll
     for (int e = 0; e < NE; ++e) live[e] = pc.live[e];
+#pragma unroll
+    for (int h = 0; h < NH; ++h) high[h] = pc.high[h];
     {
         const auto F0 = as_global(static_cast<const T*>(src ? g.fb : g.fa)) + d.field_off;
         const auto F1 = F0 + g.ncell;
@@ -397,11 +417,12 @@ __device__ __forceinline__ void p2_advance(const ChanDev& d, const InstDev& g, c
     const int ms = d.meas_slot;
 
     auto b_e = [&](int e, int k) __attribute__((always_inline)) -> T {
-        if constexpr (COEF == kMaskB) return masked(be, live[e], k);
+        if constexpr (MASK_E) return masked(be, live[e], k);
         else return ke[e][k % KE];
     };
     auto b_h = [&](int h, int k) __attribute__((always_inline)) -> T {
         if constexpr (COEF == kRegAll) return kh[h][k % KH];
+        else if constexpr (MASK_H) return selected(bh2, bh, high[h], k);
         else return bh;
     };
     // large patches take their rows in turn, so that the registers hold one row's
@@ -410,6 +431,9 @@ __device__ __forceinline__ void p2_advance(const ChanDev& d, const InstDev& g, c
     // a half step, or (START) its part of the consistent start, the (b / 2) curl
     auto half_h = [&](auto mode) __attribute__((always_inline)) {
         constexpr bool START = decltype(mode)::value;
+        if constexpr (MASK_H)
+#pragma unroll
+            for (int h = 0; h < NH; ++h) asm volatile("" : "+v"(high[h]));
         T eR[B], eU[CX];
         p2_col<false, X>(er, eR);
 #pragma unroll
@@ -437,7 +461,7 @@ __device__ __forceinline__ void p2_advance(const ChanDev& d, const InstDev& g, c
     };
     auto half_e = [&](auto mode) __attribute__((always_inline)) {
         constexpr bool START = decltype(mode)::value;
-        if constexpr (COEF == kMaskB)   // no b values kept across steps
+        if constexpr (MASK_E)   // no b values kept across steps
 #pragma unroll
             for (int e = 0; e < NE; ++e) asm volatile("" : "+v"(live[e]));
         T hL[B], hD[CX];
@@ -549,22 +573,25 @@ void k_patch2d(const ChanDev* __restrict__ ch, const int* __restrict__ items, co
 
 // Shapes (columns, rows, waves per SIMD of the register budget, coefficients).
 // None spills in the step loop; 128 registers hold up to 32 cells with masks,
-// 20 with E values, 12 with all values (12, 8, 6 in FP64).
+// 20 with E values, 12 with all values (12, 8, 6 in FP64).  Twelve pistons of
+// 400 x (84 .. 160) with mu = 5 sidewalls (FP32, 1000 steps): 246 ms with kMaskH,
+// 328 on tiles, where kRegAll holds only the smallest.
 template <typename T>
 struct P2Shapes;
 template <>
 struct P2Shapes<float> {
-    static constexpr int n = 11;
+    static constexpr int n = 14;
     static constexpr Patch2DShape s[n] = {{8, 4, 4, kMaskB},  {6, 5, 4, kMaskB}, {5, 5, 4, kMaskB}, {5, 4, 4, kRegE},
                                           {4, 4, 4, kRegE},   {4, 2, 4, kRegE},  {2, 2, 4, kRegE},  {4, 3, 4, kRegAll},
-                                          {3, 2, 4, kRegAll}, {2, 2, 4, kRegAll}, {2, 1, 4, kRegE}};
+                                          {3, 2, 4, kRegAll}, {2, 2, 4, kRegAll}, {2, 1, 4, kRegE},  {8, 4, 4, kMaskH},
+                                          {5, 5, 4, kMaskH},  {4, 4, 4, kMaskH}};
 };
 template <>
 struct P2Shapes<double> {
-    static constexpr int n = 7;
+    static constexpr int n = 9;
     static constexpr Patch2DShape s[n] = {{4, 3, 4, kMaskB}, {4, 2, 4, kRegE},   {3, 2, 4, kRegE},
                                           {2, 2, 4, kRegE},  {3, 2, 4, kRegAll}, {2, 2, 4, kRegAll},
-                                         {2, 1, 4, kRegE}};
+                                         {2, 1, 4, kRegE},  {4, 3, 4, kMaskH},  {3, 3, 4, kMaskH}};
 };
 
 template <typename T, int V = 0>

@@ -12,15 +12,16 @@ namespace cf {
 // How a shape holds the cells' coefficients b (a is one value per field group
 // wherever b != 0).  kMaskB: one bit per E component, for grids whose H
 // components share one material and whose E components share one or are held
-// at 0.  kRegE: E values in registers, one H material.  kRegAll: all in
-// registers, any materials.
-enum Patch2DCoef { kMaskB = 0, kRegE = 1, kRegAll = 2 };
+// at 0.  kMaskH: besides, one bit per H component, for H components of two
+// materials (one may hold H at 0).  kRegE: E values in registers, one H
+// material.  kRegAll: all in registers, any materials.
+enum Patch2DCoef { kMaskB = 0, kRegE = 1, kRegAll = 2, kMaskH = 3 };
 
 // Patch of cx x b cells per thread, register budget of mw waves per SIMD.
 struct Patch2DShape {
     int cx, b, mw, coef;
 };
-constexpr int kMaxShapes2D = 12;
+constexpr int kMaxShapes2D = 16;
 // Small shapes, of grids whose solve takes a fraction of a millisecond: a launch
 // may hold both polarizations, and a block can start its channel itself.  (The
 // registers of the larger ones have no room for either.)
@@ -30,14 +31,15 @@ int patch2d_shapes(Patch2DShape* out, int max);
 
 // One patch of an instance's list, on the device: first cell, the list indices
 // of the patches to the right and left, above and below (the list's length
-// stands for "none": fields there are 0), and the cells whose E components
-// (TM: E_z; TE: E_x, E_y) are not held at 0, cell (r, j) at bit r cx + j.
+// stands for "none": fields there are 0), the cells whose E components (TM: E_z;
+// TE: E_x, E_y) are not held at 0, cell (r, j) at bit r cx + j, and those whose H
+// components (TM: H_x, H_y; TE: H_z) are of the second H material.
 enum { kPatchUsed = 1, kPatchStored = 2 };
 struct Patch2DCell {
     uint16_t x0, y0, right, left, up, down, flags, pad;
-    uint32_t live[2];
+    uint32_t live[2], high[2];
 };
-static_assert(sizeof(Patch2DCell) == 24, "three 8-byte loads per thread");
+static_assert(sizeof(Patch2DCell) == 32, "four 8-byte loads per thread");
 
 // Head of an instance: per polarization (0 TM, 1 TE) its lists (one per part,
 // of one length n, the shorter ones filled up with unused patches), the part
@@ -53,6 +55,7 @@ struct Patch2DInst {
     int32_t n[2], surf_part[2];
     int32_t id_e, id_h;
     int32_t masks;      // E components share one material: b = b(id_e) where live
+    int32_t id_h2;      // second H material (kMaskH)
     int32_t start;      // the block of step 0 kicks and starts its channel itself (whole channels only)
 };
 

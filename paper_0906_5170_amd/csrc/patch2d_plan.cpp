@@ -21,10 +21,11 @@ int most_patches(const Patch2DShape& q) { return 256 * q.mw - 64; }
 
 // Estimated cycles of a step on a compute unit with `waves` waves of the shape,
 // polarization slot k.  VALU issue: about 11 instructions per cell and step, 2
-// more per masked E component, 4 cycles each; a step's latency (LDS, two
+// more per masked component, 4 cycles each; a step's latency (LDS, two
 // barriers) is 700 cycles beyond a wave's own instructions.
 double step_cycles(const Patch2DShape& q, int k, int waves) {
-    const double instr = (q.cx * q.b) * (q.coef == kMaskB ? (k == 0 ? 13.0 : 15.0) : 11.0) + 40;
+    const double per_cell = q.coef == kMaskH ? 17.0 : q.coef == kMaskB ? (k == 0 ? 13.0 : 15.0) : 11.0;
+    const double instr = (q.cx * q.b) * per_cell + 40;
     return std::max(std::ceil(waves / 4.0) * instr * 4, 700 + instr * 4.5);
 }
 
@@ -46,23 +47,32 @@ bool holds_field(const Problem& p, const std::vector<double>& v, int id) {
     return id != kWallId && id < p.nmat && std::isfinite(v[id]);
 }
 
-// The material every component of `comps` uses in every cell: `single` when
-// the ids with a field share one value, `all` when no cell is without a field.
+// The materials the components `comps` use: `single` when the ids with a field
+// share one value, `all` when no cell is without a field, `two` when there are
+// two kinds of cells, of two values (id, second) or of one and without a field.
 struct Uniform {
-    bool single = true, all = true;
-    int id = kNullId;
+    bool single = true, all = true, two = false;
+    int id = kNullId, second = kNullId;
 };
 Uniform uniform(const Problem& p, const std::vector<double>& v, std::initializer_list<int> comps) {
     bool used[256] = {};
     for (int c : comps)
         for (int64_t k = 0; k < p.ncell; ++k) used[p.ids[c][k]] = true;
     Uniform u;
+    bool more = false;
     for (int id = 0; id < 256; ++id) {
         if (!used[id]) continue;
-        if (!holds_field(p, v, id)) u.all = false;
-        else if (u.id == kNullId) u.id = id;
-        else if (v[id] != v[u.id]) u.single = false;
+        if (!holds_field(p, v, id)) {
+            u.all = false;
+        } else if (u.id == kNullId) {
+            u.id = id;
+        } else if (v[id] != v[u.id]) {
+            u.single = false;
+            if (u.second == kNullId) u.second = id;
+            else if (v[id] != v[u.second]) more = true;
+        }
     }
+    u.two = u.id != kNullId && !more && u.single != u.all;
     return u;
 }
 
@@ -82,11 +92,12 @@ std::vector<uint8_t> live_e(const Problem& p, int k) {
 struct PatchGrid {
     const Problem& p;
     const std::vector<uint8_t>& live;
+    const std::vector<uint8_t>& high;                 // as live, H components of the second material
     int cx, b, LX, LY;
     bool perx, pery;
     std::vector<uint8_t> on;
-    PatchGrid(const Problem& p_, const std::vector<uint8_t>& live_, int cx_, int b_)
-        : p(p_), live(live_), cx(cx_), b(b_), LX((p_.nx + cx_ - 1) / cx_), LY((p_.ny + b_ - 1) / b_),
+    PatchGrid(const Problem& p_, const std::vector<uint8_t>& live_, const std::vector<uint8_t>& high_, int cx_, int b_)
+        : p(p_), live(live_), high(high_), cx(cx_), b(b_), LX((p_.nx + cx_ - 1) / cx_), LY((p_.ny + b_ - 1) / b_),
           perx(p_.grid.bc[0] == CF_BC_PERIODIC), pery(p_.grid.bc[1] == CF_BC_PERIODIC) {
         on.assign((size_t)LX * LY, 0);
         for (int y = 0; y < p.ny; ++y) {
@@ -138,6 +149,9 @@ struct PatchGrid {
                         const uint8_t v = live[(size_t)(j * b + r) * p.nx + i * cx + q];
                         c.live[0] |= (uint32_t)(v & 1) << (r * cx + q);
                         c.live[1] |= (uint32_t)(v >> 1) << (r * cx + q);
+                        const uint8_t w = high[(size_t)(j * b + r) * p.nx + i * cx + q];
+                        c.high[0] |= (uint32_t)(w & 1) << (r * cx + q);
+                        c.high[1] |= (uint32_t)(w >> 1) << (r * cx + q);
                     }
                 out[first + k] = c;
             }
@@ -229,6 +243,7 @@ Patch2DSet patch2d_set(const Problem& p, int precision) {
     const Uniform ue = uniform(p, p.eps, {CF_EX, CF_EY, CF_EZ}), uh = uniform(p, p.mu, {CF_HX, CF_HY, CF_HZ});
     s.id_e = ue.id;
     s.id_h = uh.id;
+    s.id_h2 = uh.second;
     s.masks = ue.single;
     s.ncell = p.ncell;
     const bool fits = p.grid.ndim == 2 && p.nx < 65536 && p.ny < 65536;
@@ -246,15 +261,32 @@ Patch2DSet patch2d_set(const Problem& p, int precision) {
         s.lists[k].resize(n);
         if (!fits) continue;
         const std::vector<uint8_t> live = live_e(p, k);
+        // H components of the second material (of none, where that is the second kind)
+        std::vector<uint8_t> high(p.ncell, 0);
+        if (uh.two)
+            for (int c = 0; c < (k == 0 ? 2 : 1); ++c) {
+                const auto& ids = p.ids[(k == 0 ? CF_HX : CF_HZ) + c];
+                for (int64_t q = 0; q < p.ncell; ++q)
+                    high[q] |= (uint8_t)(!(holds_field(p, p.mu, ids[q]) && p.mu[ids[q]] == p.mu[uh.id]) << c);
+            }
+        // whether a shape's coefficients can hold the materials
+        auto holds = [&](const Patch2DShape& q) {
+            const bool one_h = uh.single && uh.all;
+            switch (q.coef) {
+                case kMaskB: return one_h && ue.single;
+                case kMaskH: return uh.two && ue.single;
+                case kRegE: return one_h;
+                default: return true;
+            }
+        };
         bool covered = false;
         for (int v = 0; v < n; ++v) {
             const Patch2DShape& q = s.shapes[v];
-            if (q.coef != kRegAll && !(uh.single && uh.all)) continue;
-            if (q.coef == kMaskB && !ue.single) continue;
+            if (!holds(q)) continue;
             // a periodic axis wraps at a patch edge
             if (p.grid.bc[0] == CF_BC_PERIODIC && p.nx % q.cx) continue;
             if (p.grid.bc[1] == CF_BC_PERIODIC && p.ny % q.b) continue;
-            s.lists[k][v] = PatchGrid(p, live, q.cx, q.b).whole();
+            s.lists[k][v] = PatchGrid(p, live, high, q.cx, q.b).whole();
             if (s.lists[k][v].n > most_patches(q)) s.lists[k][v] = Patch2DList();
             covered = covered || s.lists[k][v].parts > 0;
         }
@@ -263,10 +295,10 @@ Patch2DSet patch2d_set(const Problem& p, int precision) {
         // unless the tiles are estimated to take less
         for (int v = 0; v < n; ++v) {
             const Patch2DShape& q = s.shapes[v];
-            if (q.coef != kMaskB || !ue.single || !(uh.single && uh.all)) continue;
+            if ((q.coef != kMaskB && q.coef != kMaskH) || !holds(q)) continue;
             if (p.grid.bc[0] == CF_BC_PERIODIC && p.nx % q.cx) continue;
             if (p.grid.bc[1] == CF_BC_PERIODIC && p.ny % q.b) continue;
-            const PatchGrid grid(p, live, q.cx, q.b);
+            const PatchGrid grid(p, live, high, q.cx, q.b);
             double best = 0;
             for (int steps : kPartSteps) {
                 Patch2DList l = grid.parts(most_patches(q), steps, lo, hi);

@@ -23,6 +23,7 @@ struct Patch2DSet {
     std::vector<Patch2DShape> shapes;
     std::vector<Patch2DList> lists[2];                // per polarization (0 TM, 1 TE) and shape (parts == 0: not usable)
     int id_e = kNullId, id_h = kNullId;               // an E and an H material with a field
+    int id_h2 = kNullId;                              // and the other one where H has two
     bool masks = false;                               // E components share one material
     int64_t ncell = 0;
 };

@@ -35,6 +35,12 @@ def problem(nx, ny, bc, media="vacuum", slab=1, pol="TM+TE", n_steps=130):
     if media == "mixed":                     # two dielectrics, one of them magnetic
         prims.append(Box((nx - 3, slab + 2, -BIG), (nx - 1, ny - 5, BIG), 2))
         eps, mu = [1.0, PEC, 3.1], [1.0, 1.0, 1.7]
+    if media == "mu5":                       # one dielectric, two permeabilities
+        prims.append(Box((nx - 3, slab + 2, -BIG), (nx - 1, ny - 5, BIG), 2))
+        eps, mu = [1.0, PEC, 1.0], [1.0, 1.0, 5.0]
+    if media == "three":                     # three permeabilities
+        prims += [Box((nx - 3, slab + 2, -BIG), (nx - 1, ny - 5, BIG), 2), Box((0, ny - 4, -BIG), (4, ny - 2, BIG), 3)]
+        eps, mu = [1.0, PEC, 1.0, 1.0], [1.0, 1.0, 5.0, 2.0]
     if media == "pmc":                       # a magnetic conductor (H held at 0)
         prims.append(Box((nx - 3, slab + 2, -BIG), (nx - 1, ny - 5, BIG), 2))
         eps, mu = [1.0, PEC, 1.0], [1.0, 1.0, PEC]
@@ -68,7 +74,7 @@ SHAPES = [((13, 14), W), ((16, 16), P), ((23, 19), ("pec", "pec", "periodic")), 
 
 
 @pytest.mark.parametrize("precision", ["fp32", "fp64"])
-@pytest.mark.parametrize("media", ["vacuum", "filled", "mixed", "pmc"])
+@pytest.mark.parametrize("media", ["vacuum", "filled", "mixed", "pmc", "mu5", "three"])
 @pytest.mark.parametrize("shape,bc", SHAPES)
 def test_bitwise(cf, shape, bc, media, precision):
     # 8000 cells and more fit no shape in FP64 or with several materials
@@ -88,7 +94,7 @@ def test_small_one_polarization(cf, media, pol, precision):
 @pytest.mark.parametrize("pol", ["TM", "TE"])
 @pytest.mark.parametrize("shape,slab,media", [((150, 120), 1, "vacuum"), ((180, 160), 1, "vacuum"),
                                               ((176, 170), 1, "filled"), ((400, 200), 150, "vacuum"),
-                                              ((110, 100), 1, "mixed")])
+                                              ((110, 100), 1, "mixed"), ((170, 160), 1, "mu5"), ((150, 120), 1, "pmc")])
 def test_largest_shapes(cf, shape, slab, media, pol):
     """Grids that take the largest FP32 shapes, and one mostly of conductor."""
     both(cf, problem(*shape, W, media, slab, pol, n_steps=60), "fp32")
@@ -97,13 +103,14 @@ def test_largest_shapes(cf, shape, slab, media, pol):
 @pytest.mark.parametrize("shape,bc,slab,pol", [
     ((260, 200), W, 1, "TM+TE"), ((200, 260), W, 1, "TM"), ((512, 96), ("periodic", "pec", "periodic"), 1, "TM+TE"),
     ((96, 512), ("pec", "periodic", "periodic"), 1, "TE"), ((400, 300), W, 150, "TM+TE"), ((417, 203), W, 2, "TE")])
+@pytest.mark.parametrize("media", ["vacuum", "mu5", "pmc"])
 @pytest.mark.parametrize("precision", ["fp32", "fp64"])
-def test_parts(cf, shape, bc, slab, pol, precision):
+def test_parts(cf, shape, bc, slab, pol, precision, media):
     """Grids beyond one compute unit go in parts, cut along either axis, over
     periodic edges too; several launches, the last one shorter."""
     # FP64 lists of a grid without conductor may find no room: tiles
-    both(cf, problem(*shape, bc, "vacuum", slab, pol, n_steps=75), precision,
-         patch=True if precision == "fp32" or slab > 100 else None)
+    both(cf, problem(*shape, bc, media, slab, pol, n_steps=75), precision,
+         patch=True if media == "vacuum" and (precision == "fp32" or slab > 100) else None)
 
 
 def test_parts_waves_graph_and_stop(cf):
@@ -195,5 +202,5 @@ def test_batch_of_parts(cf):
 
 def test_parts_long(cf):
     """Waves that cross the cuts many times."""
-    for shape, slab in (((260, 200), 1), ((400, 300), 150)):
-        both(cf, problem(*shape, W, slab=slab, n_steps=1500).replace(n_harm=1), "fp32")
+    for shape, slab, media in (((260, 200), 1, "vacuum"), ((400, 300), 150, "vacuum"), ((260, 200), 1, "mu5")):
+        both(cf, problem(*shape, W, media, slab, n_steps=1500).replace(n_harm=1), "fp32")
