@@ -473,7 +473,7 @@ def bench_open_space(cf, torch):
            "force_per_length": r["force"], "force_per_length_fp64_fields": r64["force"],
            "fp32_vs_fp64_fields_rel": abs(r["force"] / r64["force"] - 1),
            "wall_s": wall, "device_ms": r["device_ms"], "device_ms_fp64": r64["device_ms"], "value": rate,
-           "unit": "cell-updates/s", "path": "split half-step kernels (CPML and Lorentz polarizations)",
+           "unit": "cell-updates/s", "path": "patch kernel (FP32 fields), split half-step kernels (FP64): CPML and Lorentz polarizations",
            "alg_bytes_per_s": rate * 48.0, "alg_frac_of_hbm_peak": rate * 48.0 / (HBM_PEAK_GBS * 1e9)}
     log(f"[bench] open space (Sec. III B waveguides): {wall:.2f} s wall ({r['device_ms']:.0f} ms device), "
         f"{rate:.3e} cell-updates/s, force {r['force']:.6e} (FP64 fields {r64['force']:.6e})")

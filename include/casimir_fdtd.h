@@ -284,7 +284,10 @@ typedef struct cf_opts {
                         /* 3D problems; results do not depend on it.          */
     int tile_variant;   /* fused kernel variant (2D tile shape, or 3D band shape): 0 = autotune (timed on */
                         /* the solve's own data, cached per shape in the      */
-                        /* process and in $CF_AUTOTUNE_CACHE when set),       */
+                        /* process and in $CF_AUTOTUNE_CACHE when set; a 2D    */
+                        /* grid whose cells outside conductors fit the        */
+                        /* registers of compute units, whole or in parts, is  */
+                        /* advanced there instead of in tiles, untimed),      */
                         /* k >= 1 = variant k-1.  3D: 1..4 one time step per  */
                         /* launch, 5..6 two (paired steps; an odd last step   */
                         /* on the one-step shape).  Results do not depend on it. */
@@ -337,8 +340,9 @@ typedef struct cf_result {
                                  /* one read + one write of the state it advances                   */
     double stencil_cell_updates; /* cell-updates one field-update launch performs                   */
     int fused;                   /* 1 when the fused multi-step kernel advanced the fields          */
-    int tile_variant;            /* fused kernel variant used (1-based), 0 if not fused             */
-    int tile_halo;               /* steps per fused launch of that variant                          */
+    int tile_variant;            /* fused kernel variant used (1-based), 0 if not fused; where a    */
+                                 /* 2D solve did without tiles, the first variant that fits it       */
+    int tile_halo;               /* steps per fused launch (at most 8 with 2D tiles)                */
     int n_steps_run;             /* time steps run (< n_steps when the convergence stop ended it)   */
     double advanced_cell_updates; /* cell-updates the field kernels actually performed: below        */
                                   /* cell_updates when the fused 2D kernel skips rows that hold only  */
@@ -428,7 +432,8 @@ const char* cf_last_error(void);
  * budget (a later request may pass an earlier one that does not fit yet) and
  * leaves when all its time steps have run, returning its memory.  In every
  * scheduler tick the 2D requests whose stress surface fits a fused tile
- * share fused launches and advance steps_per_tick steps; every other
+ * share fused launches and advance steps_per_tick steps (several ticks may
+ * run as one where no request needs the device in between); every other
  * resident request (3D, wider 2D) advances the steps that an equal share of
  * the tick's device time buys it, from its measured time per step.
  * Cylindrical and k_z requests (Sec. III B, III C: one launch runs every

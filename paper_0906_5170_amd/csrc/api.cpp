@@ -212,7 +212,7 @@ std::shared_ptr<const cf::Patch2DSet> cached_patches(const cf::Problem& p, int p
         auto it = g_patches.find(key);
         if (it != g_patches.end()) return it->second;
     }
-    auto set = std::make_shared<const cf::Patch2DSet>(cf::patch2d_set(p, precision));
+    auto set = cf::patch2d_set(p, precision);
     std::lock_guard<std::mutex> lk(g_plan_mu);
     if (g_patches.size() >= 256) g_patches.clear();
     g_patches[key] = set;
@@ -241,6 +241,13 @@ void patch2d_sizes(const Staged& st, int nx, cf::Patch2DSizes& z) {
     }
 }
 
+static size_t patch2d_bytes(const cf::Patch2DSet& set, const PatchShapes& shape) {
+    size_t n = 0;
+    for (int q = 0; q < 2; ++q)
+        if (shape[q] >= 0) n += set.lists[q][shape[q]].size();
+    return n * sizeof(cf::Patch2DCell);
+}
+
 bool patch2d_pick(const cf::Patch2DSet& set, int precision, const int used[2], const int together[2],
                   const cf::Patch2DSizes& z, PatchShapes& shape) {
     const size_t lim = cf::device_lds_limit();
@@ -252,7 +259,7 @@ bool patch2d_pick(const cf::Patch2DSet& set, int precision, const int used[2], c
     // lists in the ids' place: no shape that reads the ids, and room for them
     for (int q = 0; q < 2; ++q)
         if (shape[q] >= 0 && (set.shapes[shape[q]].coef == cf::kRegAll || !set.masks)) return false;
-    return patch2d_cells(set, shape).size() * sizeof(cf::Patch2DCell) <= (size_t)cf::kNumComp * set.ncell;
+    return patch2d_bytes(set, shape) <= (size_t)cf::kNumComp * set.nx * set.ny;
 }
 
 bool patch2d_in_parts(const cf::Patch2DSet& set, const PatchShapes& shape) {
@@ -275,7 +282,7 @@ std::vector<cf::Patch2DCell> patch2d_cells(const cf::Patch2DSet& set, const Patc
     std::vector<cf::Patch2DCell> out;
     for (int q = 0; q < 2; ++q) {
         if (shape[q] < 0) continue;
-        const auto& c = set.lists[q][shape[q]].cells;
+        const auto& c = cf::patch2d_cells(set, q, shape[q]);
         out.insert(out.end(), c.begin(), c.end());
     }
     return out;
@@ -295,7 +302,7 @@ cf::Patch2DInst patch2d_head(const cf::Patch2DSet& set, const PatchShapes& shape
         h.cells[q] = at;
         h.n[q] = l.n;
         h.surf_part[q] = l.surf_part;
-        at += l.cells.size();
+        at += l.size();
     }
     return h;
 }

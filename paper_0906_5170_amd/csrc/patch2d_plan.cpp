@@ -3,6 +3,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <numeric>
 
 namespace cf {
@@ -35,7 +36,7 @@ double step_cycles(const Patch2DShape& q, int k, int waves) {
 // in 6.2 us, FP32).
 double parts_cost(const Patch2DShape& q, int k, const Patch2DList& l, int precision) {
     const double value = precision == CF_FP64 ? 8.0 : 4.0;
-    const double bytes = 3 * value * (l.cells.size() * (double)(q.cx * q.b) + l.live_cells);
+    const double bytes = 3 * value * (l.size() * (double)(q.cx * q.b) + l.live_cells);
     return l.parts * step_cycles(q, k, (l.n + 63) / 64 + 1) + bytes / 7.6 / l.steps;
 }
 double tiles_cost(double cells, int precision) { return cells * (precision == CF_FP64 ? 2.2 : 1.05); }
@@ -76,57 +77,56 @@ Uniform uniform(const Problem& p, const std::vector<double>& v, std::initializer
     return u;
 }
 
-// Which E components of a polarization can change: bit 0 E_z (TM) or E_x (TE),
-// bit 1 E_y (TE).
-std::vector<uint8_t> live_e(const Problem& p, int k) {
-    std::vector<uint8_t> live(p.ncell, 0);
-    const int first = k == 0 ? CF_EZ : CF_EX, n = k == 0 ? 1 : 2;
-    for (int c = 0; c < n; ++c)
-        for (int64_t q = 0; q < p.ncell; ++q) live[q] |= (uint8_t)(holds_field(p, p.eps, p.ids[first + c][q]) << c);
-    return live;
+// Runs of live cells of every row: [begin, end) pairs of row y at runs[y].
+using Runs = std::vector<std::vector<int>>;
+Runs live_runs(const std::vector<uint8_t>& live, int nx, int ny) {
+    Runs r(ny);
+    for (int y = 0; y < ny; ++y) {
+        const uint8_t* row = live.data() + (size_t)y * nx;
+        for (int x = 0; x < nx; ++x)
+            if ((row[x] != 0) != (x > 0 && row[x - 1] != 0)) r[y].push_back(x);
+        if (r[y].size() % 2) r[y].push_back(nx);
+    }
+    return r;
 }
 
 // The patches of cx x b cells of a grid, row by row; `on` marks those with a
 // cell that can change: E where its coefficient is not 0, H where an E value of
 // its curl is such a one.
 struct PatchGrid {
-    const Problem& p;
-    const std::vector<uint8_t>& live;
-    const std::vector<uint8_t>& high;                 // as live, H components of the second material
+    const Patch2DSet& s;
     int cx, b, LX, LY;
-    bool perx, pery;
     std::vector<uint8_t> on;
-    PatchGrid(const Problem& p_, const std::vector<uint8_t>& live_, const std::vector<uint8_t>& high_, int cx_, int b_)
-        : p(p_), live(live_), high(high_), cx(cx_), b(b_), LX((p_.nx + cx_ - 1) / cx_), LY((p_.ny + b_ - 1) / b_),
-          perx(p_.grid.bc[0] == CF_BC_PERIODIC), pery(p_.grid.bc[1] == CF_BC_PERIODIC) {
+    PatchGrid(const Patch2DSet& s_, const Runs& runs, int cx_, int b_)
+        : s(s_), cx(cx_), b(b_), LX((s_.nx + cx_ - 1) / cx_), LY((s_.ny + b_ - 1) / b_) {
         on.assign((size_t)LX * LY, 0);
-        for (int y = 0; y < p.ny; ++y) {
-            const uint8_t* row = live.data() + (size_t)y * p.nx;
-            const int yb = y / b, yd = (y > 0 ? y - 1 : pery ? p.ny - 1 : y) / b;
-            for (int x = 0; x < p.nx; ++x) {
-                if (!row[x]) continue;
-                const int xb = x / cx;
-                on[(size_t)yb * LX + xb] = on[(size_t)yd * LX + xb] = 1;
-                on[(size_t)yb * LX + (x > 0 ? x - 1 : perx ? p.nx - 1 : x) / cx] = 1;
+        for (int y = 0; y < s.ny; ++y) {
+            uint8_t* own = on.data() + (size_t)(y / b) * LX;
+            uint8_t* below = on.data() + (size_t)((y > 0 ? y - 1 : s.pery ? s.ny - 1 : y) / b) * LX;
+            for (size_t k = 0; k < runs[y].size(); k += 2) {
+                const int x0 = runs[y][k], x1 = runs[y][k + 1], c0 = x0 / cx, c1 = (x1 - 1) / cx + 1;
+                std::memset(own + c0, 1, c1 - c0);
+                std::memset(below + c0, 1, c1 - c0);
+                own[(x0 > 0 ? x0 - 1 : s.perx ? s.nx - 1 : x0) / cx] = 1;
             }
         }
     }
     // Appends the patches of columns [i0, i1) and rows [j0, j1) (wrapped on a
     // periodic axis), those of the columns [s0, s1) and rows [t0, t1) stored;
     // `none` marks a neighbour outside the list.  Returns how many.
-    int append(int i0, int i1, int j0, int j1, int s0, int s1, int t0, int t1, int none,
-               std::vector<Patch2DCell>& out) const {
+    int append(const std::vector<uint8_t>& live, const std::vector<uint8_t>& high, int i0, int i1, int j0, int j1, int s0,
+               int s1, int t0, int t1, int none, std::vector<Patch2DCell>& out) const {
         std::vector<int> at((size_t)LX * LY, -1);
         auto wrap = [](int v, int n) { return ((v % n) + n) % n; };
         int n = 0;
         for (int j = j0; j < j1; ++j)
             for (int i = i0; i < i1; ++i) {
-                if ((!perx && (i < 0 || i >= LX)) || (!pery && (j < 0 || j >= LY))) continue;
+                if ((!s.perx && (i < 0 || i >= LX)) || (!s.pery && (j < 0 || j >= LY))) continue;
                 const size_t q = (size_t)wrap(j, LY) * LX + wrap(i, LX);
                 if (on[q] && at[q] < 0) at[q] = n++;
             }
         auto ref = [&](int i, int j) -> uint16_t {
-            if ((!perx && (i < 0 || i >= LX)) || (!pery && (j < 0 || j >= LY))) return (uint16_t)none;
+            if ((!s.perx && (i < 0 || i >= LX)) || (!s.pery && (j < 0 || j >= LY))) return (uint16_t)none;
             const int a = at[(size_t)wrap(j, LY) * LX + wrap(i, LX)];
             return (uint16_t)(a < 0 ? none : a);
         };
@@ -144,12 +144,12 @@ struct PatchGrid {
                 c.up = ref(i, j + 1);
                 c.down = ref(i, j - 1);
                 c.flags = kPatchUsed | (i >= s0 && i < s1 && j >= t0 && j < t1 ? kPatchStored : 0);
-                for (int r = 0; r < b && j * b + r < p.ny; ++r)
-                    for (int q = 0; q < cx && i * cx + q < p.nx; ++q) {
-                        const uint8_t v = live[(size_t)(j * b + r) * p.nx + i * cx + q];
+                for (int r = 0; r < b && j * b + r < s.ny; ++r)
+                    for (int q = 0; q < cx && i * cx + q < s.nx; ++q) {
+                        const size_t cell = (size_t)(j * b + r) * s.nx + i * cx + q;
+                        const uint8_t v = live[cell], w = high[cell];
                         c.live[0] |= (uint32_t)(v & 1) << (r * cx + q);
                         c.live[1] |= (uint32_t)(v >> 1) << (r * cx + q);
-                        const uint8_t w = high[(size_t)(j * b + r) * p.nx + i * cx + q];
                         c.high[0] |= (uint32_t)(w & 1) << (r * cx + q);
                         c.high[1] |= (uint32_t)(w >> 1) << (r * cx + q);
                     }
@@ -157,19 +157,20 @@ struct PatchGrid {
             }
         return n;
     }
+    double cells() const {
+        double n = 0;
+        for (int j = 0; j < LY; ++j)
+            for (int i = 0; i < LX; ++i)
+                if (on[(size_t)j * LX + i]) n += (double)std::min(cx, s.nx - i * cx) * std::min(b, s.ny - j * b);
+        return n;
+    }
     Patch2DList whole() const {
         Patch2DList l;
         l.n = (int)std::count(on.begin(), on.end(), 1);
         if (l.n == 0 || l.n >= 65535) return Patch2DList();
         l.parts = 1;
-        append(0, LX, 0, LY, 0, LX, 0, LY, l.n, l.cells);
-        count(l);
+        l.live_cells = cells();
         return l;
-    }
-    void count(Patch2DList& l) const {
-        for (const Patch2DCell& c : l.cells)
-            if (c.flags & kPatchStored)
-                l.live_cells += (double)std::min(cx, p.nx - c.x0) * std::min(b, p.ny - c.y0);
     }
     // Parts of at most `most` patches, cut across x or y where the fewest blocks
     // (then patches) result; a rim of at least `steps` cells beyond a cut.  The
@@ -183,7 +184,7 @@ struct PatchGrid {
                 for (int i = 0; i < LX; ++i) load[axis == 0 ? i : j] += on[(size_t)j * LX + i];
             const int total = std::accumulate(load.begin(), load.end(), 0);
             const int s0 = lo[axis] / w, s1 = hi[axis] / w;
-            const bool per = axis == 0 ? perx : pery;
+            const bool per = axis == 0 ? s.perx : s.pery;
             for (int m = 2; m <= kMaxParts; ++m) {
                 // equal shares; a cut through the measured points moves to their nearer end
                 std::vector<int> cut{0};
@@ -201,7 +202,7 @@ struct PatchGrid {
                 Patch2DList l;
                 l.parts = m;
                 l.steps = steps;
-                int n = 0;
+                l.axis = axis;
                 bool ok = true;
                 for (int q = 0; q < m; ++q) {
                     const int c0 = cut[q] - rim, c1 = cut[q + 1] + rim;
@@ -210,23 +211,17 @@ struct PatchGrid {
                     for (int c = c0; c < c1; ++c)
                         if (per) k += load[((c % N) + N) % N];
                         else if (c >= 0 && c < N) k += load[c];
-                    n = std::max(n, k);
+                    l.n = std::max(l.n, k);
                     if (s0 >= cut[q] && s1 < cut[q + 1]) l.surf_part = q;
                 }
-                if (!ok || n == 0 || n > most) continue;
-                if (best.parts && (m > best.parts || (m == best.parts && n >= best.n))) break;
-                l.n = n;
-                for (int q = 0; q < m; ++q) {
-                    const int c0 = cut[q] - rim, c1 = cut[q + 1] + rim;
-                    const int have = axis == 0 ? append(c0, c1, 0, LY, cut[q], cut[q + 1], 0, LY, n, l.cells)
-                                               : append(0, LX, c0, c1, 0, LX, cut[q], cut[q + 1], n, l.cells);
-                    l.cells.resize(l.cells.size() + n - have);
-                }
-                count(l);
+                if (!ok || l.n == 0 || l.n > most) continue;
+                if (best.parts && (m > best.parts || (m == best.parts && l.n >= best.n))) break;
+                l.cut = std::move(cut);
                 best = std::move(l);
                 break;
             }
         }
+        if (best.parts) best.live_cells = cells();
         return best;
     }
     static constexpr int kMaxParts = 16;
@@ -234,8 +229,9 @@ struct PatchGrid {
 
 }  // namespace
 
-Patch2DSet patch2d_set(const Problem& p, int precision) {
-    Patch2DSet s;
+std::shared_ptr<const Patch2DSet> patch2d_set(const Problem& p, int precision) {
+    const auto set = std::make_shared<Patch2DSet>();
+    Patch2DSet& s = *set;
     Patch2DShape sh[kMaxShapes2D];
     const int n = precision == CF_FP64 ? patch2d_shapes<double>(sh, kMaxShapes2D)
                                        : patch2d_shapes<float>(sh, kMaxShapes2D);
@@ -245,8 +241,23 @@ Patch2DSet patch2d_set(const Problem& p, int precision) {
     s.id_h = uh.id;
     s.id_h2 = uh.second;
     s.masks = ue.single;
-    s.ncell = p.ncell;
+    s.nx = p.nx;
+    s.ny = p.ny;
+    s.perx = p.grid.bc[0] == CF_BC_PERIODIC;
+    s.pery = p.grid.bc[1] == CF_BC_PERIODIC;
     const bool fits = p.grid.ndim == 2 && p.nx < 65536 && p.ny < 65536;
+    // whether a shape's coefficients can hold the materials, and a periodic axis
+    // wraps at a patch edge
+    auto holds = [&](const Patch2DShape& q) {
+        if ((s.perx && p.nx % q.cx) || (s.pery && p.ny % q.b)) return false;
+        const bool one_h = uh.single && uh.all;
+        switch (q.coef) {
+            case kMaskB: return one_h && ue.single;
+            case kMaskH: return uh.two && ue.single;
+            case kRegE: return one_h;
+            default: return true;
+        }
+    };
     // box of every point a channel can measure
     int lo[2] = {p.nx, p.ny}, hi[2] = {-1, -1};
     for (const Gather& g : p.gathers)
@@ -257,36 +268,29 @@ Patch2DSet patch2d_set(const Problem& p, int precision) {
                 hi[a] = std::max(hi[a], c[a]);
             }
         }
+    uint8_t live_id[256], high_id[256];
+    for (int id = 0; id < 256; ++id) {
+        live_id[id] = holds_field(p, p.eps, id);
+        // the second material, or none where that is the second kind
+        high_id[id] = uh.two && !(holds_field(p, p.mu, id) && p.mu[id] == p.mu[uh.id]);
+    }
     for (int k = 0; k < 2; ++k) {
         s.lists[k].resize(n);
         if (!fits) continue;
-        const std::vector<uint8_t> live = live_e(p, k);
-        // H components of the second material (of none, where that is the second kind)
-        std::vector<uint8_t> high(p.ncell, 0);
-        if (uh.two)
-            for (int c = 0; c < (k == 0 ? 2 : 1); ++c) {
-                const auto& ids = p.ids[(k == 0 ? CF_HX : CF_HZ) + c];
-                for (int64_t q = 0; q < p.ncell; ++q)
-                    high[q] |= (uint8_t)(!(holds_field(p, p.mu, ids[q]) && p.mu[ids[q]] == p.mu[uh.id]) << c);
-            }
-        // whether a shape's coefficients can hold the materials
-        auto holds = [&](const Patch2DShape& q) {
-            const bool one_h = uh.single && uh.all;
-            switch (q.coef) {
-                case kMaskB: return one_h && ue.single;
-                case kMaskH: return uh.two && ue.single;
-                case kRegE: return one_h;
-                default: return true;
-            }
+        auto bits = [&](const uint8_t* of, int first, int count) {
+            std::vector<uint8_t> out(p.ncell, 0);
+            for (int c = 0; c < count; ++c)
+                for (int64_t q = 0; q < p.ncell; ++q) out[q] |= (uint8_t)(of[p.ids[first + c][q]] << c);
+            return out;
         };
+        s.live[k] = k == 0 ? bits(live_id, CF_EZ, 1) : bits(live_id, CF_EX, 2);
+        s.high[k] = k == 0 ? bits(high_id, CF_HX, 2) : bits(high_id, CF_HZ, 1);
+        const Runs runs = live_runs(s.live[k], p.nx, p.ny);
         bool covered = false;
         for (int v = 0; v < n; ++v) {
             const Patch2DShape& q = s.shapes[v];
             if (!holds(q)) continue;
-            // a periodic axis wraps at a patch edge
-            if (p.grid.bc[0] == CF_BC_PERIODIC && p.nx % q.cx) continue;
-            if (p.grid.bc[1] == CF_BC_PERIODIC && p.ny % q.b) continue;
-            s.lists[k][v] = PatchGrid(p, live, high, q.cx, q.b).whole();
+            s.lists[k][v] = PatchGrid(s, runs, q.cx, q.b).whole();
             if (s.lists[k][v].n > most_patches(q)) s.lists[k][v] = Patch2DList();
             covered = covered || s.lists[k][v].parts > 0;
         }
@@ -296,23 +300,43 @@ Patch2DSet patch2d_set(const Problem& p, int precision) {
         for (int v = 0; v < n; ++v) {
             const Patch2DShape& q = s.shapes[v];
             if ((q.coef != kMaskB && q.coef != kMaskH) || !holds(q)) continue;
-            if (p.grid.bc[0] == CF_BC_PERIODIC && p.nx % q.cx) continue;
-            if (p.grid.bc[1] == CF_BC_PERIODIC && p.ny % q.b) continue;
-            const PatchGrid grid(p, live, high, q.cx, q.b);
+            const PatchGrid grid(s, runs, q.cx, q.b);
+            Patch2DList& l = s.lists[k][v];
             double best = 0;
             for (int steps : kPartSteps) {
-                Patch2DList l = grid.parts(most_patches(q), steps, lo, hi);
-                if (!l.parts) continue;
-                const double cost = parts_cost(q, k, l, precision);
-                if (s.lists[k][v].parts && cost >= best) continue;
+                Patch2DList t = grid.parts(most_patches(q), steps, lo, hi);
+                if (!t.parts) continue;
+                const double cost = parts_cost(q, k, t, precision);
+                if (l.parts && cost >= best) continue;
                 best = cost;
-                s.lists[k][v] = std::move(l);
+                l = std::move(t);
             }
-            if (s.lists[k][v].parts && best > tiles_cost(s.lists[k][v].live_cells, precision)) s.lists[k][v] = Patch2DList();
-            if (s.lists[k][v].parts) break;
+            if (l.parts && best > tiles_cost(l.live_cells, precision)) l = Patch2DList();
+            if (l.parts) break;
         }
     }
-    return s;
+    return set;
+}
+
+const std::vector<Patch2DCell>& patch2d_cells(const Patch2DSet& s, int k, int shape) {
+    std::lock_guard<std::mutex> lk(s.mu);
+    std::vector<Patch2DCell>& out = s.cells[{k, shape}];
+    if (!out.empty()) return out;
+    const Patch2DShape& q = s.shapes[shape];
+    const Patch2DList& l = s.lists[k][shape];
+    const PatchGrid g(s, live_runs(s.live[k], s.nx, s.ny), q.cx, q.b);
+    if (l.parts == 1) {
+        g.append(s.live[k], s.high[k], 0, g.LX, 0, g.LY, 0, g.LX, 0, g.LY, l.n, out);
+        return out;
+    }
+    const int w = l.axis == 0 ? q.cx : q.b, rim = (l.steps + w - 1) / w;
+    for (int r = 0; r < l.parts; ++r) {
+        const int a = l.cut[r], z = l.cut[r + 1], c0 = a - rim, c1 = z + rim;
+        const int have = l.axis == 0 ? g.append(s.live[k], s.high[k], c0, c1, 0, g.LY, a, z, 0, g.LY, l.n, out)
+                                     : g.append(s.live[k], s.high[k], 0, g.LX, c0, c1, 0, g.LX, a, z, l.n, out);
+        out.resize(out.size() + l.n - have);
+    }
+    return out;
 }
 
 int patch2d_choose(const Patch2DSet& s, int precision, int k, int nslots, const Patch2DSizes& z, size_t lds_limit) {

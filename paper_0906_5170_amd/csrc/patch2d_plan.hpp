@@ -3,7 +3,10 @@
 // shape a launch takes.
 #pragma once
 
+#include <map>
 #include <memory>
+#include <mutex>
+#include <utility>
 #include <vector>
 
 #include "patch2d.hpp"
@@ -12,11 +15,13 @@
 namespace cf {
 
 // A polarization's lists for one shape: `parts` lists of n patches each, at
-// most `steps` steps per launch (0: any number, one part).
+// most `steps` steps per launch (0: any number, one part), cut across `axis`
+// before the patch columns (rows) of `cut`.
 struct Patch2DList {
-    int n = 0, parts = 0, surf_part = 0, steps = 0;
-    std::vector<Patch2DCell> cells;
+    int n = 0, parts = 0, surf_part = 0, steps = 0, axis = 0;
+    std::vector<int> cut;
     double live_cells = 0;                            // cells of the stored patches inside the grid
+    size_t size() const { return (size_t)n * parts; }
 };
 
 struct Patch2DSet {
@@ -25,11 +30,20 @@ struct Patch2DSet {
     int id_e = kNullId, id_h = kNullId;               // an E and an H material with a field
     int id_h2 = kNullId;                              // and the other one where H has two
     bool masks = false;                               // E components share one material
-    int64_t ncell = 0;
+    int nx = 0, ny = 0;
+    bool perx = false, pery = false;
+    // per polarization and cell: which E components can change (bit 0 E_z or
+    // E_x, bit 1 E_y), which H components are of the second material
+    std::vector<uint8_t> live[2], high[2];
+    // the patches of the lists in use so far, by (polarization, shape)
+    mutable std::mutex mu;
+    mutable std::map<std::pair<int, int>, std::vector<Patch2DCell>> cells;
 };
 
-// The lists of a fusable 2D problem for every shape of the precision.
-Patch2DSet patch2d_set(const Problem& p, int precision);
+// The lists of a fusable 2D problem for every shape of the precision (sizes and
+// cuts), and the patches of one of them, formed on first use.
+std::shared_ptr<const Patch2DSet> patch2d_set(const Problem& p, int precision);
+const std::vector<Patch2DCell>& patch2d_cells(const Patch2DSet& s, int k, int shape);
 
 // Shape with the least estimated time for nslots channels of polarization
 // slot k, or -1 when none covers the problem.
