@@ -1766,12 +1766,15 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
         if (smp.on) patch_launch_steps = std::min(patch_launch_steps, 256);
         patch_launch_steps = std::min({patch_launch_steps, o.n_steps, 1 << 14});
         timing->launch_steps = patch_launch_steps;
-        for (int q = 0; q < 2; ++q)
-            if (pshape[0][q] >= 0) {
-                const cf::Patch2DList& l = patches->lists[q][pshape[0][q]];
-                timing->live_cells[q] = l.live_cells;
+        for (size_t k = 0; k < st.waves.size(); ++k) {
+            const int num[2] = {st.waves[k].n_tm, st.waves[k].n_te};
+            for (int q = 0; q < 2; ++q) {
+                if (num[q] == 0) continue;
+                const cf::Patch2DList& l = patches->lists[q][pshape[k][q]];
+                timing->patch_cells += num[q] * l.live_cells;
                 if (l.steps > 0) timing->launch_steps = std::min(timing->launch_steps, l.steps);
             }
+        }
         if (smp.on)
             smp.stride = std::max(1, 2 * ((o.n_steps + timing->launch_steps - 1) / timing->launch_steps) *
                                          (int)st.waves.size() / 200);
@@ -2221,10 +2224,9 @@ bool fill_result(const cf::Problem& p, const std::vector<cf::Channel>& chans, co
     if (tim.variant >= 0 && tim.variant < (int)sg.plans.size() && p.grid.ndim == 2 && !p.reduced()) {
         // the fused 2D kernel advances the live waves' tile interiors only
         const TBPlan& pl = sg.plans[tim.variant];
-        double a = 0;
-        // (the 2D patch kernel its patches' cells)
-        const double* live = tim.launch_steps > 0 ? tim.live_cells : pl.live_cells;
-        for (size_t c = 0; c < C; ++c) a += live[chans[c].pol == CF_POL_TE ? 1 : 0];
+        double a = tim.patch_cells;   // (the 2D patch kernel its patches' cells)
+        if (tim.launch_steps == 0)
+            for (size_t c = 0; c < C; ++c) a += pl.live_cells[chans[c].pol == CF_POL_TE ? 1 : 0];
         out->advanced_cell_updates = a * (double)steps;
     }
     if (tim.variant >= 0 && tim.variant < 8 && p.grid.ndim == 3 && sg.f3d && !sg.zr.empty()) {
@@ -2637,7 +2639,7 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
             for (int q = 0; q < 2; ++q) {
                 if (pshapes[i][q] < 0) continue;
                 const cf::Patch2DList& l = psets[i]->lists[q][pshapes[i][q]];
-                timing[i].live_cells[q] = l.live_cells;
+                timing[i].patch_cells += (q == 0 ? B.inst_tm_n[i] : B.inst_te_n[i]) * l.live_cells;
                 if (l.steps > 0) timing[i].launch_steps = std::min(timing[i].launch_steps, l.steps);
             }
         }

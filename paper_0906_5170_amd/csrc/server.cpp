@@ -73,7 +73,7 @@ struct Req {
     bool parts = false;               // some polarization goes in parts, between the two field arrays
     cf::Patch2DSizes psizes{1, 1, 1};
     std::vector<cf::Patch2DCell> cells;   // its patch lists
-    double live_cells[2] = {0, 0};
+    double patch_cells = 0;               // cells it advances in a step, over all channels
     int v3 = -1;                      // fused 3D step variant (-1: split 3D kernels)
     int v3s = -1;                     // its single-step band shape (a step without a partner in the tick)
     cfi::ConvergenceStop conv;        // time-convergence stop (single-wave requests)
@@ -256,6 +256,7 @@ std::string prepare(cf_server* S, Req& r) {
     // second field array; a larger one goes in parts, with the lists in the place
     // of its ids, which are not read after the start.  Shapes are chosen for a full device.
     r.patches = nullptr;
+    r.patch_cells = 0;
     if (r.fused && !S->tiles_only) {
         auto set = cfi::cached_patches(p, S->precision);
         cfi::patch2d_sizes(r.st, p.nx, r.psizes);
@@ -268,7 +269,7 @@ std::string prepare(cf_server* S, Req& r) {
             const size_t room = (size_t)r.C * r.st.ncomp * p.ncell * (S->precision == CF_FP64 ? 8 : 4);
             if (r.parts || r.cells.size() * sizeof(cf::Patch2DCell) <= room) r.patches = set;
             for (int q = 0; q < 2; ++q)
-                if (r.pshape[q] >= 0) r.live_cells[q] = set->lists[q][r.pshape[q]].live_cells;
+                if (r.pshape[q] >= 0) r.patch_cells += used[q] * set->lists[q][r.pshape[q]].live_cells;
             // parts take a launch of at least a tick
             for (int q = 0; q < 2; ++q)
                 if (r.pshape[q] >= 0 && r.parts && set->lists[q][r.pshape[q]].parts > 1 &&
@@ -1194,7 +1195,7 @@ static cf_status report(cf_server* S, const std::shared_ptr<Req>& r, int* state,
         tim.variant = r->variant >= 0 ? r->variant : r->v3;   // fused 2D tile or fused 3D band shape
         if (r->patches) {
             tim.launch_steps = S->kh;
-            std::copy(r->live_cells, r->live_cells + 2, tim.live_cells);
+            tim.patch_cells = r->patch_cells;
         }
         cf_opts o = r->opts;
         const bool ok = cfi::fill_result(*r->prob, r->chans, r->acc, {}, o, (r->t_done - r->t_admit) * 1e3, tim,

@@ -108,7 +108,7 @@ struct StencilTiming {
     int variant = -1;
     int steps_run = -1;     // time steps run (-1: all of opts.n_steps)
     int launch_steps = 0;   // 2D patch kernel: steps of a launch (0: not used),
-    double live_cells[2] = {0, 0};   // and cells it advances per channel and polarization slot
+    double patch_cells = 0;   // and cells it advances in a step, over all channels
 };
 
 // Time-convergence stop: every `every` steps the partial force F(T') is

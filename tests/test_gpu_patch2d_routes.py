@@ -1,0 +1,45 @@
+"""Which calls the 2D patch kernel takes and what it reports of them: channel
+waves of one polarization, batches of many small problems, grids in parts by
+their number of channels, served requests beside others."""
+import numpy as np
+import pytest
+
+from casimir_inputs.geometry import PEC, Box, Workload, rasterize
+
+pytestmark = pytest.mark.gpu
+
+BIG = 1e30
+RUN = dict(sigma=0.9, courant=0.5, kernel="general")
+
+
+@pytest.fixture(scope="module")
+def cf():
+    import torch
+    assert torch.cuda.is_available()
+    import paper_0906_5170_amd as cf
+    cf.load()
+    return cf
+
+
+def vacuum(nx, ny, bc, pol, s_hi=None, n_harm=3, prims=()):
+    return Workload(name="route", ndim=2, shape=(nx, ny, 1), res=8.0, bc=bc, pml_cells=(0, 0, 0), eps=[1.0, PEC],
+                    mu=[1.0, 1.0], comp_ids=rasterize((nx, ny, 1), list(prims)), s_lo=(3, 0 if s_hi else 3, 0),
+                    s_hi=s_hi or (9, 9, 1), n_harm=n_harm, force_axis=0, sigma=0.9, courant=0.5, n_steps=60, pol=pol,
+                    kernel="general")
+
+
+def tiled(r, precision):
+    """Whether the tiles advanced a 2D result (8 steps a launch at most, 4 in FP64)."""
+    return r["fused"] and r["tile_halo"] <= (8 if precision == "fp32" else 4)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_waves_of_one_polarization(cf, precision):
+    """Without a conductor every cell is in a patch: the cells advanced are all
+    cells, whatever polarizations a wave of channels holds."""
+    wl = vacuum(24, 36, ("periodic", "periodic", "periodic"), "TM+TE")
+    p = cf.Problem.from_workload(wl)
+    o = dict(RUN, n_steps=60, pol=wl.pol, precision=precision)
+    for kw in ({}, dict(max_resident=5), dict(max_resident=3)):
+        r = p.solve(**o, **kw)
+        assert not tiled(r, precision) and r["advanced_cell_updates"] == r["cell_updates"], kw
