@@ -2549,30 +2549,52 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
                                     false);
         }
     }
-    for (int q = 0; q < 2; ++q) {
-        for (int sl : q == 0 ? B.tm : B.te) {
-            const int i = B.dev[sl].inst;
-            if (!psets[i]) {
-                tiles[q].push_back(sl);
-                continue;
+    auto make_groups = [&]() {
+        for (int q = 0; q < 2; ++q) {
+            groups[q].clear();
+            tiles[q].clear();
+            items[q].clear();
+            for (int sl : q == 0 ? B.tm : B.te) {
+                const int i = B.dev[sl].inst;
+                if (!psets[i]) {
+                    tiles[q].push_back(sl);
+                    continue;
+                }
+                const int v = pshapes[i][q];
+                const cf::Patch2DList& l = psets[i]->lists[q][v];
+                PatchGroup& gr = groups[q].try_emplace({l.steps, v}, PatchGroup{v, 0, l.steps, {}, 0, 0}).first->second;
+                gr.n = std::max(gr.n, l.n);
+                gr.slots.emplace_back(-(double)l.n, sl);
             }
-            const int v = pshapes[i][q];
-            const cf::Patch2DList& l = psets[i]->lists[q][v];
-            PatchGroup& gr = groups[q].try_emplace({l.steps, v}, PatchGroup{v, 0, l.steps, {}, 0, 0}).first->second;
-            gr.n = std::max(gr.n, l.n);
-            gr.slots.emplace_back(-(double)l.n, sl);
+            for (auto& kv : groups[q]) {
+                PatchGroup& gr = kv.second;
+                std::stable_sort(gr.slots.begin(), gr.slots.end(),
+                                 [](const auto& a, const auto& b) { return a.first < b.first; });
+                gr.at = items[q].size();
+                for (const auto& c : gr.slots) {
+                    const int i = B.dev[c.second].inst;
+                    const auto it = patch2d_items(*psets[i], pshapes[i], q, &c.second, 1);
+                    items[q].insert(items[q].end(), it.begin(), it.end());
+                }
+                gr.count = (int)(items[q].size() - gr.at);
+            }
         }
-        for (auto& kv : groups[q]) {
-            PatchGroup& gr = kv.second;
-            std::stable_sort(gr.slots.begin(), gr.slots.end(),
-                             [](const auto& a, const auto& b) { return a.first < b.first; });
-            gr.at = items[q].size();
-            for (const auto& c : gr.slots) {
-                const int i = B.dev[c.second].inst;
-                const auto it = patch2d_items(*psets[i], pshapes[i], q, &c.second, 1);
-                items[q].insert(items[q].end(), it.begin(), it.end());
-            }
-            gr.count = (int)(items[q].size() - gr.at);
+    };
+    make_groups();
+    // Many problems of few channels each (strips of one polarization) have more
+    // heads and items than their tiles' work items leave room for: tiles then.
+    const size_t region = B.work_items * sizeof(cf::WorkItem);
+    if (!groups[0].empty() || !groups[1].empty()) {
+        size_t work[2] = {0, 0};
+        for (int v : B.variants_ok)
+            for (int q = 0; q < 2; ++q)
+                if (!tiles[q].empty()) work[q] = std::max(work[q], work_for(v, tiles[q]).size());
+        const size_t tm = work[0] * sizeof(cf::WorkItem) + items[0].size() * sizeof(int);
+        const size_t te = work[1] * sizeof(cf::WorkItem) + items[1].size() * sizeof(int);
+        if (tm > region || align_up(te, 16) + 16 + n * sizeof(heads[0]) > region) {
+            psets.assign(n, nullptr);
+            cells.clear();
+            make_groups();
         }
     }
     const bool any_patch = !groups[0].empty() || !groups[1].empty();
@@ -2652,7 +2674,6 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
         const int nw_te = (int)keepW.back().size();
         BSTEP(up(L.work + B.work_items * sizeof(cf::WorkItem), keepW.back().data(), nw_te * sizeof(cf::WorkItem)));
         // the items, and behind the TE ones the heads
-        const size_t region = B.work_items * sizeof(cf::WorkItem);
         const size_t pat[2] = {L.work + nw_tm * sizeof(cf::WorkItem), L.work + region + nw_te * sizeof(cf::WorkItem)};
         const size_t heads_at = align_up(pat[1] + items[1].size() * sizeof(int), 16);
         if (any_patch) {

@@ -43,3 +43,17 @@ def test_waves_of_one_polarization(cf, precision):
     for kw in ({}, dict(max_resident=5), dict(max_resident=3)):
         r = p.solve(**o, **kw)
         assert not tiled(r, precision) and r["advanced_cell_updates"] == r["cell_updates"], kw
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("n", [8, 72])
+def test_batch_of_strips(cf, n, precision):
+    """Strips of six channels each: the patch kernel's heads and items of many
+    of them need more room than their tiles' work items have."""
+    wl = vacuum(20, 8, ("pec", "periodic", "periodic"), "TE", s_hi=(9, 8, 1), n_harm=1)
+    p = cf.Problem.from_workload(wl)
+    o = dict(RUN, n_steps=60, pol="TE", precision=precision)
+    ref = p.solve(split=True, **o)
+    for r in cf.batch_solve([p] * n, **o):
+        assert r["n_channels"] == 6 and tiled(r, precision) == (n > 40)
+        assert np.array_equal(r["per_channel"], ref["per_channel"])
