@@ -639,7 +639,8 @@ int patch2d_shapes(Patch2DShape* out, int max) {
 
 template <typename T>
 size_t patch2d_lds(const Patch2DShape& q, int n, const Patch2DSizes& z) {
-    return (size_t)p2_lds<T>(p2_stride_of<T>(q), n, z).total;
+    // the static part: s_box, once per polarization a kernel holds
+    return (size_t)p2_lds<T>(p2_stride_of<T>(q), n, z).total + 2 * 8 * sizeof(int);
 }
 
 template <typename T>

@@ -65,7 +65,7 @@ struct Patch2DSizes {
     int box, samples, points;
 };
 
-// LDS bytes of a block for n patches.
+// LDS bytes of a block for n patches, dynamic and static.
 template <typename T>
 size_t patch2d_lds(const Patch2DShape& q, int n, const Patch2DSizes& z);
 
