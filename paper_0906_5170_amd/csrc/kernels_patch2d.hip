@@ -75,6 +75,35 @@ __device__ __forceinline__ void p2_col(T* e, T (&v)[N]) {
     p2_move<X::col_rest - X::col_full, X::col_full, N, PUT>(e, v);
 }
 
+// Row of a patch in memory, in accesses of 16 bytes (aligned as its values are).
+// With an access per value, CX values apart in neighbouring threads, every line
+// was read and written several times over: a launch of 16 steps of 260 x 200
+// cells in two parts (8 x 4 cells, 16 waves, FP32) took 114 us, 44 of them the
+// steps; it takes 63.
+template <int C, typename T>
+using P2Mem = T __attribute__((ext_vector_type(C), aligned(sizeof(T))));
+template <int I, typename P, typename T, int N>
+__device__ __forceinline__ void p2_load_row(P p, T (&v)[N]) {
+    if constexpr (I < N) {
+        constexpr int left = N - I, V = 16 / (int)sizeof(T), C = V >= 4 && left >= 4 ? 4 : left >= 2 ? 2 : 1;
+        const P2Mem<C, T> x = *reinterpret_cast<yee::gmem<const P2Mem<C, T>>>(p + I);
+#pragma unroll
+        for (int k = 0; k < C; ++k) v[I + k] = x[k];
+        p2_load_row<I + C>(p, v);
+    }
+}
+template <int I, typename P, typename T, int N>
+__device__ __forceinline__ void p2_store_row(P p, const T (&v)[N]) {
+    if constexpr (I < N) {
+        constexpr int left = N - I, V = 16 / (int)sizeof(T), C = V >= 4 && left >= 4 ? 4 : left >= 2 ? 2 : 1;
+        P2Mem<C, T> x;
+#pragma unroll
+        for (int k = 0; k < C; ++k) x[k] = v[I + k];
+        *reinterpret_cast<yee::gmem<P2Mem<C, T>>>(p + I) = x;
+        p2_store_row<I + C>(p, v);
+    }
+}
+
 struct P2Lds {
     int xe, xh, stage, sw, sb, so, total;
 };
@@ -340,6 +369,7 @@ __device__ __forceinline__ void p2_advance(const ChanDev& d, const InstDev& g, c
     }
     const bool act = (pc.flags & kPatchUsed) != 0;
     const int x0 = pc.x0, y0 = pc.y0;
+    const bool whole = act && x0 + CX <= nx && y0 + B <= ny;   // no cell beyond the grid
     T* const er = XE + (act ? pc.right : n) * S;   // E column of the patch to the right
     T* const eu = XE + (act ? pc.up : n) * S;      // E row of the patch above
     T* const hl = XH + (act ? pc.left : n) * S;    // H column of the patch to the left
@@ -369,6 +399,38 @@ __device__ __forceinline__ void p2_advance(const ChanDev& d, const InstDev& g, c
         const auto F2 = F1 + g.ncell;
         const int kick = (int)((d.src_off - d.field_off) / g.ncell);   // slot of the kicked component
         const auto I0 = as_global(g.ids[C0]), I1 = as_global(g.ids[C1]), I2 = as_global(g.ids[C2]);
+        if (whole && !start) {
+#pragma unroll
+            for (int r = 0; r < B; ++r) {
+                const uint32_t c = (uint32_t)((y0 + r) * nx + x0);
+                p2_load_row<0>(F0 + c, f0[r]);
+                p2_load_row<0>(F1 + c, f1[r]);
+                p2_load_row<0>(F2 + c, f2[r]);
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < B; ++r) {
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < CX; ++j) {
+                    const int x = x0 + j, y = y0 + r;
+                    const bool in = act && x < nx && y < ny;
+                    const uint32_t c = in ? (uint32_t)(y * nx + x) : 0u;
+                    if (start) {
+                        const bool at = in && x >= kx0 && x <= kx1 && y >= ky0 && y <= ky1;
+                        const T v = at ? stage[(y - ky0) * kbw + x - kx0] : T(0);
+                        f0[r][j] = kick == 0 ? v : T(0);
+                        f1[r][j] = kick == 1 ? v : T(0);
+                        f2[r][j] = kick == 2 ? v : T(0);
+                    } else {
+                        const T v0 = F0[c], v1 = F1[c], v2 = F2[c];
+                        f0[r][j] = in ? v0 : T(0);
+                        f1[r][j] = in ? v1 : T(0);
+                        f2[r][j] = in ? v2 : T(0);
+                    }
+                }
+            }
+        }
 #pragma unroll
         for (int r = 0; r < B; ++r) {
             __builtin_amdgcn_sched_barrier(0);
@@ -377,18 +439,6 @@ __device__ __forceinline__ void p2_advance(const ChanDev& d, const InstDev& g, c
                 const int x = x0 + j, y = y0 + r, k = r * CX + j;
                 const bool in = act && x < nx && y < ny;
                 const uint32_t c = in ? (uint32_t)(y * nx + x) : 0u;
-                if (start) {
-                    const bool at = in && x >= kx0 && x <= kx1 && y >= ky0 && y <= ky1;
-                    const T v = at ? stage[(y - ky0) * kbw + x - kx0] : T(0);
-                    f0[r][j] = kick == 0 ? v : T(0);
-                    f1[r][j] = kick == 1 ? v : T(0);
-                    f2[r][j] = kick == 2 ? v : T(0);
-                } else {
-                    const T v0 = F0[c], v1 = F1[c], v2 = F2[c];
-                    f0[r][j] = in ? v0 : T(0);
-                    f1[r][j] = in ? v1 : T(0);
-                    f2[r][j] = in ? v2 : T(0);
-                }
                 if constexpr (COEF == kRegE) {
                     ke[0][k % KE] = masked(be, pc.live[0], k);
                     if constexpr (!TM) ke[NE - 1][k % KE] = masked(be, pc.live[1], k);
@@ -541,11 +591,22 @@ __device__ __forceinline__ void p2_advance(const ChanDev& d, const InstDev& g, c
     const auto F0 = as_global(static_cast<T*>(dst ? g.fb : g.fa)) + d.field_off;
     const auto F1 = F0 + g.ncell;
     const auto F2 = F1 + g.ncell;
+    if (!(pc.flags & kPatchStored)) return;
+    if (whole) {
+#pragma unroll
+        for (int r = 0; r < B; ++r) {
+            const uint32_t c = (uint32_t)((y0 + r) * nx + x0);
+            p2_store_row<0>(F0 + c, f0[r]);
+            p2_store_row<0>(F1 + c, f1[r]);
+            p2_store_row<0>(F2 + c, f2[r]);
+        }
+        return;
+    }
 #pragma unroll
     for (int r = 0; r < B; ++r)
 #pragma unroll
         for (int j = 0; j < CX; ++j)
-            if ((pc.flags & kPatchStored) && x0 + j < nx && y0 + r < ny) {
+            if (x0 + j < nx && y0 + r < ny) {
                 const uint32_t c = (uint32_t)((y0 + r) * nx + x0 + j);
                 F0[c] = f0[r][j];
                 F1[c] = f1[r][j];

@@ -57,3 +57,31 @@ def test_batch_of_strips(cf, n, precision):
     for r in cf.batch_solve([p] * n, **o):
         assert r["n_channels"] == 6 and tiled(r, precision) == (n > 40)
         assert np.array_equal(r["per_channel"], ref["per_channel"])
+
+
+def best_ms(p, o, **kw):
+    return min(p.solve(**o, **kw)["device_ms"] for _ in range(4))
+
+
+def check_speed(cf, wl, slack, n_steps=200):
+    """The route left to the library is not slower than the tiles' best shape."""
+    p = cf.Problem.from_workload(wl)
+    o = dict(RUN, n_steps=n_steps, pol=wl.pol, precision="fp32")
+    tiles = []
+    for v in range(1, 20):
+        r = p.solve(**o, tile_variant=v)
+        if r["tile_variant"] == v:
+            tiles.append(best_ms(p, o, tile_variant=v))
+    mine = best_ms(p, o)
+    print(wl.shape, wl.n_harm, f"{mine:.3f} ms, tiles {min(tiles):.3f}", flush=True)
+    assert len(tiles) > 2 and mine <= slack * min(tiles), (mine, tiles)
+
+
+WALLS = ("pec", "pec", "periodic")
+
+
+@pytest.mark.parametrize("shape", [(300, 300), (440, 330)])
+def test_speed_of_parts(cf, shape):
+    """Large grids in parts, more channels than the device takes at once."""
+    prims = [Box((-BIG, -BIG, -BIG), (BIG, 1, BIG), 1)]
+    check_speed(cf, vacuum(*shape, WALLS, "TM+TE", n_harm=20, prims=prims).replace(s_hi=(43, 43, 1)), 1.1)
