@@ -251,15 +251,25 @@ static size_t patch2d_bytes(const cf::Patch2DSet& set, const PatchShapes& shape)
 bool patch2d_pick(const cf::Patch2DSet& set, int precision, const int used[2], const int together[2],
                   const cf::Patch2DSizes& z, PatchShapes& shape) {
     const size_t lim = cf::device_lds_limit();
-    for (int q = 0; q < 2; ++q) {
-        shape[q] = used[q] > 0 ? cf::patch2d_choose(set, precision, q, together[q], z, lim) : -1;
-        if (used[q] > 0 && shape[q] < 0) return false;
+    // lists of parts lie in the ids' place: half of it for each polarization, or
+    // what one leaves the other
+    const size_t room = (size_t)cf::kNumComp * set.nx * set.ny, n = room / sizeof(cf::Patch2DCell);
+    for (size_t share : {used[0] > 0 && used[1] > 0 ? n / 2 : n, n}) {
+        bool ok = true;
+        for (int q = 0; q < 2; ++q) {
+            shape[q] = used[q] > 0 ? cf::patch2d_choose(set, precision, q, together[q], z, lim, together[1 - q], share) : -1;
+            ok = ok && (used[q] == 0 || shape[q] >= 0);
+        }
+        if (ok && (!patch2d_in_parts(set, shape) || patch2d_bytes(set, shape) <= room)) {
+            // and no shape that reads the ids
+            for (int q = 0; q < 2; ++q)
+                if (patch2d_in_parts(set, shape) && shape[q] >= 0 &&
+                    (set.shape(shape[q]).coef == cf::kRegAll || !set.masks))
+                    return false;
+            return true;
+        }
     }
-    if (!patch2d_in_parts(set, shape)) return true;
-    // lists in the ids' place: no shape that reads the ids, and room for them
-    for (int q = 0; q < 2; ++q)
-        if (shape[q] >= 0 && (set.shapes[shape[q]].coef == cf::kRegAll || !set.masks)) return false;
-    return patch2d_bytes(set, shape) <= (size_t)cf::kNumComp * set.nx * set.ny;
+    return false;
 }
 
 bool patch2d_in_parts(const cf::Patch2DSet& set, const PatchShapes& shape) {
@@ -271,7 +281,7 @@ bool patch2d_in_parts(const cf::Patch2DSet& set, const PatchShapes& shape) {
 bool patch2d_own_start(const cf::Patch2DSet& set, const PatchShapes& shape, int precision) {
     for (int q = 0; q < 2; ++q) {
         if (shape[q] < 0) continue;
-        const cf::Patch2DShape& s = set.shapes[shape[q]];
+        const cf::Patch2DShape& s = set.shape(shape[q]);
         if (set.lists[q][shape[q]].parts != 1 || !cf::patch2d_small(s.cx * s.b, precision == CF_FP64 ? 8 : 4))
             return false;
     }
@@ -1950,7 +1960,7 @@ cf_status run_solve(const cf::Problem& p, const cf_opts& o, const Staged& st, co
                 const size_t blocks = pitems[q]->size() + (mixed ? pitems[1]->size() : 0);
                 const bool take = smp.begin(ls);
                 const hipError_t e = cf::launch_patch2d<T>(
-                    sh[q], mixed ? 0 : q == 0 ? CF_POL_TM : CF_POL_TE, dch, ditems[q], (int)blocks, dinst, heads, longest,
+                    patches->kernel(sh[q]), mixed ? 0 : q == 0 ? CF_POL_TM : CF_POL_TE, dch, ditems[q], (int)blocks, dinst, heads, longest,
                     psizes, ks, m, parity[q], l.parts > 1 ? parity[q] ^ 1 : parity[q],
                     split_pol && q == 1 ? side.s[0] : ls);
                 if (l.parts > 1) parity[q] ^= 1;
@@ -2560,8 +2570,8 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
                     tiles[q].push_back(sl);
                     continue;
                 }
-                const int v = pshapes[i][q];
-                const cf::Patch2DList& l = psets[i]->lists[q][v];
+                const cf::Patch2DList& l = psets[i]->lists[q][pshapes[i][q]];
+                const int v = psets[i]->kernel(pshapes[i][q]);
                 PatchGroup& gr = groups[q].try_emplace({l.steps, v}, PatchGroup{v, 0, l.steps, {}, 0, 0}).first->second;
                 gr.n = std::max(gr.n, l.n);
                 gr.slots.emplace_back(-(double)l.n, sl);

@@ -11,11 +11,14 @@ namespace cf {
 namespace {
 
 // Steps of a launch of a grid in parts, and so the width of their rims: a
-// longer launch loads and stores the fields less often but computes wider rims.
-// Pistons of 34000 and 38000 live cells in two parts (FP32, 448 channels, 900
-// steps): 12.6 and 17.3 ms with at most 32 steps, 10.8 and 11.9 with 48, 9.9
-// and 10.4 with 64 and 96 (about 23 and 25 on tiles).
-constexpr int kPartSteps[] = {96, 64, 48, 32, 24, 16, 8};
+// longer launch loads and stores the fields less often but computes wider rims,
+// and a smaller shape steps faster but needs more parts.  Which is best depends
+// on the channels: few leave compute units idle, so a step's latency counts;
+// many fill the device, so all parts' work counts (see patch2d_choose).
+// Fewer than 16 steps do not pay for a launch (200 x 90 cells in FP64, 16
+// channels: 5.0 us a step with 8, 3.8 on tiles).
+constexpr int kPartSteps[] = {96, 64, 48, 32, 24, 16};
+constexpr int kNumPartSteps = 6;
 
 // Patches a block of the shape may hold (its last wave takes the surface sums).
 int most_patches(const Patch2DShape& q) { return 256 * q.mw - 64; }
@@ -30,18 +33,26 @@ double step_cycles(const Patch2DShape& q, int k, int waves) {
     return std::max(std::ceil(waves / 4.0) * instr * 4, 700 + instr * 4.5);
 }
 
-// Estimated cycles of a compute unit per channel and step: of a grid in parts
-// (with its share of the copy rate, 4.7 TB/s: 7.6 bytes a cycle, for the loads
-// and stores of a launch), and of the tiles (400 x 200 piston: 14000 live cells
-// in 6.2 us, FP32).
-double parts_cost(const Patch2DShape& q, int k, const Patch2DList& l, int precision) {
-    const double value = precision == CF_FP64 ? 8.0 : 4.0;
-    const double bytes = 3 * value * (l.size() * (double)(q.cx * q.b) + l.live_cells);
-    return l.parts * step_cycles(q, k, (l.n + 63) / 64 + 1) + bytes / 7.6 / l.steps;
+// Estimated cycles of a block in parts per step, with its share of a launch: the
+// longer of a latency of 26 us (launch, tables, first loads) and, with `fill` of
+// the compute units at work, its share of the copy rate, 4.7 TB/s or 7.6 bytes a
+// cycle, for the loads and stores of its field values.  No other block's steps
+// overlap with them: a block of parts fills its compute unit.  Measured, 16
+// channels of 260 x 200 cells, FP32: 8 x 4 cells 30 us a launch and 2.6 us a step,
+// 5 x 5 24 and 2.2, 5 x 4 (kRegE) 23 and 2.1, kMaskH 8 x 4 32 and 2.7, 5 x 5 27 and
+// 2.2; FP64 4 x 3 31 and 1.1.
+double part_cycles(const Patch2DShape& q, int k, int waves, const Patch2DList& l, int precision, double fill) {
+    const double value = precision == CF_FP64 ? 8.0 : 4.0, scale = q.coef == kRegE ? 1.2 : q.coef == kMaskH ? 0.7 : 0.8;
+    const double bytes = 3 * value * (l.n * (double)(q.cx * q.b) + l.live_cells / l.parts);
+    return scale * step_cycles(q, k, waves) + std::max(62000.0, fill * bytes / 7.6) / l.steps;
 }
-double tiles_cost(double cells, int precision) { return cells * (precision == CF_FP64 ? 2.2 : 1.05); }
+
+// And of the tiles, per live cell with the device full (FP32 640 channels:
+// 260 x 200 cells 0.86, 300 x 300 0.74, 440 x 330 0.67; FP64 2.6 to 3.4).
+double tiles_cost(double cells, int precision) { return cells * (precision == CF_FP64 ? 2.6 : 0.7); }
 
 constexpr int kCUs = 256;
+constexpr int kMaxParts = 16;
 
 // Whether an id's material lets the field change.
 bool holds_field(const Problem& p, const std::vector<double>& v, int id) {
@@ -97,6 +108,7 @@ struct PatchGrid {
     const Patch2DSet& s;
     int cx, b, LX, LY;
     std::vector<uint8_t> on;
+    std::vector<int> loads[2];                        // patches per column and per row
     PatchGrid(const Patch2DSet& s_, const Runs& runs, int cx_, int b_)
         : s(s_), cx(cx_), b(b_), LX((s_.nx + cx_ - 1) / cx_), LY((s_.ny + b_ - 1) / b_) {
         on.assign((size_t)LX * LY, 0);
@@ -157,6 +169,15 @@ struct PatchGrid {
             }
         return n;
     }
+    void count_loads() {
+        loads[0].assign(LX, 0);
+        loads[1].assign(LY, 0);
+        for (int j = 0; j < LY; ++j)
+            for (int i = 0; i < LX; ++i) {
+                loads[0][i] += on[(size_t)j * LX + i];
+                loads[1][j] += on[(size_t)j * LX + i];
+            }
+    }
     double cells() const {
         double n = 0;
         for (int j = 0; j < LY; ++j)
@@ -174,14 +195,12 @@ struct PatchGrid {
     }
     // Parts of at most `most` patches, cut across x or y where the fewest blocks
     // (then patches) result; a rim of at least `steps` cells beyond a cut.  The
-    // measured points (box lo .. hi) stay inside one part.
+    // measured points (box lo .. hi) stay inside one part.  After count_loads.
     Patch2DList parts(int most, int steps, const int lo[2], const int hi[2]) const {
         Patch2DList best;
         for (int axis = 0; axis < 2; ++axis) {
             const int N = axis == 0 ? LX : LY, w = axis == 0 ? cx : b, rim = (steps + w - 1) / w;
-            std::vector<int> load(N, 0);
-            for (int j = 0; j < LY; ++j)
-                for (int i = 0; i < LX; ++i) load[axis == 0 ? i : j] += on[(size_t)j * LX + i];
+            const std::vector<int>& load = loads[axis];
             const int total = std::accumulate(load.begin(), load.end(), 0);
             const int s0 = lo[axis] / w, s1 = hi[axis] / w;
             const bool per = axis == 0 ? s.perx : s.pery;
@@ -221,10 +240,8 @@ struct PatchGrid {
                 break;
             }
         }
-        if (best.parts) best.live_cells = cells();
         return best;
     }
-    static constexpr int kMaxParts = 16;
 };
 
 }  // namespace
@@ -275,7 +292,7 @@ std::shared_ptr<const Patch2DSet> patch2d_set(const Problem& p, int precision) {
         high_id[id] = uh.two && !(holds_field(p, p.mu, id) && p.mu[id] == p.mu[uh.id]);
     }
     for (int k = 0; k < 2; ++k) {
-        s.lists[k].resize(n);
+        s.lists[k].resize(n * (1 + kNumPartSteps));
         if (!fits) continue;
         auto bits = [&](const uint8_t* of, int first, int count) {
             std::vector<uint8_t> out(p.ncell, 0);
@@ -295,35 +312,36 @@ std::shared_ptr<const Patch2DSet> patch2d_set(const Problem& p, int precision) {
             covered = covered || s.lists[k][v].parts > 0;
         }
         if (covered || hi[0] < 0) continue;
-        // too large for one compute unit: parts, with the shape of the most cells,
-        // unless the tiles are estimated to take less
+        // too large for one compute unit: parts, of the shapes that hold their E
+        // values in masks, unless the tiles are estimated to take less
+        double best = 0, live = 0;
         for (int v = 0; v < n; ++v) {
             const Patch2DShape& q = s.shapes[v];
-            if ((q.coef != kMaskB && q.coef != kMaskH) || !holds(q)) continue;
-            const PatchGrid grid(s, runs, q.cx, q.b);
-            Patch2DList& l = s.lists[k][v];
-            double best = 0;
-            for (int steps : kPartSteps) {
-                Patch2DList t = grid.parts(most_patches(q), steps, lo, hi);
-                if (!t.parts) continue;
-                const double cost = parts_cost(q, k, t, precision);
-                if (l.parts && cost >= best) continue;
-                best = cost;
-                l = std::move(t);
+            if (q.coef == kRegAll || !s.masks || !holds(q)) continue;
+            PatchGrid grid(s, runs, q.cx, q.b);
+            grid.count_loads();
+            live = grid.cells();
+            for (int t = 0; t < kNumPartSteps; ++t) {
+                Patch2DList& l = s.lists[k][n * (1 + t) + v];
+                l = grid.parts(most_patches(q), kPartSteps[t], lo, hi);
+                if (!l.parts) continue;
+                l.live_cells = live;
+                const double cost = l.parts * part_cycles(q, k, (l.n + 63) / 64 + 1, l, precision, 1);
+                if (best == 0 || cost < best) best = cost;
             }
-            if (l.parts && best > tiles_cost(l.live_cells, precision)) l = Patch2DList();
-            if (l.parts) break;
         }
+        if (best > tiles_cost(live, precision))
+            for (Patch2DList& l : s.lists[k]) l = Patch2DList();
     }
     return set;
 }
 
-const std::vector<Patch2DCell>& patch2d_cells(const Patch2DSet& s, int k, int shape) {
+const std::vector<Patch2DCell>& patch2d_cells(const Patch2DSet& s, int k, int entry) {
     std::lock_guard<std::mutex> lk(s.mu);
-    std::vector<Patch2DCell>& out = s.cells[{k, shape}];
+    std::vector<Patch2DCell>& out = s.cells[{k, entry}];
     if (!out.empty()) return out;
-    const Patch2DShape& q = s.shapes[shape];
-    const Patch2DList& l = s.lists[k][shape];
+    const Patch2DShape& q = s.shape(entry);
+    const Patch2DList& l = s.lists[k][entry];
     const PatchGrid g(s, live_runs(s.live[k], s.nx, s.ny), q.cx, q.b);
     if (l.parts == 1) {
         g.append(s.live[k], s.high[k], 0, g.LX, 0, g.LY, 0, g.LX, 0, g.LY, l.n, out);
@@ -339,22 +357,24 @@ const std::vector<Patch2DCell>& patch2d_cells(const Patch2DSet& s, int k, int sh
     return out;
 }
 
-int patch2d_choose(const Patch2DSet& s, int precision, int k, int nslots, const Patch2DSizes& z, size_t lds_limit) {
+int patch2d_choose(const Patch2DSet& s, int precision, int k, int nslots, const Patch2DSizes& z, size_t lds_limit,
+                   int others, size_t room) {
     int best = -1;
     double best_cost = 0;
     // the surface wave addresses the box by 16-bit offsets
     if (z.box > 65535) return -1;
-    for (int v = 0; v < (int)s.shapes.size(); ++v) {
-        const Patch2DShape& q = s.shapes[v];
+    for (int v = 0; v < (int)s.lists[k].size(); ++v) {
+        const Patch2DShape& q = s.shape(v);
         const Patch2DList& l = s.lists[k][v];
-        const int n = l.n, waves = (n + 63) / 64 + 1, nblocks = nslots * l.parts;
-        if (l.parts == 0) continue;
+        if (l.parts == 0 || (l.parts > 1 && l.size() > room)) continue;
+        const int n = l.n, waves = (n + 63) / 64 + 1, nblocks = (nslots + (l.parts > 1 ? others : 0)) * l.parts;
         const size_t lds = precision == CF_FP64 ? patch2d_lds<double>(q, n, z) : patch2d_lds<float>(q, n, z);
         if (lds > lds_limit) continue;
         const int per_cu = std::max(1, std::min(4 * q.mw / waves, (int)(lds_limit / std::max<size_t>(lds, 1))));
         const int c = std::min(per_cu, (nblocks + kCUs - 1) / kCUs);
         const int rounds = (nblocks + kCUs * c - 1) / (kCUs * c);
-        const double cost = rounds * step_cycles(q, k, c * waves);
+        const double cost = rounds * (l.parts > 1 ? part_cycles(q, k, c * waves, l, precision, std::min(1.0, (double)nblocks / kCUs))
+                                                  : step_cycles(q, k, c * waves));
         if (best < 0 || cost < best_cost) {
             best = v;
             best_cost = cost;

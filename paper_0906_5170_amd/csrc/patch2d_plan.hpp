@@ -14,7 +14,7 @@
 
 namespace cf {
 
-// A polarization's lists for one shape: `parts` lists of n patches each, at
+// A polarization's lists for one entry: `parts` lists of n patches each, at
 // most `steps` steps per launch (0: any number, one part), cut across `axis`
 // before the patch columns (rows) of `cut`.
 struct Patch2DList {
@@ -26,7 +26,12 @@ struct Patch2DList {
 
 struct Patch2DSet {
     std::vector<Patch2DShape> shapes;
-    std::vector<Patch2DList> lists[2];                // per polarization (0 TM, 1 TE) and shape (parts == 0: not usable)
+    // per polarization (0 TM, 1 TE) and entry (parts == 0: not usable): every shape
+    // with whole channels, then, for grids beyond a compute unit, every shape with
+    // parts of each number of steps
+    std::vector<Patch2DList> lists[2];
+    const Patch2DShape& shape(int entry) const { return shapes[entry % shapes.size()]; }
+    int kernel(int entry) const { return entry % (int)shapes.size(); }   // shape index of its launches
     int id_e = kNullId, id_h = kNullId;               // an E and an H material with a field
     int id_h2 = kNullId;                              // and the other one where H has two
     bool masks = false;                               // E components share one material
@@ -35,22 +40,24 @@ struct Patch2DSet {
     // per polarization and cell: which E components can change (bit 0 E_z or
     // E_x, bit 1 E_y), which H components are of the second material
     std::vector<uint8_t> live[2], high[2];
-    // the patches of the lists in use so far, by (polarization, shape)
+    // the patches of the lists in use so far, by (polarization, entry)
     mutable std::mutex mu;
     mutable std::map<std::pair<int, int>, std::vector<Patch2DCell>> cells;
 };
 
-// The lists of a fusable 2D problem for every shape of the precision (sizes and
+// The lists of a fusable 2D problem for every entry of the precision (sizes and
 // cuts), and the patches of one of them, formed on first use.
 std::shared_ptr<const Patch2DSet> patch2d_set(const Problem& p, int precision);
-const std::vector<Patch2DCell>& patch2d_cells(const Patch2DSet& s, int k, int shape);
+const std::vector<Patch2DCell>& patch2d_cells(const Patch2DSet& s, int k, int entry);
 
-// Shape with the least estimated time for nslots channels of polarization
-// slot k, or -1 when none covers the problem.
-int patch2d_choose(const Patch2DSet& s, int precision, int k, int nslots, const Patch2DSizes& z, size_t lds_limit);
+// Entry with the least estimated time for nslots channels of polarization slot k,
+// or -1 when none covers the problem; parts share the device with `others`
+// channels of the other polarization and have room for `room` patches.
+int patch2d_choose(const Patch2DSet& s, int precision, int k, int nslots, const Patch2DSizes& z, size_t lds_limit,
+                   int others = 0, size_t room = SIZE_MAX);
 
-// The small shape with the least time for a launch of whole channels of both
-// polarizations (nslots in all) that the device takes at once, or -1.
+// The small shape (whole channels) with the least time for a launch of both
+// polarizations (nslots channels in all) that the device takes at once, or -1.
 int patch2d_choose_mixed(const Patch2DSet& s, int precision, int nslots, const Patch2DSizes& z, size_t lds_limit);
 
 }  // namespace cf

@@ -540,7 +540,7 @@ hipError_t rebuild_group(cf_server* S) {
             size_t idx[2] = {0, 0};
             for (int q = 0; q < 2; ++q) {
                 if (r.pshape[q] < 0) continue;
-                const int v = r.pshape[q], pol = q == 0 ? CF_POL_TM : CF_POL_TE, n = heads.back().n[q];
+                const int v = r.patches->kernel(r.pshape[q]), pol = q == 0 ? CF_POL_TM : CF_POL_TE, n = heads.back().n[q];
                 // a launch of the shape whose LDS still fits with this request
                 size_t k = 0;
                 cf_server::Launch l;

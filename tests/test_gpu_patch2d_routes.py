@@ -85,3 +85,13 @@ def test_speed_of_parts(cf, shape):
     """Large grids in parts, more channels than the device takes at once."""
     prims = [Box((-BIG, -BIG, -BIG), (BIG, 1, BIG), 1)]
     check_speed(cf, vacuum(*shape, WALLS, "TM+TE", n_harm=20, prims=prims).replace(s_hi=(43, 43, 1)), 1.1)
+
+
+@pytest.mark.parametrize("n_harm,slack", [(1, 1.3), (2, 1.15), (4, 1.1)])
+@pytest.mark.parametrize("shape", [(260, 200), (300, 300)])
+def test_speed_of_parts_with_few_channels(cf, shape, n_harm, slack):
+    """16 channels a harmonic leave most compute units idle: the parts chosen
+    are those with the shortest step, not the least work.  (One harmonic: a
+    step of the smallest parts that fit is as long as the tiles' launches.)"""
+    prims = [Box((-BIG, -BIG, -BIG), (BIG, 1, BIG), 1)]
+    check_speed(cf, vacuum(*shape, WALLS, "TM+TE", n_harm=n_harm, prims=prims).replace(s_hi=(43, 43, 1)), slack, 600)
