@@ -65,12 +65,24 @@ bool holds_field(const Problem& p, const std::vector<double>& v, int id) {
 struct Uniform {
     bool single = true, all = true, two = false;
     int id = kNullId, second = kNullId;
+    bool used[256];                                   // the ids
 };
 Uniform uniform(const Problem& p, const std::vector<double>& v, std::initializer_list<int> comps) {
     bool used[256] = {};
-    for (int c : comps)
-        for (int64_t k = 0; k < p.ncell; ++k) used[p.ids[c][k]] = true;
+    for (int c : comps) {
+        const uint8_t* ids = p.ids[c].data();
+        uint64_t last = 0, word;
+        int64_t k = 0;
+        for (; k + 8 <= p.ncell; k += 8) {             // eight ids like the eight before them: seen
+            std::memcpy(&word, ids + k, 8);
+            if (word == last && k > 0) continue;
+            last = word;
+            for (int j = 0; j < 8; ++j) used[ids[k + j]] = true;
+        }
+        for (; k < p.ncell; ++k) used[ids[k]] = true;
+    }
     Uniform u;
+    std::copy(used, used + 256, u.used);
     bool more = false;
     for (int id = 0; id < 256; ++id) {
         if (!used[id]) continue;
@@ -88,17 +100,55 @@ Uniform uniform(const Problem& p, const std::vector<double>& v, std::initializer
     return u;
 }
 
+// Cells of component c whose id lets the field change.
+int64_t count_live(const Problem& p, int c) {
+    bool on[256];
+    for (int id = 0; id < 256; ++id) on[id] = holds_field(p, p.eps, id);
+    const uint8_t* ids = p.ids[c].data();
+    uint64_t last = 0, word;
+    int64_t n = 0, k = 0, of_last = 0;
+    for (; k + 8 <= p.ncell; k += 8) {
+        std::memcpy(&word, ids + k, 8);
+        if (word != last || k == 0) {
+            last = word;
+            of_last = 0;
+            for (int j = 0; j < 8; ++j) of_last += on[ids[k + j]];
+        }
+        n += of_last;
+    }
+    for (; k < p.ncell; ++k) n += on[ids[k]];
+    return n;
+}
+
 // Runs of live cells of every row: [begin, end) pairs of row y at runs[y].
 using Runs = std::vector<std::vector<int>>;
 Runs live_runs(const std::vector<uint8_t>& live, int nx, int ny) {
     Runs r(ny);
     for (int y = 0; y < ny; ++y) {
         const uint8_t* row = live.data() + (size_t)y * nx;
-        for (int x = 0; x < nx; ++x)
-            if ((row[x] != 0) != (x > 0 && row[x - 1] != 0)) r[y].push_back(x);
+        for (int x = 0; x < nx; ++x) {
+            // an end of a run at x, the next one after the values like it
+            if ((row[x] != 0) != (r[y].size() % 2 != 0)) r[y].push_back(x);
+            uint64_t word;
+            for (const uint64_t like = row[x] * 0x0101010101010101ull; x + 8 < nx; x += 8) {
+                std::memcpy(&word, row + x + 1, 8);
+                if (word != like) break;
+            }
+        }
         if (r[y].size() % 2) r[y].push_back(nx);
     }
     return r;
+}
+int64_t count_cells(const Runs& runs) {
+    int64_t n = 0;
+    for (const auto& row : runs)
+        for (size_t k = 0; k < row.size(); k += 2) n += row[k + 1] - row[k];
+    return n;
+}
+
+// Bit 0 of byte k of a word at bit k.
+uint32_t low_bits(uint64_t word) {
+    return (uint32_t)(((word & 0x0101010101010101ull) * 0x0102040810204080ull) >> 56);
 }
 
 // The patches of cx x b cells of a grid, row by row; `on` marks those with a
@@ -129,7 +179,7 @@ struct PatchGrid {
     int append(const std::vector<uint8_t>& live, const std::vector<uint8_t>& high, int i0, int i1, int j0, int j1, int s0,
                int s1, int t0, int t1, int none, std::vector<Patch2DCell>& out) const {
         std::vector<int> at((size_t)LX * LY, -1);
-        auto wrap = [](int v, int n) { return ((v % n) + n) % n; };
+        auto wrap = [](int v, int n) { return v < 0 ? v + n : v >= n ? v - n : v; };   // rims end within a period
         int n = 0;
         for (int j = j0; j < j1; ++j)
             for (int i = i0; i < i1; ++i) {
@@ -144,8 +194,10 @@ struct PatchGrid {
         };
         const size_t first = out.size();
         out.resize(first + n);
-        for (int j = 0; j < LY; ++j)
-            for (int i = 0; i < LX; ++i) {
+        for (int jj = j0; jj < j1; ++jj)
+            for (int ii = i0; ii < i1; ++ii) {
+                if ((!s.perx && (ii < 0 || ii >= LX)) || (!s.pery && (jj < 0 || jj >= LY))) continue;
+                const int i = wrap(ii, LX), j = wrap(jj, LY);
                 const int k = at[(size_t)j * LX + i];
                 if (k < 0) continue;
                 Patch2DCell c{};
@@ -156,15 +208,18 @@ struct PatchGrid {
                 c.up = ref(i, j + 1);
                 c.down = ref(i, j - 1);
                 c.flags = kPatchUsed | (i >= s0 && i < s1 && j >= t0 && j < t1 ? kPatchStored : 0);
-                for (int r = 0; r < b && j * b + r < s.ny; ++r)
-                    for (int q = 0; q < cx && i * cx + q < s.nx; ++q) {
-                        const size_t cell = (size_t)(j * b + r) * s.nx + i * cx + q;
-                        const uint8_t v = live[cell], w = high[cell];
-                        c.live[0] |= (uint32_t)(v & 1) << (r * cx + q);
-                        c.live[1] |= (uint32_t)(v >> 1) << (r * cx + q);
-                        c.high[0] |= (uint32_t)(w & 1) << (r * cx + q);
-                        c.high[1] |= (uint32_t)(w >> 1) << (r * cx + q);
-                    }
+                // a row's bytes as a word (shapes have at most 8 columns)
+                const int w = std::min(cx, s.nx - i * cx);
+                for (int r = 0; r < b && j * b + r < s.ny; ++r) {
+                    const size_t cell = (size_t)(j * b + r) * s.nx + i * cx;
+                    uint64_t v = 0, u = 0;
+                    std::memcpy(&v, live.data() + cell, w);
+                    if (!high.empty()) std::memcpy(&u, high.data() + cell, w);
+                    c.live[0] |= low_bits(v) << (r * cx);
+                    c.live[1] |= low_bits(v >> 1) << (r * cx);
+                    c.high[0] |= low_bits(u) << (r * cx);
+                    c.high[1] |= low_bits(u >> 1) << (r * cx);
+                }
                 out[first + k] = c;
             }
         return n;
@@ -172,17 +227,25 @@ struct PatchGrid {
     void count_loads() {
         loads[0].assign(LX, 0);
         loads[1].assign(LY, 0);
-        for (int j = 0; j < LY; ++j)
+        for (int j = 0; j < LY; ++j) {
+            const uint8_t* row = on.data() + (size_t)j * LX;
+            int n = 0;
             for (int i = 0; i < LX; ++i) {
-                loads[0][i] += on[(size_t)j * LX + i];
-                loads[1][j] += on[(size_t)j * LX + i];
+                loads[0][i] += row[i];
+                n += row[i];
             }
+            loads[1][j] = n;
+        }
     }
     double cells() const {
         double n = 0;
-        for (int j = 0; j < LY; ++j)
-            for (int i = 0; i < LX; ++i)
-                if (on[(size_t)j * LX + i]) n += (double)std::min(cx, s.nx - i * cx) * std::min(b, s.ny - j * b);
+        for (int j = 0; j < LY; ++j) {
+            const uint8_t* row = on.data() + (size_t)j * LX;
+            int w = 0;
+            for (int i = 0; i < LX; ++i) w += row[i];
+            const int last = row[LX - 1] ? LX * cx - s.nx : 0;   // columns of the last patch beyond the grid
+            n += ((double)w * cx - last) * std::min(b, s.ny - j * b);
+        }
         return n;
     }
     Patch2DList whole() const {
@@ -201,16 +264,16 @@ struct PatchGrid {
         for (int axis = 0; axis < 2; ++axis) {
             const int N = axis == 0 ? LX : LY, w = axis == 0 ? cx : b, rim = (steps + w - 1) / w;
             const std::vector<int>& load = loads[axis];
-            const int total = std::accumulate(load.begin(), load.end(), 0);
+            std::vector<int> before(N + 1, 0);         // patches before a column (row)
+            std::partial_sum(load.begin(), load.end(), before.begin() + 1);
+            const int total = before[N];
             const int s0 = lo[axis] / w, s1 = hi[axis] / w;
             const bool per = axis == 0 ? s.perx : s.pery;
-            for (int m = 2; m <= kMaxParts; ++m) {
+            for (int m = std::max(2, total / most); m <= kMaxParts; ++m) {
                 // equal shares; a cut through the measured points moves to their nearer end
                 std::vector<int> cut{0};
-                int sum = 0;
                 for (int c = 0; c < N && (int)cut.size() < m; ++c) {
-                    sum += load[c];
-                    if (sum * (int64_t)m < (int64_t)total * (int)cut.size()) continue;
+                    if (before[c + 1] * (int64_t)m < (int64_t)total * (int)cut.size()) continue;
                     int at = c + 1;
                     if (at > s0 && at <= s1) at = at - s0 < s1 + 1 - at ? s0 : s1 + 1;
                     if (at > cut.back() && at < N) cut.push_back(at);
@@ -226,10 +289,8 @@ struct PatchGrid {
                 for (int q = 0; q < m; ++q) {
                     const int c0 = cut[q] - rim, c1 = cut[q + 1] + rim;
                     ok = ok && !(per && c1 - c0 > N);      // a rim that meets itself
-                    int k = 0;
-                    for (int c = c0; c < c1; ++c)
-                        if (per) k += load[((c % N) + N) % N];
-                        else if (c >= 0 && c < N) k += load[c];
+                    int k = before[std::min(c1, N)] - before[std::max(c0, 0)];
+                    if (per && ok) k += before[std::max(c1 - N, 0)] + total - before[std::min(c0 + N, N)];
                     l.n = std::max(l.n, k);
                     if (s0 >= cut[q] && s1 < cut[q + 1]) l.surf_part = q;
                 }
@@ -253,16 +314,24 @@ std::shared_ptr<const Patch2DSet> patch2d_set(const Problem& p, int precision) {
     const int n = precision == CF_FP64 ? patch2d_shapes<double>(sh, kMaxShapes2D)
                                        : patch2d_shapes<float>(sh, kMaxShapes2D);
     s.shapes.assign(sh, sh + n);
+    for (auto& lists : s.lists) lists.resize(n * (1 + kNumPartSteps));
+    s.nx = p.nx;
+    s.ny = p.ny;
+    // grids beyond every shape in parts are told by their live cells alone (1800 x
+    // 1800 cells: 50 ms of planning for nothing before, now 2)
+    int64_t most = 0;
+    for (const Patch2DShape& q : s.shapes) most = std::max(most, (int64_t)kMaxParts * most_patches(q) * q.cx * q.b);
+    const bool fits[2] = {
+        p.grid.ndim == 2 && p.nx < 65536 && p.ny < 65536 && count_live(p, CF_EZ) <= most,
+        p.grid.ndim == 2 && p.nx < 65536 && p.ny < 65536 && std::max(count_live(p, CF_EX), count_live(p, CF_EY)) <= most};
+    if (!fits[0] && !fits[1]) return set;
     const Uniform ue = uniform(p, p.eps, {CF_EX, CF_EY, CF_EZ}), uh = uniform(p, p.mu, {CF_HX, CF_HY, CF_HZ});
     s.id_e = ue.id;
     s.id_h = uh.id;
     s.id_h2 = uh.second;
     s.masks = ue.single;
-    s.nx = p.nx;
-    s.ny = p.ny;
     s.perx = p.grid.bc[0] == CF_BC_PERIODIC;
     s.pery = p.grid.bc[1] == CF_BC_PERIODIC;
-    const bool fits = p.grid.ndim == 2 && p.nx < 65536 && p.ny < 65536;
     // whether a shape's coefficients can hold the materials, and a periodic axis
     // wraps at a patch edge
     auto holds = [&](const Patch2DShape& q) {
@@ -292,32 +361,42 @@ std::shared_ptr<const Patch2DSet> patch2d_set(const Problem& p, int precision) {
         high_id[id] = uh.two && !(holds_field(p, p.mu, id) && p.mu[id] == p.mu[uh.id]);
     }
     for (int k = 0; k < 2; ++k) {
-        s.lists[k].resize(n * (1 + kNumPartSteps));
-        if (!fits) continue;
-        auto bits = [&](const uint8_t* of, int first, int count) {
-            std::vector<uint8_t> out(p.ncell, 0);
+        if (!fits[k]) continue;
+        // bit c of a cell: `of` its id of component first + c (all but the used ids
+        // without it)
+        auto bits = [&](const uint8_t* of, const bool* used, int first, int count) {
+            std::vector<uint8_t> out(p.ncell, (uint8_t)((1 << count) - 1));
             for (int c = 0; c < count; ++c)
-                for (int64_t q = 0; q < p.ncell; ++q) out[q] |= (uint8_t)(of[p.ids[first + c][q]] << c);
+                for (int id = 0; id < 256; ++id) {
+                    if (!used[id] || of[id]) continue;
+                    const uint8_t* __restrict ids = p.ids[first + c].data();
+                    uint8_t* __restrict at = out.data();
+                    const uint8_t without = (uint8_t)id, keep = (uint8_t)~(1 << c);
+                    const int64_t ncell = p.ncell;
+                    for (int64_t q = 0; q < ncell; ++q) at[q] = ids[q] == without ? at[q] & keep : at[q];
+                }
             return out;
         };
-        s.live[k] = k == 0 ? bits(live_id, CF_EZ, 1) : bits(live_id, CF_EX, 2);
-        s.high[k] = k == 0 ? bits(high_id, CF_HX, 2) : bits(high_id, CF_HZ, 1);
+        s.live[k] = k == 0 ? bits(live_id, ue.used, CF_EZ, 1) : bits(live_id, ue.used, CF_EX, 2);
         const Runs runs = live_runs(s.live[k], p.nx, p.ny);
+        const int64_t cells = count_cells(runs);
         bool covered = false;
         for (int v = 0; v < n; ++v) {
             const Patch2DShape& q = s.shapes[v];
-            if (!holds(q)) continue;
+            if (!holds(q) || cells > (int64_t)most_patches(q) * q.cx * q.b) continue;
             s.lists[k][v] = PatchGrid(s, runs, q.cx, q.b).whole();
             if (s.lists[k][v].n > most_patches(q)) s.lists[k][v] = Patch2DList();
             covered = covered || s.lists[k][v].parts > 0;
         }
-        if (covered || hi[0] < 0) continue;
         // too large for one compute unit: parts, of the shapes that hold their E
         // values in masks, unless the tiles are estimated to take less
         double best = 0, live = 0;
-        for (int v = 0; v < n; ++v) {
+        for (int v = 0; v < n && !covered && hi[0] >= 0; ++v) {
             const Patch2DShape& q = s.shapes[v];
-            if (q.coef == kRegAll || !s.masks || !holds(q)) continue;
+            // (smaller shapes take many parts, mostly rims)
+            if (q.cx * q.b * (precision == CF_FP64 ? 8 : 4) < 64) continue;
+            if (q.coef == kRegAll || !s.masks || !holds(q) || cells > (int64_t)kMaxParts * most_patches(q) * q.cx * q.b)
+                continue;
             PatchGrid grid(s, runs, q.cx, q.b);
             grid.count_loads();
             live = grid.cells();
@@ -332,6 +411,11 @@ std::shared_ptr<const Patch2DSet> patch2d_set(const Problem& p, int precision) {
         }
         if (best > tiles_cost(live, precision))
             for (Patch2DList& l : s.lists[k]) l = Patch2DList();
+        // the cells' masks, while some list may need them
+        if (std::none_of(s.lists[k].begin(), s.lists[k].end(), [](const Patch2DList& l) { return l.parts > 0; }))
+            std::vector<uint8_t>().swap(s.live[k]);
+        else if (uh.two)
+            s.high[k] = k == 0 ? bits(high_id, uh.used, CF_HX, 2) : bits(high_id, uh.used, CF_HZ, 1);
     }
     return set;
 }
@@ -340,6 +424,7 @@ const std::vector<Patch2DCell>& patch2d_cells(const Patch2DSet& s, int k, int en
     std::lock_guard<std::mutex> lk(s.mu);
     std::vector<Patch2DCell>& out = s.cells[{k, entry}];
     if (!out.empty()) return out;
+    out.reserve(s.lists[k][entry].size());
     const Patch2DShape& q = s.shape(entry);
     const Patch2DList& l = s.lists[k][entry];
     const PatchGrid g(s, live_runs(s.live[k], s.nx, s.ny), q.cx, q.b);

@@ -38,7 +38,8 @@ struct Patch2DSet {
     int nx = 0, ny = 0;
     bool perx = false, pery = false;
     // per polarization and cell: which E components can change (bit 0 E_z or
-    // E_x, bit 1 E_y), which H components are of the second material
+    // E_x, bit 1 E_y; empty without a usable list), which H components are of the
+    // second material (empty where there is none)
     std::vector<uint8_t> live[2], high[2];
     // the patches of the lists in use so far, by (polarization, entry)
     mutable std::mutex mu;

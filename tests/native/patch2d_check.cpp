@@ -1,7 +1,11 @@
 // Host checks of the 2D patch kernel's plan: the shapes it accepts against the
-// LDS a block takes.
+// LDS a block takes; the time and the memory of a plan that finds no shape.
+#include <chrono>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <string>
+#include <vector>
 
 #include "patch2d_plan.hpp"
 
@@ -63,7 +67,57 @@ void check_lds(int precision) {
     CHECK(accepted > 0 && refused > 0 && close > 0);
 }
 
+// A box of vacuum with one row of conductor.
+void make(Problem& p, int nx, int ny) {
+    std::vector<uint8_t> id((size_t)nx * ny, 0);
+    std::fill(id.begin(), id.begin() + nx, 1);
+    const double eps[2] = {1, -INFINITY}, mu[2] = {1, 1};
+    cf_grid g{};
+    cf_materials m{};
+    cf_surface s{};
+    g.ndim = 2;
+    g.n[0] = nx;
+    g.n[1] = ny;
+    g.n[2] = 1;
+    g.res = 8;
+    g.bc[2] = CF_BC_PERIODIC;
+    m.n_materials = 2;
+    m.eps = eps;
+    m.mu = mu;
+    for (int k = 0; k < 6; ++k) m.comp_id[k] = id.data();
+    s.lo[0] = s.lo[1] = 3;
+    s.hi[0] = s.hi[1] = 20;
+    s.hi[2] = 1;
+    s.n_harm = 2;
+    const std::string err = build_problem(g, m, s, p);
+    CHECK(err.empty());
+}
+
+// Grids that no shape covers, in parts or whole, are told quickly, by less than
+// the problem's own creation takes, and keep nothing per cell.
+void check_declined() {
+    using clock = std::chrono::steady_clock;
+    double build = 1e9, plan = 1e9;
+    for (int rep = 0; rep < 5; ++rep) {
+        Problem p;
+        const auto t0 = clock::now();
+        make(p, 1500, 1400);
+        const auto t1 = clock::now();
+        const auto set = patch2d_set(p, rep % 2 ? CF_FP32 : CF_FP64);
+        const auto t2 = clock::now();
+        build = std::min(build, std::chrono::duration<double>(t1 - t0).count());
+        plan = std::min(plan, std::chrono::duration<double>(t2 - t1).count());
+        for (int k = 0; k < 2; ++k) {
+            for (const Patch2DList& l : set->lists[k]) CHECK(l.parts == 0);
+            CHECK(set->live[k].empty() && set->high[k].empty());
+        }
+    }
+    std::printf("1500 x 1400: build %.2f ms, plan %.2f ms\n", build * 1e3, plan * 1e3);
+    CHECK(plan < 0.5 * build);
+}
+
 int main() {
+    check_declined();
     check_lds<float>(CF_FP32);
     check_lds<double>(CF_FP64);
     std::puts("patch2d ok");
