@@ -202,8 +202,25 @@ std::vector<TBPlan> cached_plans(const cf::Problem& p, const std::vector<cf::Cha
     return plans;
 }
 
-// Patch lists of a 2D problem (patch2d_plan.hpp) per problem and precision.
+// Patch lists of a 2D problem (patch2d_plan.hpp) per problem and precision; all
+// are dropped (those in use live on) when they hold more than kPatchBytes.
 std::map<std::pair<uint64_t, int>, std::shared_ptr<const cf::Patch2DSet>> g_patches;
+size_t g_patch_bytes = 0;
+constexpr size_t kPatchBytes = (size_t)256 << 20;
+
+// What a set may come to hold: its masks, and lists of a few entries.
+size_t patch2d_footprint(const cf::Patch2DSet& s) {
+    size_t n = 4096;
+    for (int q = 0; q < 2; ++q)
+        n += s.live[q].size() + s.high[q].size() + (s.live[q].empty() ? 0 : (size_t)cf::kNumComp * s.nx * s.ny);
+    return n;
+}
+
+void drop_patches(std::map<std::pair<uint64_t, int>, std::shared_ptr<const cf::Patch2DSet>>::iterator it) {
+    if (it == g_patches.end()) return;
+    g_patch_bytes -= patch2d_footprint(*it->second);
+    g_patches.erase(it);
+}
 
 std::shared_ptr<const cf::Patch2DSet> cached_patches(const cf::Problem& p, int precision) {
     const std::pair<uint64_t, int> key{p.uid, precision};
@@ -214,8 +231,14 @@ std::shared_ptr<const cf::Patch2DSet> cached_patches(const cf::Problem& p, int p
     }
     auto set = cf::patch2d_set(p, precision);
     std::lock_guard<std::mutex> lk(g_plan_mu);
-    if (g_patches.size() >= 256) g_patches.clear();
+    auto it = g_patches.find(key);   // another thread's
+    if (it != g_patches.end()) return it->second;
+    if (g_patch_bytes + patch2d_footprint(*set) > kPatchBytes) {
+        g_patches.clear();
+        g_patch_bytes = 0;
+    }
     g_patches[key] = set;
+    g_patch_bytes += patch2d_footprint(*set);
     return set;
 }
 
@@ -352,8 +375,8 @@ void forget_plans(uint64_t uid) {
     for (auto it = g_plans.begin(); it != g_plans.end();) it = (uint64_t)it->first[0] == uid ? g_plans.erase(it) : std::next(it);
     g_erows.erase(uid);
     g_zranges.erase(uid);
-    g_patches.erase(std::make_pair(uid, (int)CF_FP32));
-    g_patches.erase(std::make_pair(uid, (int)CF_FP64));
+    drop_patches(g_patches.find(std::make_pair(uid, (int)CF_FP32)));
+    drop_patches(g_patches.find(std::make_pair(uid, (int)CF_FP64)));
 }
 
 // Per band of each fused 3D variant, the planes [lo, hi) the band's region

@@ -1,13 +1,15 @@
 // Host checks of the 2D patch kernel's plan: the shapes it accepts against the
-// LDS a block takes; the time and the memory of a plan that finds no shape.
+// LDS a block takes; the time and the memory of the plans kept per problem.
 #include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <memory>
 #include <string>
 #include <vector>
 
 #include "patch2d_plan.hpp"
+#include "solver.hpp"
 
 #define CHECK(c)                                                              \
     do {                                                                      \
@@ -116,8 +118,26 @@ void check_declined() {
     CHECK(plan < 0.5 * build);
 }
 
+// Kept plans are bounded by what they hold, not by their number.
+void check_kept() {
+    std::vector<std::unique_ptr<Problem>> probs;
+    std::weak_ptr<const Patch2DSet> first;
+    size_t cells = 0;
+    for (int k = 0; k < 90; ++k) {
+        probs.push_back(std::make_unique<Problem>());
+        make(*probs.back(), 1600, 150);
+        const auto set = cfi::cached_patches(*probs.back(), CF_FP32);
+        CHECK(!set->live[0].empty() && !set->live[1].empty());
+        if (k == 0) first = set;
+        if (k < 5) CHECK(cfi::cached_patches(*probs.front(), CF_FP32) == first.lock());
+        cells += (size_t)1600 * 150;
+    }
+    CHECK(cells * 14 > (size_t)256 << 20 && first.expired());
+}
+
 int main() {
     check_declined();
+    check_kept();
     check_lds<float>(CF_FP32);
     check_lds<double>(CF_FP64);
     std::puts("patch2d ok");
