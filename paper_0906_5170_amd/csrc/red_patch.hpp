@@ -3,6 +3,7 @@
 #pragma once
 
 #include <deque>
+#include <memory>
 #include <vector>
 
 #include "device.hpp"
@@ -45,12 +46,16 @@ struct PatchOpen {
 
 // Patches without a cell that can change are left out: host copy of the
 // classes, device memory for the list of the others, and the host lists, which
-// live until the stream has drained.
+// live until the stream has drained.  The plan of the last launch, with its list
+// in `dev`, serves further ones of as many channels (a run's spans between
+// convergence checks).
 struct PatchLive {
     const uint16_t* cls;
     char* dev;
     size_t room;
     std::deque<std::vector<uint16_t>>* keep;
+    std::shared_ptr<const void> plan;
+    int plan_slots = -1;
 };
 
 // As launch_red_resident_span, for grids a patch shape covers: *launched
@@ -61,7 +66,7 @@ struct PatchLive {
 template <typename T>
 hipError_t launch_red_patch(T* fields, const ChanDev* ch, const int* slots, int nslots, const Grid2D& g,
                             const RedOrders& ord, const RedSpan& span, const SurfTables& t, const PatchClasses& pc,
-                            const PatchSizes& ps, const PatchOpen* op, const PatchLive* live, double dA, double* acc, double* gamma,
+                            const PatchSizes& ps, const PatchOpen* op, PatchLive* live, double dA, double* acc, double* gamma,
                             int gamma_stride, hipStream_t s, bool* launched);
 
 }  // namespace cf

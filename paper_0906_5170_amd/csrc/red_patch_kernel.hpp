@@ -1159,21 +1159,30 @@ PatchPlan plan_patch(bool cyl, const Grid2D& g, int nslots, const PatchClasses& 
 template <typename T, bool CYL, bool CPLX, bool OPEN>
 hipError_t patch_dispatch(T* fields, const ChanDev* ch, const int* slots, int nslots, const Grid2D& g,
                           const RedOrders& ord, const RedSpan& sp, const SurfTables& t, const PatchClasses& pc,
-                          const PatchSizes& z, const PatchOpen* op, const PatchLive* live, double dA, double* acc,
+                          const PatchSizes& z, const PatchOpen* op, PatchLive* live, double dA, double* acc,
                           double* gamma, int gamma_stride, hipStream_t s, bool* launched) {
     using SH = PatchShapes<T, CPLX, OPEN>;
-    std::vector<uint16_t> list;
-    PatchPlan pl = plan_patch<T, CPLX, OPEN>(CYL, g, nslots, pc, z, op, device_lds_limit(), OPEN ? nullptr : live, list);
-    if (pl.shape < 0) return hipSuccess;
-    if (OPEN) pl.args.scratch = op->scratch;
     hipError_t e = hipSuccess;
-    if (!list.empty()) {
-        live->keep->push_back(std::move(list));
-        const std::vector<uint16_t>& l = live->keep->back();
-        pl.args.list = reinterpret_cast<const uint16_t*>(live->dev);
-        e = hipMemcpyAsync(live->dev, l.data(), l.size() * sizeof(l[0]), hipMemcpyHostToDevice, s);
-        if (e != hipSuccess) return e;
+    PatchPlan pl;
+    if (!OPEN && live && live->plan_slots == nslots) {
+        pl = *static_cast<const PatchPlan*>(live->plan.get());
+    } else {
+        std::vector<uint16_t> list;
+        pl = plan_patch<T, CPLX, OPEN>(CYL, g, nslots, pc, z, op, device_lds_limit(), OPEN ? nullptr : live, list);
+        if (OPEN) pl.args.scratch = op->scratch;
+        if (!list.empty()) {
+            live->keep->push_back(std::move(list));
+            const std::vector<uint16_t>& l = live->keep->back();
+            pl.args.list = reinterpret_cast<const uint16_t*>(live->dev);
+            e = hipMemcpyAsync(live->dev, l.data(), l.size() * sizeof(l[0]), hipMemcpyHostToDevice, s);
+            if (e != hipSuccess) return e;
+        }
+        if (!OPEN && live) {
+            live->plan = std::make_shared<PatchPlan>(pl);
+            live->plan_slots = nslots;
+        }
     }
+    if (pl.shape < 0) return hipSuccess;
     auto attempt = [&](auto v) {
         constexpr int V = decltype(v)::value;
         if constexpr (V < SH::n) {
@@ -1210,7 +1219,7 @@ hipError_t patch_dispatch(T* fields, const ChanDev* ch, const int* slots, int ns
 template <typename T>
 hipError_t launch_red_patch(T* fields, const ChanDev* ch, const int* slots, int nslots, const Grid2D& g,
                             const RedOrders& ord, const RedSpan& span, const SurfTables& t, const PatchClasses& pc,
-                            const PatchSizes& ps, const PatchOpen* op, const PatchLive* live, double dA, double* acc,
+                            const PatchSizes& ps, const PatchOpen* op, PatchLive* live, double dA, double* acc,
                             double* gamma, int gamma_stride, hipStream_t s, bool* launched) {
     *launched = false;
     if (nslots <= 0 || pc.cls == nullptr) return hipSuccess;
