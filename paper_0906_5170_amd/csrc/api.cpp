@@ -1349,7 +1349,13 @@ cf_status run_reduced(const cf::Problem& p, const cf_opts& o, const Staged& st, 
     cf::PatchSizes psizes{};
     std::deque<std::vector<uint16_t>> live_lists;
     cf::PatchLive live{nullptr, nullptr, 0, &live_lists};
-    if (st.red_res && o.tile_variant != 2 && patch_classes(p, cls, classes)) {
+    // (a check every few steps: the patch kernel's launches load and store more
+    // and start slower; 288 channels of 40 x 31 cells, 126 of 150 x 7 in FP64 took
+    // 31 and 30 ms for 400 spans of one step, 27 and 25 on the register kernel, 9.4
+    // and 9.6 against 9.9 and 9.0 for 100 of four, 3.3 and 4.1 against 5.3 and 4.7
+    // for 20 of twenty)
+    const bool short_spans = o.stop_tol > 0 && o.stop_every > 0 && o.stop_every < 8;
+    if (st.red_res && o.tile_variant != 2 && !short_spans && patch_classes(p, cls, classes)) {
         CF_HIP(up(L.idp, cls.data(), cls.size() * 2));
         classes.cls = reinterpret_cast<const uint16_t*>(ws + L.idp);
         psizes = patch_sizes(p, st);
