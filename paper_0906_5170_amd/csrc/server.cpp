@@ -73,7 +73,8 @@ struct Req {
     bool parts = false;               // some polarization goes in parts, between the two field arrays
     cf::Patch2DSizes psizes{1, 1, 1};
     std::vector<cf::Patch2DCell> cells;   // its patch lists
-    double patch_cells = 0;               // cells it advances in a step, over all channels
+    double work_cells = 0;            // fused: cells it advances in a step, over all channels
+    int launch_steps = 0;             // patch kernel: steps of its longest launch
     int v3 = -1;                      // fused 3D step variant (-1: split 3D kernels)
     int v3s = -1;                     // its single-step band shape (a step without a partner in the tick)
     cfi::ConvergenceStop conv;        // time-convergence stop (single-wave requests)
@@ -150,7 +151,8 @@ struct cf_server {
     std::map<uint64_t, std::shared_ptr<Req>> all;
     uint64_t next_ticket = 1;
     long long clock = 0;
-    int parity = 0;
+    int parity = 0;                   // field array the tiles read next
+    int parts_parity = 0;             // and the patch launches in parts
     int kh = 8;                       // steps per tick
     bool tiles_only = false;          // a tile variant was asked for
     std::vector<int> prefer;          // fused variants in order of preference (same steps per launch)
@@ -166,7 +168,7 @@ struct cf_server {
         // 2D patch kernel (shape >= 0): byte offset of the channel list behind
         // the work items, channels, longest patch list, LDS sizes
         int shape = -1;
-        bool pingpong = false;        // from the field array of the clock's parity to the other
+        bool pingpong = false;        // from the field array of parts_parity to the other
         int longest = 0;
         cf::Patch2DSizes sizes{1, 1, 1};
     };
@@ -177,6 +179,7 @@ struct cf_server {
     std::vector<hipEvent_t> ev;
     size_t n_marks = 0;
     double group_s = 0;
+    double group_cells = 0;           // and the cells they advanced in a step
     // second stream for the TE launches of the fused group (forked from and
     // joined back to the server's stream every tick); default priority
     hipStream_t side = nullptr;
@@ -256,7 +259,6 @@ std::string prepare(cf_server* S, Req& r) {
     // second field array; a larger one goes in parts, with the lists in the place
     // of its ids, which are not read after the start.  Shapes are chosen for a full device.
     r.patches = nullptr;
-    r.patch_cells = 0;
     if (r.fused && !S->tiles_only) {
         auto set = cfi::cached_patches(p, S->precision);
         cfi::patch2d_sizes(r.st, p.nx, r.psizes);
@@ -268,8 +270,6 @@ std::string prepare(cf_server* S, Req& r) {
             r.parts = cfi::patch2d_in_parts(*set, r.pshape);
             const size_t room = (size_t)r.C * r.st.ncomp * p.ncell * (S->precision == CF_FP64 ? 8 : 4);
             if (r.parts || r.cells.size() * sizeof(cf::Patch2DCell) <= room) r.patches = set;
-            for (int q = 0; q < 2; ++q)
-                if (r.pshape[q] >= 0) r.patch_cells += used[q] * set->lists[q][r.pshape[q]].live_cells;
             // parts take a launch of at least a tick
             for (int q = 0; q < 2; ++q)
                 if (r.pshape[q] >= 0 && r.parts && set->lists[q][r.pshape[q]].parts > 1 &&
@@ -277,6 +277,12 @@ std::string prepare(cf_server* S, Req& r) {
                     r.patches = nullptr;
             if (!r.patches) r.parts = false;
         }
+    }
+    r.work_cells = 0;
+    for (const cf::Channel& c : r.chans) {
+        const int q = c.pol == CF_POL_TE ? 1 : 0;
+        if (r.patches) r.work_cells += r.patches->lists[q][r.pshape[q]].live_cells;
+        else if (r.fused) r.work_cells += r.st.plans[r.variant].live_cells[q];
     }
     // 3D requests take the fused z-streaming step when it applies: in FP32
     // the two-step kernel (12 waves of 1 row; steps go in pairs within a clock
@@ -471,7 +477,7 @@ hipError_t admit(cf_server* S, Req& r) {
     r.sps = 0;
     // a request that goes between the field arrays is kicked into the one the
     // next fused launch reads; the launches take its TM and TE channels alike
-    T* f = reinterpret_cast<T*>(b + (r.fused && (!r.patches || r.parts) && S->parity ? r.o_fb : r.o_fa));
+    T* f = reinterpret_cast<T*>(b + (r.fused && (r.patches ? r.parts && S->parts_parity : S->parity != 0) ? r.o_fb : r.o_fa));
     if ((e = start_wave<T>(S, r, f)) != hipSuccess || !r.parts) return e;
     return hipMemcpyAsync(b + r.o_ids, r.cells.data(), r.cells.size() * sizeof(cf::Patch2DCell),
                           hipMemcpyHostToDevice, s);
@@ -635,34 +641,47 @@ hipError_t rebuild_group(cf_server* S) {
     return hipSuccess;
 }
 
-// Ticks run as one take no more device time than this (seconds).
+// Ticks run as one are meant to take no more device time than this (seconds).
 constexpr double kMergedTick = 2e-3;
 
-// Ticks that may run as one: where every resident request is on the 2D patch
-// kernel, whose launches take any number of steps (in parts, as many as the rim is
-// wide), as many as stay within kMergedTick and end by the next tick in which a request
-// finishes or is checked for convergence.  Longer launches load and store the
-// fields less often.
+// Cells that the fused requests resident now advance in a step.
+double fused_cells(const cf_server* S) {
+    double n = 0;
+    for (const auto& rp : S->active)
+        if (rp->fused) n += rp->work_cells;
+    return n;
+}
+
+// Ticks that may run as one: as many as stay within kMergedTick (by the last
+// tick's time, in proportion to the cells when more have joined since) and end by
+// the next tick in which a fused request finishes or is checked for convergence.
+// The patch kernel's launches take any number of steps (in parts, as many as the
+// rim is wide) and load and store the fields less often when they are longer;
+// tiles take a launch per tick as ever.
 int merged_ticks(const cf_server* S) {
     if (!(S->group_s > 0)) return 1;
-    long long n = std::min<long long>((long long)(kMergedTick / S->group_s), 64);
+    const double cells = fused_cells(S);
+    const double tick_s = S->group_s * (S->group_cells > 0 ? std::max(1.0, cells / S->group_cells) : 1.0);
+    long long n = std::min<long long>((long long)(kMergedTick / tick_s), 64);
+    bool any_patch = false;
     for (const auto& rp : S->active) {
         const Req& r = *rp;
-        if (!r.fused || !r.patches) return 1;
+        if (!r.fused) continue;
+        any_patch = any_patch || r.patches;
         const long long done = S->clock - r.start;
         long long left = r.opts.n_steps - done;
         if (r.conv.on) left = std::min<long long>(left, r.conv.next - done);
         n = std::min(n, (left + S->kh - 1) / S->kh);
         for (int q = 0; q < 2; ++q) {
-            const int steps = r.pshape[q] >= 0 ? r.patches->lists[q][r.pshape[q]].steps : 0;
+            const int steps = r.patches && r.pshape[q] >= 0 ? r.patches->lists[q][r.pshape[q]].steps : 0;
             if (steps > 0) n = std::min<long long>(n, steps / S->kh);
         }
     }
-    return (int)std::max<long long>(n, 1);
+    return any_patch ? (int)std::max<long long>(n, 1) : 1;
 }
 
-// One tick: K steps of every resident request (`ticks` times K where every one
-// is on the patch kernel).
+// One tick: K steps of every resident fused request, `ticks` times over
+// (merged_ticks), and the steps planned for the others.
 template <typename T>
 hipError_t tick(cf_server* S, int ticks) {
     hipStream_t s = S->stream;
@@ -700,10 +719,12 @@ hipError_t tick(cf_server* S, int ticks) {
                 e = cf::launch_patch2d<T>(
                     l.shape, l.pol, gch, reinterpret_cast<const int*>(S->group + S->g_work + l.off), l.n, gin,
                     reinterpret_cast<const cf::Patch2DInst*>(S->group + S->g_work + S->heads_off), l.longest, l.sizes,
-                    S->kh * ticks, (int)S->clock, l.pingpong ? S->parity : 0, l.pingpong ? S->parity ^ 1 : 0, ls);
+                    S->kh * ticks, (int)S->clock, l.pingpong ? S->parts_parity : 0, l.pingpong ? S->parts_parity ^ 1 : 0,
+                    ls);
             else
-                e = cf::launch_tb2d<T>(l.variant, l.pol, gch, gw + l.off, l.n, gin, S->kh, (int)S->clock, S->parity,
-                                       ls);
+                for (int k = 0; k < ticks && (k == 0 || e == hipSuccess); ++k)
+                    e = cf::launch_tb2d<T>(l.variant, l.pol, gch, gw + l.off, l.n, gin, S->kh,
+                                           (int)S->clock + k * S->kh, S->parity ^ (k & 1), ls);
             if (e != hipSuccess) return e;
         }
         if (split) {
@@ -813,14 +834,14 @@ hipError_t tick(cf_server* S, int ticks) {
 // request runs K steps.  Convergence checks fall on tick boundaries, and
 // two-step 3D requests run their steps in pairs (a single step only at the
 // end or before a check).
-void plan_steps(cf_server* S) {
+void plan_steps(cf_server* S, int ticks) {
     int nf = 0;
     double min_sps = 0;
     for (auto& rp : S->active) {
         if (rp->fused) ++nf;
         else if (!rp->whole && rp->sps > 0 && (min_sps == 0 || rp->sps < min_sps)) min_sps = rp->sps;
     }
-    const double share = nf > 0 ? (S->group_s > 0 ? S->group_s / nf : 0.0) : S->kh * min_sps;
+    const double share = nf > 0 ? (S->group_s > 0 ? S->group_s * ticks / nf : 0.0) : S->kh * min_sps;
     for (auto& rp : S->active) {
         Req& r = *rp;
         if (r.fused || r.whole) continue;
@@ -852,7 +873,12 @@ void read_times(cf_server* S, int ticks) {
     bool any_fused = false;
     for (auto& rp : S->active) any_fused = any_fused || rp->fused;
     const double g = span(0) / ticks;
-    if (any_fused && g > 0) S->group_s = S->group_s > 0 ? 0.5 * (S->group_s + g) : g;
+    if (any_fused && g > 0) {
+        // other requests than at the last tick's time: this one's alone
+        const double cells = fused_cells(S);
+        S->group_s = S->group_s > 0 && cells == S->group_cells ? 0.5 * (S->group_s + g) : g;
+        S->group_cells = cells;
+    }
     size_t k = 1;
     for (auto& rp : S->active) {
         Req& r = *rp;
@@ -936,8 +962,10 @@ void loop(cf_server* S) {
             continue;
         }
         // ---- one tick ----
-        plan_steps(S);
         const int ticks = merged_ticks(S);
+        plan_steps(S, ticks);
+        for (auto& rp : S->active)
+            if (rp->patches) rp->launch_steps = std::max(rp->launch_steps, S->kh * ticks);
         const double t0 = now_s();
         lk.unlock();
         hipError_t e = tick<T>(S, ticks);
@@ -961,7 +989,8 @@ void loop(cf_server* S) {
         }
         read_times(S, ticks);
         S->clock += S->kh * ticks;
-        S->parity ^= 1;
+        S->parity ^= ticks & 1;
+        S->parts_parity ^= 1;
         for (auto& rp : S->active)
             if (!rp->fused && !rp->whole) rp->done += rp->tick_steps;
         // the stream has drained: staged group tables are no longer read
@@ -1194,8 +1223,8 @@ static cf_status report(cf_server* S, const std::shared_ptr<Req>& r, int* state,
         tim.steps_run = r->steps_run;
         tim.variant = r->variant >= 0 ? r->variant : r->v3;   // fused 2D tile or fused 3D band shape
         if (r->patches) {
-            tim.launch_steps = S->kh;
-            tim.patch_cells = r->patch_cells;
+            tim.launch_steps = std::max(r->launch_steps, S->kh);
+            tim.patch_cells = r->work_cells;
         }
         cf_opts o = r->opts;
         const bool ok = cfi::fill_result(*r->prob, r->chans, r->acc, {}, o, (r->t_done - r->t_admit) * 1e3, tim,

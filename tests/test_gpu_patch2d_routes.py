@@ -95,3 +95,81 @@ def test_speed_of_parts_with_few_channels(cf, shape, n_harm, slack):
     step of the smallest parts that fit is as long as the tiles' launches.)"""
     prims = [Box((-BIG, -BIG, -BIG), (BIG, 1, BIG), 1)]
     check_speed(cf, vacuum(*shape, WALLS, "TM+TE", n_harm=n_harm, prims=prims).replace(s_hi=(43, 43, 1)), slack, 600)
+
+
+def burst(srv, items):
+    import time
+    t = time.perf_counter()
+    tickets = [srv.submit(p, **o) for p, o in items]
+    out = [srv.wait(k, timeout=100) for k in tickets]
+    t = time.perf_counter() - t
+    for k in tickets:
+        srv.release(k)
+    return t * 1e3, out
+
+
+def test_server_large_requests_join_small_ones(cf):
+    """Ticks that run as one for small requests are not as long in steps when
+    large ones have joined: their device time stays near the 2 ms meant."""
+    import time
+    prims = [Box((-BIG, -BIG, -BIG), (BIG, 1, BIG), 1)]
+    small, large = vacuum(13, 14, WALLS, "TM+TE"), vacuum(180, 160, WALLS, "TM+TE", n_harm=40, prims=prims)
+    large = large.replace(s_hi=(43, 43, 1))
+    ps, pl = cf.Problem.from_workload(small), cf.Problem.from_workload(large)
+    halos = []
+    with cf.Server(16 << 30, precision="fp32") as srv:
+        for _ in range(2):
+            long = srv.submit(ps, **RUN, n_steps=400000, pol=small.pol)
+            time.sleep(0.05)
+            tickets = [srv.submit(pl, **RUN, n_steps=1500, pol=large.pol) for _ in range(6)]
+            longest, last, joined = 0.0, srv.stats(), False
+            while not joined or srv.poll(tickets[-1])[0] != "done":
+                now = srv.stats()
+                if now["clock_steps"] != last["clock_steps"]:
+                    longest = max(longest, now["busy_s"] - last["busy_s"])
+                    last = now
+                joined = joined or srv.poll(tickets[-1])[0] == "running"
+            srv.cancel(long)
+            for t in tickets:
+                r = srv.wait(t, timeout=100)
+                assert r["fused"]
+                halos.append(r["tile_halo"])
+        print(f"longest tick {longest * 1e3:.1f} ms", flush=True)
+        assert longest < 8e-3 and min(halos) > 8
+
+
+@pytest.mark.parametrize("beside", ["3d", "tiles"])
+def test_server_beside_other_requests(cf, beside):
+    """Requests on patches next to a 3D one or one on tiles keep launches of many
+    steps: results as alone, in no more time than with everything on tiles."""
+    from casimir_inputs.configs import sphere_plate3d
+    prims = [Box((-BIG, -BIG, -BIG), (BIG, 1, BIG), 1)]
+    wls = [vacuum(61, 37, WALLS, "TM+TE"), vacuum(150, 120, WALLS, "TM+TE", n_harm=4, prims=prims).replace(s_hi=(43, 43, 1)),
+           vacuum(260, 200, WALLS, "TM+TE", n_harm=4, prims=prims).replace(s_hi=(43, 43, 1))]
+    items = [(cf.Problem.from_workload(w), dict(RUN, n_steps=n, pol=w.pol)) for w, n in zip(wls, (700, 900, 801))]
+    refs = [p.solve(split=True, precision="fp32", **o) for p, o in items]
+    if beside == "3d":
+        w = sphere_plate3d(64, 1.0, n_harm=2)
+        other = (cf.Problem.from_workload(w), dict(sigma=w.sigma, courant=w.courant, n_steps=200000, pol="3D", kernel=w.kernel))
+    else:
+        w = vacuum(180, 160, WALLS, "TM+TE")
+        ids = {k: v.copy() for k, v in w.comp_ids.items()}
+        for v in ids.values():
+            v.reshape(160, 180)[100:120, 100:150] = 2
+            v.reshape(160, 180)[130:150, 100:150] = 3
+        w = w.replace(eps=[1.0, PEC, 3.1, 2.0], mu=[1.0, 1.0, 1.7, 1.3], comp_ids=ids)
+        other = (cf.Problem.from_workload(w), dict(RUN, n_steps=300000, pol=w.pol))
+    ms = {}
+    for variant in (0, 13):
+        with cf.Server(16 << 30, precision="fp32", tile_variant=variant) as srv:
+            t = srv.submit(other[0], **other[1])
+            times = [burst(srv, items) for _ in range(5)]
+            ms[variant] = min(x[0] for x in times)
+            patched = times[0][1] if variant == 0 else patched
+            srv.cancel(t)
+            for _, out in times:
+                for r, ref in zip(out, refs):
+                    assert r["fused"] and np.array_equal(r["per_channel"], ref["per_channel"])
+                    assert variant == 0 or r["tile_halo"] == 8
+    print(beside, ms, flush=True)
+    assert ms[0] <= 1.1 * ms[13] and all(r["tile_halo"] > 8 for r in patched)
