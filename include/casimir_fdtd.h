@@ -432,10 +432,10 @@ const char* cf_last_error(void);
  * budget (a later request may pass an earlier one that does not fit yet) and
  * leaves when all its time steps have run, returning its memory.  In every
  * scheduler tick the 2D requests whose stress surface fits a fused tile
- * share fused launches and advance steps_per_tick steps (several ticks may
- * run as one where no request needs the device in between); every other
- * resident request (3D, wider 2D) advances the steps that an equal share of
- * the tick's device time buys it, from its measured time per step.
+ * share fused launches and advance steps_per_tick steps (several ticks, about
+ * 2 ms of them, may run as one until a 2D request finishes or is checked);
+ * every other resident request (3D, wider 2D) advances the steps that an equal
+ * share of the ticks' device time buys it, from its measured time per step.
  * Cylindrical and k_z requests (Sec. III B, III C: one launch runs every
  * step of a channel) run their whole solve as cf_solve in one tick, on
  * their region of the budget; the convergence stop is not available for

@@ -828,8 +828,8 @@ hipError_t tick(cf_server* S, int ticks) {
 // Steps of each non-fused request in the coming tick.  Every resident
 // request is entitled to the same device time per tick: the fused launches
 // advance all fused requests by K steps in group_s seconds, so the share is
-// group_s / (fused requests); with no fused request resident it is K steps
-// of the cheapest non-fused request.  A request earns share / (its seconds
+// group_s / (fused requests) for each of the `ticks` that run as one; with no
+// fused request resident it is K steps of the cheapest non-fused request.  A request earns share / (its seconds
 // per step) of step credit per tick.  Until its time per step is measured a
 // request runs K steps.  Convergence checks fall on tick boundaries, and
 // two-step 3D requests run their steps in pairs (a single step only at the
