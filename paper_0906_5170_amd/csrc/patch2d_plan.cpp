@@ -38,13 +38,14 @@ double step_cycles(const Patch2DShape& q, int k, int waves) {
 // the compute units at work, its share of the copy rate, 4.7 TB/s or 7.6 bytes a
 // cycle, for the loads and stores of its field values.  No other block's steps
 // overlap with them: a block of parts fills its compute unit.  Measured, 16
-// channels of 260 x 200 cells, FP32: 8 x 4 cells 30 us a launch and 2.6 us a step,
-// 5 x 5 24 and 2.2, 5 x 4 (kRegE) 23 and 2.1, kMaskH 8 x 4 32 and 2.7, 5 x 5 27 and
-// 2.2; FP64 4 x 3 31 and 1.1.
-double part_cycles(const Patch2DShape& q, int k, int waves, const Patch2DList& l, int precision, double fill) {
+// channels of 260 x 200 cells, FP32: 8 x 4 cells 30 us a launch and 2.6 us a step
+// (2.24 with 675 patches), 5 x 5 24 and 2.2, 5 x 4 (kRegE) 23 and 2.1, kMaskH 8 x 4
+// 32 and 2.7, 5 x 5 27 and 2.2; FP64 4 x 3 31 and 1.1.
+double part_cycles(const Patch2DShape& q, int k, const Patch2DList& l, int precision, double fill) {
     const double value = precision == CF_FP64 ? 8.0 : 4.0, scale = q.coef == kRegE ? 1.2 : q.coef == kMaskH ? 0.7 : 0.8;
     const double bytes = 3 * value * (l.n * (double)(q.cx * q.b) + l.live_cells / l.parts);
-    return scale * step_cycles(q, k, waves) + std::max(62000.0, fill * bytes / 7.6) / l.steps;
+    const double step = scale * step_cycles(q, k, 4 * q.mw) * (0.55 + 0.45 * l.n / most_patches(q));
+    return step + std::max(62000.0, fill * bytes / 7.6) / l.steps;
 }
 
 // And of the tiles, per live cell with the device full (FP32 640 channels:
@@ -405,7 +406,7 @@ std::shared_ptr<const Patch2DSet> patch2d_set(const Problem& p, int precision) {
                 l = grid.parts(most_patches(q), kPartSteps[t], lo, hi);
                 if (!l.parts) continue;
                 l.live_cells = live;
-                const double cost = l.parts * part_cycles(q, k, (l.n + 63) / 64 + 1, l, precision, 1);
+                const double cost = l.parts * part_cycles(q, k, l, precision, 1);
                 if (best == 0 || cost < best) best = cost;
             }
         }
@@ -455,10 +456,11 @@ int patch2d_choose(const Patch2DSet& s, int precision, int k, int nslots, const 
         const int n = l.n, waves = (n + 63) / 64 + 1, nblocks = (nslots + (l.parts > 1 ? others : 0)) * l.parts;
         const size_t lds = precision == CF_FP64 ? patch2d_lds<double>(q, n, z) : patch2d_lds<float>(q, n, z);
         if (lds > lds_limit) continue;
-        const int per_cu = std::max(1, std::min(4 * q.mw / waves, (int)(lds_limit / std::max<size_t>(lds, 1))));
+        const int per_cu =
+            l.parts > 1 ? 1 : std::max(1, std::min(4 * q.mw / waves, (int)(lds_limit / std::max<size_t>(lds, 1))));
         const int c = std::min(per_cu, (nblocks + kCUs - 1) / kCUs);
         const int rounds = (nblocks + kCUs * c - 1) / (kCUs * c);
-        const double cost = rounds * (l.parts > 1 ? part_cycles(q, k, c * waves, l, precision, std::min(1.0, (double)nblocks / kCUs))
+        const double cost = rounds * (l.parts > 1 ? part_cycles(q, k, l, precision, std::min(1.0, (double)nblocks / kCUs))
                                                   : step_cycles(q, k, c * waves));
         if (best < 0 || cost < best_cost) {
             best = v;
