@@ -173,3 +173,25 @@ def test_server_beside_other_requests(cf, beside):
                     assert variant == 0 or r["tile_halo"] == 8
     print(beside, ms, flush=True)
     assert ms[0] <= 1.1 * ms[13] and all(r["tile_halo"] > 8 for r in patched)
+
+
+def test_batch_of_few_channels(cf):
+    """Groups of unlike shapes and rims that leave compute units idle run beside
+    each other: a batch takes no longer than its tiles, and gives each problem
+    what its own split solve gives."""
+    prims = [Box((-BIG, -BIG, -BIG), (BIG, 1, BIG), 1)]
+    wls = [vacuum(260, 200, WALLS, "TM+TE", n_harm=2, prims=prims).replace(s_hi=(43, 43, 1)), vacuum(61, 37, WALLS, "TM+TE", n_harm=2),
+           vacuum(300, 300, WALLS, "TM+TE", n_harm=2, prims=prims).replace(s_hi=(43, 43, 1))]
+    probs = [cf.Problem.from_workload(w) for w in wls]
+    o = dict(RUN, n_steps=600, pol="TM+TE", precision="fp32")
+    refs = [p.solve(split=True, **o) for p in probs]
+    ms = {}
+    for variant in (0, 7, 13):
+        for graph in (False, True):
+            for _ in range(4):
+                rs = cf.batch_solve(probs, graph=graph, tile_variant=variant, **o)
+                for r, ref in zip(rs, refs):
+                    assert np.array_equal(r["per_channel"], ref["per_channel"]) and tiled(r, "fp32") == (variant > 0)
+                ms[variant, graph] = min(ms.get((variant, graph), 1e9), rs[0]["device_ms"])
+    print(ms, flush=True)
+    assert ms[0, True] <= 1.15 * min(ms[v, True] for v in (7, 13))
