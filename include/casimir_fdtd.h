@@ -342,7 +342,8 @@ typedef struct cf_result {
     int fused;                   /* 1 when the fused multi-step kernel advanced the fields          */
     int tile_variant;            /* fused kernel variant used (1-based), 0 if not fused; where a    */
                                  /* 2D solve did without tiles, the first variant that fits it       */
-    int tile_halo;               /* steps per fused launch (at most 8 with 2D tiles)                */
+    int tile_halo;               /* steps per fused launch (at most 8 with 2D tiles; cylindrical and */
+                                 /* k_z problems: base steps per launch in patches, 0 elsewhere)     */
     int n_steps_run;             /* time steps run (< n_steps when the convergence stop ended it)   */
     double advanced_cell_updates; /* cell-updates the field kernels actually performed: below        */
                                   /* cell_updates when the fused 2D kernel skips rows that hold only  */

@@ -1426,6 +1426,7 @@ cf_status run_reduced(const cf::Problem& p, const cf_opts& o, const Staged& st, 
         err = (expr);                     \
         if (err != hipSuccess) goto done; \
     } while (0)
+    cf::PatchRan ran;
     bool opened = false;
     STEP_OK(hipEventRecord(e0, s));
     if (try_open) {
@@ -1434,8 +1435,13 @@ cf_status run_reduced(const cf::Problem& p, const cf_opts& o, const Staged& st, 
         const double cu = (double)C * p.ncell * o.n_steps;
         const bool take = smp.begin(s);
         STEP_OK(cf::launch_red_patch<T>(fields, dch, nullptr, (int)C, g, ord, span, tabs, classes, psizes, &open, nullptr, dA,
-                                        dacc, dgam, (int)C, s, &opened));
-        if (opened) smp.end(take, s, cu, cu * state_bytes);
+                                        dacc, dgam, (int)C, s, &ran));
+        opened = ran.launched;
+        if (opened) {
+            smp.end(take, s, cu, cu * state_bytes);
+            timing->launch_steps = o.n_steps;
+            timing->patch_cells = ran.cells * (double)C;
+        }
     }
     for (const Wave& w : st.waves) {
         if (opened) break;
@@ -1452,10 +1458,11 @@ cf_status run_reduced(const cf::Problem& p, const cf_opts& o, const Staged& st, 
                 }
                 const bool take = smp.begin(s);
                 int used = 0;
-                bool patched = false;
                 STEP_OK(cf::launch_red_patch<T>(fields, dch, sl, w.n_all, g, ord, span, tabs, classes, psizes,
-                                                nullptr, &live, dA, dacc, dgam, (int)C, s, &patched));
-                if (patched) {
+                                                nullptr, &live, dA, dacc, dgam, (int)C, s, &ran));
+                if (ran.launched) {
+                    timing->launch_steps = std::max(timing->launch_steps, d1 - d0);
+                    if (d0 == 0) timing->patch_cells += ran.cells * w.n_all;
                     used = cf::red_regs_covers<T>(g, ord.cplx) ? 1 : 2;
                 } else {
                     if (o.tile_variant != 2) STEP_OK(pack_ids());
@@ -2268,6 +2275,8 @@ bool fill_result(const cf::Problem& p, const std::vector<cf::Channel>& chans, co
             for (size_t c = 0; c < C; ++c) a += pl.live_cells[chans[c].pol == CF_POL_TE ? 1 : 0];
         out->advanced_cell_updates = a * (double)steps;
     }
+    if (p.reduced() && tim.launch_steps > 0)   // (orders of unlike steps: each its share)
+        out->advanced_cell_updates = out->cell_updates * (tim.patch_cells / ((double)C * (double)p.ncell));
     if (tim.variant >= 0 && tim.variant < 8 && p.grid.ndim == 3 && sg.f3d && !sg.zr.empty()) {
         // the fused 3D steps advance each band's planes [z0, z1) only
         int W, B, ks;

@@ -5,6 +5,6 @@ namespace cf {
 
 template hipError_t launch_red_patch<double>(double*, const ChanDev*, const int*, int, const Grid2D&, const RedOrders&,
                                          const RedSpan&, const SurfTables&, const PatchClasses&, const PatchSizes&,
-                                         const PatchOpen*, PatchLive*, double, double*, double*, int, hipStream_t, bool*);
+                                         const PatchOpen*, PatchLive*, double, double*, double*, int, hipStream_t, PatchRan*);
 
 }  // namespace cf

@@ -58,8 +58,14 @@ struct PatchLive {
     int plan_slots = -1;
 };
 
-// As launch_red_resident_span, for grids a patch shape covers: *launched
-// tells whether one did (nothing is launched otherwise).  slots == nullptr:
+// What a launch did: whether a shape covers the grid (nothing is launched
+// otherwise), and the cells its patches hold.
+struct PatchRan {
+    bool launched = false;
+    double cells = 0;
+};
+
+// As launch_red_resident_span, for grids a patch shape covers (see PatchRan).  slots == nullptr:
 // the channels 0 .. nslots - 1.  op: an open or dispersive run (whole span
 // only, the grid's CPML set as for the split kernels); it uses no field
 // blocks.  live: as above, or null (every patch of the grid).
@@ -67,6 +73,6 @@ template <typename T>
 hipError_t launch_red_patch(T* fields, const ChanDev* ch, const int* slots, int nslots, const Grid2D& g,
                             const RedOrders& ord, const RedSpan& span, const SurfTables& t, const PatchClasses& pc,
                             const PatchSizes& ps, const PatchOpen* op, PatchLive* live, double dA, double* acc, double* gamma,
-                            int gamma_stride, hipStream_t s, bool* launched);
+                            int gamma_stride, hipStream_t s, PatchRan* ran);
 
 }  // namespace cf

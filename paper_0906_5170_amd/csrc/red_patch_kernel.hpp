@@ -1025,7 +1025,7 @@ struct PatchPlan {
     int shape = -1;
     PatchArgs args{};
     int threads = 0, blocks = 0;
-    double cost = 0;
+    double cost = 0, cells = 0;                    // cells: of its patches, inside the grid
 };
 
 // Issue slots of a lane per step (the cost model's unit): the updates, the
@@ -1068,9 +1068,6 @@ inline bool plan_open(const PatchShape& q, const Grid2D& g, const PatchOpen& op,
     return true;
 }
 
-// The shape that takes the least modelled time for nslots channels on an
-// nx x ny grid: steps of a CU's resident blocks at the waves its fullest SIMD
-// holds, times the rounds of blocks.  shape -1 when none covers the grid.
 // The list (see PatchArgs) of the patches of cx x b cells with a cell that can
 // change: E of a class that holds a field, H where an E value of its curl is of
 // such a one.
@@ -1106,6 +1103,9 @@ inline std::vector<uint16_t> live_list(const uint16_t* cls, const Grid2D& g, boo
     return out;
 }
 
+// The shape that takes the least modelled time for nslots channels on an
+// nx x ny grid: steps of a CU's resident blocks at the waves its fullest SIMD
+// holds, times the rounds of blocks.  shape -1 when none covers the grid.
 // live: the list of the best shape lands in `list` (empty: every patch).
 template <typename T, bool CPLX, bool OPEN>
 PatchPlan plan_patch(bool cyl, const Grid2D& g, int nslots, const PatchClasses& pc, const PatchSizes& z,
@@ -1153,6 +1153,12 @@ PatchPlan plan_patch(bool cyl, const Grid2D& g, int nslots, const PatchClasses& 
             list = std::move(l);
         }
     }
+    if (best.shape >= 0) {
+        const PatchShape& q = SH::s[best.shape];
+        best.cells = list.empty() ? (double)g.ncell : 0;
+        for (size_t k = 0; k < list.size(); k += 6)
+            best.cells += (double)std::min(q.cx, g.nx - list[k] * q.cx) * std::min(q.b, g.ny - list[k + 1] * q.b);
+    }
     return best;
 }
 
@@ -1160,7 +1166,7 @@ template <typename T, bool CYL, bool CPLX, bool OPEN>
 hipError_t patch_dispatch(T* fields, const ChanDev* ch, const int* slots, int nslots, const Grid2D& g,
                           const RedOrders& ord, const RedSpan& sp, const SurfTables& t, const PatchClasses& pc,
                           const PatchSizes& z, const PatchOpen* op, PatchLive* live, double dA, double* acc,
-                          double* gamma, int gamma_stride, hipStream_t s, bool* launched) {
+                          double* gamma, int gamma_stride, hipStream_t s, PatchRan* ran) {
     using SH = PatchShapes<T, CPLX, OPEN>;
     hipError_t e = hipSuccess;
     PatchPlan pl;
@@ -1190,7 +1196,8 @@ hipError_t patch_dispatch(T* fields, const ChanDev* ch, const int* slots, int ns
             if (V != pl.shape) return;
             const auto run = [&](auto kernel) {
                 if (!lds_allow(reinterpret_cast<const void*>(kernel), pl.args.lds.total)) return;
-                *launched = true;
+                ran->launched = true;
+                ran->cells = pl.cells;
                 // an open run's launches take as many channels as there are scratch regions
                 for (int first = 0; first < nslots && e == hipSuccess; first += pl.blocks) {
                     hipLaunchKernelGGL(kernel, dim3(std::min(pl.blocks, nslots - first)), dim3(pl.threads),
@@ -1220,22 +1227,22 @@ template <typename T>
 hipError_t launch_red_patch(T* fields, const ChanDev* ch, const int* slots, int nslots, const Grid2D& g,
                             const RedOrders& ord, const RedSpan& span, const SurfTables& t, const PatchClasses& pc,
                             const PatchSizes& ps, const PatchOpen* op, PatchLive* live, double dA, double* acc,
-                            double* gamma, int gamma_stride, hipStream_t s, bool* launched) {
-    *launched = false;
+                            double* gamma, int gamma_stride, hipStream_t s, PatchRan* ran) {
+    *ran = PatchRan();
     if (nslots <= 0 || pc.cls == nullptr) return hipSuccess;
     if (op) {
         if (ord.axis || ord.cplx) return hipSuccess;
         return patch_dispatch<T, false, false, true>(fields, ch, slots, nslots, g, ord, span, t, pc, ps, op, live, dA, acc,
-                                                     gamma, gamma_stride, s, launched);
+                                                     gamma, gamma_stride, s, ran);
     }
     if (ord.axis)
         return patch_dispatch<T, true, false, false>(fields, ch, slots, nslots, g, ord, span, t, pc, ps, op, live, dA, acc,
-                                                     gamma, gamma_stride, s, launched);
+                                                     gamma, gamma_stride, s, ran);
     if (ord.cplx)
         return patch_dispatch<T, false, true, false>(fields, ch, slots, nslots, g, ord, span, t, pc, ps, op, live, dA, acc,
-                                                     gamma, gamma_stride, s, launched);
+                                                     gamma, gamma_stride, s, ran);
     return patch_dispatch<T, false, false, false>(fields, ch, slots, nslots, g, ord, span, t, pc, ps, op, live, dA, acc,
-                                                  gamma, gamma_stride, s, launched);
+                                                  gamma, gamma_stride, s, ran);
 }
 
 }  // namespace cf
