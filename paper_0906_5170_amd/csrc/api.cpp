@@ -1148,27 +1148,9 @@ bool patch_lorentz(const cf::Problem& p, const std::vector<double>& lor, const c
 
 // LDS table sizes of the patch kernel over a solve's channels.
 cf::PatchSizes patch_sizes(const cf::Problem& p, const Staged& st) {
-    cf::PatchSizes z{1, 1, 1};
-    auto box = [&](const int32_t* idx, int n) {
-        int x0 = p.nx, x1 = -1, y0 = p.ny, y1 = -1;
-        for (int k = 0; k < n; ++k) {
-            const int x = idx[k] % p.nx, y = idx[k] / p.nx;
-            x0 = std::min(x0, x);
-            x1 = std::max(x1, x);
-            y0 = std::min(y0, y);
-            y1 = std::max(y1, y);
-        }
-        if (n > 0) z.box = std::max(z.box, (x1 - x0 + 1) * (y1 - y0 + 1));
-    };
-    std::map<std::pair<int, int>, bool> seen;   // channels of a face share their tables
-    for (const cf::ChanDev& d : st.dev) {
-        z.samples = std::max(z.samples, d.nsamp);
-        z.points = std::max(z.points, d.P);
-        if (!seen.emplace(std::make_pair(d.g_off, d.u_off), true).second) continue;
-        box(st.gidx.data() + d.g_off, d.nsamp * d.P);
-        box(st.uidx.data() + d.u_off, d.n_uniq);
-    }
-    return z;
+    cf::Patch2DSizes z{1, 1, 1};
+    patch2d_sizes(st, p.nx, z);
+    return {z.box, z.samples, z.points};
 }
 
 // Uploads of a solve's tables.  They lie one behind another in the workspace, so

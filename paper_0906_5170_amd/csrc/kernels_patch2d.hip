@@ -304,54 +304,37 @@ __device__ __forceinline__ void p2_advance(const ChanDev& d, const InstDev& g, c
             total(ksteps - 1, kt);
         };
         __syncthreads();
-        constexpr int NV = 2, NPT = 4;
-        if (nsamp <= 64 * NV && P <= NPT) {
-            // the lane's samples: offsets, weights and basis values in registers
-            double w[NV][NPT], b[NV], part[NV];
-            uint32_t at[NV][NPT];
+        constexpr int NV = kPatchSamples / 64, NPT = kPatchPoints;
+        // the lane's samples: offsets, weights and basis values in registers
+        double w[NV][NPT], b[NV], part[NV];
+        uint32_t at[NV][NPT];
 #pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                const int i = v * 64 + lane;
-                b[v] = i < nsamp ? sb[i] : 0.0;
+        for (int v = 0; v < NV; ++v) {
+            const int i = v * 64 + lane;
+            b[v] = i < nsamp ? sb[i] : 0.0;
 #pragma unroll
-                for (int q = 0; q < NPT; ++q) {
-                    const bool in = i < nsamp && q < P;
-                    at[v][q] = in ? so[i * P + q] : 0u;
-                    w[v][q] = in ? sw[i * P + q] : 0.0;
-                }
+            for (int q = 0; q < NPT; ++q) {
+                const bool in = i < nsamp && q < P;
+                at[v][q] = in ? so[i * P + q] : 0u;
+                w[v][q] = in ? sw[i * P + q] : 0.0;
             }
-            advance(
-                [&]() __attribute__((always_inline)) {
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) {
-                        if (v * 64 >= nsamp) break;
-                        T f[NPT];
-#pragma unroll
-                        for (int q = 0; q < NPT; ++q) f[q] = stage[at[v][q]];
-                        double x = 0.0;
-#pragma unroll
-                        for (int q = 0; q < NPT; ++q)
-                            if (q < P) x += w[v][q] * (double)f[q];
-                        part[v] = v * 64 + lane < nsamp ? 0.0 + b[v] * x : 0.0;
-                    }
-                },
-                part);
-        } else {
-            double part[4];
-            advance(
-                [&]() __attribute__((always_inline)) {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        part[v] = 0.0;
-                        for (int i = v * 64 + lane; i < nsamp; i += yee::kSurfThreads) {
-                            double x = 0.0;
-                            for (int q = 0; q < P; ++q) x += sw[i * P + q] * (double)stage[so[i * P + q]];
-                            part[v] += sb[i] * x;
-                        }
-                    }
-                },
-                part);
         }
+        advance(
+            [&]() __attribute__((always_inline)) {
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    if (v * 64 >= nsamp) break;
+                    T f[NPT];
+#pragma unroll
+                    for (int q = 0; q < NPT; ++q) f[q] = stage[at[v][q]];
+                    double x = 0.0;
+#pragma unroll
+                    for (int q = 0; q < NPT; ++q)
+                        if (q < P) x += w[v][q] * (double)f[q];
+                    part[v] = v * 64 + lane < nsamp ? 0.0 + b[v] * x : 0.0;
+                }
+            },
+            part);
         if (lane == 0) {
             acc[0] = acc_s;
             acc[1] = acc_c;

@@ -42,7 +42,6 @@
 // projection, in a single launch for channels of any mix of orders, with the
 // fields in registers (LDS neighbour exchange) or in global memory (a
 // channel's block stays in the L2 of its XCD).
-#include <mutex>
 #include <type_traits>
 
 #include "../../include/casimir_fdtd.h"
@@ -942,7 +941,6 @@ size_t regs_lds_bytes(const Grid2D& g, int np) {
            4 * (size_t)g.ncell;
 }
 
-
 // Register variants (cells per thread K, threads per block NTH), each
 // without register spills, smallest first: FP32 up to 10240 cells, FP64 up
 // to 6144 (the LDS of a CU, 16 or 28 bytes per cell, bounds both first).
@@ -955,28 +953,6 @@ constexpr RegVariant kRegVariants[kNumRegVariants] = {{1, 1024}, {2, 1024}, {4, 
 template <>
 constexpr RegVariant kRegVariants<double>[kNumRegVariants] = {{1, 1024}, {2, 1024}, {3, 1024}, {4, 1024}, {6, 1024},
                                                                {6, 1024}};
-
-// Dynamic LDS above 64 KB needs the kernel's attribute raised first.  The
-// attribute is a cap and is only ever raised (under a lock), so solves on
-// concurrent host threads never lower it below what another one launches
-// with; false when the runtime refuses (the caller then takes the
-// global-memory variant).
-template <typename T, int K, int NTH, bool CYL, bool CPLX>
-bool regs_lds_ok(size_t lds) {
-    if (lds <= 65536) return true;
-    static std::mutex mu;
-    static size_t cap = 65536;
-    std::lock_guard<std::mutex> lk(mu);
-    if (lds <= cap) return true;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_red_regs<T, K, NTH, CYL, CPLX>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    cap = lds;
-    return true;
-}
 
 // Register variants a complex run may take (both parts of every field in
 // registers): the first kCplxRegVariants, which do not spill (FP32 up to 6
@@ -996,7 +972,9 @@ hipError_t regs_try(int64_t ncell, size_t lds, bool* launched, T* fields, const 
         return hipSuccess;
     } else {
         constexpr int K = kRegVariants<T>[V].K, NTH = kRegVariants<T>[V].NTH;
-        if (ncell > (int64_t)K * NTH || !regs_lds_ok<T, K, NTH, CYL, CPLX>(lds)) return hipSuccess;
+        if (ncell > (int64_t)K * NTH || 
+            !lds_allow(reinterpret_cast<const void*>(&k_red_regs<T, K, NTH, CYL, CPLX>), lds))
+            return hipSuccess;
         *launched = true;
         hipLaunchKernelGGL((k_red_regs<T, K, NTH, CYL, CPLX>), dim3(nslots), dim3(NTH), lds, s, fields, ch, slots, g,
                            ord, sp, t, dA, acc, gamma, gamma_stride);

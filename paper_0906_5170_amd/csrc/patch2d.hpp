@@ -64,6 +64,10 @@ struct Patch2DInst {
 struct Patch2DSizes {
     int box, samples, points;
 };
+// The most samples of a channel and points of a sample: the surface wave keeps
+// them in registers.  (Surfaces that fit a tile have at most 118 samples, of 4
+// points.)
+constexpr int kPatchSamples = 128, kPatchPoints = 4;
 
 // LDS bytes of a block for n patches, dynamic and static.
 template <typename T>

@@ -52,6 +52,9 @@ double part_cycles(const Patch2DShape& q, int k, const Patch2DList& l, int preci
 // 260 x 200 cells 0.86, 300 x 300 0.74, 440 x 330 0.67; FP64 2.6 to 3.4).
 double tiles_cost(double cells, int precision) { return cells * (precision == CF_FP64 ? 2.6 : 0.7); }
 
+// The surface wave addresses the box by 16-bit offsets.
+bool sizes_fit(const Patch2DSizes& z) { return z.box <= 65535 && z.samples <= kPatchSamples && z.points <= kPatchPoints; }
+
 constexpr int kCUs = 256;
 constexpr int kMaxParts = 16;
 
@@ -447,8 +450,7 @@ int patch2d_choose(const Patch2DSet& s, int precision, int k, int nslots, const 
                    int others, size_t room) {
     int best = -1;
     double best_cost = 0;
-    // the surface wave addresses the box by 16-bit offsets
-    if (z.box > 65535) return -1;
+    if (!sizes_fit(z)) return -1;
     for (int v = 0; v < (int)s.lists[k].size(); ++v) {
         const Patch2DShape& q = s.shape(v);
         const Patch2DList& l = s.lists[k][v];
@@ -473,7 +475,7 @@ int patch2d_choose(const Patch2DSet& s, int precision, int k, int nslots, const 
 int patch2d_choose_mixed(const Patch2DSet& s, int precision, int nslots, const Patch2DSizes& z, size_t lds_limit) {
     int best = -1;
     double best_cost = 0;
-    if (nslots > kCUs || z.box > 65535) return -1;
+    if (nslots > kCUs || !sizes_fit(z)) return -1;
     for (int v = 0; v < (int)s.shapes.size(); ++v) {
         const Patch2DShape& q = s.shapes[v];
         const Patch2DList &tm = s.lists[0][v], &te = s.lists[1][v];

@@ -1036,7 +1036,7 @@ inline double patch_issue(const PatchShape& q, int np) {
 
 // The open part of a launch: layer columns / rows of patches, sizes of the
 // LDS entries, scratch values per block.
-inline bool plan_open(const PatchShape& q, const Grid2D& g, const PatchOpen& op, PatchArgs& a, OpenSizes& os) {
+inline void plan_open(const PatchShape& q, const Grid2D& g, const PatchOpen& op, PatchArgs& a, OpenSizes& os) {
     auto split = [](int P, int n, int w, int L, int* lo, int* hi) {
         *lo = P > 0 ? std::min(L, (P + w - 1) / w) : 0;
         *hi = P > 0 ? std::max(*lo, (n - P) / w) : L;
@@ -1065,7 +1065,6 @@ inline bool plan_open(const PatchShape& q, const Grid2D& g, const PatchOpen& op,
         a.items = 3 * n;
         a.scratch_stride += (int64_t)2 * op.n_lor * a.items;
     }
-    return true;
 }
 
 // The list (see PatchArgs) of the patches of cx x b cells with a cell that can

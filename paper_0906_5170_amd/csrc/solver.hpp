@@ -144,7 +144,6 @@ struct ConvergenceStop {
 // `at`, and the work items of n channels.
 using PatchShapes = std::array<int, 2>;
 std::shared_ptr<const cf::Patch2DSet> cached_patches(const cf::Problem& p, int precision);
-struct Staged;
 void patch2d_sizes(const Staged& st, int nx, cf::Patch2DSizes& z);
 bool patch2d_pick(const cf::Patch2DSet& set, int precision, const int used[2], const int together[2],
                   const cf::Patch2DSizes& z, PatchShapes& shape);

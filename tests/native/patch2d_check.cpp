@@ -61,6 +61,11 @@ void check_lds(int precision) {
                         CHECK(!one || dyn + 32 <= kLimit);
                         CHECK(!both || dyn + 64 <= kLimit);
                         CHECK(one || dyn + 256 > kLimit);
+                        const Patch2DSizes more{box, kPatchSamples + 1, points}, wider{box, samples, kPatchPoints + 1};
+                        for (const Patch2DSizes& w : {more, wider}) {
+                            CHECK(patch2d_choose(s, precision, 0, 1, w, kLimit) < 0);
+                            CHECK(patch2d_choose_mixed(s, precision, 2, w, kLimit) < 0);
+                        }
                         accepted += one;
                         refused += !one;
                         close += dyn <= kLimit && dyn + 64 > kLimit;
