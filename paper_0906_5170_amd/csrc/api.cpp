@@ -2771,7 +2771,7 @@ cf_status run_batch(const BatchPlan& B, const BatchLayout& L, const cf_opts& o, 
         // (two where they fill the device by themselves: six pistons of 448 channels
         // 33.4 ms, 34.3 on four)
         const size_t blocks = items[0].size() + items[1].size() + nw_tm + nw_te;
-        const int n_lane = (o.flags & CF_FLAG_TIME_STENCIL) ? 1 : std::min<int>(blocks <= 1024 ? 4 : 2, (int)chains.size());
+        const int n_lane = (o.flags & CF_FLAG_TIME_STENCIL) ? 1 : std::min<int>(blocks <= 512 ? 4 : 2, (int)chains.size());
         {
             std::vector<double> load(n_lane, 0.0);
             for (Chain& c : chains) {

@@ -15,10 +15,8 @@ namespace {
 // and a smaller shape steps faster but needs more parts.  Which is best depends
 // on the channels: few leave compute units idle, so a step's latency counts;
 // many fill the device, so all parts' work counts (see patch2d_choose).
-// Fewer than 16 steps do not pay for a launch (200 x 90 cells in FP64, 16
-// channels: 5.0 us a step with 8, 3.8 on tiles).
-constexpr int kPartSteps[] = {96, 64, 48, 32, 24, 16};
-constexpr int kNumPartSteps = 6;
+constexpr int kPartSteps[] = {96, 64, 48, 32, 24, 16, 8};
+constexpr int kNumPartSteps = 7;
 
 // Patches a block of the shape may hold (its last wave takes the surface sums).
 int most_patches(const Patch2DShape& q) { return 256 * q.mw - 64; }
@@ -57,6 +55,13 @@ bool sizes_fit(const Patch2DSizes& z) { return z.box <= 65535 && z.samples <= kP
 
 constexpr int kCUs = 256;
 constexpr int kMaxParts = 16;
+
+// Cycles of the tiles' step of nslots channels: a launch's latency (2.6 us a step,
+// FP64 3.7), most of it while it has little to do.
+double tiles_step(double cells, int nslots, int precision) {
+    const double all = tiles_cost(cells, precision) * nslots / kCUs;
+    return std::max(all, (precision == CF_FP64 ? 7900.0 : 5400.0) + all / 2);
+}
 
 // Whether an id's material lets the field change.
 bool holds_field(const Problem& p, const std::vector<double>& v, int id) {
@@ -464,6 +469,10 @@ int patch2d_choose(const Patch2DSet& s, int precision, int k, int nslots, const 
         const int rounds = (nblocks + kCUs * c - 1) / (kCUs * c);
         const double cost = rounds * (l.parts > 1 ? part_cycles(q, k, l, precision, std::min(1.0, (double)nblocks / kCUs))
                                                   : step_cycles(q, k, c * waves));
+        // launches of 8 steps are mostly start, loads and stores: only well below the
+        // tiles (FP64, 200 x 90 cells: 5.0 us a step with 16 channels, 3.8 on tiles,
+        // 8.2 against 18 with 256)
+        if (l.parts > 1 && l.steps < 16 && 1.15 * cost > tiles_step(l.live_cells, nslots + others, precision)) continue;
         if (best < 0 || cost < best_cost) {
             best = v;
             best_cost = cost;
