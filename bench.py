@@ -145,7 +145,8 @@ def serving_source_hash():
     """sha256 over the scheduler and the kernels it launches."""
     import hashlib
     h = hashlib.sha256()
-    for name in ("server.cpp", "kernels2d.hip", "kernels3d.hip", "device.hpp"):
+    for name in ("server.cpp", "kernels2d.hip", "kernels_patch2d.hip", "patch2d_plan.cpp", "kernels3d.hip",
+                 "device.hpp"):
         with open(os.path.join(ROOT, "paper_0906_5170_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()

@@ -5,10 +5,11 @@
 // is admitted (later requests may pass an earlier one that does not fit yet):
 // its tables are uploaded, its fields zeroed and kicked, and it joins the
 // resident set.  A tick advances the resident requests:
-//   - all 2D requests whose stress surface fits a fused tile share one fused
-//     launch per polarization and advance K steps per tick (each instance
-//     reads its own buffers, tables and K(t) and starts at its own step of
-//     the scheduler clock);
+//   - all 2D requests whose stress surface fits a fused tile share fused
+//     launches, one per polarization and tile or patch shape, and advance K
+//     steps per tick (each instance reads its own buffers, tables and K(t) and
+//     starts at its own step of the scheduler clock); where one is on the 2D
+//     patch kernel several ticks run as one (merged_ticks);
 //   - other requests (3D on the fused z-streaming step, or split kernels
 //     for surfaces wider than a tile) run one after another, in channel
 //     waves that bound their memory, each with its own step count.  Each
